@@ -1292,117 +1292,120 @@ __device__ __forceinline__ float scaled(float s, float inv_tau)
 
 // s / tau is formed with an explicitly rounded multiply everywhere, so that the same value
 // enters the max, the exponent and the label term (no fused multiply-add may split them).
-// Gradient: one wavefront per row, rows dealt round-robin to the wavefronts of the grid.
+__device__ __forceinline__ float ce_grad_value(float scaled_s, float mx, float z, bool label, float scale)
+{
+    const float pj = expf(scaled_s - mx) / z;
+    return (pj - (label ? 1.0f : 0.0f)) * scale;
+}
+
+// The column beside the diagonal whose slot of g carries a row's sum from ce_grad_kernel to ce_loss_kernel (b >= 2)
+__device__ __forceinline__ int ce_second_slot(int i, int b) { return i + 1 < b ? i + 1 : i - 1; }
+
+// Gradient: one wavefront per row, rows dealt round-robin to the wavefronts of the grid.  Rows of up to 64 * KEEP
+// columns are read once and stay in registers (KEEP = 0: wider rows are read again for each of the three sweeps).
+// STASH (a loss is wanted): the row's maximum and sum go into g[i, i] and the slot beside it instead of the two
+// gradients; ce_loss_kernel reads them and puts the gradients there.  The library owns no memory that two calls
+// could share safely, and g is an output that the call overwrites whole.
+template <int KEEP, bool STASH>
 __global__ void __launch_bounds__(256) ce_grad_kernel(const float *s, int n, int b, float inv_tau, float *g)
 {
     const int lane = threadIdx.x & 63;
     const int n_waves = (int)gridDim.x * 4;
+    const float scale = inv_tau / (float)n;
     for (int i = (int)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += n_waves) {
         const float *row = s + (int64_t)i * b;
-        float mx = neg_inf();
-        for (int j = lane; j < b; j += 64)
-            mx = fmaxf(mx, scaled(row[j], inv_tau));
-        mx = wave_max(mx);
-        float z = 0.0f;
-        for (int j = lane; j < b; j += 64)
-            z += expf(scaled(row[j], inv_tau) - mx);
-        z = wave_sum(z);
-        float scale = inv_tau / (float)n;
-        for (int j = lane; j < b; j += 64) {
-            float pj = expf(scaled(row[j], inv_tau) - mx) / z;
-            g[(int64_t)i * b + j] = (pj - (j == i ? 1.0f : 0.0f)) * scale;
+        float *dst = g + (int64_t)i * b;
+        const int second = ce_second_slot(i, b);
+        float mx = neg_inf(), z = 0.0f;
+        auto put = [&](int j, float v) {
+            if (STASH && j == i)
+                dst[j] = mx;
+            else if (STASH && j == second)
+                dst[j] = z;
+            else
+                dst[j] = ce_grad_value(v, mx, z, j == i, scale);
+        };
+        if constexpr (KEEP > 0) {
+            float v[KEEP];
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k) {
+                const int j = lane + 64 * k;
+                v[k] = scaled(row[j < b ? j : b - 1], inv_tau);
+                mx = j < b ? fmaxf(mx, v[k]) : mx;
+            }
+            mx = wave_max(mx);
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k)
+                z += lane + 64 * k < b ? expf(v[k] - mx) : 0.0f;
+            z = wave_sum(z);
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k)
+                if (lane + 64 * k < b)
+                    put(lane + 64 * k, v[k]);
+        } else {
+            for (int j = lane; j < b; j += 64)
+                mx = fmaxf(mx, scaled(row[j], inv_tau));
+            mx = wave_max(mx);
+            for (int j = lane; j < b; j += 64)
+                z += expf(scaled(row[j], inv_tau) - mx);
+            z = wave_sum(z);
+            for (int j = lane; j < b; j += 64)
+                put(j, scaled(row[j], inv_tau));
         }
     }
 }
 
-// Loss: a single block (fixed summation order); 16 lanes per row, 64 rows at a time.  When a row has at most
-// 16 * KEEP columns (KEEP = 16 or 32) the scaled scores of a lane live in registers, and the loads of two to four
-// rows are issued together before any of them is reduced: the kernel is a chain of memory latencies, not
-// of arithmetic.  Wider rows (KEEP = 0) are re-read from memory for each of the sweeps.
-template <int KEEP>
-__global__ void __launch_bounds__(1024) ce_loss_kernel(const float *s, int n, int b, float inv_tau, float *loss)
+// Loss: mean over the rows of log(sum) + max - s[i, i] / tau, from the maxima and sums that ce_grad_kernel left in g,
+// whose two slots per row get their gradients here.  One block in a fixed order: a row per thread, then a tree.  (It
+// used to repeat the softmax of every row: 65 536 exponentials on one compute unit, 25 us at 256 x 256 against 4 us.)
+__global__ void __launch_bounds__(1024) ce_loss_kernel(const float *s, int n, int b, float inv_tau, float *g, float *loss)
 {
-    __shared__ float part[64];
-    const int sub = threadIdx.x & 15;
-    const int slot = threadIdx.x >> 4;
+    __shared__ float part[16];
+    const float scale = inv_tau / (float)n;
     float local = 0.0f;
-    if constexpr (KEEP > 0) {
-        constexpr int ROWS = 64 / KEEP; // rows of a slot in flight together (64 registers)
-        for (int i0 = slot; i0 < n; i0 += 64 * ROWS) {
-            float v[ROWS][KEEP];
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) {
-                const int i = i0 + 64 * r;
-                const float *row = s + (int64_t)(i < n ? i : i0) * b;
-#pragma unroll
-                for (int k = 0; k < KEEP; ++k) {
-                    const int j = sub + 16 * k;
-                    v[r][k] = j < b ? scaled(row[j], inv_tau) : neg_inf();
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) {
-                const int i = i0 + 64 * r;
-                float mx = neg_inf();
-#pragma unroll
-                for (int k = 0; k < KEEP; ++k)
-                    mx = fmaxf(mx, v[r][k]);
-#pragma unroll
-                for (int o = 8; o > 0; o >>= 1)
-                    mx = fmaxf(mx, __shfl_xor(mx, o));
-                float z = 0.0f;
-#pragma unroll
-                for (int k = 0; k < KEEP; ++k)
-                    z += (sub + 16 * k < b) ? expf(v[r][k] - mx) : 0.0f; // same order as the sweep over memory
-#pragma unroll
-                for (int o = 8; o > 0; o >>= 1)
-                    z += __shfl_xor(z, o);
-                if (i < n)
-                    local += logf(z) + mx - scaled(s[(int64_t)i * b + i], inv_tau);
-            }
-        }
-    } else {
-        for (int i = slot; i < n; i += 64) {
-            const float *row = s + (int64_t)i * b;
-            float mx = neg_inf();
-            for (int j = sub; j < b; j += 16)
-                mx = fmaxf(mx, scaled(row[j], inv_tau));
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1)
-                mx = fmaxf(mx, __shfl_xor(mx, o));
-            float z = 0.0f;
-            for (int j = sub; j < b; j += 16)
-                z += expf(scaled(row[j], inv_tau) - mx);
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1)
-                z += __shfl_xor(z, o);
-            local += logf(z) + mx - scaled(row[i], inv_tau);
-        }
+    for (int i = threadIdx.x; i < n && b > 1; i += 1024) { // (one document: the loss is 0)
+        const int second = ce_second_slot(i, b);
+        float *row = g + (int64_t)i * b;
+        const float mx = row[i], z = row[second];
+        const float own = scaled(s[(int64_t)i * b + i], inv_tau), next = scaled(s[(int64_t)i * b + second], inv_tau);
+        local += logf(z) + mx - own;
+        row[i] = ce_grad_value(own, mx, z, true, scale);
+        row[second] = ce_grad_value(next, mx, z, false, scale);
     }
-    if (sub == 0)
-        part[slot] = local;
+    local = wave_sum(local);
+    if ((threadIdx.x & 63) == 0)
+        part[threadIdx.x >> 6] = local;
     __syncthreads();
     if (threadIdx.x == 0) {
         float t = 0.0f;
-        for (int k = 0; k < 64; ++k)
+        for (int k = 0; k < 16; ++k)
             t += part[k];
         *loss = t / (float)n;
     }
 }
 
+template <bool STASH> static void launch_ce_grad(const float *s, int n, int b, float inv_tau, float *g, hipStream_t stream)
+{
+    const dim3 grid((n + 3) / 4), block(256);
+    if (b <= 64 * 4)
+        hipLaunchKernelGGL((ce_grad_kernel<4, STASH>), grid, block, 0, stream, s, n, b, inv_tau, g);
+    else if (b <= 64 * 16)
+        hipLaunchKernelGGL((ce_grad_kernel<16, STASH>), grid, block, 0, stream, s, n, b, inv_tau, g);
+    else
+        hipLaunchKernelGGL((ce_grad_kernel<0, STASH>), grid, block, 0, stream, s, n, b, inv_tau, g);
+}
+
 hipError_t ce_grad_launch(const float *scores, int n, int b, float tau, float *g, float *loss, hipStream_t stream)
 {
-    int row_blocks = (n + 3) / 4;
-    hipLaunchKernelGGL(ce_grad_kernel, dim3(row_blocks), dim3(256), 0, stream, scores, n, b, 1.0f / tau, g);
+    const float inv_tau = 1.0f / tau;
+    if (loss && b > 1)
+        launch_ce_grad<true>(scores, n, b, inv_tau, g, stream);
+    else
+        launch_ce_grad<false>(scores, n, b, inv_tau, g, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !loss)
         return e;
-    if (b <= 256)
-        hipLaunchKernelGGL(ce_loss_kernel<16>, dim3(1), dim3(1024), 0, stream, scores, n, b, 1.0f / tau, loss);
-    else if (b <= 512)
-        hipLaunchKernelGGL(ce_loss_kernel<32>, dim3(1), dim3(1024), 0, stream, scores, n, b, 1.0f / tau, loss);
-    else
-        hipLaunchKernelGGL(ce_loss_kernel<0>, dim3(1), dim3(1024), 0, stream, scores, n, b, 1.0f / tau, loss);
+    hipLaunchKernelGGL(ce_loss_kernel, dim3(1), dim3(1024), 0, stream, scores, n, b, inv_tau, g, loss);
     return hipGetLastError();
 }
 

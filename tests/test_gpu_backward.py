@@ -279,3 +279,19 @@ def test_autograd_wrapper_matches_the_oracle():
     rQ, rD = O.backward(W.to_raw_numpy(Qf.detach()), W.to_raw_numpy(Df.detach()), "f32", A2, wf.cpu().numpy().astype(np.float64))
     close(Qf.grad, rQ, "dQ")
     close(Df.grad, rD, "dD")
+
+
+@pytest.mark.parametrize("n,b", [(1, 2), (2, 2), (3, 3), (256, 257), (70, 1024), (65, 1025), (1100, 1100)])
+def test_ce_grad_row_lengths(n, b):
+    """Rows at the edges of what a wavefront keeps in registers, and more rows than the loss kernel has threads; with the loss (whose
+    kernel writes two gradients of every row) and without it the gradient has the same bits."""
+    s = (torch.randn(n, b, device=DEV, generator=torch.Generator(DEV).manual_seed(n + b)) * 3 + 10).contiguous()
+    g, loss = M.maxsim_ce_grad(s, 0.02)
+    g2 = torch.empty_like(g)
+    rc = M.load().maxsim_ce_grad(s.data_ptr(), n, b, 0.02, g2.data_ptr(), None, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0
+    rloss, rg = O.ce_grad(s.cpu().numpy().astype(np.float64), 0.02)
+    assert abs(float(loss) - rloss) <= 1e-5 * max(1.0, abs(rloss))
+    assert np.abs(g.cpu().numpy() - rg).max() <= 1e-4 * max(np.abs(rg).max(), 1e-30)
+    assert torch.equal(g, g2)
