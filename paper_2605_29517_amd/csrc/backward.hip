@@ -572,8 +572,9 @@ __global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr 
 
     int64_t j_first, j_last;
     if (p.offsets) {
-        j_first = lower_bound_offsets(p.offsets, p.b, row0 + 1) - 1;
-        j_last = lower_bound_offsets(p.offsets, p.b, row_end) - 1;
+        lower_bound_offsets2(p.offsets, p.b, row0 + 1, row_end, j_first, j_last);
+        j_first -= 1;
+        j_last -= 1;
         j_first = j_first < 0 ? 0 : j_first; // only offsets that break their contract get here
         j_last = j_last > p.b - 1 ? p.b - 1 : j_last;
     } else { // rows are below 2^31 (checked by the caller)

@@ -257,3 +257,12 @@ def test_mid_block_counts_on_many_documents(ragged, n_q, l_q, want_argmax, dtype
     else:
         D = W.unit_rows((b, 32 if l_q > 100 else 40, d), dtype, 132, DEV)
         forward_parity_uniform(Q, D, M.maxsim_forward, want_argmax, rtol)
+
+
+@pytest.mark.parametrize("b", [1, 2, 62, 63, 64, 65, 128, 4094, 4095, 4096, 4160])
+def test_runs_of_documents_are_found(b):
+    """Where a run of a ragged corpus begins is searched for with 64 probes a step: numbers of documents around the powers of 64."""
+    lens = np.random.default_rng(b).integers(0, 4, b)
+    lens[b // 2] = 40
+    Q, Dp, off = _ragged_case(1, 8, lens, "f16", 91)
+    forward_parity_ragged(Q, Dp, off, M.maxsim_forward_ragged, False, 1e-5)
