@@ -80,11 +80,24 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
     if (nu <= 8 && total_blocks > 4)
         s_groups = 0;
 
+    const int64_t tokens = ragged ? p.total_tokens : p.b * (int64_t)p.l_d;
+    // Up to 64 documents per CU and two tiles per document on average: a workgroup of two wavefronts per document, four
+    // workgroups per CU resident (512 to 2048 workgroups in all were slower).  At one query (fp16, 64-300 tokens) 1000 / 4000 / 16 000 documents take 12.6 / 32.1 /
+    // 114.7 us instead of 14.3 / 35.2 / 117.3, four queries 142 instead of 147 us at 16 000; at 32 000 documents and four
+    // queries the long runs win (275 against 280 us), with documents of 8-40 tokens already at 20 000 (25.7 against 30.0),
+    // and with two blocks of 512-byte rows, which leave room for one wavefront per SIMD, everywhere (53 against 59 us).
+    if (s_groups == 1 && p.b <= (int64_t)num_cu * 64 && tokens >= p.b * 2 * TILE_ROWS && (nu <= 8 || s_ncb == 1)) {
+        p.n_chunks = 0; // no runs of documents: the kernel takes a document per workgroup
+        p.n_groups = 1;
+        p.qpg = p.n_q;
+        p.n_pass = 1;
+        const int64_t resident = (int64_t)num_cu * 4;
+        return run(false, s_ncb, (int)(p.b < resident ? p.b : resident));
+    }
     if (s_groups > 0) {
         // one work chunk per group of wavefronts; enough chunks to oversubscribe the chip a few times, but no
         // chunk smaller than about 2K tokens -- unless that leaves wavefront slots empty (a small corpus is a chain
         // of memory latencies per wavefront): then chunks go down to 128 tokens until every slot has one
-        const int64_t tokens = ragged ? p.total_tokens : p.b * (int64_t)p.l_d;
         int64_t want = (int64_t)num_cu * 16 * 4 / s_groups;
         int64_t by_size = (tokens + 2047) / 2048;
         const int64_t slots = (int64_t)num_cu * 16 / s_groups;

@@ -181,19 +181,11 @@ __device__ __forceinline__ void stream_load_tile(const FwdParams &p, const TileP
         a[u] = *reinterpret_cast<const uint4 *>(ptr + u * 32);
 }
 
+// One tile (operands `a`, first row t0 of its document) against the wavefront's column blocks
 template <int DT, int NCB, bool ARGMAX>
-__device__ __forceinline__ void stream_compute(const FwdParams &p, const Cursor &c,
-                                               StreamState<DT, NCB, ARGMAX> &st,
-                                               const uint4 (&a)[Traits<DT>::NU], int gb0, int lane, int rho, int h)
+__device__ __forceinline__ void stream_tile(StreamState<DT, NCB, ARGMAX> &st, const uint4 (&a)[Traits<DT>::NU], int t0, int h)
 {
     using TR = Traits<DT>;
-    if (c.t0 == 0) {
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-            st.m[cb] = neg_inf();
-            st.idx[cb] = 0;
-        }
-    }
     // two column blocks at a time (two accumulator chains in flight); the scheduling barrier keeps
     // the pairs apart so that only two accumulators are live and more wavefronts fit on a SIMD
 #pragma unroll
@@ -210,29 +202,54 @@ __device__ __forceinline__ void stream_compute(const FwdParams &p, const Cursor 
             if (cb + 1 < NCB)
                 TR::mma(a[u], st.qf[cb + 1][u], acc1);
         }
-        fold_tile<ARGMAX>(acc0, st.m[cb], st.idx[cb], c.t0, h);
+        fold_tile<ARGMAX>(acc0, st.m[cb], st.idx[cb], t0, h);
         if (cb + 1 < NCB)
-            fold_tile<ARGMAX>(acc1, st.m[cb + 1], st.idx[cb + 1], c.t0, h);
+            fold_tile<ARGMAX>(acc1, st.m[cb + 1], st.idx[cb + 1], t0, h);
         if (cb + 2 < NCB)
             __builtin_amdgcn_sched_barrier(0);
     }
+}
 
-    if (c.t0 + TILE_ROWS >= c.len) { // last tile of the document
-        float part[NCB];
+template <int DT, int NCB, bool ARGMAX> __device__ __forceinline__ void stream_reset(StreamState<DT, NCB, ARGMAX> &st)
+{
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-            part[cb] = finish_block<ARGMAX>(p, st.m[cb], st.idx[cb], st.col_valid[cb], gb0 + cb, c.doc, c.len, rho, h);
-        // this wavefront holds whole queries: lane k adds up the blocks of its k-th query in block
-        // order and writes the score
-        float s = 0.0f;
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-            if (cb / p.bpq == lane)
-                s += part[cb];
-        const int q = gb0 / p.bpq + lane;
-        if (lane < NCB / p.bpq && q < p.n_q)
-            p.scores[(int64_t)q * p.ld + c.doc] = s;
+    for (int cb = 0; cb < NCB; ++cb) {
+        st.m[cb] = neg_inf();
+        st.idx[cb] = 0;
     }
+}
+
+// End of a document: scores (and argmax) of the wavefront's queries
+template <int DT, int NCB, bool ARGMAX>
+__device__ __forceinline__ void stream_finish(const FwdParams &p, StreamState<DT, NCB, ARGMAX> &st, int gb0, int64_t doc, int len,
+                                              int lane, int rho, int h)
+{
+    float part[NCB];
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+        part[cb] = finish_block<ARGMAX>(p, st.m[cb], st.idx[cb], st.col_valid[cb], gb0 + cb, doc, len, rho, h);
+    // the wavefront holds whole queries: lane k adds up the blocks of its k-th query in block
+    // order and writes the score
+    float s = 0.0f;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+        if (cb / p.bpq == lane)
+            s += part[cb];
+    const int q = gb0 / p.bpq + lane;
+    if (lane < NCB / p.bpq && q < p.n_q)
+        p.scores[(int64_t)q * p.ld + doc] = s;
+}
+
+template <int DT, int NCB, bool ARGMAX>
+__device__ __forceinline__ void stream_compute(const FwdParams &p, const Cursor &c,
+                                               StreamState<DT, NCB, ARGMAX> &st,
+                                               const uint4 (&a)[Traits<DT>::NU], int gb0, int lane, int rho, int h)
+{
+    if (c.t0 == 0)
+        stream_reset(st);
+    stream_tile(st, a, c.t0, h);
+    if (c.t0 + TILE_ROWS >= c.len) // last tile of the document
+        stream_finish(p, st, gb0, c.doc, c.len, lane, rho, h);
 }
 
 template <int DT, int NCB, bool ARGMAX>
@@ -383,6 +400,115 @@ __global__ void __launch_bounds__(lin_waves<DT>() * 64) fwd_stream_lin_kernel(Fw
         if (!cc.valid)
             break;
         cursor_next_tile(pc, p, off);
+    }
+}
+
+// The streaming kernel for corpora of up to some thousand documents: a workgroup of two wavefronts per document, each
+// taking every other tile.  With a thousand documents a run of one document per wavefront is a chain of memory round
+// trips on a chip that is mostly idle (and the runs of a ragged corpus, equal in tokens, hold up to three documents);
+// here twice as many wavefronts have half as long a chain, and nothing is searched for, since a workgroup's document
+// is its number.  At the end of a document the two sets of maxima (and winners) meet in LDS, lane by lane, and the first
+// wavefront finishes it.  A maximum does not depend on how the tiles were shared out, and of equal ones the lower row
+// wins, so scores and winners are those of the other kernels.  Four wavefronts per document were no faster (they
+// read the queries twice as often): ragged fp16 texts of 64-300 tokens, four queries, 1000 / 4000 documents: 20.8 /
+// 52.9 us one wavefront per run, 17.6 / 42.5 here, 18.7 / 46.1 with four; fp32, one query, 1000 x 128 tokens with
+// winners: 24.0 -> 18.5 us.
+constexpr int SPLIT_WAVES = 2;
+
+template <int DT, int NCB, bool ARGMAX>
+__global__ void __launch_bounds__(SPLIT_WAVES * 64) fwd_stream_split_kernel(FwdParams p, OffsetsPtr off)
+{
+    using TR = Traits<DT>;
+    using LT = LdsTile<DT>;
+    constexpr int NU = TR::NU;
+    constexpr int W = SPLIT_WAVES;
+    constexpr int CPR = TR::ROW_BYTES / 16; // 16-byte chunks (= lanes) per row
+    constexpr int RPI = 64 / CPR;           // rows per load instruction
+    static_assert((ARGMAX ? 2 : 1) * NCB * 64 * 4 <= LT::BYTES, "a wavefront's maxima fit in its tile");
+    __shared__ __attribute__((aligned(16))) char lds_all[W][LT::BYTES];
+    const int lane = threadIdx.x & 63;
+    const int rho = lane & 31, h = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    char *lds = lds_all[w];
+
+    StreamState<DT, NCB, ARGMAX> st;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+        load_q_block<DT>(p, cb, rho, h, st.qf[cb], st.col_valid[cb]);
+
+    const int lrow = lane / CPR, lcol = (lane % CPR) * 16;
+    const int st_off = lrow * LT::ROW_STRIDE + lcol;
+    const int rd_off = rho * LT::ROW_STRIDE + h * 16;
+    for (int doc = blockIdx.x; doc < p.b; doc += gridDim.x) {
+        int64_t start;
+        int len;
+        if (p.offsets) {
+            start = clamp_offset(off[doc], 0, p.total_tokens);
+            len = (int)(clamp_offset(off[doc + 1], start, p.total_tokens) - start);
+        } else {
+            start = (int64_t)doc * p.l_d;
+            len = p.l_d;
+        }
+        if (len <= 0) {
+            write_empty_docs(p, doc, doc + 1, threadIdx.x, W * 64);
+            continue;
+        }
+        const char *base = p.D + start * TR::ROW_BYTES + lcol;
+        uint4 g[NU], a[NU];
+        auto load_lin = [&](int t0) { // rows past the document's end repeat its last token
+#pragma unroll
+            for (int i = 0; i < NU; ++i) {
+                const int row = min(t0 + i * RPI + lrow, len - 1);
+                g[i] = load_stream16(base + (int64_t)row * TR::ROW_BYTES);
+            }
+        };
+        stream_reset(st);
+        int t0 = w * TILE_ROWS;
+        if (t0 < len) {
+            load_lin(t0);
+            for (;;) {
+#pragma unroll
+                for (int i = 0; i < NU; ++i)
+                    *reinterpret_cast<uint4 *>(&lds[st_off + i * RPI * LT::ROW_STRIDE]) = g[i];
+                const int next = t0 + W * TILE_ROWS;
+                if (next < len)
+                    load_lin(next);
+#pragma unroll
+                for (int u = 0; u < NU; ++u)
+                    a[u] = *reinterpret_cast<const uint4 *>(&lds[rd_off + u * 32]);
+                stream_tile(st, a, t0, h);
+                if (next >= len)
+                    break;
+                t0 = next;
+            }
+        }
+        // the maxima take the place of the wavefront's own tile
+        float *mine = reinterpret_cast<float *>(lds);
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) {
+            mine[cb * 64 + lane] = st.m[cb];
+            if (ARGMAX)
+                mine[(NCB + cb) * 64 + lane] = __int_as_float(st.idx[cb]);
+        }
+        __syncthreads();
+        if (w == 0) {
+#pragma unroll
+            for (int x = 1; x < W; ++x) {
+                const float *other = reinterpret_cast<const float *>(lds_all[x]);
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) {
+                    const float mo = other[cb * 64 + lane];
+                    if (ARGMAX) {
+                        const int io = __float_as_int(other[(NCB + cb) * 64 + lane]);
+                        const bool take = mo > st.m[cb] || (mo == st.m[cb] && io < st.idx[cb]);
+                        st.idx[cb] = take ? io : st.idx[cb];
+                    }
+                    st.m[cb] = fmaxf(st.m[cb], mo);
+                }
+            }
+            stream_finish(p, st, 0, doc, len, lane, rho, h);
+        }
+        __syncthreads(); // the tiles are overwritten by the next document
     }
 }
 
@@ -1148,6 +1274,10 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
 template <int DT, int NCB, bool ARGMAX>
 static hipError_t launch_stream(const FwdParams &p, int grid, hipStream_t stream)
 {
+    if (p.n_chunks == 0) { // small corpus: a workgroup per document
+        hipLaunchKernelGGL((fwd_stream_split_kernel<DT, NCB, ARGMAX>), dim3(grid), dim3(SPLIT_WAVES * 64), 0, stream, p, p.offsets);
+        return hipGetLastError();
+    }
     if (p.n_groups == 1) { // one wavefront per run: whole-line loads through LDS
         constexpr int WPB = lin_waves<DT>();
         const int grid_lin = (p.n_chunks + WPB - 1) / WPB;

@@ -259,6 +259,26 @@ def test_mid_block_counts_on_many_documents(ragged, n_q, l_q, want_argmax, dtype
         forward_parity_uniform(Q, D, M.maxsim_forward, want_argmax, rtol)
 
 
+# Small corpora take a workgroup per document, whose two wavefronts share its tiles: documents of one to five tiles
+# (an empty second wavefront, uneven shares, ragged ends), every number of column blocks, more documents than
+# workgroups; fp32 accumulation of 128 products and a sum of at most 128 maxima: 1e-5 relative
+@pytest.mark.parametrize("dtype,n_q,l_q", [("f16", 1, 32), ("bf16", 2, 30), ("f16", 1, 90), ("bf16", 4, 32), ("f32", 1, 17)])
+@pytest.mark.parametrize("want_argmax", [False, True])
+def test_a_workgroup_per_document(dtype, n_q, l_q, want_argmax):
+    lens = [64, 65, 1, 32, 33, 0, 95, 96, 97, 128, 129, 160, 2, 300] * 2 + [70] * 3
+    Q, Dp, off = _ragged_case(n_q, l_q, lens, dtype, 71)
+    forward_parity_ragged(Q, Dp, off, M.maxsim_forward_ragged, want_argmax, 1e-5)
+    for b, l_d in ((3, 64), (5, 100), (1, 1000)):
+        D = W.unit_rows((b, l_d, 128), dtype, 72 + b, DEV)
+        forward_parity_uniform(Q, D, M.maxsim_forward, want_argmax, 1e-5)
+
+
+def test_more_documents_than_workgroups():
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 4 + 13
+    Q, D = W.unit_rows((2, 32, 128), "f16", 81, DEV), W.unit_rows((n, 66, 128), "f16", 82, DEV)
+    forward_parity_uniform(Q, D, M.maxsim_forward, True, 1e-5)
+
+
 @pytest.mark.parametrize("b", [1, 2, 62, 63, 64, 65, 128, 4094, 4095, 4096, 4160])
 def test_runs_of_documents_are_found(b):
     """Where a run of a ragged corpus begins is searched for with 64 probes a step: numbers of documents around the powers of 64."""
