@@ -31,6 +31,7 @@ hipError_t forward_i8_launch(const int8_t *Q, const float *qs, int n_q, int l_q,
                              int64_t ld, int num_cu, hipStream_t stream);
 hipError_t ce_grad_launch(const float *scores, int n, int b, float tau, float *g, float *loss, hipStream_t stream);
 hipError_t forward_splitd_init_device();
+hipError_t forward_wide_init_device();
 hipError_t forward_i8_init_device();
 hipError_t backward_init_device();
 } // namespace maxsim
@@ -93,8 +94,8 @@ int ensure_init()
         return MAXSIM_ERR_LAUNCH;
     if (done[dev])
         return MAXSIM_OK;
-    if (maxsim::forward_splitd_init_device() != hipSuccess || maxsim::forward_i8_init_device() != hipSuccess ||
-        maxsim::backward_init_device() != hipSuccess)
+    if (maxsim::forward_wide_init_device() != hipSuccess || maxsim::forward_splitd_init_device() != hipSuccess ||
+        maxsim::forward_i8_init_device() != hipSuccess || maxsim::backward_init_device() != hipSuccess)
         return MAXSIM_ERR_LAUNCH;
     done[dev] = true;
     return MAXSIM_OK;

@@ -11,6 +11,7 @@ hipError_t forward_run_f32(const FwdParams &p, int nu, bool argmax, bool tile, i
 static int round_up(int64_t x, int m) { return (int)((x + m - 1) / m * m); }
 
 hipError_t forward_splitd_launch(FwdParams p, int dtype, int row_bytes, int num_cu, hipStream_t stream);
+hipError_t forward_wide_launch(FwdParams p, int dtype, int row_bytes, int num_cu, hipStream_t stream);
 
 constexpr int MAX_ROW_BYTES = 16384; // d = 8192 (16-bit) or 4096 (fp32)
 
@@ -37,10 +38,18 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         return hipErrorNotSupported;
     const int row_bytes = d * (dtype == MAXSIM_F32 ? 4 : 2);
     // any other width: both operands stream through LDS in slabs of the width; so do rows of 512 bytes from 8 column
-    // blocks on (two blocks per wavefront in the register-stationary kernel: measured 3-11 % slower there)
+    // blocks on (two blocks per wavefront in the register-stationary kernel: measured 3-11 % slower there).  Macro tiles
+    // of 256 query tokens and whole cache lines (forward_wide.hip), except where a document is little work: narrow rows
+    // and documents of 65-128 tokens with more than 8 blocks, which then go by 512 query tokens at once (20 000 x 100
+    // tokens, 16 blocks, d = 256 / 160: 790 / 515 us in slabs of half a line, 800 / 573 in whole ones; 8 blocks, d = 96:
+    // 258 against 222; 100 000 x 10 tokens, 16 blocks, d = 96: 1335 against 1250), or of half a line with 8 and more (d = 32: 113 against 121).
     const int64_t all_blocks = (int64_t)p.n_q * ((p.l_q + BLOCK_COLS - 1) / BLOCK_COLS);
-    if (!register_stationary_width(row_bytes) || (row_bytes == 512 && all_blocks >= 8))
-        return forward_splitd_launch(p, dtype, row_bytes, num_cu, stream);
+    if (!register_stationary_width(row_bytes) || (row_bytes == 512 && all_blocks >= 8)) {
+        const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b; // (uniform corpora: total_tokens = b * l_d)
+        const bool little = dtype != MAXSIM_F32 && mean_len <= 128 &&
+                            ((all_blocks > 8 && row_bytes <= 512 && mean_len > 64) || (all_blocks >= 8 && row_bytes == 64));
+        return little ? forward_splitd_launch(p, dtype, row_bytes, num_cu, stream) : forward_wide_launch(p, dtype, row_bytes, num_cu, stream);
+    }
     const int nu = row_bytes / 32; // 16-byte chunk pairs per row
     const bool ragged = p.offsets != nullptr;
     const bool am = p.argmax != nullptr;

@@ -192,6 +192,31 @@ def test_ragged_split_d(n_q, l_q, dtype, d):
     forward_parity_ragged(Q, Dp, off, M.maxsim_forward_ragged, True, RTOL_F32 if dtype == "f32" else RTOL_16)
 
 
+# The wide kernel's shapes: by column blocks of a workgroup (1, 2, 4, 6, 8; one query of 9 and of 19 blocks in several
+# passes; groups of unequal numbers of queries) and by the documents' length (macro tiles of 64, 128 and 256 rows: one
+# row either side of them, a single tile, several); widths of one, two and several slabs of 128 bytes, with and without a half one.
+# fp32 accumulation of at most 384 products and sums of at most 600 maxima: 1e-5 relative to the score
+@pytest.mark.parametrize("n_q,l_q", [(1, 30), (2, 32), (3, 40), (3, 60), (1, 256), (5, 50), (1, 270), (1, 600)])
+@pytest.mark.parametrize("l_d", [1, 32, 64, 65, 128, 129, 255, 256, 257, 545])
+def test_wide_shapes(l_d, n_q, l_q):
+    for dtype, d, want_argmax in (("f16", 160, False), ("bf16", 384, True), ("f32", 48, True)):
+        Q = W.unit_rows((n_q, l_q, d), dtype, 61 + l_q, DEV)
+        D = W.unit_rows((5, l_d, d), dtype, 62 + l_d, DEV)
+        forward_parity_uniform(Q, D, M.maxsim_forward, want_argmax, 1e-5)
+
+
+@pytest.mark.parametrize("n_q,l_q", [(1, 20), (2, 130), (1, 300)])
+def test_wide_many_documents(n_q, l_q):
+    """More documents than workgroups, ragged and uniform: a workgroup goes from one document to the next."""
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 2 + 7
+    lens = np.random.default_rng(l_q).integers(0, 300, n)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV)
+    Dp = W.unit_rows((int(lens.sum()), 96), "f16", 63, DEV)
+    Q = W.unit_rows((n_q, l_q, 96), "f16", 64, DEV)
+    forward_parity_ragged(Q, Dp, off, M.maxsim_forward_ragged, True, 1e-5)
+    forward_parity_uniform(Q, W.unit_rows((n, 70, 96), "f16", 65, DEV), M.maxsim_forward, False, 1e-5)
+
+
 # Ragged corpora scored by more than 16 queries of one column block take 32-row windows over the packed rows (a window
 # may hold the end of one document and the start of the next).  Length mixes: runs of tiny documents (several
 # boundaries close together, a document that lies inside one window whole), empty documents at the start, in a row
