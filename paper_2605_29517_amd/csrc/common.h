@@ -186,6 +186,13 @@ __device__ __forceinline__ void cursor_next_tile(Cursor &c, const FwdParams &p, 
         cursor_next_doc(c, p, off);
 }
 
+// Workgroup ids are dealt round-robin to the 8 XCDs.  This renumbering of n ids gives every XCD a contiguous range.
+__device__ __forceinline__ int xcd_grouped(unsigned id, unsigned n)
+{
+    const unsigned xcd = id & 7;
+    return (int)(xcd * (n >> 3) + (xcd < (n & 7) ? xcd : n & 7) + (id >> 3));
+}
+
 // Documents [doc0, doc1) of work chunk `chunk`.  Uniform corpus: equal document counts.
 // Ragged corpus: the packed token range is cut into equal pieces and a chunk owns every
 // document that starts inside its piece (binary search over the offsets).
@@ -259,6 +266,34 @@ __device__ __forceinline__ void chunk_doc_range(const FwdParams &p, int64_t chun
         if (doc1 > p.b)
             doc1 = p.b;
     }
+}
+
+// How a corpus is cut into chunks for `groups` column groups when `slots` workgroups are resident at a time: units
+// (documents, or tokens of a ragged corpus) per chunk.  Of 1 to 8 rounds of workgroups over the chip the number with which
+// the slot that has the most to do is done first.  A workgroup costs what about 200 tokens do beside its documents
+// (its query fragments and the first loads), and a chunk of a ragged corpus may be half a document longer than its
+// share.  `time`: of that slot, in tokens.
+struct ChunkPlan {
+    int64_t per_chunk, n_chunks, time;
+};
+inline ChunkPlan plan_chunks(const FwdParams &p, int64_t groups, int64_t slots)
+{
+    const bool ragged = p.offsets != nullptr;
+    const int64_t units = ragged ? p.total_tokens : p.b;
+    const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b; // (uniform: l_d)
+    ChunkPlan best = {1, 1, INT64_MAX};
+    for (int64_t rounds = 1; rounds <= 8; ++rounds) {
+        int64_t chunks = slots * rounds / groups;
+        chunks = chunks < 1 ? 1 : chunks > p.b ? p.b : chunks;
+        int64_t per = (units + chunks - 1) / chunks;
+        per = per < 1 ? 1 : per;
+        const int64_t n = units < 1 ? 1 : (units + per - 1) / per;
+        const int64_t tokens = ragged ? (per > mean_len ? per : mean_len) + mean_len / 2 : per * mean_len;
+        const int64_t time = (n * groups + slots - 1) / slots * (tokens + 200);
+        if (time < best.time)
+            best = {per, n, time};
+    }
+    return best;
 }
 
 // Walks the tiles (32 tokens unless told otherwise) of documents [doc, doc_end), the same in every lane.  All

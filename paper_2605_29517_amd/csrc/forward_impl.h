@@ -637,10 +637,7 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
     // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Renumber so
     // that the column groups sharing a document chunk are neighbours on one XCD and run at
     // the same time: the chunk then comes from HBM once and from L2 for the other groups.
-    const int n_wg = gridDim.x;
-    int v = blockIdx.x;
-    if ((n_wg & 7) == 0)
-        v = (blockIdx.x & 7) * (n_wg >> 3) + (blockIdx.x >> 3);
+    const int v = xcd_grouped(blockIdx.x, gridDim.x);
     const int group = v % p.n_groups;
     const int chunk = v / p.n_groups;
 
@@ -1053,10 +1050,7 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
     const int rho = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    const int n_wg = gridDim.x;
-    int v = blockIdx.x;
-    if ((n_wg & 7) == 0)
-        v = (blockIdx.x & 7) * (n_wg >> 3) + (blockIdx.x >> 3);
+    const int v = xcd_grouped(blockIdx.x, gridDim.x);
     const int group = v % p.n_groups;
     const int chunk = v / p.n_groups;
 
@@ -1120,7 +1114,8 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
             static_for<CPT>([&](auto i) {
                 const int wr = cp_row(i);
                 const int row = wr < lw.pa ? min(wr, lw.n_a - 1) : lw.n_a + min(wr - lw.pa, lw.n_b - 1);
-                g(i) = *reinterpret_cast<const uint4 *>(base + row * TR::ROW_BYTES + cp_goff(i));
+                // (read once, or by a few workgroups at the same time: 2-5 % at five to sixteen queries)
+                g(i) = load_stream16(base + row * TR::ROW_BYTES + cp_goff(i));
             });
         }
         win_advance<UNI>(li, lw, p, off);

@@ -116,8 +116,7 @@ __global__ void __launch_bounds__(WD_W * 64) fwd_wide_kernel(FwdParams p, Offset
 
     // Workgroup ids are dealt round-robin to the 8 XCDs: every XCD takes a contiguous range of (chunk, group), so that
     // the column groups that share a document chunk meet in one L2
-    const unsigned n_wg = gridDim.x, xcd = blockIdx.x & 7;
-    const int v = (int)(xcd * (n_wg >> 3) + min(xcd, n_wg & 7) + (blockIdx.x >> 3));
+    const int v = xcd_grouped(blockIdx.x, gridDim.x);
     const int group = v % p.n_groups;
     const int chunk = v / p.n_groups;
 
@@ -471,26 +470,7 @@ hipError_t forward_wide_launch(FwdParams p, int dtype, int row_bytes, int num_cu
     p.bpq = (p.l_q + BLOCK_COLS - 1) / BLOCK_COLS;
     if (p.ld == 0)
         p.ld = p.b;
-    // One workgroup per CU at a time.  Uniform corpus: of 1 to 8 rounds of workgroups over the chip the number that
-    // leaves the least of the last one idle; ragged: about four chunks per CU so that the tail is short.
-    const bool ragged = p.offsets != nullptr;
-    const int64_t units = ragged ? p.total_tokens : p.b;
-    int64_t best = 1;
-    auto split = [&](int64_t groups, int64_t &per_chunk) { // time of the longest CU, in units
-        int64_t best_cost = INT64_MAX;
-        for (int64_t rounds = ragged ? 4 : 1; rounds <= (ragged ? 4 : 8); ++rounds) {
-            int64_t chunks = (int64_t)num_cu * rounds / groups;
-            chunks = chunks < 1 ? 1 : chunks > p.b ? p.b : chunks;
-            const int64_t per = (units + chunks - 1) / chunks;
-            const int64_t need = per > 0 ? (units + per - 1) / per : 1;
-            const int64_t cost = (need * groups + num_cu - 1) / num_cu * per;
-            if (cost < best_cost) {
-                best_cost = cost;
-                per_chunk = per;
-            }
-        }
-        return best_cost;
-    };
+    ChunkPlan plan = {1, 1, 0}; // (one workgroup per CU at a time)
     int blocks = 0, blocks_per_pass = 0; // the workgroup's column blocks
     if (p.bpq <= WD_MAX_BLOCKS) {
         // Whole queries per workgroup.  More of them read a document less often, fewer make more workgroups, which
@@ -503,11 +483,11 @@ hipError_t forward_wide_launch(FwdParams p, int dtype, int row_bytes, int num_cu
             if (qpg > 1 && (p.n_q + groups - 1) / groups < qpg)
                 continue; // fewer queries in each of as many groups will do
             const int nb = qpg * p.bpq;
-            int64_t per = 1;
-            const int64_t time = split(groups, per) * (nb <= 1 ? 60 : nb <= 2 ? 65 : nb <= 4 ? 80 : nb <= 6 ? 105 : 127);
+            const ChunkPlan c = plan_chunks(p, groups, num_cu);
+            const int64_t time = c.time * (nb <= 1 ? 60 : nb <= 2 ? 65 : nb <= 4 ? 80 : nb <= 6 ? 105 : 127);
             if (time < best_time) {
                 best_time = time;
-                best = per;
+                plan = c;
                 p.qpg = qpg;
                 p.n_groups = groups;
                 blocks = nb;
@@ -519,14 +499,13 @@ hipError_t forward_wide_launch(FwdParams p, int dtype, int row_bytes, int num_cu
         p.n_pass = (p.bpq + WD_MAX_BLOCKS - 1) / WD_MAX_BLOCKS;
         blocks = blocks_per_pass = (p.bpq + p.n_pass - 1) / p.n_pass;
         p.n_pass = (p.bpq + blocks - 1) / blocks;
-        (void)split(p.n_groups, best);
+        plan = plan_chunks(p, p.n_groups, num_cu);
     }
-    p.unit_per_chunk = best < 1 ? 1 : best;
-    const int64_t n_chunks = units < 1 ? 1 : (units + p.unit_per_chunk - 1) / p.unit_per_chunk;
-    p.n_chunks = (int)n_chunks;
-    if (n_chunks * p.n_groups >= (int64_t(1) << 31))
+    p.unit_per_chunk = plan.per_chunk;
+    p.n_chunks = (int)plan.n_chunks;
+    if (plan.n_chunks * p.n_groups >= (int64_t(1) << 31))
         return hipErrorInvalidValue;
-    const int grid = (int)(n_chunks * p.n_groups);
+    const int grid = (int)(plan.n_chunks * p.n_groups);
     const bool am = p.argmax != nullptr;
     const int rows = (int)((p.total_tokens + p.b - 1) / p.b); // the mean length (uniform corpora: total_tokens = b * l_d)
     switch (dtype) {

@@ -192,6 +192,16 @@ def test_ragged_split_d(n_q, l_q, dtype, d):
     forward_parity_ragged(Q, Dp, off, M.maxsim_forward_ragged, True, RTOL_F32 if dtype == "f32" else RTOL_16)
 
 
+# Chunk counts that are no multiple of the 8 XCDs, one and several rounds of workgroups, fewer documents than chunks asked for
+@pytest.mark.parametrize("n_q,l_q,b,l_d", [(20, 300, 60, 33), (3, 700, 37, 40), (33, 32, 301, 20), (1, 130, 509, 64), (2, 1100, 11, 70)])
+def test_chunk_counts(n_q, l_q, b, l_d):
+    Q = W.unit_rows((n_q, l_q, 128), "f16", 66, DEV)
+    forward_parity_uniform(Q, W.unit_rows((b, l_d, 128), "f16", 67, DEV), M.maxsim_forward, True, RTOL_16)
+    lens = np.random.default_rng(b).integers(0, 2 * l_d, b)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV)
+    forward_parity_ragged(Q, W.unit_rows((int(lens.sum()), 128), "f16", 68, DEV), off, M.maxsim_forward_ragged, False, RTOL_16)
+
+
 # The wide kernel's shapes: by column blocks of a workgroup (1, 2, 4, 6, 8; one query of 9 and of 19 blocks in several
 # passes; groups of unequal numbers of queries) and by the documents' length (macro tiles of 64, 128 and 256 rows: one
 # row either side of them, a single tile, several); widths of one, two and several slabs of 128 bytes, with and without a half one.
