@@ -273,6 +273,9 @@ __global__ void __launch_bounds__(W * 64, W >= 4 ? 2 : 1) fwd_i8_kernel(I8Params
 // this lane's accumulator registers".
 constexpr int I8D_WAVES = 8;
 constexpr int I8D_LIN_BLOCKS = 2;                        // up to this many column blocks the tiles are read as whole lines (no gain from 4 on)
+constexpr int I8D_DEPTH = 2;                             // tiles in flight per wavefront (up to 16 blocks; beyond, a tile takes long enough): 128 tokens x 8000 x 300 66 -> 60 us
+constexpr int i8d_depth(int nb) { return nb <= 16 ? I8D_DEPTH : 1; }
+constexpr int I8D_SPLIT_BLOCKS = 16;                     // column blocks per group of the kernel whose wavefronts share documents
 constexpr int I8D_MAX_BLOCKS = 32;                       // column blocks per group (1024 query tokens)
 constexpr int I8D_QSTRIDE = I8_ROW_BYTES + 16;           // padded LDS row of a query token
 
@@ -307,7 +310,10 @@ __device__ __forceinline__ void i8d_tile_scales(float *w_scale, float *w_bias, f
 // scales and biases); the whole-line variant adds a document tile per wavefront
 constexpr size_t i8_doc_lds(int nb) { return (size_t)nb * BLOCK_COLS * (I8D_QSTRIDE + 4) + I8D_WAVES * 64 * sizeof(float); }
 constexpr size_t i8_doc_lin_lds(int nb) { return i8_doc_lds(nb) + (size_t)I8D_WAVES * TILE_ROWS * I8D_QSTRIDE; }
-constexpr size_t i8_split_lds(int nb) { return i8_doc_lds(nb) + (size_t)2 * I8D_WAVES * nb * BLOCK_COLS * sizeof(float); }
+constexpr size_t i8_split_lds(int nb, int w)
+{
+    return (size_t)nb * BLOCK_COLS * (I8D_QSTRIDE + 4) + w * 64 * sizeof(float) + (size_t)2 * w * nb * BLOCK_COLS * sizeof(float);
+}
 
 constexpr int I8D_LAG_STEPS = 2; // steps between a block's MFMAs and its epilogue in the document-stationary kernels
 
@@ -352,6 +358,35 @@ __device__ __forceinline__ void i8d_tile_blocks(const i32x4 (&a)[I8_NU], const f
     }
 }
 
+// Cross-lane steps on the VALU: a shuffle goes through the LDS, and ten in a row per query at the end of every document
+// (five steps of an fp64 butterfly) took longer than the document's MFMAs (4 / 8 queries x 100 000 / 50 000
+// texts: 570 -> 533, 440 -> 409 us).
+__device__ __forceinline__ float max_halves(float x) // both lane halves get the maximum of the two
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int N> __device__ __forceinline__ double add_rotated(double v) // + the value N lanes on within the row of sixteen
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x120 + N, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), 0x120 + N, 0xf, 0xf, true);
+    return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// Sum over lanes 0 .. 31 (lanes 32 .. 63 hold the same): a butterfly over distances 16, 8, 4, 2, 1.  Once the lanes repeat with
+// period 2N, the lane N away by XOR and the one N away by rotation hold the same value.
+__device__ __forceinline__ double sum32(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    v = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) + __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+    v = add_rotated<8>(v);
+    v = add_rotated<4>(v);
+    v = add_rotated<2>(v);
+    return add_rotated<1>(v);
+}
+
 // End of a document: mm[blk] is the maximum per query token (column rho of block blk; in lanes 0..31 and again
 // in lanes 32..63) in the halved-negatives form of the seeded accumulator.  Per query: one IEEE fp32 multiply
 // by the query scale per token, a lane-local fp64 sum over the query's blocks, one butterfly over the 32
@@ -372,9 +407,7 @@ __device__ __forceinline__ void i8d_finish(const I8Params &P, const float (&mmv)
         float r = q_scale[blk * BLOCK_COLS + rho] * mm;    // one IEEE fp32 multiply per query token
         dv += (iq * BLOCK_COLS + rho < p.l_q) ? (double)r : 0.0;
         if (++iq == p.bpq) {
-#pragma unroll
-            for (int o = 16; o > 0; o >>= 1)
-                dv += __shfl_xor(dv, o);
+            dv = sum32(dv);
             if (lane == 0)
                 P.scores[(int64_t)(q_first + j) * p.ld + doc] = (float)dv;
             dv = 0.0;
@@ -385,11 +418,11 @@ __device__ __forceinline__ void i8d_finish(const I8Params &P, const float (&mmv)
 }
 
 // Copies the group's query rows (padded) and scales (0 for padding columns) into LDS.
-template <int NB>
+template <int NB, int W>
 __device__ __forceinline__ void i8d_load_queries(const I8Params &P, char *q_tile, float *q_scale, int gb0, int nb, int tid)
 {
     const FwdParams &p = P.f;
-    for (int c = tid; c < NB * BLOCK_COLS * 8; c += I8D_WAVES * 64) { // 16-byte chunks of the group's query rows
+    for (int c = tid; c < NB * BLOCK_COLS * 8; c += W * 64) { // 16-byte chunks of the group's query rows
         int col = c >> 3, part = c & 7;
         uint4 chunk = make_uint4(0, 0, 0, 0);
         float qsv = 0.0f;
@@ -417,7 +450,7 @@ __device__ __forceinline__ void i8d_load_queries(const I8Params &P, char *q_tile
 // is read as such, with four non-temporal loads of 1 KB (eight lanes per row), parked in a piece of LDS of the
 // wavefront's own and read back in operand layout; the direct loads take 32 bytes of each of 32 lines per
 // instruction and cannot carry the hint (see load_stream16).
-template <int NB, bool LIN>
+template <int NB, bool LIN, int DEPTH>
 __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, OffsetsPtr off)
 {
     const FwdParams &p = P.f;
@@ -442,7 +475,7 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, 
     float *w_bias = w_scale + 32;
     char *w_tile = smem + i8_doc_lds(NB) + w * (TILE_ROWS * I8D_QSTRIDE); // LIN only: this wavefront's document tile
 
-    i8d_load_queries<NB>(P, q_tile, q_scale, gb0, nb, tid);
+    i8d_load_queries<NB, I8D_WAVES>(P, q_tile, q_scale, gb0, nb, tid);
     __syncthreads(); // the only barrier: from here on every wavefront is on its own
 
     int64_t doc0_, doc1_;
@@ -463,32 +496,37 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, 
     if (!it_valid(ci))
         return;
 
-    i32x4 a_n[I8_NU]; // LIN: piece i holds 16 bytes of row 8 i + lane / 8, else chunk 2 u + h of row rho
-    float s_n = 0.0f;
-    auto gload = [&]() {
-        if (!it_valid(li))
-            return;
-        const int last = li.len - li.t0 - 1; // rows past the document re-read its last token
-        const int row = rho < last ? rho : last;
-        const int64_t grow = (int64_t)li.row0 + row;
+    // DEPTH tiles in flight.  LIN: piece i holds 16 bytes of row 8 i + lane / 8, else chunk 2 u + h of row rho
+    i32x4 a_n[DEPTH][I8_NU];
+    float s_n[DEPTH];
+    int l_row0 = 0, l_last = 0; // past the end of the run the last tile is loaded again: a load that may not be there would
+                                // make every wait one for all of them
+    auto gload = [&](auto set) {
+        constexpr int X = decltype(set)::value;
+        if (it_valid(li)) {
+            l_row0 = li.row0;
+            l_last = li.len - li.t0 - 1; // rows past the document re-read its last token
+            it_next(li, p, off);
+        }
+        const int row = rho < l_last ? rho : l_last;
+        const int64_t grow = (int64_t)l_row0 + row;
         if constexpr (LIN) {
 #pragma unroll
             for (int i = 0; i < I8_NU; ++i) {
                 int r = i * 8 + (lane >> 3);
-                r = r < last ? r : last;
-                const uint4 t = load_stream16(P.D + ((int64_t)li.row0 + r) * I8_ROW_BYTES + (lane & 7) * 16);
-                a_n[i] = i32x4{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
+                r = r < l_last ? r : l_last;
+                const uint4 t = load_stream16(P.D + ((int64_t)l_row0 + r) * I8_ROW_BYTES + (lane & 7) * 16);
+                a_n[X][i] = i32x4{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
             }
         } else {
             const char *src = P.D + grow * I8_ROW_BYTES + h * 16;
 #pragma unroll
             for (int u = 0; u < I8_NU; ++u)
-                a_n[u] = *reinterpret_cast<const i32x4 *>(src + u * 32);
+                a_n[X][u] = *reinterpret_cast<const i32x4 *>(src + u * 32);
         }
-        s_n = P.ds[grow];
-        it_next(li, p, off);
+        s_n[X] = P.ds[grow];
     };
-    gload();
+    static_for<DEPTH>(gload);
 
     i32x16 seed;
 #pragma unroll
@@ -501,20 +539,21 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, 
     float m[NB];
     const int b_off = rho * I8D_QSTRIDE + h * 16; // this lane's B operand chunk 0 inside a block
 
-    while (it_valid(ci)) {
+    auto tile = [&](auto set) {
+        constexpr int X = decltype(set)::value;
         // the prefetched tile becomes the current one; its scales go through the wavefront's LDS area
         i32x4 a[I8_NU];
         if constexpr (LIN) {
 #pragma unroll
             for (int i = 0; i < I8_NU; ++i)
-                *reinterpret_cast<i32x4 *>(w_tile + (i * 8 + (lane >> 3)) * I8D_QSTRIDE + (lane & 7) * 16) = a_n[i];
+                *reinterpret_cast<i32x4 *>(w_tile + (i * 8 + (lane >> 3)) * I8D_QSTRIDE + (lane & 7) * 16) = a_n[X][i];
         } else {
 #pragma unroll
             for (int u = 0; u < I8_NU; ++u)
-                a[u] = a_n[u];
+                a[u] = a_n[X][u];
         }
-        const float s_cur = s_n;
-        gload(); // next tile, in flight during this one
+        const float s_cur = s_n[X];
+        gload(set); // the tile DEPTH further on, in flight during this one
         if constexpr (LIN) {
 #pragma unroll
             for (int u = 0; u < I8_NU; ++u)
@@ -534,25 +573,35 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, 
             float mm[NB];
 #pragma unroll
             for (int blk = 0; blk < NB; ++blk)
-                mm[blk] = fmaxf(m[blk], __shfl_xor(m[blk], 32));
+                mm[blk] = max_halves(m[blk]);
             i8d_finish<NB>(P, mm, q_scale, nb, q_first, ci.doc, lane, rho);
         }
         it_next(ci, p, off);
+    };
+    for (;;) {
+        tile(std::integral_constant<int, 0>{});
+        if (!it_valid(ci))
+            break;
+        if constexpr (DEPTH > 1) {
+            tile(std::integral_constant<int, 1>{});
+            if (!it_valid(ci))
+                break;
+        }
     }
 }
 
 // ---------------------------------------------------------------------------------------
-// the same for uniform corpora too small to give every wavefront documents of its own
+// the same for corpora too small to give every wavefront documents of its own
 // ---------------------------------------------------------------------------------------
-// With a thousand long documents and a short query the corpus read is the cost, and a wavefront per document
-// would leave most of the chip idle.  Here a workgroup takes documents one after the other and its eight
-// wavefronts share each document's tiles (wavefront w the w-th eighth); the query tokens sit in LDS as above and
-// every wavefront still streams its tiles HBM -> registers, one tile ahead, across document borders.  At the end
-// of a document the eight partial maxima per query token meet in LDS (double-buffered, one barrier per
-// document) and one wavefront, a different one each time, finishes the score.  Built for up to 16 column
-// blocks (512 query tokens): beyond that the maxima of eight wavefronts no longer fit beside the queries in LDS.
-template <int NB>
-__global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_split_kernel(I8Params P)
+// With a thousand documents and a short query the corpus read is the cost, and a wavefront per document would leave most
+// of the chip idle.  Here a workgroup takes documents one after the other and its W wavefronts share each document's
+// tiles, every W-th each; the query tokens sit in LDS as above and every wavefront still streams its tiles HBM ->
+// registers, one tile ahead, across document borders.  At the end of a document the W partial maxima per query token
+// meet in LDS (double-buffered, one barrier per document) and one wavefront, a different one each time, finishes the
+// score.  Built for up to 16 column blocks (512 query tokens): beyond that the maxima of eight wavefronts no longer fit
+// beside the queries in LDS.
+template <int NB, int W>
+__global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, OffsetsPtr off)
 {
     const FwdParams &p = P.f;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -569,50 +618,59 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_split_kernel(I8Params P
     const int nb = nq * p.bpq;
 
     // LDS: query rows and scales, per wavefront 32 token scales and 32 biases, then the partial maxima
-    // comb[2][8 wavefronts][NB][32 columns]
+    // comb[2][W wavefronts][NB][32 columns]
     char *q_tile = smem;
     float *q_scale = reinterpret_cast<float *>(smem + NB * BLOCK_COLS * I8D_QSTRIDE);
     float *w_scale = q_scale + NB * BLOCK_COLS + w * 64;
     float *w_bias = w_scale + 32;
-    float *comb = q_scale + NB * BLOCK_COLS + I8D_WAVES * 64;
-    i8d_load_queries<NB>(P, q_tile, q_scale, gb0, nb, tid);
+    float *comb = q_scale + NB * BLOCK_COLS + W * 64;
+    i8d_load_queries<NB, W>(P, q_tile, q_scale, gb0, nb, tid);
     __syncthreads();
 
     int64_t doc0_, doc1_;
     chunk_doc_range(p, chunk, doc0_, doc1_);
     if (doc0_ >= doc1_)
         return;
-    const int doc0 = (int)doc0_, n_docs = (int)(doc1_ - doc0_);
+    const int doc0 = (int)doc0_, doc1 = (int)doc1_;
 
-    // this wavefront's tiles of every document: [t_lo, t_lo + cnt)
-    const int n_tiles = (p.l_d + TILE_ROWS - 1) / TILE_ROWS;
-    const int t_lo = w * (n_tiles / I8D_WAVES) + min(w, n_tiles % I8D_WAVES);
-    const int cnt = n_tiles / I8D_WAVES + (w < n_tiles % I8D_WAVES ? 1 : 0);
-
-    // the loader walks (document, tile) pairs in order; past the end it stays on the last pair
+    // first row and length of a document (offsets forced into the corpus, see clamp_offset)
+    auto extent = [&](int doc, int &first, int &len) {
+        if (p.offsets) {
+            const int t_all = (int)p.total_tokens;
+            first = min(max(off[doc], 0), t_all);
+            len = min(max(off[doc + 1], first), t_all) - first;
+        } else {
+            first = doc * p.l_d;
+            len = p.l_d;
+        }
+    };
+    // the loader walks this wavefront's tiles (every W-th of a document) in order; past the end it stays on the last one
     i32x4 a_n[I8_NU];
     float s_n = 0.0f;
-    int ld_doc = 0, ld_t = 0; // document (relative to doc0) and tile (relative to t_lo) of the next load
+    int l_doc = doc0, l_first, l_len, l_t0 = w * TILE_ROWS;
+    extent(l_doc, l_first, l_len);
+    int l_row = 0, l_last = 0;
     auto gload = [&]() {
-        if (cnt == 0)
-            return;
-        const int t0 = (t_lo + ld_t) * TILE_ROWS;
-        int row = p.l_d - t0 - 1; // rows past the document re-read its last token
-        row = rho < row ? rho : row;
-        const int64_t grow = (int64_t)(doc0 + ld_doc) * p.l_d + t0 + row;
+        while (l_doc < doc1 && l_t0 >= l_len) {
+            l_doc += 1;
+            l_t0 = w * TILE_ROWS;
+            if (l_doc < doc1)
+                extent(l_doc, l_first, l_len);
+        }
+        if (l_doc < doc1) {
+            l_row = l_first + l_t0;
+            l_last = l_len - l_t0 - 1; // rows past the document re-read its last token
+            l_t0 += W * TILE_ROWS;
+        }
+        const int64_t grow = (int64_t)l_row + (rho < l_last ? rho : l_last);
         const char *src = P.D + grow * I8_ROW_BYTES + h * 16;
 #pragma unroll
         for (int u = 0; u < I8_NU; ++u)
             a_n[u] = *reinterpret_cast<const i32x4 *>(src + u * 32);
         s_n = P.ds[grow];
-        if (ld_t + 1 < cnt) {
-            ld_t += 1;
-        } else if (ld_doc + 1 < n_docs) {
-            ld_doc += 1;
-            ld_t = 0;
-        }
     };
-    gload();
+    if (p.total_tokens > 0) // (a packed corpus of empty documents has no row to load)
+        gload();
 
     i32x16 seed;
 #pragma unroll
@@ -623,13 +681,20 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_split_kernel(I8Params P
     }
     const int b_off = rho * I8D_QSTRIDE + h * 16;
 
-    int par = 0;
-    for (int d = 0; d < n_docs; ++d) {
+    int par = 0, turn = 0;
+    for (int doc = doc0; doc < doc1; ++doc) {
+        int first, len;
+        extent(doc, first, len);
+        if (len <= 0) { // empty: -inf
+            for (int j = tid; j < nq; j += W * 64)
+                P.scores[(int64_t)(q_first + j) * p.ld + doc] = neg_inf();
+            continue;
+        }
         float m[NB];
 #pragma unroll
         for (int blk = 0; blk < NB; ++blk)
             m[blk] = neg_inf();
-        for (int t = 0; t < cnt; ++t) {
+        for (int t0 = w * TILE_ROWS; t0 < len; t0 += W * TILE_ROWS) {
             i32x4 a[I8_NU];
 #pragma unroll
             for (int u = 0; u < I8_NU; ++u)
@@ -642,34 +707,35 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_split_kernel(I8Params P
         }
         // partial maxima of this wavefront (the halved-negatives form keeps the order, so they can be compared
         // as they are)
-        float *mine = comb + ((par * I8D_WAVES + w) * NB) * BLOCK_COLS;
+        float *mine = comb + ((par * W + w) * NB) * BLOCK_COLS;
 #pragma unroll
         for (int blk = 0; blk < NB; ++blk) {
-            float mm = fmaxf(m[blk], __shfl_xor(m[blk], 32));
+            const float mm = max_halves(m[blk]);
             if (h == 0)
                 mine[blk * BLOCK_COLS + rho] = mm;
         }
         __syncthreads();
-        if (w == (d & (I8D_WAVES - 1))) {
+        if (w == turn) {
             float mm[NB];
 #pragma unroll
             for (int blk = 0; blk < NB; ++blk) {
                 float x = neg_inf();
 #pragma unroll
-                for (int ww = 0; ww < I8D_WAVES; ++ww)
-                    x = fmaxf(x, comb[((par * I8D_WAVES + ww) * NB + blk) * BLOCK_COLS + rho]);
+                for (int ww = 0; ww < W; ++ww)
+                    x = fmaxf(x, comb[((par * W + ww) * NB + blk) * BLOCK_COLS + rho]);
                 mm[blk] = x;
             }
-            i8d_finish<NB>(P, mm, q_scale, nb, q_first, doc0 + d, lane, rho);
+            i8d_finish<NB>(P, mm, q_scale, nb, q_first, doc, lane, rho);
         }
         par ^= 1;
+        turn = turn + 1 == W ? 0 : turn + 1;
     }
 }
 
 
-template <int NB> static hipError_t launch_i8_split(const I8Params &P, int grid, hipStream_t s)
+template <int NB, int W> static hipError_t launch_i8_split(const I8Params &P, int grid, hipStream_t s)
 {
-    hipLaunchKernelGGL((fwd_i8_split_kernel<NB>), dim3(grid), dim3(I8D_WAVES * 64), i8_split_lds(NB), s, P);
+    hipLaunchKernelGGL((fwd_i8_split_kernel<NB, W>), dim3(grid), dim3(W * 64), i8_split_lds(NB, W), s, P, P.f.offsets);
     return hipGetLastError();
 }
 
@@ -682,38 +748,52 @@ template <int W> static hipError_t launch_i8(const I8Params &P, int grid, hipStr
 template <int NB> static hipError_t launch_i8_doc(const I8Params &P, int grid, hipStream_t s)
 {
     if constexpr (NB <= I8D_LIN_BLOCKS)
-        hipLaunchKernelGGL((fwd_i8_doc_kernel<NB, true>), dim3(grid), dim3(I8D_WAVES * 64), i8_doc_lin_lds(NB), s, P, P.f.offsets);
+        hipLaunchKernelGGL((fwd_i8_doc_kernel<NB, true, I8D_DEPTH>), dim3(grid), dim3(I8D_WAVES * 64), i8_doc_lin_lds(NB), s, P, P.f.offsets);
     else
-        hipLaunchKernelGGL((fwd_i8_doc_kernel<NB, false>), dim3(grid), dim3(I8D_WAVES * 64), i8_doc_lds(NB), s, P, P.f.offsets);
+        hipLaunchKernelGGL((fwd_i8_doc_kernel<NB, false, i8d_depth(NB)>), dim3(grid), dim3(I8D_WAVES * 64), i8_doc_lds(NB), s, P, P.f.offsets);
     return hipGetLastError();
+}
+
+// f(integral_constant<int, NB>) for the smallest NB of those the kernels are built for that holds `nb` column blocks.  The
+// tile loop has no guard per block (each one made every MFMA wait for all LDS reads), so the surplus is multiplied too:
+// with 8, 16, 24 and 32 only, a query of 300 tokens paid for 512.
+template <int MAX, typename F> static hipError_t with_blocks(int nb, F &&f)
+{
+#define MAXSIM_BLOCKS(N)                                                                                               \
+    if constexpr (N <= MAX)                                                                                            \
+        if (nb <= N)                                                                                                   \
+            return f(std::integral_constant<int, N>{});
+    MAXSIM_BLOCKS(1) MAXSIM_BLOCKS(2) MAXSIM_BLOCKS(3) MAXSIM_BLOCKS(4) MAXSIM_BLOCKS(5) MAXSIM_BLOCKS(6)
+    MAXSIM_BLOCKS(7) MAXSIM_BLOCKS(8) MAXSIM_BLOCKS(10) MAXSIM_BLOCKS(12) MAXSIM_BLOCKS(14) MAXSIM_BLOCKS(16)
+    MAXSIM_BLOCKS(20) MAXSIM_BLOCKS(24) MAXSIM_BLOCKS(28) MAXSIM_BLOCKS(32)
+#undef MAXSIM_BLOCKS
+    return hipErrorInvalidValue;
 }
 
 // More than 64 KB of dynamic LDS has to be allowed per kernel and device: every instantiation that needs it, for
 // the current device (called once per device by the library's set-up).
-template <int NB> static hipError_t allow_i8_lds()
-{
-    if (i8_doc_lds(NB) > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_i8_doc_kernel<NB, false>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)i8_doc_lds(NB));
-        if (e != hipSuccess)
-            return e;
-    }
-    if (NB <= 16 && i8_split_lds(NB) > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_i8_split_kernel<(NB <= 16 ? NB : 16)>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)i8_split_lds(NB <= 16 ? NB : 16));
-        if (e != hipSuccess)
-            return e;
-    }
-    return hipSuccess;
-}
-
 hipError_t forward_i8_init_device()
 {
-    hipError_t e = hipSuccess;
-    if ((e = allow_i8_lds<1>()) != hipSuccess || (e = allow_i8_lds<2>()) != hipSuccess || (e = allow_i8_lds<4>()) != hipSuccess ||
-        (e = allow_i8_lds<8>()) != hipSuccess || (e = allow_i8_lds<16>()) != hipSuccess || (e = allow_i8_lds<24>()) != hipSuccess ||
-        (e = allow_i8_lds<32>()) != hipSuccess)
-        return e;
+    for (int nb = 1; nb <= I8D_MAX_BLOCKS; ++nb) {
+        hipError_t e = with_blocks<I8D_MAX_BLOCKS>(nb, [](auto n) {
+            constexpr int NB = decltype(n)::value;
+            if constexpr (NB > I8D_LIN_BLOCKS && i8_doc_lds(NB) > 64 * 1024)
+                return hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_i8_doc_kernel<NB, false, i8d_depth(NB)>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)i8_doc_lds(NB));
+            return hipSuccess;
+        });
+        if (e == hipSuccess && nb <= I8D_SPLIT_BLOCKS)
+            e = with_blocks<I8D_SPLIT_BLOCKS>(nb, [](auto n) {
+                constexpr int NB = decltype(n)::value;
+                if constexpr (i8_split_lds(NB, 8) > 64 * 1024)
+                    return hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_i8_split_kernel<NB, 8>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)i8_split_lds(NB, 8));
+                static_assert(i8_split_lds(8, 4) <= 64 * 1024, "the smaller workgroups need no more than that");
+                return hipSuccess;
+            });
+        if (e != hipSuccess)
+            return e;
+    }
     return hipSuccess;
 }
 
@@ -747,9 +827,9 @@ hipError_t forward_i8_launch(const int8_t *Q, const float *qs, int n_q, int l_q,
 
     // Large corpora: document-stationary kernel, one run of documents per wavefront.
     if (b >= (int64_t)num_cu * I8D_WAVES * 2) {
-        p.qpg = I8D_MAX_BLOCKS / p.bpq;
-        if (p.qpg > n_q)
-            p.qpg = n_q;
+        const int most = I8D_MAX_BLOCKS / p.bpq; // whole queries, spread evenly over as few groups as hold them
+        p.n_groups = (n_q + most - 1) / most;
+        p.qpg = (n_q + p.n_groups - 1) / p.n_groups;
         p.n_groups = (n_q + p.qpg - 1) / p.qpg;
         int wgs = num_cu / p.n_groups; // per group; the query copy in LDS allows one workgroup per CU
         if (wgs < 1)
@@ -762,38 +842,36 @@ hipError_t forward_i8_launch(const int8_t *Q, const float *qs, int n_q, int l_q,
         wgs = (int)((n_chunks + I8D_WAVES - 1) / I8D_WAVES);
         const int nb = p.qpg * p.bpq;
         const int grid = wgs * p.n_groups;
-        if (nb <= 1) return launch_i8_doc<1>(P, grid, stream);
-        if (nb <= 2) return launch_i8_doc<2>(P, grid, stream);
-        if (nb <= 4) return launch_i8_doc<4>(P, grid, stream);
-        if (nb <= 8) return launch_i8_doc<8>(P, grid, stream);
-        if (nb <= 16) return launch_i8_doc<16>(P, grid, stream);
-        if (nb <= 24) return launch_i8_doc<24>(P, grid, stream);
-        return launch_i8_doc<32>(P, grid, stream);
+        return with_blocks<I8D_MAX_BLOCKS>(nb, [&](auto n) { return launch_i8_doc<decltype(n)::value>(P, grid, stream); });
     }
 
-    // Uniform corpora of long documents, up to 16 column blocks per query and one or two groups of 16: the
-    // wavefronts of a workgroup share each document (document-stationary like the kernel above, at any number
-    // of documents)
-    constexpr int SPLIT_BLOCKS = 16;
-    if (!offsets && p.bpq <= SPLIT_BLOCKS && total_blocks <= 2 * SPLIT_BLOCKS && l_d >= I8D_WAVES * TILE_ROWS) {
-        p.qpg = SPLIT_BLOCKS / p.bpq;
-        if (p.qpg > n_q)
-            p.qpg = n_q;
+    // Fewer documents, up to 16 column blocks per query and one or two groups of 16: the wavefronts of a workgroup share
+    // each document (document-stationary like the kernel above, at any number of documents): eight of them where a
+    // document has a tile for each, else two, or four (fewer copies of the queries) from five blocks on.  One query x 1000 /
+    // 3000 texts of 64-300 tokens 26 -> 10, 53 -> 18 us against the kernel below, four x 1000 32 -> 21, eight x 2000 45 -> 44
+    // (with two wavefronts 59); with 16 blocks and documents of 60-512 tokens the kernel below is faster (46 against 80).
+    const int64_t mean_len = (total_tokens + b - 1) / b; // (uniform: l_d)
+    const bool eight = !offsets && l_d >= I8D_WAVES * TILE_ROWS;
+    if (p.bpq <= I8D_SPLIT_BLOCKS && total_blocks <= 2 * I8D_SPLIT_BLOCKS && (eight || (mean_len >= 2 * TILE_ROWS && total_blocks <= 8))) {
+        const int most = I8D_SPLIT_BLOCKS / p.bpq;
+        p.n_groups = (n_q + most - 1) / most;
+        p.qpg = (n_q + p.n_groups - 1) / p.n_groups;
         p.n_groups = (n_q + p.qpg - 1) / p.qpg;
         const int nb = p.qpg * p.bpq;
-        // about four workgroups per CU while the queries are small, one when their LDS copy is large
-        int64_t n_chunks = ((int64_t)num_cu * (nb <= 4 ? 4 : 1) + p.n_groups - 1) / p.n_groups;
+        // about four workgroups of eight wavefronts per CU while the queries are small, one when their LDS copy is large; eight
+        // wavefronts per CU in the smaller workgroups
+        const int64_t per_cu = eight ? (nb <= 4 ? 4 : 1) : nb <= 4 ? 4 : 2;
+        int64_t n_chunks = ((int64_t)num_cu * per_cu + p.n_groups - 1) / p.n_groups;
         if (n_chunks > b)
             n_chunks = b;
-        p.unit_per_chunk = (b + n_chunks - 1) / n_chunks;
-        n_chunks = (b + p.unit_per_chunk - 1) / p.unit_per_chunk;
+        p.unit_per_chunk = (units + n_chunks - 1) / n_chunks;
+        n_chunks = (units + p.unit_per_chunk - 1) / p.unit_per_chunk;
         p.n_chunks = (int)n_chunks;
         const int grid = p.n_chunks * p.n_groups;
-        if (nb <= 1) return launch_i8_split<1>(P, grid, stream);
-        if (nb <= 2) return launch_i8_split<2>(P, grid, stream);
-        if (nb <= 4) return launch_i8_split<4>(P, grid, stream);
-        if (nb <= 8) return launch_i8_split<8>(P, grid, stream);
-        return launch_i8_split<16>(P, grid, stream);
+        return with_blocks<I8D_SPLIT_BLOCKS>(nb, [&](auto n) {
+            constexpr int NB = decltype(n)::value;
+            return eight ? launch_i8_split<NB, 8>(P, grid, stream) : launch_i8_split<(NB <= 8 ? NB : 8), (NB <= 4 ? 2 : 4)>(P, grid, stream);
+        });
     }
 
     int w = 8;

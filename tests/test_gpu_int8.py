@@ -224,6 +224,29 @@ def test_forward_i8_shared_documents_negative_maxima():
     assert float(s[0, 0]) < 0 < float(s[0, 1])
 
 
+# Every number of column blocks the document kernels are built for, and one that is rounded up: small corpora, whose
+# documents are shared by two or four wavefronts (ragged, or uniform of under 256 tokens), and large ones
+@pytest.mark.parametrize("n_q,l_q", [(1, 30), (2, 32), (1, 90), (4, 20), (1, 160), (3, 60), (1, 224), (8, 32), (1, 290), (3, 128), (7, 50), (1, 500)])
+def test_forward_i8_block_counts_bit_exact(n_q, l_q):
+    g, o = ragged_case(n_q, l_q, [64, 65, 1, 32, 33, 0, 95, 96, 97, 128, 129, 160, 2, 300, 0] * 3, 51)
+    s = M.maxsim_forward_i8_ragged(*g)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(s.cpu().numpy()), bits(O.forward_i8_ragged(*o)))
+    for b, l_d in ((7, 100), (4200, 33)):
+        g, o = quantised_case(n_q, l_q, b, l_d, 53)
+        s = M.maxsim_forward_i8(*g)
+        torch.cuda.synchronize()
+        assert np.array_equal(bits(s.cpu().numpy()), bits(O.forward_i8(*o)))
+
+
+@pytest.mark.parametrize("n_q,l_q,b,l_d", [(1, 545, 4100, 40), (3, 260, 4100, 33), (4, 200, 4097, 35)])
+def test_forward_i8_many_blocks_bit_exact(n_q, l_q, b, l_d):
+    g, o = quantised_case(n_q, l_q, b, l_d, 54)
+    s = M.maxsim_forward_i8(*g)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(s.cpu().numpy()), bits(O.forward_i8(*o)))
+
+
 # ---- embedding widths other than 128 (every multiple of 32 up to 8192): the slab kernel (multiples of 64) and the
 # plain inner loop over d ----
 
