@@ -53,6 +53,22 @@ def test_backward_parity(shape, dtype):
     run_case(*shape, dtype, 7)
 
 
+# More entries in a document's argmax column than one round takes (8192): whole rounds and a partial one, tokens per query that
+# divide 64 or do not, and enough rows for blocks of 32, 64 and 128
+@pytest.mark.parametrize("n_q,l_q,b,l_d", [(10, 900, 41, 1001), (9, 1024, 21, 1000), (288, 32, 11, 999), (17, 1000, 3, 700), (512, 32, 5, 33)])
+def test_backward_several_rounds(n_q, l_q, b, l_d):
+    Q = W.unit_rows((n_q, l_q, 128), "f16", 41, DEV)
+    D = W.unit_rows((b, l_d, 128), "f16", 42, DEV)
+    rng = np.random.default_rng(43)
+    A = rng.integers(-1, l_d, (n_q, b, l_q)).astype(np.int32)
+    g = rng.standard_normal((n_q, b)).astype(np.float32)
+    rQ, rD = O.backward(W.to_raw_numpy(Q), W.to_raw_numpy(D), "f16", A, g.astype(np.float64))
+    dQ, dD = M.maxsim_backward(Q, D, torch.from_numpy(A).to(DEV), torch.from_numpy(g).to(DEV))
+    torch.cuda.synchronize()
+    close(dQ, rQ, "dQ")
+    close(dD, rD, "dD")
+
+
 # Embedding widths other than 128 (App. "Split-d Speedup": training verified at d = 512 .. 2048): every multiple of 8;
 # columns beyond 128 are further slabs of the same kernels.  The explicit CSR must give the same bits.
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
