@@ -150,7 +150,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
     // Five to sixteen blocks of narrow rows.  What a wavefront spends per tile beside its MFMAs (iterator, copies,
     // barrier) does not depend on how many blocks it holds, so workgroups of two (up to 8 blocks) or four wavefronts
     // with four blocks each beat eight wavefronts with one or two blocks by 6-15 % -- as long as there are documents
-    // enough for their many workgroups (at least two per workgroup; a small corpus is a chain of memory latencies
+    // enough for their many workgroups (at least four per workgroup; a small corpus is a chain of memory latencies
     // per workgroup, and the shapes below keep several tiles in flight for that).
     const int narrow_w = total_blocks <= 8 ? 2 : 4;
     // (fp32 rows carry four times the MFMAs per block: there two wavefronts are 3 % behind four with two blocks each)

@@ -147,8 +147,10 @@ __global__ void __launch_bounds__(WD_W * 64) fwd_wide_kernel(FwdParams p, Offset
         return;
 
     uint32_t a_off[S::NA], b_off[S::NB]; // byte offsets of this lane's chunks within the tile's rows / the group's queries
-    const char *const q_base = p.Q + (int64_t)q_first * p.l_q * row_bytes;
+    const char *q_base = p.Q + (int64_t)q_first * p.l_q * row_bytes; // first query row of the pass
     auto query_rows = [&](int pass) {
+        const int tok0 = pass * blocks_per_pass * BLOCK_COLS; // (one pass: 0)
+        q_base = p.Q + ((int64_t)q_first * p.l_q + tok0) * row_bytes;
 #pragma unroll
         for (int j = 0; j < S::NB; ++j) { // columns past the query or past the group's blocks re-read a valid row and are never summed
             const int r = S::COLS >= 64 ? r0 + 64 * j : (r0 & (S::COLS - 1));
@@ -158,10 +160,8 @@ __global__ void __launch_bounds__(WD_W * 64) fwd_wide_kernel(FwdParams p, Offset
                 blk -= q * p.bpq;
                 if (q >= nq)
                     q = blk = 0;
-            } else {
-                blk += pass * blocks_per_pass;
             }
-            b_off[j] = (uint32_t)((q * p.l_q + min(blk * BLOCK_COLS + (r & 31), p.l_q - 1)) * row_bytes + cc * 16);
+            b_off[j] = (uint32_t)((q * p.l_q + min(blk * BLOCK_COLS + (r & 31), p.l_q - 1 - tok0)) * row_bytes + cc * 16);
         }
     };
     int lks = 0;
@@ -173,9 +173,9 @@ __global__ void __launch_bounds__(WD_W * 64) fwd_wide_kernel(FwdParams p, Offset
         for (int j = 0; j < S::NA; ++j)
             a_off[j] = (uint32_t)(min(r0 + 64 * j, last) * row_bytes + cc * 16);
         l_a = p.D + (int64_t)li.it.row0 * row_bytes;
-        l_b = q_base;
         if (p.n_pass > 1)
             query_rows(li.pass);
+        l_b = q_base;
     };
     // Addresses of the loader's slab; past the end of the stream the last slab is loaded again (in bounds, never used)
     auto next_slab = [&]() {
