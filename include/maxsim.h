@@ -247,6 +247,7 @@ int maxsim_forward_i8_streamed(const int8_t *Q_i8, const float *q_scale, int n_q
  * contrastive training step; the paper leaves the loss open, this is softmax
  * cross-entropy with temperature tau, label of query i = document i, mean over queries).
  *   scores [n, b] float32 (b >= n);  g [n, b] float32 = (softmax_j(s_i/tau) - [i==j]) / (tau n)
+ *   (g may be scores itself: the gradient then takes the scores' place)
  *   loss   [1] float32 or NULL
  */
 int maxsim_ce_grad(const float *scores, int n, int b, float tau, float *g, float *loss,

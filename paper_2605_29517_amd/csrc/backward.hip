@@ -1317,7 +1317,9 @@ __device__ __forceinline__ int ce_second_slot(int i, int b) { return i + 1 < b ?
 // columns are read once and stay in registers (KEEP = 0: wider rows are read again for each of the three sweeps).
 // STASH (a loss is wanted): the row's maximum and sum go into g[i, i] and the slot beside it instead of the two
 // gradients; ce_loss_kernel reads them and puts the gradients there.  The library owns no memory that two calls
-// could share safely, and g is an output that the call overwrites whole.
+// could share safely, and g is an output that the call overwrites whole.  (Where g takes the scores' place the scores are
+// gone by then: ce_loss_direct_kernel runs first instead, and this kernel without STASH, which reads an element before it
+// writes it.)
 template <int KEEP, bool STASH>
 __global__ void __launch_bounds__(256) ce_grad_kernel(const float *s, int n, int b, float inv_tau, float *g)
 {
@@ -1396,6 +1398,35 @@ __global__ void __launch_bounds__(1024) ce_loss_kernel(const float *s, int n, in
     }
 }
 
+// Loss of scores that the gradient is about to take the place of: every row is read for it, before ce_grad_kernel runs.
+// One block, a row per wavefront at a time.
+__global__ void __launch_bounds__(1024) ce_loss_direct_kernel(const float *s, int n, int b, float inv_tau, float *loss)
+{
+    __shared__ float part[16];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    float local = 0.0f;
+    for (int i = w; i < n; i += 16) {
+        const float *row = s + (int64_t)i * b;
+        float mx = neg_inf(), z = 0.0f;
+        for (int j = lane; j < b; j += 64)
+            mx = fmaxf(mx, scaled(row[j], inv_tau));
+        mx = wave_max(mx);
+        for (int j = lane; j < b; j += 64)
+            z += expf(scaled(row[j], inv_tau) - mx);
+        z = wave_sum(z);
+        local += logf(z) + mx - scaled(row[i], inv_tau);
+    }
+    if (lane == 0)
+        part[w] = local;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = 0.0f;
+        for (int k = 0; k < 16; ++k)
+            t += part[k];
+        *loss = t / (float)n;
+    }
+}
+
 template <bool STASH> static void launch_ce_grad(const float *s, int n, int b, float inv_tau, float *g, hipStream_t stream)
 {
     const dim3 grid((n + 3) / 4), block(256);
@@ -1410,6 +1441,16 @@ template <bool STASH> static void launch_ce_grad(const float *s, int n, int b, f
 hipError_t ce_grad_launch(const float *scores, int n, int b, float tau, float *g, float *loss, hipStream_t stream)
 {
     const float inv_tau = 1.0f / tau;
+    const size_t bytes = (size_t)n * b * sizeof(float);
+    const uintptr_t s0 = reinterpret_cast<uintptr_t>(scores), g0 = reinterpret_cast<uintptr_t>(g);
+    if (loss && b > 1 && s0 < g0 + bytes && g0 < s0 + bytes) { // in place
+        hipLaunchKernelGGL(ce_loss_direct_kernel, dim3(1), dim3(1024), 0, stream, scores, n, b, inv_tau, loss);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+        launch_ce_grad<false>(scores, n, b, inv_tau, g, stream);
+        return hipGetLastError();
+    }
     if (loss && b > 1)
         launch_ce_grad<true>(scores, n, b, inv_tau, g, stream);
     else

@@ -311,3 +311,18 @@ def test_ce_grad_row_lengths(n, b):
     assert abs(float(loss) - rloss) <= 1e-5 * max(1.0, abs(rloss))
     assert np.abs(g.cpu().numpy() - rg).max() <= 1e-4 * max(np.abs(rg).max(), 1e-30)
     assert torch.equal(g, g2)
+
+
+@pytest.mark.parametrize("n,b", [(1, 1), (1, 2), (2, 2), (3, 5), (17, 64), (256, 257), (65, 1025), (1100, 1100)])
+def test_ce_grad_in_place(n, b):
+    """The gradient may take the scores' place: the same bits as into a buffer of its own, with the loss and without it."""
+    s = (torch.randn(n, b, device=DEV, generator=torch.Generator(DEV).manual_seed(n + b)) * 3 + 10).contiguous()
+    g, _ = M.maxsim_ce_grad(s, 0.02)
+    rloss, _ = O.ce_grad(s.cpu().numpy().astype(np.float64), 0.02)
+    a, a2 = s.clone(), s.clone()
+    _, loss = M.maxsim_ce_grad(a, 0.02, g=a)
+    rc = M.load().maxsim_ce_grad(a2.data_ptr(), n, b, 0.02, a2.data_ptr(), None, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0
+    assert torch.equal(a, g) and torch.equal(a2, g)
+    assert abs(float(loss) - rloss) <= 1e-5 * max(1.0, abs(rloss))
