@@ -1377,7 +1377,9 @@ __global__ void __launch_bounds__(1024) ce_loss_kernel(const float *s, int n, in
     __shared__ float part[16];
     const float scale = inv_tau / (float)n;
     float local = 0.0f;
-    for (int i = threadIdx.x; i < n && b > 1; i += 1024) { // (one document: the loss is 0)
+    if (b == 1 && threadIdx.x == 0) // one document: loss and gradient are 0, or both NaN where the score is not finite
+        local = g[0];
+    for (int i = threadIdx.x; i < n && b > 1; i += 1024) {
         const int second = ce_second_slot(i, b);
         float *row = g + (int64_t)i * b;
         const float mx = row[i], z = row[second];

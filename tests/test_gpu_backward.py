@@ -326,3 +326,12 @@ def test_ce_grad_in_place(n, b):
     assert rc == 0
     assert torch.equal(a, g) and torch.equal(a2, g)
     assert abs(float(loss) - rloss) <= 1e-5 * max(1.0, abs(rloss))
+
+
+@pytest.mark.parametrize("value", [3.7, -3.7, float("-inf"), float("inf"), float("nan")])
+def test_ce_grad_of_one_document(value):
+    """One document: gradient and loss are 0, and NaN where the score is not finite (an empty document scores -inf)."""
+    g, loss = M.maxsim_ce_grad(torch.full((1, 1), value, device=DEV), 0.02)
+    torch.cuda.synchronize()
+    for x in (float(g), float(loss)):
+        assert x == 0.0 if np.isfinite(value) else np.isnan(x)
