@@ -1295,31 +1295,37 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// s / tau as one rounded multiply that may not be contracted into a fused multiply-add
+// s / tau as one explicitly rounded multiply everywhere, so that the same value enters the max, the exponent and the
+// label term: it may not be contracted into a fused multiply-add
 __device__ __forceinline__ float scaled(float s, float inv_tau)
 {
 #pragma clang fp contract(off)
     return s * inv_tau;
 }
 
-// s / tau is formed with an explicitly rounded multiply everywhere, so that the same value
-// enters the max, the exponent and the label term (no fused multiply-add may split them).
-__device__ __forceinline__ float ce_grad_value(float scaled_s, float mx, float z, bool label, float scale)
+// A row's own column carries one number from ce_grad_kernel to ce_loss_kernel from which both the gradient, (p - 1) * scale,
+// and the row's term of the loss, -log p, are formed: the softmax p, or where p is too small for its logarithm the term
+// itself, log(z) - (own - max), which is then above 1 while p is not.  (own - max first: next to log(z) the scores
+// themselves, in the thousands at tau = 0.02, would cost the term its digits.)
+__device__ __forceinline__ float ce_own_pack(float scaled_s, float mx, float z)
 {
-    const float pj = expf(scaled_s - mx) / z;
-    return (pj - (label ? 1.0f : 0.0f)) * scale;
+    const float p = expf(scaled_s - mx) / z;
+    return p < 1e-30f ? logf(z) - (scaled_s - mx) : p;
 }
-
-// The column beside the diagonal whose slot of g carries a row's sum from ce_grad_kernel to ce_loss_kernel (b >= 2)
-__device__ __forceinline__ int ce_second_slot(int i, int b) { return i + 1 < b ? i + 1 : i - 1; }
+struct CeOwn {
+    float p, term;
+};
+__device__ __forceinline__ CeOwn ce_own_unpack(float x) // (NaN, by its bits above 1 too, gives NaN for both)
+{
+    const bool is_term = __float_as_uint(x) > 0x3f800000u;
+    return {is_term ? expf(-x) : x, is_term ? x : -logf(x)};
+}
 
 // Gradient: one wavefront per row, rows dealt round-robin to the wavefronts of the grid.  Rows of up to 64 * KEEP
 // columns are read once and stay in registers (KEEP = 0: wider rows are read again for each of the three sweeps).
-// STASH (a loss is wanted): the row's maximum and sum go into g[i, i] and the slot beside it instead of the two
-// gradients; ce_loss_kernel reads them and puts the gradients there.  The library owns no memory that two calls
-// could share safely, and g is an output that the call overwrites whole.  (Where g takes the scores' place the scores are
-// gone by then: ce_loss_direct_kernel runs first instead, and this kernel without STASH, which reads an element before it
-// writes it.)
+// STASH (a loss is wanted): g[i, i] gets what ce_loss_kernel forms the row's term of the loss and the gradient from.  The
+// library owns no memory that two calls could share safely, and g is an output that the call overwrites whole.  g may be
+// s: a lane reads its elements before it writes them.
 template <int KEEP, bool STASH>
 __global__ void __launch_bounds__(256) ce_grad_kernel(const float *s, int n, int b, float inv_tau, float *g)
 {
@@ -1329,15 +1335,12 @@ __global__ void __launch_bounds__(256) ce_grad_kernel(const float *s, int n, int
     for (int i = (int)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += n_waves) {
         const float *row = s + (int64_t)i * b;
         float *dst = g + (int64_t)i * b;
-        const int second = ce_second_slot(i, b);
         float mx = neg_inf(), z = 0.0f;
         auto put = [&](int j, float v) {
             if (STASH && j == i)
-                dst[j] = mx;
-            else if (STASH && j == second)
-                dst[j] = z;
+                dst[j] = ce_own_pack(v, mx, z);
             else
-                dst[j] = ce_grad_value(v, mx, z, j == i, scale);
+                dst[j] = (expf(v - mx) / z - (j == i ? 1.0f : 0.0f)) * scale;
         };
         if constexpr (KEEP > 0) {
             float v[KEEP];
@@ -1369,57 +1372,23 @@ __global__ void __launch_bounds__(256) ce_grad_kernel(const float *s, int n, int
     }
 }
 
-// Loss: mean over the rows of log(sum) + max - s[i, i] / tau, from the maxima and sums that ce_grad_kernel left in g,
-// whose two slots per row get their gradients here.  One block in a fixed order: a row per thread, then a tree.  (It
-// used to repeat the softmax of every row: 65 536 exponentials on one compute unit, 25 us at 256 x 256 against 4 us.)
-__global__ void __launch_bounds__(1024) ce_loss_kernel(const float *s, int n, int b, float inv_tau, float *g, float *loss)
+// Loss: mean over the rows of -log p, from what ce_grad_kernel left in g[i, i], where the gradient goes now.  One block in a
+// fixed order: a row per thread, then a tree.  (It used to repeat the softmax of every row: 65 536 exponentials on one
+// compute unit, 25 us at 256 x 256 against 4 us.)
+__global__ void __launch_bounds__(1024) ce_loss_kernel(int n, int b, float inv_tau, float *g, float *loss)
 {
     __shared__ float part[16];
     const float scale = inv_tau / (float)n;
     float local = 0.0f;
-    if (b == 1 && threadIdx.x == 0) // one document: loss and gradient are 0, or both NaN where the score is not finite
-        local = g[0];
-    for (int i = threadIdx.x; i < n && b > 1; i += 1024) {
-        const int second = ce_second_slot(i, b);
-        float *row = g + (int64_t)i * b;
-        const float mx = row[i], z = row[second];
-        const float own = scaled(s[(int64_t)i * b + i], inv_tau), next = scaled(s[(int64_t)i * b + second], inv_tau);
-        local += logf(z) + mx - own;
-        row[i] = ce_grad_value(own, mx, z, true, scale);
-        row[second] = ce_grad_value(next, mx, z, false, scale);
+    for (int i = threadIdx.x; i < n; i += 1024) {
+        float *own = g + (int64_t)i * b + i;
+        const CeOwn x = ce_own_unpack(*own);
+        local += x.term;
+        *own = (x.p - 1.0f) * scale;
     }
     local = wave_sum(local);
     if ((threadIdx.x & 63) == 0)
         part[threadIdx.x >> 6] = local;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float t = 0.0f;
-        for (int k = 0; k < 16; ++k)
-            t += part[k];
-        *loss = t / (float)n;
-    }
-}
-
-// Loss of scores that the gradient is about to take the place of: every row is read for it, before ce_grad_kernel runs.
-// One block, a row per wavefront at a time.
-__global__ void __launch_bounds__(1024) ce_loss_direct_kernel(const float *s, int n, int b, float inv_tau, float *loss)
-{
-    __shared__ float part[16];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    float local = 0.0f;
-    for (int i = w; i < n; i += 16) {
-        const float *row = s + (int64_t)i * b;
-        float mx = neg_inf(), z = 0.0f;
-        for (int j = lane; j < b; j += 64)
-            mx = fmaxf(mx, scaled(row[j], inv_tau));
-        mx = wave_max(mx);
-        for (int j = lane; j < b; j += 64)
-            z += expf(scaled(row[j], inv_tau) - mx);
-        z = wave_sum(z);
-        local += logf(z) + mx - scaled(row[i], inv_tau);
-    }
-    if (lane == 0)
-        part[w] = local;
     __syncthreads();
     if (threadIdx.x == 0) {
         float t = 0.0f;
@@ -1443,24 +1412,14 @@ template <bool STASH> static void launch_ce_grad(const float *s, int n, int b, f
 hipError_t ce_grad_launch(const float *scores, int n, int b, float tau, float *g, float *loss, hipStream_t stream)
 {
     const float inv_tau = 1.0f / tau;
-    const size_t bytes = (size_t)n * b * sizeof(float);
-    const uintptr_t s0 = reinterpret_cast<uintptr_t>(scores), g0 = reinterpret_cast<uintptr_t>(g);
-    if (loss && b > 1 && s0 < g0 + bytes && g0 < s0 + bytes) { // in place
-        hipLaunchKernelGGL(ce_loss_direct_kernel, dim3(1), dim3(1024), 0, stream, scores, n, b, inv_tau, loss);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-        launch_ce_grad<false>(scores, n, b, inv_tau, g, stream);
-        return hipGetLastError();
-    }
-    if (loss && b > 1)
+    if (loss)
         launch_ce_grad<true>(scores, n, b, inv_tau, g, stream);
     else
         launch_ce_grad<false>(scores, n, b, inv_tau, g, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !loss)
         return e;
-    hipLaunchKernelGGL(ce_loss_kernel, dim3(1), dim3(1024), 0, stream, scores, n, b, inv_tau, g, loss);
+    hipLaunchKernelGGL(ce_loss_kernel, dim3(1), dim3(1024), 0, stream, n, b, inv_tau, g, loss);
     return hipGetLastError();
 }
 

@@ -328,6 +328,20 @@ def test_ce_grad_in_place(n, b):
     assert abs(float(loss) - rloss) <= 1e-5 * max(1.0, abs(rloss))
 
 
+def test_ce_grad_unlikely_labels():
+    """Labels whose softmax has no logarithm in fp32, and one beside it on either side: loss and gradient of every row."""
+    s = torch.full((5, 6), 3.0, device=DEV)
+    s[range(5), range(5)] = torch.tensor([0.0, 3.0 - 88 * 0.02, 3.0 - 66 * 0.02, 3.0 - 68 * 0.02, 9.0], device=DEV)
+    g, loss = M.maxsim_ce_grad(s, 0.02)
+    g2 = torch.empty_like(g)
+    rc = M.load().maxsim_ce_grad(s.data_ptr(), 5, 6, 0.02, g2.data_ptr(), None, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0 and torch.equal(g, g2)
+    rloss, rg = O.ce_grad(s.cpu().numpy().astype(np.float64), 0.02)
+    assert abs(float(loss) - rloss) <= 1e-5 * abs(rloss)
+    assert np.abs(g.cpu().numpy() - rg).max() <= 1e-4 * np.abs(rg).max()
+
+
 @pytest.mark.parametrize("value", [3.7, -3.7, float("-inf"), float("inf"), float("nan")])
 def test_ce_grad_of_one_document(value):
     """One document: gradient and loss are 0, and NaN where the score is not finite (an empty document scores -inf)."""
