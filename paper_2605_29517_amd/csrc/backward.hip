@@ -614,60 +614,56 @@ __global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr 
         if (hi_rel <= lo_rel)
             continue; // only offsets that break their contract get here
 
-        // (1a) this lane's entries of a round: entry n = c0 + x -> (q, i); all loads are issued before the first result is
-        // used.  The entry 64 further on is dq queries and di tokens ahead: its address is one of two increments away.
-        constexpr int PER = SEG / 64;
-        int t[PER];
-        auto load_entries = [&](int c0) {
-            const int cn = min(DW_COL, n_entries - c0);
-            int x = w * SEG + lane;
-            // (opaque to the optimiser: it would otherwise keep x + 64 k for all k in registers across the rounds)
-            asm volatile("" : "+v"(x));
-            const uint32_t n = (uint32_t)c0 + (uint32_t)x; // entries past the end of the column are masked below
-            const uint32_t q0 = magic_div(n < (uint32_t)n_entries ? n : 0u, lq_magic);
-            int i = (int)((n < (uint32_t)n_entries ? n : 0u) - q0 * (uint32_t)p.l_q);
-            const int32_t *ptr = p.A + ((int64_t)q0 * p.b + j) * p.l_q + i;
-            if (cn == DW_COL && di64 == 0) { // l_q divides 64: the same increment every time
-#pragma unroll
-                for (int k = 0; k < PER; ++k) {
-                    t[k] = *ptr;
-                    ptr += inc_plain;
-                }
-            } else if (cn == DW_COL) {
-#pragma unroll
-                for (int k = 0; k < PER; ++k) {
-                    t[k] = *ptr;
-                    i += di64;
-                    const bool wrap = i >= p.l_q;
-                    i -= wrap ? p.l_q : 0;
-                    ptr += wrap ? inc_wrap : inc_plain;
-                }
-            } else {
-                const int32_t *const ptr0 = ptr;
-#pragma unroll
-                for (int k = 0; k < PER; ++k) {
-                    const bool live = (x + k * 64) < cn;
-                    const int v = *(live ? ptr : ptr0); // past the end of the column: a harmless re-read
-                    t[k] = live ? v : -1;
-                    i += di64;
-                    const bool wrap = i >= p.l_q;
-                    i -= wrap ? p.l_q : 0;
-                    ptr += wrap ? inc_wrap : inc_plain;
-                }
-            }
-        };
-        load_entries(0);
         for (int64_t c64 = 0; c64 < n_entries; c64 += DW_COL) { // 64-bit: n_entries may be within DW_COL of 2^31
             const int c0 = (int)c64;
+            const int cn = min(DW_COL, n_entries - c0);
             __syncthreads(); // the previous round's lists have been walked
             for (int x = tid; x < W * R; x += W * 64)
                 (&hist[0][0])[x] = 0;
             __syncthreads();
             int kept = 0;
             {
-                // (1b)
+                // (1) entry n = c0 + x -> (q, i); all loads are issued before the first result is used.  The entry 64
+                // further on is dq queries and di tokens ahead: its address is one of two increments away.  (Loads that
+                // travel during the walk of the round before hold sixteen more registers there, which costs a resident
+                // workgroup per CU: 64 x 1000 x 64 x 1000 gains 1 %, 256 x 32 x 256 x 180 loses 8 with blocks of 64 rows.)
+                constexpr int PER = SEG / 64;
                 int x = w * SEG + lane;
+                // (opaque to the optimiser: it would otherwise keep x + 64 k for all k in registers across the rounds)
                 asm volatile("" : "+v"(x));
+                const uint32_t n = (uint32_t)c0 + (uint32_t)x; // entries past the end of the column are masked below
+                const uint32_t q0 = magic_div(n < (uint32_t)n_entries ? n : 0u, lq_magic);
+                int i = (int)((n < (uint32_t)n_entries ? n : 0u) - q0 * (uint32_t)p.l_q);
+                const int32_t *ptr = p.A + ((int64_t)q0 * p.b + j) * p.l_q + i;
+                int t[PER];
+                if (cn == DW_COL && di64 == 0) { // l_q divides 64: the same increment every time
+#pragma unroll
+                    for (int k = 0; k < PER; ++k) {
+                        t[k] = *ptr;
+                        ptr += inc_plain;
+                    }
+                } else if (cn == DW_COL) {
+#pragma unroll
+                    for (int k = 0; k < PER; ++k) {
+                        t[k] = *ptr;
+                        i += di64;
+                        const bool wrap = i >= p.l_q;
+                        i -= wrap ? p.l_q : 0;
+                        ptr += wrap ? inc_wrap : inc_plain;
+                    }
+                } else {
+                    const int32_t *const ptr0 = ptr;
+#pragma unroll
+                    for (int k = 0; k < PER; ++k) {
+                        const bool live = (x + k * 64) < cn;
+                        const int v = *(live ? ptr : ptr0); // past the end of the column: a harmless re-read
+                        t[k] = live ? v : -1;
+                        i += di64;
+                        const bool wrap = i >= p.l_q;
+                        i -= wrap ? p.l_q : 0;
+                        ptr += wrap ? inc_wrap : inc_plain;
+                    }
+                }
                 // An entry lands in the block iff y = t - (t_base + lo_rel), taken modulo 2^32, is below the number of
                 // the document's rows in the block (that also rules out t < 0, t >= len and the -1 of masked entries);
                 // y counts rows from the document's first row in the block.
@@ -753,8 +749,6 @@ __global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr 
                 }
             }
             __syncthreads();
-            if (c64 + DW_COL < n_entries) // the next round's entries travel during the walk
-                load_entries(c0 + DW_COL);
             {
                 // (4) walk this wavefront's keys w * RPW .. w * RPW + RPW - 1
                 const int startv = start[w * RPW + (lane < RPW ? lane : RPW)];
@@ -825,11 +819,25 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
     hipError_t e = launch_dq<DT>(p, stream);
     if (e != hipSuccess)
         return e;
-    // Blocks of 128 rows unless that leaves the chip short of workgroups: every block filters the argmax columns of its
-    // documents, so halving the blocks doubles that work.  5 per 4 CUs wanted: at 4 per CU 64 x 1000 x 64 x 1000 took 264 us and
-    // takes 212, 60 x 300 x 60 x 900 98 and 86, 64 x 32 x 64 x 500 31 and 28; at 1 per CU 32 x 1024 x 32 x 1024 is slower (69
-    // against 67, 73 at 4).
-    const int64_t want = (int64_t)num_cu * 5 / 4;
+    // Rows per block.  Every block filters the argmax columns of its documents, so halving the blocks doubles that work;
+    // but fewer than four blocks per CU leave some CUs with more of them than others, and a block that spans two
+    // documents takes twice as long.  So, with documents of several blocks, blocks of 128 rows also where they fill a
+    // round of two per CU (what is resident) to five sixths or two rounds to three quarters, and blocks of 64 also where
+    // there are 1.6 per CU and the CUs with most of them are no more than 0.3 ahead of the mean.  A slab of 128 columns
+    // is a workgroup of its own.  Ragged corpora with several rounds per document: by four per CU alone, there a block of
+    // three documents takes three times as long. Both gradients, f16, in us, with blocks of 32 / 64 / 128 rows (queries x
+    // tokens x documents x tokens): 256 x 32 x 256 x 180 85 / 84 / 100 (360 blocks of 128), 256 x 300 89 / 88 / 103
+    // (600), 256 x 1030 128 / 117 / 110 (2060), 128 x 32 x 128 x 500 47 / 45 / 40 (500), 128 x 128 x 128 x 700 113 / 107
+    // / 111 (700), 19 x 456 x 102 x 1024 88 / 79 / 72 (816), 64 x 1000 x 64 x 500 205 / 191 / 211 (500 blocks of 64), x
+    // 700 225 / 204 / 226 (700), x 2000 367 / 330 / 282 (1000 of 128), 32 x 1024 x 32 x 1030 81 / 86 / 92 (515 of 64,
+    // three on three CUs), 256 x 32 x 256 x 130 89 / 98 / 122 (520, documents of two blocks).
+    const int64_t cus = num_cu;
+    const int64_t mean_len = p.total_tokens / p.b;
+    const bool several = mean_len >= 384 && !(p.offsets && (int64_t)p.n_q * p.l_q > DW_COL);
+    auto blocks = [&](int rows) { return (p.total_tokens + rows - 1) / rows * (several ? (p.d + SLAB - 1) / SLAB : 1); };
+    const int64_t n128 = blocks(DD_WAVES * 16), n64 = blocks(DD_WAVES * 8);
+    const bool by128 = n128 >= 4 * cus || (several && (n128 <= 2 * cus ? n128 * 3 >= 5 * cus : n128 >= 3 * cus));
+    const bool by64 = n64 >= 4 * cus || (several && n64 * 5 >= 8 * cus && n64 * 10 >= (n64 + cus - 1) / cus * cus * 7);
     const Magic lq_magic = magic_u31((uint32_t)p.l_q);
     const unsigned slabs = (unsigned)((p.d + SLAB - 1) / SLAB);
     auto go = [&](auto rpw_tag, auto w_tag) {
@@ -839,9 +847,9 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
         hipLaunchKernelGGL((bwd_dd_kernel<DT, RPW, W>), dim3(order.grid, slabs), dim3(W * 64), 0, stream, p, p.offsets,
                            lq_magic, magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order);
     };
-    if (p.total_tokens / (DD_WAVES * 16) >= want)
+    if (by128)
         go(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
-    else if (p.total_tokens / (DD_WAVES * 8) >= want)
+    else if (by64)
         go(std::integral_constant<int, 8>(), std::integral_constant<int, 8>());
     else
         go(std::integral_constant<int, 4>(), std::integral_constant<int, 8>());
