@@ -4,9 +4,9 @@
 
 namespace maxsim {
 
-hipError_t forward_run_f16(const FwdParams &p, int nu, bool argmax, bool tile, int x, int grid, hipStream_t s);
-hipError_t forward_run_bf16(const FwdParams &p, int nu, bool argmax, bool tile, int x, int grid, hipStream_t s);
-hipError_t forward_run_f32(const FwdParams &p, int nu, bool argmax, bool tile, int x, int grid, hipStream_t s);
+hipError_t forward_run_f16(const FwdParams &p, int nu, bool argmax, bool tile, int x, int n, hipStream_t s);
+hipError_t forward_run_bf16(const FwdParams &p, int nu, bool argmax, bool tile, int x, int n, hipStream_t s);
+hipError_t forward_run_f32(const FwdParams &p, int nu, bool argmax, bool tile, int x, int n, hipStream_t s);
 
 hipError_t forward_splitd_launch(FwdParams p, int dtype, int row_bytes, int num_cu, hipStream_t stream);
 hipError_t forward_wide_launch(FwdParams p, int dtype, int row_bytes, int num_cu, hipStream_t stream);
@@ -56,11 +56,11 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         p.ld = p.b;
     const int64_t total_blocks = (int64_t)p.n_q * p.bpq;
     const int64_t units = ragged ? p.total_tokens : p.b; // what is split across chunks
-    auto run = [&](bool tile, int x, int grid) {
+    auto run = [&](bool tile, int x, int n) {
         switch (dtype) {
-        case MAXSIM_F32: return forward_run_f32(p, nu, am, tile, x, grid, stream);
-        case MAXSIM_F16: return forward_run_f16(p, nu, am, tile, x, grid, stream);
-        default: return forward_run_bf16(p, nu, am, tile, x, grid, stream);
+        case MAXSIM_F32: return forward_run_f32(p, nu, am, tile, x, n, stream);
+        case MAXSIM_F16: return forward_run_f16(p, nu, am, tile, x, n, stream);
+        default: return forward_run_bf16(p, nu, am, tile, x, n, stream);
         }
     };
 
@@ -203,13 +203,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         p.n_groups = p.n_q;
         p.n_pass = (p.bpq + group_blocks - 1) / group_blocks;
     }
-    // 256 registers per wavefront: two wavefronts per SIMD are resident.  (Sixteen wavefronts per CU in a multiple of eight
-    // chunks, as this used to be, left half of the chip idle in a second round where documents are few: one query of 130
-    // tokens x 500 documents of 260 23.5 -> 13.6 us, 2 x 1024 x 600 pages 286 -> 235, eight queries x 20 000 texts 323 -> 302.)
-    const ChunkPlan plan = plan_chunks(p, p.n_groups, (int64_t)num_cu * 8 / w);
-    p.unit_per_chunk = plan.per_chunk;
-    p.n_chunks = (int)plan.n_chunks;
-    return run(true, shape, p.n_groups * p.n_chunks);
+    return run(true, shape, num_cu); // (the chunks: launch_chunks)
 }
 
 } // namespace maxsim

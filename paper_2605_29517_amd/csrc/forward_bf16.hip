@@ -2,8 +2,8 @@
 #include "forward_impl.h"
 
 namespace maxsim {
-hipError_t forward_run_bf16(const FwdParams &p, int nu, bool argmax, bool tile, int x, int grid, hipStream_t s)
+hipError_t forward_run_bf16(const FwdParams &p, int nu, bool argmax, bool tile, int x, int n, hipStream_t s)
 {
-    return run_dtype<MAXSIM_BF16>(p, nu, argmax, tile, x, grid, s);
+    return run_dtype<MAXSIM_BF16>(p, nu, argmax, tile, x, n, s);
 }
 } // namespace maxsim

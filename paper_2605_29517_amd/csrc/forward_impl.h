@@ -1287,21 +1287,52 @@ static hipError_t launch_stream(const FwdParams &p, int grid, hipStream_t stream
     }
 }
 
-template <int DT, int W, int NCB, bool ARGMAX, int PFD = 1>
-static hipError_t launch_tile(const FwdParams &p, int grid, hipStream_t stream)
+// The tile and packed-window kernels: the chunks are cut for the workgroups that are resident at a time, which the
+// registers of the instantiation decide: two wavefronts per SIMD with four blocks of 256-byte rows in each, four with
+// one block or narrow rows.  (One number for them all left half of the wavefront slots of the others empty: one query
+// of 130 tokens x 3000 documents of 100 with argmax 38 us instead of 27, fp32 d = 32 x 20 000 of 70 377 instead of 276.
+// Sixteen wavefronts per CU for all of them, in a multiple of eight chunks, left half of the chip idle in a second
+// round where documents are few: one query of 130 tokens x 500 documents of 260 23.5 us instead of 13.6, 2 x 1024 x 600
+// pages 286 instead of 235.)  The number is a property of the code object, the same on every device the library runs
+// on; it is asked for once per instantiation.
+template <auto KERNEL> static int resident_workgroups(int threads)
 {
-    hipLaunchKernelGGL((fwd_tile_kernel<DT, W, NCB, ARGMAX, PFD>), dim3(grid), dim3(W * 64), 0, stream, p, p.offsets);
+    static std::atomic<int> known{0};
+    int n = known.load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, KERNEL, threads, 0) != hipSuccess || n < 1)
+            return 0;
+        known.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
+template <auto KERNEL> static hipError_t launch_chunks(FwdParams p, int threads, int num_cu, hipStream_t stream)
+{
+    const int resident = resident_workgroups<KERNEL>(threads);
+    if (resident == 0)
+        return hipErrorInvalidValue;
+    const ChunkPlan plan = plan_chunks(p, p.n_groups, num_cu, resident);
+    if (plan.n_chunks * p.n_groups >= (int64_t(1) << 31))
+        return hipErrorInvalidValue;
+    p.unit_per_chunk = plan.per_chunk;
+    p.n_chunks = (int)plan.n_chunks;
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(plan.n_chunks * p.n_groups)), dim3(threads), 0, stream, p, p.offsets);
     return hipGetLastError();
 }
 
+template <int DT, int W, int NCB, bool ARGMAX, int PFD = 1>
+static hipError_t launch_tile(const FwdParams &p, int num_cu, hipStream_t stream)
+{
+    return launch_chunks<&fwd_tile_kernel<DT, W, NCB, ARGMAX, PFD>>(p, W * 64, num_cu, stream);
+}
+
 template <int DT, int NCB, int W = 8>
-static hipError_t launch_pack(const FwdParams &p, int grid, hipStream_t stream)
+static hipError_t launch_pack(const FwdParams &p, int num_cu, hipStream_t stream)
 {
     if (p.offsets)
-        hipLaunchKernelGGL((fwd_pack_kernel<DT, NCB, false, W>), dim3(grid), dim3(W * 64), 0, stream, p, p.offsets);
-    else
-        hipLaunchKernelGGL((fwd_pack_kernel<DT, NCB, true, W>), dim3(grid), dim3(W * 64), 0, stream, p, p.offsets);
-    return hipGetLastError();
+        return launch_chunks<&fwd_pack_kernel<DT, NCB, false, W>>(p, W * 64, num_cu, stream);
+    return launch_chunks<&fwd_pack_kernel<DT, NCB, true, W>>(p, W * 64, num_cu, stream);
 }
 
 template <int DT, bool ARGMAX>
@@ -1321,59 +1352,59 @@ static hipError_t dispatch_stream(const FwdParams &p, int ncb, int grid, hipStre
 }
 
 template <int DT, bool ARGMAX>
-static hipError_t dispatch_tile(const FwdParams &p, int w, int grid, hipStream_t s)
+static hipError_t dispatch_tile(const FwdParams &p, int w, int num_cu, hipStream_t s)
 {
     constexpr int NU = Traits<DT>::NU;
     constexpr int NCB = NU <= 8 ? 4 : 32 / NU; // query fragments fill 128 registers
     if constexpr (NCB == 4) { // few column blocks: eight wavefronts with one or two blocks each
         if (w == 81)
-            return launch_tile<DT, 8, 1, ARGMAX, 6>(p, grid, s);
+            return launch_tile<DT, 8, 1, ARGMAX, 6>(p, num_cu, s);
         if (w == 82)
-            return launch_tile<DT, 8, 2, ARGMAX, 3>(p, grid, s);
+            return launch_tile<DT, 8, 2, ARGMAX, 3>(p, num_cu, s);
         if (w == 42)
-            return launch_tile<DT, 4, 2, ARGMAX, 4>(p, grid, s);
+            return launch_tile<DT, 4, 2, ARGMAX, 4>(p, num_cu, s);
         if constexpr (!ARGMAX) {
             if (w == 93) // ragged corpus, queries of one block: windows over the packed rows; 24 or 32 queries per workgroup
-                return launch_pack<DT, 3>(p, grid, s);
+                return launch_pack<DT, 3>(p, num_cu, s);
             if (w == 94)
-                return launch_pack<DT, 4>(p, grid, s);
+                return launch_pack<DT, 4>(p, num_cu, s);
             if (w == 943)
-                return launch_pack<DT, 3, 4>(p, grid, s);
+                return launch_pack<DT, 3, 4>(p, num_cu, s);
             if (w == 944)
-                return launch_pack<DT, 4, 4>(p, grid, s);
+                return launch_pack<DT, 4, 4>(p, num_cu, s);
             if (w == 923)
-                return launch_pack<DT, 3, 2>(p, grid, s);
+                return launch_pack<DT, 3, 2>(p, num_cu, s);
             if (w == 924)
-                return launch_pack<DT, 4, 2>(p, grid, s);
+                return launch_pack<DT, 4, 2>(p, num_cu, s);
         }
     }
     switch (w) {
-    case 1: return launch_tile<DT, 1, NCB, ARGMAX>(p, grid, s);
-    case 2: return launch_tile<DT, 2, NCB, ARGMAX>(p, grid, s);
-    case 4: return launch_tile<DT, 4, NCB, ARGMAX>(p, grid, s);
-    default: return launch_tile<DT, 8, NCB, ARGMAX>(p, grid, s);
+    case 1: return launch_tile<DT, 1, NCB, ARGMAX>(p, num_cu, s);
+    case 2: return launch_tile<DT, 2, NCB, ARGMAX>(p, num_cu, s);
+    case 4: return launch_tile<DT, 4, NCB, ARGMAX>(p, num_cu, s);
+    default: return launch_tile<DT, 8, NCB, ARGMAX>(p, num_cu, s);
     }
 }
 
 
 template <int F>
-static hipError_t run_format(const FwdParams &p, bool argmax, bool tile, int x, int grid, hipStream_t s)
+static hipError_t run_format(const FwdParams &p, bool argmax, bool tile, int x, int n, hipStream_t s)
 {
     if (tile)
-        return argmax ? dispatch_tile<F, true>(p, x, grid, s) : dispatch_tile<F, false>(p, x, grid, s);
-    return argmax ? dispatch_stream<F, true>(p, x, grid, s) : dispatch_stream<F, false>(p, x, grid, s);
+        return argmax ? dispatch_tile<F, true>(p, x, n, s) : dispatch_tile<F, false>(p, x, n, s);
+    return argmax ? dispatch_stream<F, true>(p, x, n, s) : dispatch_stream<F, false>(p, x, n, s);
 }
 
 // All widths of one element type: nu = row bytes / 32.  `tile` picks the kernel, x is its shape
 // parameter (wavefronts per workgroup for the tile kernel, column blocks per wavefront for the
-// streaming kernel).
+// streaming kernel) and n the streaming kernel's grid or, for the tile kernel, the device's CUs.
 template <int DTYPE>
-static hipError_t run_dtype(const FwdParams &p, int nu, bool argmax, bool tile, int x, int grid, hipStream_t s)
+static hipError_t run_dtype(const FwdParams &p, int nu, bool argmax, bool tile, int x, int n, hipStream_t s)
 {
     switch (nu) {
-    case 4: return run_format<fmt(DTYPE, 4)>(p, argmax, tile, x, grid, s);
-    case 8: return run_format<fmt(DTYPE, 8)>(p, argmax, tile, x, grid, s);
-    case 16: return run_format<fmt(DTYPE, 16)>(p, argmax, tile, x, grid, s);
+    case 4: return run_format<fmt(DTYPE, 4)>(p, argmax, tile, x, n, s);
+    case 8: return run_format<fmt(DTYPE, 8)>(p, argmax, tile, x, n, s);
+    case 16: return run_format<fmt(DTYPE, 16)>(p, argmax, tile, x, n, s);
     default: return hipErrorNotSupported;
     }
 }

@@ -483,7 +483,7 @@ hipError_t forward_wide_launch(FwdParams p, int dtype, int row_bytes, int num_cu
             if (qpg > 1 && (p.n_q + groups - 1) / groups < qpg)
                 continue; // fewer queries in each of as many groups will do
             const int nb = qpg * p.bpq;
-            const ChunkPlan c = plan_chunks(p, groups, num_cu);
+            const ChunkPlan c = plan_chunks(p, groups, num_cu, 1);
             const int64_t time = c.time * (nb <= 1 ? 60 : nb <= 2 ? 65 : nb <= 4 ? 80 : nb <= 6 ? 105 : 127);
             if (time < best_time) {
                 best_time = time;
@@ -499,7 +499,7 @@ hipError_t forward_wide_launch(FwdParams p, int dtype, int row_bytes, int num_cu
         p.n_pass = (p.bpq + WD_MAX_BLOCKS - 1) / WD_MAX_BLOCKS;
         blocks = blocks_per_pass = (p.bpq + p.n_pass - 1) / p.n_pass;
         p.n_pass = (p.bpq + blocks - 1) / blocks;
-        plan = plan_chunks(p, p.n_groups, num_cu);
+        plan = plan_chunks(p, p.n_groups, num_cu, 1);
     }
     p.unit_per_chunk = plan.per_chunk;
     p.n_chunks = (int)plan.n_chunks;
