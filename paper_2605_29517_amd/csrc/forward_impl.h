@@ -1029,7 +1029,7 @@ __device__ __forceinline__ void win_advance(WinIter &it, const Window &w, const 
 // NCB: column blocks (queries) per wavefront, 2 to 4; W: wavefronts per workgroup (8: 16 to 32 queries; 4 and 2 give
 //      fewer queries the same 3 or 4 blocks per wavefront, i.e. as many MFMAs per window and barrier)
 // UNI: uniform corpus (documents of l_d tokens, no offsets array)
-template <int DT, int NCB, bool UNI, int W = 8>
+template <int DT, int NCB, bool UNI, int W = 8, bool READ_ONCE>
 __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, OffsetsPtr off)
 {
     using TR = Traits<DT>;
@@ -1111,12 +1111,12 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
             // window row i holds A's row min(i, n_a - 1) below pa and B's row min(i - pa, n_b - 1) from pa on
             // (without a B that is A's last row again); A and B are neighbours in the packed corpus
             const char *base = p.D + (int64_t)li.row0 * TR::ROW_BYTES;
-            static_for<CPT>([&](auto i) {
+            auto at = [&](auto i) {
                 const int wr = cp_row(i);
                 const int row = wr < lw.pa ? min(wr, lw.n_a - 1) : lw.n_a + min(wr - lw.pa, lw.n_b - 1);
-                // (read once, or by a few workgroups at the same time: 2-5 % at five to sixteen queries)
-                g(i) = load_stream16(base + row * TR::ROW_BYTES + cp_goff(i));
-            });
+                return base + row * TR::ROW_BYTES + cp_goff(i);
+            };
+            static_for<CPT>([&](auto i) { g(i) = READ_ONCE ? load_stream16(at(i)) : *reinterpret_cast<const uint4 *>(at(i)); });
         }
         win_advance<UNI>(li, lw, p, off);
         return d;
@@ -1327,12 +1327,22 @@ static hipError_t launch_tile(const FwdParams &p, int num_cu, hipStream_t stream
     return launch_chunks<&fwd_tile_kernel<DT, W, NCB, ARGMAX, PFD>>(p, W * 64, num_cu, stream);
 }
 
+// Windows are read with the non-temporal hint (READ_ONCE) where one workgroup reads each of them and the corpus is
+// larger than the 256 MB that the device's last cache holds: 1050 instead of 1118 us for five queries x 100 000 texts,
+// 140 instead of 147 for eight x 20 000 x 96 tokens.  A corpus that stays in that cache from one call to the next is
+// slower with the hint (five queries x 10 000 x 180 tokens of d = 64 57.5 instead of 52 us, twelve x 3000 texts 59.6
+// instead of 57.4), and so are windows that two column groups share (40 queries x 50 000 texts 2054 instead of 1990
+// us); fp32 takes the same time either way.
 template <int DT, int NCB, int W = 8>
 static hipError_t launch_pack(const FwdParams &p, int num_cu, hipStream_t stream)
 {
-    if (p.offsets)
-        return launch_chunks<&fwd_pack_kernel<DT, NCB, false, W>>(p, W * 64, num_cu, stream);
-    return launch_chunks<&fwd_pack_kernel<DT, NCB, true, W>>(p, W * 64, num_cu, stream);
+    if constexpr (Traits<DT>::DT != MAXSIM_F32) {
+        if (p.n_groups == 1 && p.total_tokens * Traits<DT>::ROW_BYTES > (int64_t(256) << 20))
+            return p.offsets ? launch_chunks<&fwd_pack_kernel<DT, NCB, false, W, true>>(p, W * 64, num_cu, stream)
+                             : launch_chunks<&fwd_pack_kernel<DT, NCB, true, W, true>>(p, W * 64, num_cu, stream);
+    }
+    return p.offsets ? launch_chunks<&fwd_pack_kernel<DT, NCB, false, W, false>>(p, W * 64, num_cu, stream)
+                     : launch_chunks<&fwd_pack_kernel<DT, NCB, true, W, false>>(p, W * 64, num_cu, stream);
 }
 
 template <int DT, bool ARGMAX>

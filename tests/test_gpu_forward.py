@@ -321,3 +321,28 @@ def test_runs_of_documents_are_found(b):
     lens[b // 2] = 40
     Q, Dp, off = _ragged_case(1, 8, lens, "f16", 91)
     forward_parity_ragged(Q, Dp, off, M.maxsim_forward_ragged, False, 1e-5)
+
+
+@pytest.mark.parametrize("n_q", [6, 8, 15, 24])
+@pytest.mark.parametrize("dtype,d", [("f16", 128), ("bf16", 64)])
+def test_corpora_larger_than_the_last_cache(n_q, dtype, d):
+    """Above 256 MB the windows of five to 32 queries are read with another hint: the documents at both ends against the oracle,
+    all of them against the kernel for four queries (fp32 accumulation of 128 products, sums of 32 maxima: 1e-5 relative)."""
+    rows = (256 << 20) // (2 * d) + 5000
+    lens = np.random.default_rng(n_q).integers(0, 300, 2 * rows // 290)
+    lens = lens[:np.searchsorted(np.cumsum(lens), rows) + 1]
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV)
+    Dp, Q = W.unit_rows((int(lens.sum()), d), dtype, 141, DEV), W.unit_rows((n_q, 32, d), dtype, 142, DEV)
+    s = M.maxsim_forward_ragged(Q, Dp, off)
+    few = torch.cat([M.maxsim_forward_ragged(Q[i:i + 4].contiguous(), Dp, off) for i in range(0, n_q, 4)])
+    assert torch.equal(torch.isinf(s), torch.isinf(few))
+    assert torch.allclose(s, few, rtol=1e-5)
+    for a, b in ((0, 40), (len(lens) - 40, len(lens))):
+        part, po = Dp[off[a]:off[b]].contiguous(), (off[a:b + 1] - off[a]).contiguous()
+        forward_parity_ragged(Q, part, po, lambda q, dd, o, want_argmax: s[:, a:b], False, 1e-5)
+    l_d = 190
+    D = Dp[:rows // l_d * l_d].view(-1, l_d, d)
+    assert D.numel() * 2 > 256 << 20
+    s = M.maxsim_forward(Q, D)
+    few = torch.cat([M.maxsim_forward(Q[i:i + 4].contiguous(), D) for i in range(0, n_q, 4)])
+    assert torch.allclose(s, few, rtol=1e-5)
