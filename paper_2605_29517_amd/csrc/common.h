@@ -273,18 +273,19 @@ __device__ __forceinline__ void chunk_doc_range(const FwdParams &p, int64_t chun
 // chunk.  A workgroup costs what about 200 tokens do beside its documents (its query fragments and the first loads), a
 // chunk of a ragged corpus may be half a document longer than its share, and a CU takes as long as the workgroups that
 // fall to it, or that are resident on it at a time if those are more: `time`, in tokens, is what is minimised, over the
-// numbers of workgroups from those resident to eight times as many.  Ragged corpora of 2500 tokens a chunk and more are
-// cut for two rounds at least, so that CUs whose documents happen to be short take more of them (lengths drawn from a
-// log-normal distribution, 30 000 x 98 tokens: 6-7 % over one round; lengths within 64-300 tokens: the same).
+// numbers of workgroups from those resident to eight times as many.  With `level`, ragged corpora of 2500 tokens a
+// chunk and more are cut for two rounds at least, so that CUs whose documents happen to be short take more of them
+// (lengths drawn from a log-normal distribution, 30 000 x 98 tokens: 6-7 % over one round; lengths within 64-300
+// tokens: the same; the wide kernel, whose start costs more, loses 3-20 % that way).
 struct ChunkPlan {
     int64_t per_chunk, n_chunks, time;
 };
-inline ChunkPlan plan_chunks(const FwdParams &p, int64_t groups, int64_t num_cu, int64_t resident)
+inline ChunkPlan plan_chunks(const FwdParams &p, int64_t groups, int64_t num_cu, int64_t resident, bool level)
 {
     const bool ragged = p.offsets != nullptr;
     const int64_t units = ragged ? p.total_tokens : p.b;
     const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b; // (uniform: l_d)
-    const bool two_rounds = ragged && p.total_tokens * groups >= 2500 * num_cu * resident * 2;
+    const bool two_rounds = level && ragged && p.total_tokens * groups >= 2500 * num_cu * resident * 2;
     ChunkPlan best = {1, 1, INT64_MAX};
     for (int64_t k = two_rounds ? 2 * resident : resident; k <= 8 * resident; ++k) { // workgroups per CU
         int64_t chunks = num_cu * k / groups;

@@ -10,6 +10,8 @@ hipError_t forward_run_f32(const FwdParams &p, int nu, bool argmax, bool tile, i
 
 hipError_t forward_splitd_launch(FwdParams p, int dtype, int row_bytes, int num_cu, hipStream_t stream);
 hipError_t forward_wide_launch(FwdParams p, int dtype, int row_bytes, int num_cu, hipStream_t stream);
+double forward_splitd_time(FwdParams p, int dtype, int row_bytes, int num_cu);
+double forward_wide_time(FwdParams p, int num_cu);
 
 constexpr int MAX_ROW_BYTES = 16384; // d = 8192 (16-bit) or 4096 (fp32)
 
@@ -36,17 +38,26 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         return hipErrorNotSupported;
     const int row_bytes = d * (dtype == MAXSIM_F32 ? 4 : 2);
     // any other width: both operands stream through LDS in slabs of the width; so do rows of 512 bytes from 8 column
-    // blocks on (two blocks per wavefront in the register-stationary kernel: measured 3-11 % slower there).  Macro tiles
-    // of 256 query tokens and whole cache lines (forward_wide.hip), except where a document is little work: narrow rows
-    // and documents of 65-128 tokens with more than 8 blocks, which then go by 512 query tokens at once (20 000 x 100
-    // tokens, 16 blocks, d = 256 / 160: 790 / 515 us in slabs of half a line, 800 / 573 in whole ones; 8 blocks, d = 96:
-    // 258 against 222; 100 000 x 10 tokens, 16 blocks, d = 96: 1335 against 1250), or of half a line with 8 and more (d = 32: 113 against 121).
+    // blocks on (two blocks per wavefront in the register-stationary kernel: measured 3-11 % slower there).  Two
+    // kernels: macro tiles of 256 document tokens x 256 query tokens and whole cache lines (forward_wide.hip), or of 64
+    // x 512 and half lines (forward_splitd.hip).  Up to 8 blocks the first, except for half lines and documents of up
+    // to 128 tokens (8 blocks, d = 32: 121 against 113 us); beyond, 512 query tokens at once are ahead where documents
+    // are little work (narrow rows and 65-128 tokens: 20 000 x 100 tokens, 16 blocks, d = 256 / 160: 800 / 573 us in
+    // the first, 790 / 515 in the second) and where the first would multiply many padded blocks (three queries of 140
+    // tokens x 4000 x 128, d = 512: 72 % of its time) or documents of a few tiles of 256 leave much of one empty: the
+    // estimates of both decide.  The other way round, the second's chunks fill the chip badly on some numbers of
+    // documents (16 queries x 1500 x 100 tokens, d = 512: 1.35 times the first's time).
     const int64_t all_blocks = (int64_t)p.n_q * ((p.l_q + BLOCK_COLS - 1) / BLOCK_COLS);
     if (!register_stationary_width(row_bytes) || (row_bytes == 512 && all_blocks >= 8)) {
         const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b; // (uniform corpora: total_tokens = b * l_d)
-        const bool little = dtype != MAXSIM_F32 && mean_len <= 128 &&
-                            ((all_blocks > 8 && row_bytes <= 512 && mean_len > 64) || (all_blocks >= 8 && row_bytes == 64));
-        return little ? forward_splitd_launch(p, dtype, row_bytes, num_cu, stream) : forward_wide_launch(p, dtype, row_bytes, num_cu, stream);
+        bool slabs;
+        if (all_blocks <= 8)
+            slabs = dtype != MAXSIM_F32 && all_blocks == 8 && row_bytes == 64 && mean_len <= 128;
+        else if (dtype != MAXSIM_F32 && mean_len <= 128 && (row_bytes == 64 || (row_bytes <= 512 && mean_len > 64)))
+            slabs = true;
+        else
+            slabs = forward_splitd_time(p, dtype, row_bytes, num_cu) <= forward_wide_time(p, num_cu);
+        return slabs ? forward_splitd_launch(p, dtype, row_bytes, num_cu, stream) : forward_wide_launch(p, dtype, row_bytes, num_cu, stream);
     }
     const int nu = row_bytes / 32; // 16-byte chunk pairs per row
     const bool ragged = p.offsets != nullptr;

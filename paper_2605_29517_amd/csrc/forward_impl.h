@@ -1312,7 +1312,7 @@ template <auto KERNEL> static hipError_t launch_chunks(FwdParams p, int threads,
     const int resident = resident_workgroups<KERNEL>(threads);
     if (resident == 0)
         return hipErrorInvalidValue;
-    const ChunkPlan plan = plan_chunks(p, p.n_groups, num_cu, resident);
+    const ChunkPlan plan = plan_chunks(p, p.n_groups, num_cu, resident, true);
     if (plan.n_chunks * p.n_groups >= (int64_t(1) << 31))
         return hipErrorInvalidValue;
     p.unit_per_chunk = plan.per_chunk;

@@ -551,6 +551,41 @@ static int64_t splitd_plan(FwdParams &p, int num_cu, int max_chunk_docs = 0)
     return (int64_t)p.n_groups * n_chunks;
 }
 
+// A CU's time in the units of forward_wide_time: its documents rounded up to macro tiles of 64 tokens, and what 45
+// tokens take to begin with, at what 16 blocks cost here against twice 8 blocks there.  The factors were measured on
+// some 2900 shapes (16 bits and fp32, d = 32 to 4096, 9 to 94 blocks, documents of 20 to 3000 tokens, corpora that fill
+// the chip and that do not) and lean to this kernel: the choice by them is 2 % off the faster kernel's time on average,
+// and more than 3 % slower than this kernel on 9.
+double forward_splitd_time(FwdParams p, int dtype, int row_bytes, int num_cu)
+{
+    const int64_t grid = splitd_plan(p, num_cu);
+    const int64_t rows = (p.total_tokens + p.b - 1) / p.b; // the mean length
+    const int64_t tokens = p.offsets ? (p.unit_per_chunk > rows ? p.unit_per_chunk : rows) + rows / 2 : p.unit_per_chunk * rows;
+    const double padded = rows ? (double)tokens * (p.offsets ? rows + 32 : (rows + 63) / 64 * 64) / rows : 0.0;
+    const int64_t on_cu = (grid + num_cu - 1) / num_cu;
+    // up to 64, 96, 128 tokens and longer: the lower macro tiles that short documents take there cost more per row
+    constexpr double by_length[2][4] = {{1.35, 0.82, 0.99, 1.04}, {1.5, 0.85, 0.9, 1.03}}; // 16 bits, fp32
+    constexpr double by_length_narrow[4] = {0.85, 1.0, 0.94, 0.98};                        // rows below 1024 bytes (512 in the first), 16 bits
+    const int length = rows <= 64 ? 0 : rows <= 96 ? 1 : rows <= 128 ? 2 : 3;
+    double factor = p.offsets && rows <= 128 ? (dtype == MAXSIM_F32 ? 1.1 : 1.0) : by_length[dtype == MAXSIM_F32][length];
+    if (row_bytes == SD_SLAB) { // one slab per macro tile: a barrier for little work there
+        factor = p.argmax ? 0.82 : 0.62;
+    } else {
+        if (length == 3 && grid < num_cu)
+            factor *= 1.12;
+        if (dtype != MAXSIM_F32) {
+            const int64_t in_group = p.n_pass > 1 ? (p.bpq + p.n_pass - 1) / p.n_pass : ((int64_t)p.n_q * p.bpq + p.n_groups - 1) / p.n_groups;
+            if (p.b >= num_cu && in_group < SD_GROUP_BLOCKS) // fewer blocks draw less power
+                factor *= 1.0 - 0.03 * (double)(SD_GROUP_BLOCKS - (in_group > 8 ? in_group : 8));
+            if (row_bytes < (length == 0 ? 512 : 1024))
+                factor *= by_length_narrow[length];
+            if (p.bpq > 8 && row_bytes >= 4096 && rows > 256 && (rows + 255) / 256 * 256 * 4 >= rows * 5)
+                factor *= 0.8; // there a document leaves the L2 between its passes and most of a macro tile empty
+        }
+    }
+    return (double)on_cu * (padded * p.n_pass + 45) * 2 * 127 * factor;
+}
+
 // Any row width that is a multiple of 64 bytes.  `num_cu` is the device's CU count.
 hipError_t forward_splitd_launch(FwdParams p, int dtype, int row_bytes, int num_cu, hipStream_t stream)
 {
