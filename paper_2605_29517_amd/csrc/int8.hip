@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(W * 64, W >= 4 ? 2 : 1) fwd_i8_kernel(I8Params
 // The roles are turned around: the query tokens of a group (up to 1024, padded rows, plus
 // their scales) are copied into LDS once per workgroup, and every wavefront works alone on
 // its own run of documents.  A 32-token document tile goes from HBM straight into registers
-// in MFMA operand layout, one tile ahead, and stays there while the wavefront walks over all
+// in MFMA operand layout, one or two tiles ahead, and stays there while the wavefront walks over all
 // column blocks of the group, reading the B operands of block k + 1 from LDS during the
 // MFMAs of block k and folding block k - 1 under them.  There is no barrier, no LDS write
 // and no staging copy in the main loop, the per-tile work (scales, loads, iterator) is
@@ -490,7 +490,7 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, 
                     P.scores[(int64_t)q * p.ld + doc] = neg_inf();
     }
 
-    TileIter li, ci; // load iterator: one tile ahead of the compute iterator
+    TileIter li, ci; // load iterator: DEPTH tiles ahead of the compute iterator
     it_init(li, p, off, doc0, doc1);
     ci = li;
     if (!it_valid(ci))
@@ -595,7 +595,7 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, 
 // ---------------------------------------------------------------------------------------
 // With a thousand documents and a short query the corpus read is the cost, and a wavefront per document would leave most
 // of the chip idle.  Here a workgroup takes documents one after the other and its W wavefronts share each document's
-// tiles, every W-th each; the query tokens sit in LDS as above and every wavefront still streams its tiles HBM ->
+// tiles; the query tokens sit in LDS as above and every wavefront still streams its tiles HBM ->
 // registers, one tile ahead, across document borders.  At the end of a document the W partial maxima per query token
 // meet in LDS (double-buffered, one barrier per document) and one wavefront, a different one each time, finishes the
 // score.  Built for up to 16 column blocks (512 query tokens): beyond that the maxima of eight wavefronts no longer fit
@@ -634,8 +634,13 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
     const int doc0 = (int)doc0_, doc1 = (int)doc1_;
 
     // first row and length of a document (offsets forced into the corpus, see clamp_offset)
+    constexpr bool UNI = W == I8D_WAVES; // eight wavefronts share documents of equal length only
+    // Which tiles are a wavefront's: every W-th, or of documents of equal length and from three blocks on the w-th eighth,
+    // with a loader that counts tiles instead of rows (4 x 32 query tokens: 1000 x 300 18.6 -> 17.7 us, 3000 x 300 42.8
+    // -> 39.0, 900 x 1024 36.8 -> 33.9; one block: 2000 x 1024 43.5 -> 47)
+    constexpr bool RUNS = UNI && NB >= 3;
     auto extent = [&](int doc, int &first, int &len) {
-        if (p.offsets) {
+        if (!UNI && p.offsets) {
             const int t_all = (int)p.total_tokens;
             first = min(max(off[doc], 0), t_all);
             len = min(max(off[doc + 1], first), t_all) - first;
@@ -644,23 +649,41 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
             len = p.l_d;
         }
     };
-    // the loader walks this wavefront's tiles (every W-th of a document) in order; past the end it stays on the last one
+    // the loader walks this wavefront's tiles in order; past the end it stays on the last one
+    const int n_tiles = (p.l_d + TILE_ROWS - 1) / TILE_ROWS;
+    const int t_lo = w * (n_tiles / W) + min(w, n_tiles % W);
+    const int cnt = n_tiles / W + (w < n_tiles % W ? 1 : 0); // RUNS: tiles [t_lo, t_lo + cnt)
     i32x4 a_n[I8_NU];
     float s_n = 0.0f;
-    int l_doc = doc0, l_first, l_len, l_t0 = w * TILE_ROWS;
-    extent(l_doc, l_first, l_len);
+    int l_doc = doc0, l_first = 0, l_len = 0, l_t0 = w * TILE_ROWS, l_t = 0;
+    if (!RUNS)
+        extent(l_doc, l_first, l_len);
     int l_row = 0, l_last = 0;
     auto gload = [&]() {
-        while (l_doc < doc1 && l_t0 >= l_len) {
-            l_doc += 1;
-            l_t0 = w * TILE_ROWS;
-            if (l_doc < doc1)
-                extent(l_doc, l_first, l_len);
-        }
-        if (l_doc < doc1) {
-            l_row = l_first + l_t0;
-            l_last = l_len - l_t0 - 1; // rows past the document re-read its last token
-            l_t0 += W * TILE_ROWS;
+        if constexpr (RUNS) {
+            if (cnt == 0)
+                return;
+            const int t0 = (t_lo + l_t) * TILE_ROWS;
+            l_row = l_doc * p.l_d + t0;
+            l_last = p.l_d - t0 - 1;
+            if (l_t + 1 < cnt) {
+                l_t += 1;
+            } else if (l_doc + 1 < doc1) {
+                l_doc += 1;
+                l_t = 0;
+            }
+        } else {
+            while (l_doc < doc1 && l_t0 >= l_len) {
+                l_doc += 1;
+                l_t0 = w * TILE_ROWS;
+                if (l_doc < doc1)
+                    extent(l_doc, l_first, l_len);
+            }
+            if (l_doc < doc1) {
+                l_row = l_first + l_t0;
+                l_last = l_len - l_t0 - 1; // rows past the document re-read its last token
+                l_t0 += W * TILE_ROWS;
+            }
         }
         const int64_t grow = (int64_t)l_row + (rho < l_last ? rho : l_last);
         const char *src = P.D + grow * I8_ROW_BYTES + h * 16;
@@ -694,7 +717,8 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
 #pragma unroll
         for (int blk = 0; blk < NB; ++blk)
             m[blk] = neg_inf();
-        for (int t0 = w * TILE_ROWS; t0 < len; t0 += W * TILE_ROWS) {
+        const int mine_cnt = RUNS ? cnt : (len - w * TILE_ROWS + W * TILE_ROWS - 1) / (W * TILE_ROWS); // (not positive: none)
+        for (int t = 0; t < mine_cnt; ++t) {
             i32x4 a[I8_NU];
 #pragma unroll
             for (int u = 0; u < I8_NU; ++u)
@@ -747,7 +771,12 @@ template <int W> static hipError_t launch_i8(const I8Params &P, int grid, hipStr
 
 template <int NB> static hipError_t launch_i8_doc(const I8Params &P, int grid, hipStream_t s)
 {
-    if constexpr (NB <= I8D_LIN_BLOCKS)
+    // (one block and documents of 128 tokens and more, four and more to a wavefront: two tiles in flight are 3-4 % behind one,
+    // 50 000 x 128 127.0 against 123.6 us; with shorter or fewer ones 5-10 % ahead, 100 000 x 32 64.6 against 71.2,
+    // 4200 x 1024 85.1 against 90.5, with 64-300 tokens 2 %)
+    if (NB == 1 && !P.f.offsets && P.f.l_d >= 128 && P.f.unit_per_chunk >= 4)
+        hipLaunchKernelGGL((fwd_i8_doc_kernel<1, true, 1>), dim3(grid), dim3(I8D_WAVES * 64), i8_doc_lin_lds(1), s, P, P.f.offsets);
+    else if constexpr (NB <= I8D_LIN_BLOCKS)
         hipLaunchKernelGGL((fwd_i8_doc_kernel<NB, true, I8D_DEPTH>), dim3(grid), dim3(I8D_WAVES * 64), i8_doc_lin_lds(NB), s, P, P.f.offsets);
     else
         hipLaunchKernelGGL((fwd_i8_doc_kernel<NB, false, i8d_depth(NB)>), dim3(grid), dim3(I8D_WAVES * 64), i8_doc_lds(NB), s, P, P.f.offsets);
