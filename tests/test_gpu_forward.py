@@ -227,6 +227,21 @@ def test_wide_many_documents(n_q, l_q):
     forward_parity_uniform(Q, W.unit_rows((n, 70, 96), "f16", 65, DEV), M.maxsim_forward, False, 1e-5)
 
 
+# Rows of a single slab (d = 32 in 16 bits): one barrier per macro tile, so that with short documents the loads run up to three
+# documents ahead and the merge and the sum of one document fall into the next two.  Several documents per workgroup, a few of
+# them empty, in the shapes for 1 to 8 column blocks and for every height of the macro tiles
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("longest", [40, 200, 600])
+@pytest.mark.parametrize("n_q,l_q", [(1, 20), (2, 30), (2, 40), (3, 60), (7, 32), (8, 32), (1, 300)])
+def test_wide_one_slab(n_q, l_q, longest, dtype):
+    n = torch.cuda.get_device_properties(0).multi_processor_count * (8 if longest < 100 else 3) + 7
+    lens = np.random.default_rng(longest + l_q).integers(0, longest, n)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV)
+    Q = W.unit_rows((n_q, l_q, 32), dtype, 64, DEV)
+    forward_parity_ragged(Q, W.unit_rows((int(lens.sum()), 32), dtype, 63, DEV), off, M.maxsim_forward_ragged, True, 1e-5)
+    forward_parity_uniform(Q, W.unit_rows((n, longest // 2 + 1, 32), dtype, 65, DEV), M.maxsim_forward, True, 1e-5)
+
+
 # Ragged corpora scored by more than 16 queries of one column block take 32-row windows over the packed rows (a window
 # may hold the end of one document and the start of the next).  Length mixes: runs of tiny documents (several
 # boundaries close together, a document that lies inside one window whole), empty documents at the start, in a row
