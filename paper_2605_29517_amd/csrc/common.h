@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <cmath>
 #include <type_traits>
 
 #include "../../include/maxsim.h"
@@ -270,24 +271,26 @@ __device__ __forceinline__ void chunk_doc_range(const FwdParams &p, int64_t chun
 }
 
 // How a corpus is cut into chunks for `groups` column groups: units (documents, or tokens of a ragged corpus) per
-// chunk.  A workgroup costs what about 200 tokens do beside its documents (its query fragments and the first loads), a
+// chunk. A workgroup costs what about 200 tokens do beside its documents (its query fragments and the first loads), a
 // chunk of a ragged corpus may be half a document longer than its share, and a CU takes as long as the workgroups that
-// fall to it, or that are resident on it at a time if those are more: `time`, in tokens, is what is minimised, over the
-// numbers of workgroups from those resident to eight times as many.  With `level`, ragged corpora of 2500 tokens a
-// chunk and more are cut for two rounds at least, so that CUs whose documents happen to be short take more of them
-// (lengths drawn from a log-normal distribution, 30 000 x 98 tokens: 6-7 % over one round; lengths within 64-300
-// tokens: the same; the wide kernel, whose start costs more, loses 3-20 % that way).
+// fall to it; with fewer than are resident on it at a time it works more slowly, by the square root of the share.
+// `time`, in tokens, is what is minimised, over the numbers of workgroups from `fewest` per CU (at most those resident)
+// to eight times those resident. With `level`, ragged corpora of 2500 tokens a chunk and more are cut for two rounds at
+// least where one or two workgroups are resident, so that CUs whose documents happen to be short take more of them (9
+// queries with argmax x 30 000 documents of log-normal length, 98 tokens on average: 425 us instead of 457; with 64-200
+// tokens 2-3 % are lost). Several column groups, four resident workgroups and the wide kernel, whose start costs more,
+// lose 4-20 % that way.
 struct ChunkPlan {
     int64_t per_chunk, n_chunks, time;
 };
-inline ChunkPlan plan_chunks(const FwdParams &p, int64_t groups, int64_t num_cu, int64_t resident, bool level)
+inline ChunkPlan plan_chunks(const FwdParams &p, int64_t groups, int64_t num_cu, int64_t resident, int64_t fewest, bool level)
 {
     const bool ragged = p.offsets != nullptr;
     const int64_t units = ragged ? p.total_tokens : p.b;
     const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b; // (uniform: l_d)
-    const bool two_rounds = level && ragged && p.total_tokens * groups >= 2500 * num_cu * resident * 2;
+    const bool two_rounds = level && ragged && groups == 1 && resident <= 2 && p.total_tokens >= 2500 * num_cu * resident * 2;
     ChunkPlan best = {1, 1, INT64_MAX};
-    for (int64_t k = two_rounds ? 2 * resident : resident; k <= 8 * resident; ++k) { // workgroups per CU
+    for (int64_t k = two_rounds ? 2 * resident : fewest; k <= 8 * resident; ++k) { // workgroups per CU
         int64_t chunks = num_cu * k / groups;
         chunks = chunks < 1 ? 1 : chunks > p.b ? p.b : chunks;
         int64_t per = (units + chunks - 1) / chunks;
@@ -295,7 +298,10 @@ inline ChunkPlan plan_chunks(const FwdParams &p, int64_t groups, int64_t num_cu,
         const int64_t n = units < 1 ? 1 : (units + per - 1) / per;
         const int64_t tokens = ragged ? (per > mean_len ? per : mean_len) + mean_len / 2 : per * mean_len;
         const int64_t on_cu = (n * groups + num_cu - 1) / num_cu;
-        const int64_t time = (on_cu > resident ? on_cu : resident) * (tokens + 200);
+        int64_t time = on_cu * (tokens + 200);
+        if (on_cu < resident) // (as many as fill the CU, where nothing says that fewer will do)
+            time = fewest < resident ? (int64_t)((double)(on_cu * tokens) * std::sqrt((double)resident / (double)on_cu)) + on_cu * 200
+                                     : resident * (tokens + 200);
         if (time < best.time)
             best = {per, n, time};
     }

@@ -497,7 +497,7 @@ WidePlan plan_wide(const FwdParams &p, int num_cu)
         int n_pass = (p.bpq + WD_MAX_BLOCKS - 1) / WD_MAX_BLOCKS;
         const int blocks = (p.bpq + n_pass - 1) / n_pass;
         n_pass = (p.bpq + blocks - 1) / blocks;
-        const ChunkPlan c = plan_chunks(p, p.n_q, num_cu, 1, false);
+        const ChunkPlan c = plan_chunks(p, p.n_q, num_cu, 1, 1, false);
         return {c, time(c, p.n_q, n_pass, blocks), p.n_q, 1, n_pass, blocks};
     }
     // Whole queries per workgroup.  More of them read a document less often, fewer make more workgroups, which counts where
@@ -508,7 +508,7 @@ WidePlan plan_wide(const FwdParams &p, int num_cu)
         const int groups = (p.n_q + qpg - 1) / qpg;
         if (qpg > 1 && (p.n_q + groups - 1) / groups < qpg)
             continue; // fewer queries in each of as many groups will do
-        const ChunkPlan c = plan_chunks(p, groups, num_cu, 1, false);
+        const ChunkPlan c = plan_chunks(p, groups, num_cu, 1, 1, false);
         const double t = (double)c.time * with_shape(qpg * p.bpq, rows, [&](auto s) { return wide_weight(decltype(s)::BLOCKS, rows); });
         if (best.n_groups == 0 || t < best_time) {
             best_time = t;
