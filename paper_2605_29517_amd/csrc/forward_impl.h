@@ -1269,9 +1269,12 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
 template <int DT, int NCB, bool ARGMAX>
 static hipError_t launch_stream(const FwdParams &p, int grid, hipStream_t stream)
 {
-    if (p.n_chunks == 0) { // small corpus: a workgroup per document
-        hipLaunchKernelGGL((fwd_stream_split_kernel<DT, NCB, ARGMAX>), dim3(grid), dim3(SPLIT_WAVES * 64), 0, stream, p, p.offsets);
-        return hipGetLastError();
+    if (p.n_chunks == 0) { // small corpus: a workgroup per document (not with two blocks of 512-byte rows)
+        if constexpr (Traits<DT>::NU <= 8 || NCB == 1) {
+            hipLaunchKernelGGL((fwd_stream_split_kernel<DT, NCB, ARGMAX>), dim3(grid), dim3(SPLIT_WAVES * 64), 0, stream, p, p.offsets);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
     }
     if (p.n_groups == 1) { // one wavefront per run: whole-line loads through LDS
         constexpr int WPB = lin_waves<DT>();
