@@ -39,14 +39,14 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
     const int row_bytes = d * (dtype == MAXSIM_F32 ? 4 : 2);
     // any other width: both operands stream through LDS in slabs of the width; so do rows of 512 bytes from 8 column
     // blocks on (two blocks per wavefront in the register-stationary kernel: measured 3-11 % slower there).  Two
-    // kernels: macro tiles of 256 document tokens x 256 query tokens and whole cache lines (forward_wide.hip), or of 64
-    // x 512 and half lines (forward_splitd.hip).  Up to 8 blocks the first, except for half lines and documents of up
-    // to 128 tokens (8 blocks, d = 32: 121 against 113 us); beyond, 512 query tokens at once are ahead where documents
-    // are little work (narrow rows and 65-128 tokens: 20 000 x 100 tokens, 16 blocks, d = 256 / 160: 800 / 573 us in
-    // the first, 790 / 515 in the second) and where the first would multiply many padded blocks (three queries of 140
-    // tokens x 4000 x 128, d = 512: 72 % of its time) or documents of a few tiles of 256 leave much of one empty: the
-    // estimates of both decide.  The other way round, the second's chunks fill the chip badly on some numbers of
-    // documents (16 queries x 1500 x 100 tokens, d = 512: 1.35 times the first's time).
+    // kernels: macro tiles of 256 document tokens x 256 query tokens and whole cache lines (forward_wide.hip), or of
+    // 128 x 512 and half lines (forward_splitd.hip).  Up to 8 blocks the first, except for half lines and documents of
+    // up to 128 tokens (8 blocks, d = 32: 121 against 113 us); beyond, 512 query tokens at once are ahead where
+    // documents are little work (narrow rows and 65-128 tokens: 20 000 x 100 tokens, 16 blocks, d = 256 / 160: 800 /
+    // 573 us in the first, 790 / 515 in the second) and where the first would multiply many padded blocks (three
+    // queries of 140 tokens x 4000 x 128, d = 512: 72 % of its time) or documents of a few tiles of 256 leave much of
+    // one empty: the estimates of both decide.  The other way round, the second's chunks fill the chip badly on some
+    // numbers of documents (16 queries x 1500 x 100 tokens, d = 512: 1.35 times the first's time).
     const int64_t all_blocks = (int64_t)p.n_q * ((p.l_q + BLOCK_COLS - 1) / BLOCK_COLS);
     if (!register_stationary_width(row_bytes) || (row_bytes == 512 && all_blocks >= 8)) {
         const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b; // (uniform corpora: total_tokens = b * l_d)
