@@ -464,10 +464,9 @@ hipError_t forward_wide_init_device()
 
 namespace {
 
-// What a slab of 256 rows takes in each shape, in units of 10 ns (d = 1024, f16, no argmax, the chip full; the ratios
-// are within 8 % of these for bf16 and fp32 and at d = 256).  Documents that fill little of the lowest macro tile of a
-// shape cost more per row (12 x 32 query tokens x 8000 x 60, d = 160: 174 us by three groups of 4 blocks, 142 by two of
-// 6).
+// What a slab of 256 rows takes in each shape, in units of 10 ns, taken for all widths and types; only the ratios
+// count. Documents that fill little of the lowest macro tile of a shape cost more per row (12 x 32 query tokens x 8000
+// x 60, d = 160: 174 us by three groups of 4 blocks, 142 by two of 6).
 double wide_weight(int blocks, int rows)
 {
     const double w = blocks <= 1 ? 60 : blocks <= 2 ? 65 : blocks <= 4 ? 80 : blocks <= 6 ? 105 : 127;
