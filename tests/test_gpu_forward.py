@@ -204,7 +204,7 @@ def test_chunk_counts(n_q, l_q, b, l_d):
 
 # The wide kernel's shapes: by column blocks of a workgroup (1, 2, 4, 6, 8; one query of 9 and of 19 blocks in several
 # passes; groups of unequal numbers of queries) and by the documents' length (macro tiles of 64, 128 and 256 rows: one
-# row either side of them, a single tile, several); widths of one, two and several slabs of 128 bytes, with and without a half one.
+# row either side of them, a single tile, several); widths of two and several slabs of 128 bytes (one: test_wide_one_slab), with and without a half one.
 # fp32 accumulation of at most 384 products and sums of at most 600 maxima: 1e-5 relative to the score
 @pytest.mark.parametrize("n_q,l_q", [(1, 30), (2, 32), (3, 40), (3, 60), (1, 256), (5, 50), (1, 270), (1, 600)])
 @pytest.mark.parametrize("l_d", [1, 32, 64, 65, 128, 129, 255, 256, 257, 545])
