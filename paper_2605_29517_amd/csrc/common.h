@@ -14,6 +14,7 @@ namespace maxsim {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
@@ -47,7 +48,47 @@ template <int F> struct Traits {
             c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
         }
     }
+    // The same on 16 rows x 16 columns (see Acc16): lane quarter g = lane / 16 pairs the g-th of four chunks.
+    static __device__ __forceinline__ void mma16(const uint4 &a, const uint4 &b, f32x4 &c)
+    {
+        if constexpr (DT == MAXSIM_F16) {
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+        } else if constexpr (DT == MAXSIM_BF16) {
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+        } else { // four rank-4 updates (k = 4 per instruction: the quarters)
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+        }
+    }
 };
+
+// 32 document tokens x 32 query tokens as four 16x16 results, for the kernels that are bound by the power limit: on
+// operands of unit-norm rows a loop of 16x16x32 MFMAs (operands from LDS, folds in between) sustains 1740 TFLOP/s fp16
+// and 1860 bf16 where one of 32x32x16 MFMAs holds 1515 and 1650, in whatever order they are issued -- half as many
+// accumulator words travel per product -- and on zero operands, where the clock does not drop, both 2250.
+// Lane (c = lane % 16, g = lane / 16) keeps, of result (i, j), query token 16 j + c and document tokens 16 i + 4 g + r,
+// r = 0 .. 3.  Operand fragment f = i * NU / 2 + u is chunk 4 u + g of document row 16 i + c, for queries alike.
+struct Acc16 {
+    f32x4 t[2][2];
+};
+
+// Step u (of NU) of the chains of one column block; a is the u-th document fragment, q the block's fragments
+template <int F> __device__ __forceinline__ void mma_step16(const uint4 &a, const uint4 (&q)[Traits<F>::NU], int u, Acc16 &acc)
+{
+    constexpr int S = Traits<F>::NU / 2;
+    const int i = u / S, k = u % S;
+    if (k == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            acc.t[i][0][r] = 0.0f;
+            acc.t[i][1][r] = 0.0f;
+        }
+    }
+    Traits<F>::mma16(a, q[k], acc.t[i][0]);
+    Traits<F>::mma16(a, q[S + k], acc.t[i][1]);
+}
 
 // Row of the 32x32 MFMA result held in accumulator register r of a lane in half h.
 __device__ __forceinline__ int acc_row(int r, int h) { return (r >> 2) * 8 + h * 4 + (r & 3); }

@@ -132,6 +132,86 @@ __device__ __forceinline__ float finish_block(const FwdParams &p, float m, int i
     return sum_low32(col_valid ? m : 0.0f);
 }
 
+// The same two for 16x16 results (Acc16): fragment j * NU / 2 + u of a block is chunk 4 u + g of its query token 16 j + c.
+template <int DT> __device__ __forceinline__ void load_q_block16(const FwdParams &p, int gb, int lane, uint4 (&qf)[Traits<DT>::NU])
+{
+    using TR = Traits<DT>;
+    constexpr int S = TR::NU / 2;
+    const int total_blocks = p.n_q * p.bpq;
+    const int b = gb < total_blocks ? gb : 0;
+    const int q = b / p.bpq;
+    const int tok = (b % p.bpq) * BLOCK_COLS + (lane & 15);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const char *row = p.Q + ((int64_t)q * p.l_q + min(tok + 16 * j, p.l_q - 1)) * TR::ROW_BYTES + (lane >> 4) * 16;
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+            qf[j * S + u] = *reinterpret_cast<const uint4 *>(row + u * 64);
+    }
+}
+
+// Byte offset of a lane's u-th document fragment in an LDS tile, beside lds_off16
+template <int DT, int STRIDE> __device__ __forceinline__ constexpr int frag_off16(int u)
+{
+    constexpr int S = Traits<DT>::NU / 2;
+    return u / S * 16 * STRIDE + u % S * 64;
+}
+
+// End of a document for NCB column blocks of a wavefront.  m[b] are the lane's maxima for the columns c and 16 + c of block
+// b, found in its quarter of the rows.  One swap brings a block's two columns together and merges two quarters, one
+// between the blocks 2 k and 2 k + 1 the other two, and the lane then holds column 16 (lane / 32) + c of block
+// 2 k + lane / 16 % 2: the sum over columns (the tree of sum_low32) serves two blocks at a time.  A block by itself is some
+// thirty dependent instructions, which at four blocks and documents of 180 tokens kept a wavefront busy for a sixth of
+// its time.  Returns the sum of block lane / 16 (of lane / 16 % 2 if NCB is 1 or 2).  valid[k]: the column counts.
+constexpr int finish_pairs(int ncb) { return (ncb + 1) / 2; }
+template <int NCB, bool ARGMAX>
+__device__ __forceinline__ float finish_blocks16(const FwdParams &p, const float (&m)[NCB][2], const int (&row)[NCB][2],
+                                                 const bool (&valid)[finish_pairs(NCB)], int gb, int64_t doc, int len, int lane)
+{
+    auto merge = [](auto v, auto i, int &win) {
+        const float a = __uint_as_float(v[0]), b = __uint_as_float(v[1]);
+        if (ARGMAX) {
+            const bool take = a > b || (a == b && (int)i[0] < (int)i[1]);
+            win = take ? (int)i[0] : (int)i[1];
+            return take ? a : b;
+        }
+        return fmaxf(a, b);
+    };
+    float v[finish_pairs(NCB)];
+#pragma unroll
+    for (int k = 0; k < finish_pairs(NCB); ++k) {
+        float x[2];
+        int r[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            if (2 * k + e >= NCB) { // an odd last block stands in for its neighbour
+                x[e] = x[0];
+                r[e] = r[0];
+                continue;
+            }
+            const int b = 2 * k + e;
+            x[e] = merge(__builtin_amdgcn_permlane32_swap(__float_as_uint(m[b][0]), __float_as_uint(m[b][1]), false, false),
+                         __builtin_amdgcn_permlane32_swap((uint32_t)row[b][0], (uint32_t)row[b][1], false, false), r[e]);
+        }
+        int win;
+        const float best = merge(__builtin_amdgcn_permlane16_swap(__float_as_uint(x[0]), __float_as_uint(x[1]), false, false),
+                                 __builtin_amdgcn_permlane16_swap((uint32_t)r[0], (uint32_t)r[1], false, false), win);
+        if (ARGMAX && valid[k] && (2 * k + 1 < NCB || (lane & 16) == 0)) {
+            int col = ((lane >> 5) << 4) + (lane & 15); // (an opaque copy, as in finish_block)
+            asm volatile("" : "+v"(col));
+            auto at = [&](int b) { return ((int64_t)(b / p.bpq) * p.ld + doc) * p.l_q + (b % p.bpq) * BLOCK_COLS; };
+            p.argmax[((lane & 16) ? at(gb + 2 * k + 1) : at(gb + 2 * k)) + col] = min(win, len - 1);
+        }
+        v[k] = valid[k] ? best : 0.0f;
+        v[k] = dpp_add<0xB1>(v[k]);
+        v[k] = dpp_add<0x4E>(v[k]);
+        v[k] = dpp_add<0x141>(v[k]);
+        v[k] = dpp_add<0x140>(v[k]);
+    }
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[finish_pairs(NCB) - 1]), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
 // Documents of length 0 in [doc0, doc1): score -inf, argmax -1 (ragged corpora only).
 __device__ __forceinline__ void write_empty_docs(const FwdParams &p, int64_t doc0, int64_t doc1,
                                                  int tid, int nthreads)
@@ -512,28 +592,39 @@ __global__ void __launch_bounds__(SPLIT_WAVES * 64) fwd_stream_split_kernel(FwdP
     }
 }
 
-// Part `u` (of NU) of folding a result tile into the running max.  The first LAG steps do nothing, so
-// that the MFMA chain which produced the tile has left the matrix pipeline before its results are read
-// (no wait states); the 16 rows are spread over the remaining steps in even-sized pieces.
-template <bool ARGMAX, int NU>
-__device__ __forceinline__ void fold_step(const f32x16 &acc, int u, float &m, int &idx, int row_base, int h)
+// Folds of 16x16 results.  The two cells a v_max3 takes at a time are pair k = 0 .. 7 of an Acc16: result (i, j) =
+// (k / 4, k / 2 % 2), registers 2 (k % 2) and the next; a lane's rows grow with k for either j.
+//
+// Pairs [k0, k1) into the two running maxima.  With ARGMAX (fp32) the winner is kept as a key, the tile's first row (a
+// multiple of 32) | 7 - v, v = 4 i + r, and turned into a row at the end of the document.
+template <bool ARGMAX>
+__device__ __forceinline__ void fold_pairs16(const Acc16 &acc, int k0, int k1, float (&m)[2], int (&key)[2], int row_base)
 {
-    constexpr int LAG = NU >= 4 ? 2 : NU / 2;
-    if (u < LAG)
-        return;
-    const int lo = 2 * (8 * (u - LAG) / (NU - LAG)), hi = 2 * (8 * (u - LAG + 1) / (NU - LAG));
-    if (ARGMAX) {
 #pragma unroll
-        for (int r = lo; r < hi; ++r) {
-            bool up = acc[r] > m; // strict: the first occurrence keeps a tie
-            m = up ? acc[r] : m;
-            idx = up ? row_base + acc_row(r, h) : idx;
+    for (int k = k0; k < k1; ++k) {
+        const int i = k >> 2, j = (k >> 1) & 1, r = (k & 1) * 2;
+        const float x = acc.t[i][j][r], y = acc.t[i][j][r + 1];
+        if (ARGMAX) {
+            bool up = x > m[j]; // strict: the first occurrence keeps a tie
+            m[j] = up ? x : m[j];
+            key[j] = up ? (row_base | (7 - 4 * i - r)) : key[j];
+            up = y > m[j];
+            m[j] = up ? y : m[j];
+            key[j] = up ? (row_base | (6 - 4 * i - r)) : key[j];
+        } else {
+            m[j] = fmaxf(fmaxf(m[j], x), y); // one v_max3_f32
         }
-    } else {
-#pragma unroll
-        for (int r = lo; r < hi; r += 2)
-            m = fmaxf(fmaxf(m, acc[r]), acc[r + 1]); // one v_max3_f32
     }
+}
+
+// What is folded at step u (of NU) of a column block's chains: the half (i) of four pairs that the chains finished
+// last, i.e. half 0 of the block itself during its second half and half 1 of the block before during its first.  Two
+// halves of accumulators are live instead of two blocks.  The half's first step folds nothing, so that the MFMAs which
+// produced the results have left the matrix pipeline before they are read (no wait states).
+template <int NU> __device__ __forceinline__ constexpr int half_pair(int u) // first pair folded at step u (u < NU / 2), four in all
+{
+    constexpr int S = NU / 2;
+    return u < 1 ? 0 : 4 * (u - 1) / (S - 1);
 }
 
 // The fold with argmax for 16-bit inputs (the running maximum is an fp32 sum of 128 products).  Compare-and-select
@@ -598,6 +689,14 @@ __device__ __forceinline__ int packed_key_row(int key, int h)
     return (key & ~31) + h * 4 + (((r & 12) << 1) | (r & 3));
 }
 
+// The document-local row behind a key in lane quarter g
+__device__ __forceinline__ int key_row16(int key, int g)
+{
+    const int v = 7 - (key & 7);
+    return (key & ~31) + ((v & 4) << 2) + g * 4 + (v & 3);
+}
+constexpr int KEY_START = 7; // row 0 of the document's first tile
+
 // The main loop is software-pipelined by hand and pinned with scheduling barriers, one MFMA
 // (16-bit inputs) per step:
 //   * the MFMA chain of column block cb runs while the previous block's result tile is folded
@@ -631,7 +730,6 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int rho = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Renumber so
@@ -658,7 +756,15 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
         cp_goff[i] = (ch % CPR) * 16;
         cp_loff[i] = (ch / CPR) * LT::ROW_STRIDE + (ch % CPR) * 16;
     }
-    const int a_off = rho * LT::ROW_STRIDE + h * 16;
+    // 16-bit inputs with argmax keep the 32x32 results: their fold takes 1.5 VALU operations per cell, which with twice
+    // the MFMA instructions and twice the running maxima fills the issue slots (32 x 1024 x 32 x 1024 through autograd
+    // 376 us on 16x16 results, 336 on 32x32)
+    constexpr bool PACKED = ARGMAX && TR::DT != MAXSIM_F32;
+    const int rho = lane & 31, h = lane >> 5;
+    const int a_off = PACKED ? rho * LT::ROW_STRIDE + h * 16 : (lane & 15) * LT::ROW_STRIDE + (lane >> 4) * 16;
+    auto a_at = [&](int buf_off, int u) {
+        return *reinterpret_cast<const uint4 *>(&lds_tile[buf_off + a_off + (PACKED ? u * 32 : frag_off16<DT, LT::ROW_STRIDE>(u))]);
+    };
 
     for (int pass = 0; pass < p.n_pass; ++pass) {
         // column blocks of this pass: [gb0, gb0 + nb); queries [q_first, q_first + nq)
@@ -680,17 +786,26 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
 
         uint4 qf[NCB][NU];
         bool col_valid[NCB];
-        float m[NCB];
-        int idx[NCB];
+        bool pair_valid[finish_pairs(NCB)]; // the same for the columns that finish_blocks16 leaves in the lane
+        float m[NCB][2]; // (PACKED: the first of each)
+        int key[NCB][2];
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
             int lb = w * NCB + cb;
-            load_q_block<DT>(p, gb0 + lb, rho, h, qf[cb], col_valid[cb]);
-            col_valid[cb] = col_valid[cb] && lb < nb;
-            m[cb] = neg_inf();
-            idx[cb] = 0;
+            if constexpr (PACKED)
+                load_q_block<DT>(p, gb0 + lb, rho, h, qf[cb], col_valid[cb]);
+            else
+                load_q_block16<DT>(p, gb0 + lb, lane, qf[cb]);
+            col_valid[cb] = PACKED && col_valid[cb] && lb < nb;
+            m[cb][0] = m[cb][1] = neg_inf();
+            key[cb][0] = key[cb][1] = PACKED ? 0 : KEY_START;
         }
 
+#pragma unroll
+        for (int i = 0; i < finish_pairs(NCB); ++i) {
+            const int lb = w * NCB + 2 * i + ((lane >> 4) & 1);
+            pair_valid[i] = lb < nb && ((gb0 + lb) % p.bpq) * BLOCK_COLS + ((lane >> 5) << 4) + (lane & 15) < p.l_q;
+        }
         const bool wave_active = w * NCB < nb;
         TileIter li, ci; // load iterator (three tiles ahead of the compute iterator at steady state)
         it_init(li, p, off, doc0, doc1);
@@ -768,7 +883,7 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
         if (PF || INPLACE) {
 #pragma unroll
             for (int u = 0; u < NU; ++u)
-                a0[u] = *reinterpret_cast<const uint4 *>(&lds_tile[o_cur + a_off + u * 32]);
+                a0[u] = a_at(o_cur, u);
         }
         int par = 0;
 
@@ -779,69 +894,95 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
             if (RING) {
 #pragma unroll
                 for (int u = 0; u < 3; ++u)
-                    ring[u] = *reinterpret_cast<const uint4 *>(&lds_tile[o_cur + a_off + u * 32]);
+                    ring[u] = a_at(o_cur, u);
             }
             __builtin_amdgcn_sched_barrier(0);
-            f32x16 acc[NCB];
-            float tmax[NCB]; // the tile's maximum per column block (argmax with 16-bit inputs only)
-            auto fold = [&](int cbx, int u) {
-                if constexpr (ARGMAX && TR::DT != MAXSIM_F32)
-                    fold_step_packed<NU>(acc[cbx], u, tmax[cbx], m[cbx], idx[cbx], ci.t0);
-                else
-                    fold_step<ARGMAX, NU>(acc[cbx], u, m[cbx], idx[cbx], ci.t0, h);
+            std::conditional_t<PACKED, f32x16, Acc16> acc[NCB];
+            float tmax[NCB]; // PACKED: the tile's maximum per column block
+            auto mma = [&](const uint4 &a, int cb, int u) {
+                if constexpr (PACKED) {
+                    if (u == 0) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            acc[cb][r] = 0.0f;
+                    }
+                    TR::mma(a, qf[cb][u], acc[cb]);
+                } else {
+                    mma_step16<DT>(a, qf[cb], u, acc[cb]);
+                }
+            };
+            // what is folded at step u of block cb, and what is left after the last one (cb == NCB)
+            auto fold = [&](int cb, int u) {
+                if constexpr (PACKED) {
+                    if (cb > 0)
+                        fold_step_packed<NU>(acc[cb - 1], u, tmax[cb - 1], m[cb - 1][0], key[cb - 1][0], ci.t0);
+                } else if (u >= NU / 2) {
+                    if (cb < NCB)
+                        fold_pairs16<ARGMAX>(acc[cb], half_pair<NU>(u - NU / 2), half_pair<NU>(u - NU / 2 + 1), m[cb], key[cb], ci.t0);
+                } else if (cb > 0) {
+                    fold_pairs16<ARGMAX>(acc[cb - 1], 4 + half_pair<NU>(u), 4 + half_pair<NU>(u + 1), m[cb - 1], key[cb - 1], ci.t0);
+                }
             };
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[cb][r] = 0.0f;
-#pragma unroll
                 for (int u = 0; u < NU; ++u) {
                     if (RING) {
                         if (u + 3 < NU)
-                            ring[(u + 3) & 3] = *reinterpret_cast<const uint4 *>(&lds_tile[o_cur + a_off + (u + 3) * 32]);
-                        TR::mma(ring[u & 3], qf[cb][u], acc[cb]);
+                            ring[(u + 3) & 3] = a_at(o_cur, u + 3);
+                        mma(ring[u & 3], cb, u);
                     } else {
-                        TR::mma(ac[u], qf[cb][u], acc[cb]);
+                        mma(ac[u], cb, u);
                         if (INPLACE && cb == NCB - 1)
-                            ac[u] = *reinterpret_cast<const uint4 *>(&lds_tile[o_nxt + a_off + u * 32]);
+                            ac[u] = a_at(o_nxt, u);
                     }
                     if (cb == 0) {
                         if (PF)
-                            an[u] = *reinterpret_cast<const uint4 *>(&lds_tile[o_nxt + a_off + u * 32]);
+                            an[u] = a_at(o_nxt, u);
                         if (u == NU - 1) {
                             lstore(o_wr);
                             rotate();
                             gload();
                         }
-                    } else {
-                        fold(cb - 1, u);
                     }
+                    fold(cb, u);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
 #pragma unroll
             for (int u = 0; u < NU; ++u)
-                fold(NCB - 1, u);
+                fold(NCB, u);
 
             if (fin_doc >= 0) {
-#pragma unroll
-                for (int cb = 0; cb < NCB; ++cb) {
-                    int lb = w * NCB + cb;
-                    int row = idx[cb];
-                    if constexpr (ARGMAX && TR::DT != MAXSIM_F32)
-                        row = packed_key_row(row, h);
-                    float sum = finish_block<ARGMAX>(p, m[cb], row, col_valid[cb], gb0 + lb, ci.doc, ci.len, rho, h);
-                    if (lane == 0) {
-                        if (direct) {
-                            if (lb < nb)
-                                p.scores[(int64_t)(gb0 + lb) * p.ld + ci.doc] = sum;
-                        } else {
-                            lds_part[par][lb] = sum;
-                        }
+                auto put = [&](int lb, float sum) {
+                    if (direct) {
+                        if (lb < nb)
+                            p.scores[(int64_t)(gb0 + lb) * p.ld + ci.doc] = sum;
+                    } else {
+                        lds_part[par][lb] = sum;
                     }
-                    m[cb] = neg_inf(); // the next document starts from nothing
-                    idx[cb] = 0;
+                };
+                if constexpr (PACKED) {
+#pragma unroll
+                    for (int cb = 0; cb < NCB; ++cb) {
+                        const int lb = w * NCB + cb;
+                        const float sum = finish_block<ARGMAX>(p, m[cb][0], packed_key_row(key[cb][0], h), col_valid[cb], gb0 + lb, ci.doc, ci.len, rho, h);
+                        if (lane == 0)
+                            put(lb, sum);
+                    }
+                } else {
+                    int row[NCB][2];
+#pragma unroll
+                    for (int i = 0; i < 2 * NCB; ++i)
+                        row[i >> 1][i & 1] = ARGMAX ? key_row16(key[i >> 1][i & 1], lane >> 4) : 0;
+                    const float sum = finish_blocks16<NCB, ARGMAX>(p, m, row, pair_valid, gb0 + w * NCB, ci.doc, ci.len, lane);
+                    if ((lane & 15) == 0 && (lane >> 4) < NCB)
+                        put(w * NCB + (lane >> 4), sum);
+                }
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) { // the next document starts from nothing
+                    m[cb][0] = m[cb][1] = neg_inf();
+                    key[cb][0] = key[cb][1] = PACKED ? 0 : KEY_START;
                 }
             }
             it_next(ci, p, off);
@@ -1047,7 +1188,6 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int rho = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     const int v = xcd_grouped(blockIdx.x, gridDim.x);
@@ -1067,22 +1207,35 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
     auto cp_row = [&](int i) { return (tid + i * NT) / CPR; };
     auto cp_goff = [&](int i) { return ((tid + i * NT) % CPR) * 16; };
     auto cp_loff = [&](int i) { return ((tid + i * NT) / CPR) * LT::ROW_STRIDE + ((tid + i * NT) % CPR) * 16; };
-    const int a_off = rho * LT::ROW_STRIDE + h * 16;
+    const int a_off = (lane & 15) * LT::ROW_STRIDE + (lane >> 4) * 16;
+    auto a_at = [&](int buf_off, int u) { return *reinterpret_cast<const uint4 *>(&lds_tile[buf_off + a_off + frag_off16<DT, LT::ROW_STRIDE>(u)]); };
 
     // one column block = one query: blocks [gb0, gb0 + nb) of this group
     const int gb0 = group * GROUP_BLOCKS;
     const int nb = min(GROUP_BLOCKS, p.n_q - gb0);
     uint4 qf[NCB][NU];
-    bool col_valid[NCB];
-    float m[NCB];
+    float m[NCB][2];
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
         int lb = w * NCB + cb;
-        load_q_block<DT>(p, gb0 + lb, rho, h, qf[cb], col_valid[cb]);
-        col_valid[cb] = col_valid[cb] && lb < nb;
-        m[cb] = neg_inf();
+        load_q_block16<DT>(p, gb0 + lb, lane, qf[cb]);
+        m[cb][0] = m[cb][1] = neg_inf();
     }
     const bool wave_active = w * NCB < nb;
+    const bool counts = ((lane >> 5) << 4) + (lane & 15) < p.l_q; // (see finish_blocks16; every block is a whole query)
+    auto put_scores = [&](const float (&mm)[NCB][2], int doc) {
+        bool valid[finish_pairs(NCB)];
+#pragma unroll
+        for (int i = 0; i < finish_pairs(NCB); ++i)
+            valid[i] = counts;
+        const int none[NCB][2] = {};
+        const float sum = finish_blocks16<NCB, false>(p, mm, none, valid, gb0, doc, 0, lane);
+        int b = lane >> 4; // (an opaque copy: the address is formed here and not kept in registers)
+        asm volatile("" : "+v"(b));
+        const int lb = w * NCB + b;
+        if ((lane & 15) == 0 && b < NCB && lb < nb)
+            p.scores[(int64_t)(gb0 + lb) * p.ld + doc] = sum;
+    };
 
     // One iterator walks the windows, three ahead of the MFMAs (at load time).  What the stage needs of a window
     // later -- is there one, does it hold a boundary and where, which documents end in it -- travels in three scalar
@@ -1143,7 +1296,7 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
     uint4 ac[NU];
 #pragma unroll
     for (int u = 0; u < NU; ++u)
-        ac[u] = *reinterpret_cast<const uint4 *>(&lds_tile[o_cur + a_off + u * 32]);
+        ac[u] = a_at(o_cur, u);
 
     // BND: the window holds rows of two documents
     auto stage = [&](auto bnd_tag) {
@@ -1151,76 +1304,64 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
         const int cw_pa = d_cur.flags >> 8;
         const bool cw_fin_a = (d_cur.flags & 4) != 0, cw_fin_b = (d_cur.flags & 8) != 0;
         WinDesc d_new = {0, 0, 0};
-        constexpr int LAG = NU >= 4 ? 2 : NU / 2;
-        float mb[NCB];
+        float mb[NCB][2];
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-            mb[cb] = neg_inf();
-        // part u (of NU) of folding a result tile; nothing in the first LAG steps (see fold_step)
-        auto fold = [&](const f32x16 &acc, int u, float &ma, float &mbv) {
-            if (u < LAG)
+            mb[cb][0] = mb[cb][1] = neg_inf();
+        // rows 4 g .. 4 g + 3 of either half of the window belong to A below the boundary, to B from it on
+        const bool in_a[2] = {4 * (lane >> 4) < cw_pa, 16 + 4 * (lane >> 4) < cw_pa};
+        // what is folded at step u of block cb, and what is left after the last one (cb == NCB): see half_pair
+        auto fold = [&](const Acc16 *acc, int cb, int u) {
+            const int i = u >= NU / 2 ? 0 : 1, b = cb - i;
+            if (b < 0 || b >= NCB)
                 return;
-            if (BND) { // register groups 4q .. 4q+3 (rows 8q + 4h .. 8q + 4h + 3) go to A below the boundary, to B from it on
-                const int q0 = 4 * (u - LAG) / (NU - LAG), q1 = 4 * (u - LAG + 1) / (NU - LAG);
+            const int k0 = half_pair<NU>(u % (NU / 2)), k1 = half_pair<NU>(u % (NU / 2) + 1);
+            if (BND) {
 #pragma unroll
-                for (int q = q0; q < q1; ++q) {
-                    const float qm = fmaxf(fmaxf(fmaxf(acc[4 * q], acc[4 * q + 1]), acc[4 * q + 2]), acc[4 * q + 3]);
-                    const bool in_a = 8 * q + 4 * h < cw_pa;
-                    ma = fmaxf(ma, in_a ? qm : neg_inf());
-                    mbv = fmaxf(mbv, in_a ? neg_inf() : qm);
+                for (int j = k0 / 2; j < k1 / 2; ++j) {
+                    const f32x4 &t = acc[b].t[i][j];
+                    const float qm = fmaxf(fmaxf(fmaxf(t[0], t[1]), t[2]), t[3]);
+                    m[b][j] = fmaxf(m[b][j], in_a[i] ? qm : neg_inf());
+                    mb[b][j] = fmaxf(mb[b][j], in_a[i] ? neg_inf() : qm);
                 }
             } else {
-                const int lo = 2 * (8 * (u - LAG) / (NU - LAG)), hi = 2 * (8 * (u - LAG + 1) / (NU - LAG));
-#pragma unroll
-                for (int r = lo; r < hi; r += 2)
-                    ma = fmaxf(fmaxf(ma, acc[r]), acc[r + 1]);
+                int none[2];
+                fold_pairs16<false>(acc[b], 4 * i + k0, 4 * i + k1, m[b], none, 0);
             }
         };
         __builtin_amdgcn_sched_barrier(0);
-        f32x16 acc[NCB];
+        Acc16 acc[NCB];
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[cb][r] = 0.0f;
-#pragma unroll
             for (int u = 0; u < NU; ++u) {
-                TR::mma(ac[u], qf[cb][u], acc[cb]);
+                mma_step16<DT>(ac[u], qf[cb], u, acc[cb]);
                 if (cb == NCB - 1)
-                    ac[u] = *reinterpret_cast<const uint4 *>(&lds_tile[o_nxt + a_off + u * 32]);
-                if (cb == 0) {
-                    if (u == NU - 1) {
-                        lstore(o_wr);
-                        d_new = gload();
-                    }
-                } else {
-                    fold(acc[cb - 1], u, m[cb - 1], mb[cb - 1]);
+                    ac[u] = a_at(o_nxt, u);
+                if (cb == 0 && u == NU - 1) {
+                    lstore(o_wr);
+                    d_new = gload();
                 }
+                fold(acc, cb, u);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
         for (int u = 0; u < NU; ++u)
-            fold(acc[NCB - 1], u, m[NCB - 1], mb[NCB - 1]);
+            fold(acc, NCB, u);
 
         if (cw_fin_a) {
+            put_scores(m, d_cur.doc_a);
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
-                int lb = w * NCB + cb;
-                float sum = finish_block<false>(p, m[cb], 0, col_valid[cb], gb0 + lb, d_cur.doc_a, 0, rho, h);
-                if (lane == 0 && lb < nb)
-                    p.scores[(int64_t)(gb0 + lb) * p.ld + d_cur.doc_a] = sum;
-                m[cb] = BND ? mb[cb] : neg_inf();
+                m[cb][0] = BND ? mb[cb][0] : neg_inf();
+                m[cb][1] = BND ? mb[cb][1] : neg_inf();
             }
             if (BND && cw_fin_b) {
+                put_scores(m, d_cur.doc_b);
 #pragma unroll
-                for (int cb = 0; cb < NCB; ++cb) {
-                    int lb = w * NCB + cb;
-                    float sum = finish_block<false>(p, m[cb], 0, col_valid[cb], gb0 + lb, d_cur.doc_b, 0, rho, h);
-                    if (lane == 0 && lb < nb)
-                        p.scores[(int64_t)(gb0 + lb) * p.ld + d_cur.doc_b] = sum;
-                    m[cb] = neg_inf();
-                }
+                for (int cb = 0; cb < NCB; ++cb)
+                    m[cb][0] = m[cb][1] = neg_inf();
             }
         }
         __syncthreads();
