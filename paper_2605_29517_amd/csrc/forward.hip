@@ -202,17 +202,32 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         wave_blocks = per_group <= 24 ? 3 : 4;
         shape = 90 + wave_blocks;
     }
-    const int group_blocks = w * wave_blocks;
-    if (p.bpq <= group_blocks) {
-        p.qpg = group_blocks / p.bpq;
-        if (p.qpg > p.n_q)
-            p.qpg = p.n_q;
-        p.n_groups = (p.n_q + p.qpg - 1) / p.qpg;
-        p.n_pass = 1;
-    } else {
-        p.qpg = 1;
-        p.n_groups = p.n_q;
-        p.n_pass = (p.bpq + group_blocks - 1) / group_blocks;
+    auto share = [&](int group_blocks) {
+        if (p.bpq <= group_blocks) {
+            p.qpg = group_blocks / p.bpq;
+            if (p.qpg > p.n_q)
+                p.qpg = p.n_q;
+            p.n_groups = (p.n_q + p.qpg - 1) / p.qpg;
+            p.n_pass = 1;
+        } else {
+            p.qpg = 1;
+            p.n_groups = p.n_q;
+            p.n_pass = (p.bpq + group_blocks - 1) / group_blocks;
+        }
+    };
+    share(w * wave_blocks);
+    // Three blocks per wavefront where they hold the group too: wavefronts w and w + 4 share a SIMD, and the one that has
+    // most blocks sets the time (19 blocks in fours: 8, 4, 4 and 4, in threes 6, 6, 6 and 3; long queries of 33 to 48 blocks in
+    // two passes of 24).
+    if (ncb == 4 && shape < 900) {
+        const int blocks = p.n_pass == 1 ? p.qpg * p.bpq : 0;
+        const int threes = shape == 82 || shape == 4 ? 4 : shape == 8 || shape == 2 ? shape : 0;
+        if (threes && blocks > 0 && blocks <= threes * 3) {
+            shape = threes * 10 + 3;
+        } else if (shape == 8 && p.n_pass == 2 && p.bpq <= 48) {
+            shape = 83;
+            share(24);
+        }
     }
     return run(true, shape, num_cu); // (the chunks: launch_chunks)
 }

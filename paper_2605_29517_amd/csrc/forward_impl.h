@@ -1520,6 +1520,12 @@ static hipError_t dispatch_tile(const FwdParams &p, int w, int num_cu, hipStream
             return launch_tile<DT, 8, 2, ARGMAX, 3>(p, num_cu, s);
         if (w == 42)
             return launch_tile<DT, 4, 2, ARGMAX, 4>(p, num_cu, s);
+        if (w == 83) // three blocks each
+            return launch_tile<DT, 8, 3, ARGMAX>(p, num_cu, s);
+        if (w == 43)
+            return launch_tile<DT, 4, 3, ARGMAX, 2>(p, num_cu, s);
+        if (w == 23)
+            return launch_tile<DT, 2, 3, ARGMAX>(p, num_cu, s);
         if constexpr (!ARGMAX) {
             if (w == 93) // ragged corpus, queries of one block: windows over the packed rows; 24 or 32 queries per workgroup
                 return launch_pack<DT, 3>(p, num_cu, s);
