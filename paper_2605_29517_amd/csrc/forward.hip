@@ -217,11 +217,15 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
     };
     share(w * wave_blocks);
     // Three blocks per wavefront where they hold the group too: wavefronts w and w + 4 share a SIMD, and the one that has
-    // most blocks sets the time (19 blocks in fours: 8, 4, 4 and 4, in threes 6, 6, 6 and 3; long queries of 33 to 48 blocks in
-    // two passes of 24).
+    // most blocks sets the time (19 blocks in fours: 8, 4, 4 and 4, in threes 6, 6, 6 and 3: one query of 600 tokens x 3000 x
+    // 300 138 -> 119 us; long queries of 33 to 48 blocks in two passes of 24: 1030 tokens 265 -> 210).  Five and six
+    // blocks are then worth two wavefronts instead of four from three documents per CU on (130 tokens x 1000 / 2000 / 4000
+    // documents of 300 / 600 / 256 21.3 -> 20.9, 73 -> 60, 53 -> 47 us; x 500 x 260 11.9 -> 13.6 and x 300 x 1000 26 -> 34 are why
+    // not below).
     if (ncb == 4 && shape < 900) {
         const int blocks = p.n_pass == 1 ? p.qpg * p.bpq : 0;
-        const int threes = shape == 82 || shape == 4 ? 4 : shape == 8 || shape == 2 ? shape : 0;
+        const bool two = shape == 2 || (shape == 42 && dtype != MAXSIM_F32 && p.b >= 3 * (int64_t)num_cu);
+        const int threes = shape == 82 || shape == 4 ? 4 : shape == 8 ? 8 : two ? 2 : 0;
         if (threes && blocks > 0 && blocks <= threes * 3) {
             shape = threes * 10 + 3;
         } else if (shape == 8 && p.n_pass == 2 && p.bpq <= 48) {

@@ -803,8 +803,11 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
 
 #pragma unroll
         for (int i = 0; i < finish_pairs(NCB); ++i) {
-            const int lb = w * NCB + 2 * i + ((lane >> 4) & 1);
-            pair_valid[i] = lb < nb && ((gb0 + lb) % p.bpq) * BLOCK_COLS + ((lane >> 5) << 4) + (lane & 15) < p.l_q;
+            auto left = [&](int cb) { // query tokens from the block's first on (scalar: the quotient is load_q_block16's)
+                const int lb = w * NCB + (cb < NCB ? cb : NCB - 1);
+                return lb < nb ? p.l_q - ((gb0 + lb) % p.bpq) * BLOCK_COLS : 0;
+            };
+            pair_valid[i] = ((lane >> 5) << 4) + (lane & 15) < ((lane & 16) ? left(2 * i + 1) : left(2 * i));
         }
         const bool wave_active = w * NCB < nb;
         TileIter li, ci; // load iterator (three tiles ahead of the compute iterator at steady state)
@@ -1525,7 +1528,7 @@ static hipError_t dispatch_tile(const FwdParams &p, int w, int num_cu, hipStream
         if (w == 43)
             return launch_tile<DT, 4, 3, ARGMAX, 2>(p, num_cu, s);
         if (w == 23)
-            return launch_tile<DT, 2, 3, ARGMAX>(p, num_cu, s);
+            return launch_tile<DT, 2, 3, ARGMAX, 2>(p, num_cu, s);
         if constexpr (!ARGMAX) {
             if (w == 93) // ragged corpus, queries of one block: windows over the packed rows; 24 or 32 queries per workgroup
                 return launch_pack<DT, 3>(p, num_cu, s);
