@@ -208,6 +208,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
             if (p.qpg > p.n_q)
                 p.qpg = p.n_q;
             p.n_groups = (p.n_q + p.qpg - 1) / p.qpg;
+            p.qpg = (p.n_q + p.n_groups - 1) / p.n_groups; // as many queries in each: the fullest group sets the time
             p.n_pass = 1;
         } else {
             p.qpg = 1;
