@@ -50,6 +50,22 @@ def test_uniform_fp32(shape, want_argmax):
     forward_parity_uniform(Q, D, M.maxsim_forward, want_argmax, RTOL_F32)
 
 
+# Column blocks that do not fill wavefronts of four: three per wavefront in workgroups of 8 (17-24 blocks), 4 (9-12) and 2
+# wavefronts (5 and 6, from three documents per CU on), two passes of 24 blocks (33-48), groups of as many queries each
+THREES = [(1, 600, 5, 70), (3, 200, 6, 33), (1, 768, 3, 95), (1, 300, 7, 64), (6, 64, 9, 45), (1, 130, 800, 9), (2, 96, 770, 5),
+          (1, 1030, 4, 70), (1, 1536, 3, 40), (5, 256, 6, 50), (7, 130, 4, 61)]
+
+
+@pytest.mark.parametrize("dtype,d", [("f16", 128), ("bf16", 128), ("f32", 64), ("f16", 64)])
+@pytest.mark.parametrize("want_argmax", [False, True])
+@pytest.mark.parametrize("shape", THREES)
+def test_blocks_in_threes(shape, want_argmax, dtype, d):
+    n_q, l_q, b, l_d = shape
+    Q = W.unit_rows((n_q, l_q, d), dtype, 13 + l_q, DEV)
+    D = W.unit_rows((b, l_d, d), dtype, 14 + l_d, DEV)
+    forward_parity_uniform(Q, D, M.maxsim_forward, want_argmax, RTOL_F32 if dtype == "f32" else RTOL_16)
+
+
 def _ragged_case(n_q, l_q, lens, dtype, seed):
     lens = np.asarray(lens)
     off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV)
