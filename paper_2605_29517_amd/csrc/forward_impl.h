@@ -1022,13 +1022,18 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
                 o_wr = t;
             }
         } else if constexpr (PF) {
-            for (;;) {
+            // The loop has one exit.  With a `break` after either stage the compiler joins the two exits in the latch, where
+            // it fills the walk's undefined words through v_readfirstlane (eleven per two tiles), and keeps the loading
+            // document's length in a vector register: bf16, one query of 130 tokens x 300 documents of 1000 28.0 us instead of
+            // 26.7, of 512 tokens 53.1 instead of 50.7, 4 x 1024 tokens x 10 000 of 180 1293 instead of 1250.
+            bool more = true;
+            while (more) {
                 stage(a0, a1);
-                if (!it_valid(ci))
-                    break;
-                stage(a1, a0);
-                if (!it_valid(ci))
-                    break;
+                more = it_valid(ci);
+                if (more) {
+                    stage(a1, a0);
+                    more = it_valid(ci);
+                }
             }
         } else {
             while (it_valid(ci))
