@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmaxsim.so")
 PROBE_LIB = os.path.join(HERE, "libmaxsim_probe.so")
-SOURCES = ["api.hip", "forward.hip", "forward_f16.hip", "forward_bf16.hip", "forward_f32.hip", "forward_wide.hip", "forward_splitd.hip", "backward.hip", "int8.hip", "int8_wide.hip"]
+SOURCES = ["api.hip", "forward.hip", "forward_f16.hip", "forward_bf16.hip", "forward_f32.hip", "forward_argmax.hip", "forward_wide.hip", "forward_splitd.hip", "backward.hip", "int8.hip", "int8_wide.hip"]
 PROBE_SOURCES = ["probe.hip"]
 # packed fp32 VALU forms are switched off on purpose (they have produced wrong results on
 # the test machines); the host pass warns that it does not know the feature, which is harmless
@@ -16,6 +16,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          # inputs are finite by contract: without this every max is preceded by a NaN-quieting copy
          "-fno-honor-nans",
          "-Wall", "-Wno-unused-function"]
+FILE_FLAGS = {"forward_argmax.hip": ["-falign-loops=64"]}  # (the reason is at its top)
 
 
 def build(verbose: bool = False) -> str:
@@ -26,7 +27,7 @@ def build(verbose: bool = False) -> str:
     procs = []
     for src in SOURCES + PROBE_SOURCES:
         obj = os.path.join(bdir, src.replace(".hip", ".o"))
-        cmd = [hipcc] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc] + FLAGS + FILE_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

@@ -27,6 +27,11 @@
 #include <type_traits>
 
 namespace maxsim {
+
+// dispatch_tile<fmt(.., 8), true>, compiled in forward_argmax.hip
+hipError_t forward_tile_argmax_f16(const FwdParams &p, int w, int num_cu, hipStream_t s);
+hipError_t forward_tile_argmax_bf16(const FwdParams &p, int w, int num_cu, hipStream_t s);
+
 namespace {
 
 // ---------------------------------------------------------------------------------------
@@ -1561,8 +1566,16 @@ static hipError_t dispatch_tile(const FwdParams &p, int w, int num_cu, hipStream
 template <int F>
 static hipError_t run_format(const FwdParams &p, bool argmax, bool tile, int x, int n, hipStream_t s)
 {
-    if (tile)
-        return argmax ? dispatch_tile<F, true>(p, x, n, s) : dispatch_tile<F, false>(p, x, n, s);
+    if (tile) {
+        if (!argmax)
+            return dispatch_tile<F, false>(p, x, n, s);
+        if constexpr (F == fmt(MAXSIM_F16, 8))
+            return forward_tile_argmax_f16(p, x, n, s);
+        else if constexpr (F == fmt(MAXSIM_BF16, 8))
+            return forward_tile_argmax_bf16(p, x, n, s);
+        else
+            return dispatch_tile<F, true>(p, x, n, s);
+    }
     return argmax ? dispatch_stream<F, true>(p, x, n, s) : dispatch_stream<F, false>(p, x, n, s);
 }
 
