@@ -208,7 +208,13 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
             if (p.qpg > p.n_q)
                 p.qpg = p.n_q;
             p.n_groups = (p.n_q + p.qpg - 1) / p.qpg;
-            p.qpg = (p.n_q + p.n_groups - 1) / p.n_groups; // as many queries in each: the fullest group sets the time
+            // As many queries in each group where that lets the fullest do with three blocks per wavefront (below): four
+            // queries of 280 tokens x 1500 x 300 145 -> 116 us.  Elsewhere the wavefronts that equal shares leave half full
+            // cost more than a short last group (180 queries of 48 tokens x 180 x 350: eleven groups of 16 and one of 4
+            // 158 us, twelve of 15 164).
+            const int even = (p.n_q + p.n_groups - 1) / p.n_groups;
+            if (p.qpg * p.bpq > 24 && even * p.bpq <= 24)
+                p.qpg = even;
             p.n_pass = 1;
         } else {
             p.qpg = 1;
