@@ -225,14 +225,39 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
     share(w * wave_blocks);
     // Three blocks per wavefront where they hold the group too: wavefronts w and w + 4 share a SIMD, and the one that has
     // most blocks sets the time (19 blocks in fours: 8, 4, 4 and 4, in threes 6, 6, 6 and 3: one query of 600 tokens x 3000 x
-    // 300 138 -> 119 us; long queries of 33 to 48 blocks in two passes of 24: 1030 tokens 265 -> 210).  Five and six
-    // blocks are then worth two wavefronts instead of four from three documents per CU on (130 tokens x 1000 / 2000 / 4000
-    // documents of 300 / 600 / 256 21.3 -> 20.9, 73 -> 60, 53 -> 47 us; x 500 x 260 11.9 -> 13.6 and x 300 x 1000 26 -> 34 are why
-    // not below).
+    // 300 138 -> 119 us; long queries of 33 to 48 blocks in two passes of 24: 1030 tokens 265 -> 210).
     if (ncb == 4 && shape < 900) {
         const int blocks = p.n_pass == 1 ? p.qpg * p.bpq : 0;
-        const bool two = shape == 2 || (shape == 42 && dtype != MAXSIM_F32 && p.b >= 3 * (int64_t)num_cu);
-        const int threes = shape == 82 || shape == 4 ? 4 : shape == 8 ? 8 : two ? 2 : 0;
+        const int64_t cus = num_cu, mean_len = (p.total_tokens + p.b - 1) / p.b;
+        // Five and six blocks on less than sixteen documents per CU: two wavefronts with three blocks each, four such
+        // workgroups per CU, instead of two of four wavefronts with two blocks (2000 x 100 / 3000 x 300 tokens, d = 128: 18.3
+        // against 18.6 us, 44.4 against 49.6).  The more workgroups, the coarser the shares, which costs more than it gives
+        // * on ragged corpora of less than seven documents per CU (1000 x 100-500 tokens 29.4 against 27.6 us; six with argmax,
+        //   1500 x 100-500 1.06 times; four of up to 128 tokens: 1000 x 10-200 18.0 against 16.4, 1100 x 10-200 16.8 against 17.4)
+        // and on uniform corpora of 256-byte rows
+        // * where a workgroup has one document of two tiles (1000 x 60 10.1 against 9.3; not with argmax),
+        // * where a few have to take a second one (1200 x 70 20 % slower, 1280 x 150 7 %, but not 1100 x 500; with argmax only
+        //   those of three tiles, 9 %),
+        // * where up to every other has a second one of 8 to 20 tiles (1500 x 500 46.0 against 41.1).
+        bool two = shape == 2;
+        if (shape == 42 && dtype != MAXSIM_F32) {
+            if (ragged)
+                two = p.b >= (mean_len <= 128 ? 4 : am ? 6 : 7) * cus;
+            else if (p.b < 3 * cus || nu < 8 || p.b > 6 * cus)
+                two = p.b >= 3 * cus;
+            else if (p.b > 5 * cus)
+                two = mean_len <= 7 * TILE_ROWS || mean_len > 20 * TILE_ROWS;
+            else if (p.b > 4 * cus)
+                two = mean_len > (am ? 3 : 8) * TILE_ROWS;
+            else
+                two = am || mean_len > 2 * TILE_ROWS;
+        }
+        // Nine to twelve blocks: four wavefronts with three blocks each, but for short documents of which a CU has up to
+        // three: there eight wavefronts with two blocks each take 2-9 % less (700 x 64 tokens 10.4 against 11.3 us, 600 x 128
+        // 0.95 times; 700 x 200 and 400 x 128 the other way, and 128-byte rows from three tiles on)
+        const int64_t few_long = nu < 8 ? 64 : p.b > 2 * cus ? 160 : 96;
+        const bool four = shape == 4 || (shape == 82 && (dtype == MAXSIM_F32 || ragged || p.b > 3 * cus || mean_len > few_long));
+        const int threes = four ? 4 : shape == 8 ? 8 : two ? 2 : 0;
         if (threes && blocks > 0 && blocks <= threes * 3) {
             shape = threes * 10 + 3;
         } else if (shape == 8 && p.n_pass == 2 && p.bpq <= 48) {

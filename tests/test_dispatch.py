@@ -83,3 +83,29 @@ def test_groups_are_evened_only_for_three_blocks_per_wavefront(routes):
         assert r.n_groups == -(-c.n_q // r.qpg) == -(-c.n_q // most), c
         assert r.qpg == (even if most * bpq > 24 >= even * bpq else most), c
         assert r.shape == (83 if r.qpg * bpq <= 24 else 8), c
+
+
+# (documents, tokens of each, ragged, argmax) -> shape, of queries with five to six and with nine to twelve blocks; d = 128
+FEW = [(767, 300, 0, 0, 42, 43), (768, 300, 0, 0, 23, 43), (1024, 64, 0, 0, 42, 43), (1024, 65, 0, 0, 23, 43), (1024, 64, 0, 1, 23, 43),
+       (1025, 256, 0, 0, 42, 43), (1280, 257, 0, 0, 23, 43), (1280, 96, 0, 1, 42, 43), (1280, 97, 0, 1, 23, 43),
+       (1281, 224, 0, 0, 23, 43), (1281, 225, 0, 0, 42, 43), (1536, 640, 0, 1, 42, 43), (1536, 641, 0, 1, 23, 43), (1537, 300, 0, 0, 23, 43),
+       (1023, 100, 1, 0, 42, 43), (1024, 128, 1, 0, 23, 43), (1791, 129, 1, 0, 42, 43), (1792, 129, 1, 0, 23, 43), (1535, 129, 1, 1, 42, 43),
+       (1536, 129, 1, 1, 23, 43), (300, 96, 0, 0, 42, 82), (512, 97, 0, 0, 42, 43), (513, 160, 0, 1, 42, 82), (768, 161, 0, 0, 23, 43),
+       (700, 64, 0, 0, 42, 82), (700, 64, 1, 0, 42, 43), (4096, 100, 0, 1, 23, 43)]
+
+
+@pytest.mark.parametrize("docs,tokens,ragged,argmax,six,twelve", FEW)
+def test_three_blocks_per_wavefront_on_few_documents(routes, docs, tokens, ragged, argmax, six, twelve):
+    for blocks, want in (((2, 90), six), ((1, 130) if not argmax else (5, 32), six), ((3, 64), six), ((1, 300) if ragged else (9, 32), twelve), ((2, 192), twelve)):
+        n_q, l_q = blocks
+        if docs >= 4096 and n_q * ((l_q + 31) // 32) <= 6 and not argmax:
+            continue
+        call = Call(BF16, 128, n_q, l_q, docs, docs * tokens, ragged, argmax)
+        assert routes([call])[0].shape == want, call
+
+
+def test_fp32_and_narrow_rows_keep_three_blocks(routes):
+    for dtype, d, l_q, docs, tokens, want in ((F32, 64, 300, 700, 64, 43), (F32, 32, 180, 3000, 300, 42), (F16, 64, 300, 700, 64, 82), (F16, 64, 300, 700, 65, 43),
+                                             (F16, 64, 180, 768, 40, 23), (F16, 64, 180, 1500, 500, 23)):
+        call = Call(dtype, d, 1, l_q, docs, docs * tokens, 0, 0)
+        assert routes([call])[0].shape == want, call
