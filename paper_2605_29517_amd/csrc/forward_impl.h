@@ -717,7 +717,7 @@ constexpr int KEY_START = 7; // row 0 of the document's first tile
 //   * with one or two column blocks per wavefront a tile takes too little time for a load issued
 //     one tile ahead to have arrived: PFD tiles are then in flight in a ring of registers.
 template <int DT, int W, int NCB, bool ARGMAX, int PFD = 1>
-__global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 1) fwd_tile_kernel(FwdParams p, OffsetsPtr off)
+__global__ void __launch_bounds__(W * 64, Traits<DT>::NU <= 8 ? 2 : 1) fwd_tile_kernel(FwdParams p, OffsetsPtr off)
 {
     using TR = Traits<DT>;
     using LT = LdsTile<DT>;
@@ -822,15 +822,9 @@ __global__ void __launch_bounds__(W * 64, (Traits<DT>::NU <= 8 || W == 8) ? 2 : 
             break;
 
         // tiles in flight from HBM: ring slot 0 is the oldest (next to be stored to LDS), bit s of g_mask says that slot s holds a tile
-        constexpr bool NAMED = PFD * CPT <= 8;
+        static_assert(PFD * CPT <= 8, "at most eight chunks per thread in flight");
         uint4 g0, g1, g2, g3, g4, g5, g6, g7;
-        uint4 g_arr[NAMED ? 1 : PFD][NAMED ? 1 : CPT]; // workgroups of one wavefront and wide rows: more than eight chunks
-        auto g = [&](auto slot, auto i) -> uint4 & {
-            if constexpr (NAMED)
-                return reg_at<decltype(slot)::value * CPT + decltype(i)::value>(g0, g1, g2, g3, g4, g5, g6, g7);
-            else
-                return g_arr[decltype(slot)::value][decltype(i)::value];
-        };
+        auto g = [&](auto slot, auto i) -> uint4 & { return reg_at<decltype(slot)::value * CPT + decltype(i)::value>(g0, g1, g2, g3, g4, g5, g6, g7); };
         constexpr std::integral_constant<int, 0> OLDEST{};
         constexpr std::integral_constant<int, PFD - 1> NEWEST{};
         unsigned g_mask = 0;
@@ -1436,7 +1430,7 @@ static hipError_t launch_stream(const FwdParams &p, int grid, hipStream_t stream
         hipLaunchKernelGGL((fwd_stream_lin_kernel<DT, NCB, ARGMAX>), dim3(grid_lin), dim3(WPB * 64), 0, stream, p, p.offsets);
         return hipGetLastError();
     }
-    if constexpr (Traits<DT>::NU <= 8) { // narrow rows: more than four column blocks go to the tile kernel
+    if constexpr (Traits<DT>::NU <= 8 || NCB == 1) { // narrow rows: more than four column blocks go to the tile kernel; several groups hold two blocks each
         return hipErrorInvalidValue;
     } else {
         hipLaunchKernelGGL((fwd_stream_kernel<DT, NCB, ARGMAX>), dim3(grid), dim3(256), 0, stream, p, p.offsets);
@@ -1525,43 +1519,47 @@ template <int DT, bool ARGMAX>
 static hipError_t dispatch_tile(const FwdParams &p, int w, int num_cu, hipStream_t s)
 {
     constexpr int NU = Traits<DT>::NU;
-    constexpr int NCB = NU <= 8 ? 4 : 32 / NU; // query fragments fill 128 registers
-    if constexpr (NCB == 4) { // few column blocks: eight wavefronts with one or two blocks each
-        if (w == 81)
-            return launch_tile<DT, 8, 1, ARGMAX, 6>(p, num_cu, s);
-        if (w == 82)
-            return launch_tile<DT, 8, 2, ARGMAX, 3>(p, num_cu, s);
-        if (w == 42)
-            return launch_tile<DT, 4, 2, ARGMAX, 4>(p, num_cu, s);
-        if (w == 83) // three blocks each
-            return launch_tile<DT, 8, 3, ARGMAX>(p, num_cu, s);
-        if (w == 43)
-            return launch_tile<DT, 4, 3, ARGMAX, 2>(p, num_cu, s);
-        if (w == 23)
-            return launch_tile<DT, 2, 3, ARGMAX, 2>(p, num_cu, s);
-        if constexpr (!ARGMAX) {
-            if (w == 93) // ragged corpus, queries of one block: windows over the packed rows; 24 or 32 queries per workgroup
-                return launch_pack<DT, 3>(p, num_cu, s);
-            if (w == 94)
-                return launch_pack<DT, 4>(p, num_cu, s);
-            if (w == 943)
-                return launch_pack<DT, 3, 4>(p, num_cu, s);
-            if (w == 944)
-                return launch_pack<DT, 4, 4>(p, num_cu, s);
-            if (w == 923)
-                return launch_pack<DT, 3, 2>(p, num_cu, s);
-            if (w == 924)
-                return launch_pack<DT, 4, 2>(p, num_cu, s);
+    constexpr bool TWO_WAVES = Traits<DT>::DT != MAXSIM_F32; // fp32 takes no shapes of two wavefronts (see forward_launch)
+    if constexpr (NU <= 8) {
+        switch (w) {
+        case 82: return launch_tile<DT, 8, 2, ARGMAX, 3>(p, num_cu, s); // few column blocks
+        case 42: return launch_tile<DT, 4, 2, ARGMAX, 4>(p, num_cu, s);
+        case 83: return launch_tile<DT, 8, 3, ARGMAX>(p, num_cu, s); // three blocks each
+        case 43: return launch_tile<DT, 4, 3, ARGMAX, 2>(p, num_cu, s);
+        case 4: return launch_tile<DT, 4, 4, ARGMAX>(p, num_cu, s); // four: query fragments fill 128 registers
+        case 8: return launch_tile<DT, 8, 4, ARGMAX>(p, num_cu, s);
         }
+        if constexpr (TWO_WAVES) {
+            if (w == 23)
+                return launch_tile<DT, 2, 3, ARGMAX, 2>(p, num_cu, s);
+            if (w == 2)
+                return launch_tile<DT, 2, 4, ARGMAX>(p, num_cu, s);
+        }
+        if constexpr (ARGMAX) { // one long query of five to eight blocks
+            if (w == 81)
+                return launch_tile<DT, 8, 1, true, 6>(p, num_cu, s);
+        } else { // queries of one block on ragged corpora: windows over the packed rows, 3 or 4 queries per wavefront
+            switch (w) {
+            case 93: return launch_pack<DT, 3>(p, num_cu, s);
+            case 94: return launch_pack<DT, 4>(p, num_cu, s);
+            case 943: return launch_pack<DT, 3, 4>(p, num_cu, s);
+            case 944: return launch_pack<DT, 4, 4>(p, num_cu, s);
+            }
+            if constexpr (TWO_WAVES) {
+                if (w == 923)
+                    return launch_pack<DT, 3, 2>(p, num_cu, s);
+                if (w == 924)
+                    return launch_pack<DT, 4, 2>(p, num_cu, s);
+            }
+        }
+    } else { // 512-byte rows, three to seven blocks: two fill 128 registers
+        if (w == 2)
+            return launch_tile<DT, 2, 2, ARGMAX>(p, num_cu, s);
+        if (w == 4)
+            return launch_tile<DT, 4, 2, ARGMAX>(p, num_cu, s);
     }
-    switch (w) {
-    case 1: return launch_tile<DT, 1, NCB, ARGMAX>(p, num_cu, s);
-    case 2: return launch_tile<DT, 2, NCB, ARGMAX>(p, num_cu, s);
-    case 4: return launch_tile<DT, 4, NCB, ARGMAX>(p, num_cu, s);
-    default: return launch_tile<DT, 8, NCB, ARGMAX>(p, num_cu, s);
-    }
+    return hipErrorInvalidValue;
 }
-
 
 template <int F>
 static hipError_t run_format(const FwdParams &p, bool argmax, bool tile, int x, int n, hipStream_t s)

@@ -109,3 +109,25 @@ def test_fp32_and_narrow_rows_keep_three_blocks(routes):
                                              (F16, 64, 180, 768, 40, 23), (F16, 64, 180, 1500, 500, 23)):
         call = Call(dtype, d, 1, l_q, docs, docs * tokens, 0, 0)
         assert routes([call])[0].shape == want, call
+
+
+def test_every_shape_is_reached_and_no_other(routes):
+    """dispatch_tile and launch_stream instantiate exactly what forward_launch asks for."""
+    calls = [Call(dt, row // (4 if dt == F32 else 2), n_q, l_q, b, b * t, ragged, am)
+             for dt in (F32, F16) for row in (128, 256, 512) for am in (0, 1) for ragged in (0, 1)
+             for n_q in (1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 13, 16, 17, 24, 30, 64)
+             for l_q in (1, 32, 33, 65, 97, 130, 190, 250, 300, 512, 600, 1024, 1030, 2100) for b in (1, 200, 768, 1800, 4096, 20000) for t in (20, 100, 300)]
+    tile = collections.defaultdict(set)
+    stream = collections.defaultdict(set)
+    for c, r in zip(calls, routes(calls)):
+        if r.kind == "tile":
+            tile[c.dtype == F32, r.nu == 16, c.argmax].add(r.shape)
+        elif r.kind != "slabs":
+            stream[r.nu == 16].add((r.kind, r.shape, r.n_groups))
+    for fp32 in (False, True):
+        narrow = {82, 42, 83, 43, 4, 8} | (set() if fp32 else {23, 2})
+        assert tile[fp32, False, 1] == narrow | {81}
+        assert tile[fp32, False, 0] == narrow | {93, 94, 943, 944} | (set() if fp32 else {923, 924})
+        assert tile[fp32, True, 0] == tile[fp32, True, 1] == {2, 4}
+    assert stream[False] == {(kind, n, 1) for kind in ("split", "stream") for n in (1, 2, 3, 4)}
+    assert stream[True] == {("split", 1, 1), ("stream", 1, 1), ("stream", 2, 1), ("stream", 2, 2), ("stream", 2, 4)}
