@@ -1,26 +1,30 @@
 // Fused MaxSim forward for gfx950 (Alg. 1 of the paper, re-designed around 64-wide
-// wavefronts and the 32x32 MFMA result layout).
+// wavefronts and the MFMA result layouts).
 //
 // Orientation.  Document tokens sit on the MFMA rows (A operand), query tokens on the
-// columns (B operand).  A lane of the 32x32 result holds ONE query token (column
+// columns (B operand).  A lane of a 32x32 result holds ONE query token (column
 // lane % 32) and 16 document tokens, so the max over document tokens (the running row-max step of Alg. 1)
 // is an in-lane chain of v_max3 over the accumulator registers and the running row-max is
 // one register per lane per 32 query tokens.  The two lane halves are merged once per
-// document; the sum over query tokens (the final reduction of Alg. 1) is a butterfly over 32 lanes.
+// document; the sum over query tokens (the final reduction of Alg. 1) is a butterfly over 32 lanes
+// (finish_block).  That is the streaming kernels and the tile kernel with argmax on 16-bit inputs.
+// Otherwise the tile kernel, and the packed-window kernel, take the same 32 x 32 tokens as four 16x16
+// results (Acc16): two query tokens per lane, eight document tokens of each, two running maxima, and
+// four lane quarters to merge, two column blocks at a time (finish_blocks16).
 //
 // Masking (the -inf step of Alg. 1).  Rows past the end of a document are not set to -inf after
 // the product; instead the loads clamp the row index to the document's last token.  A
 // duplicated token cannot change a max, and it cannot win the argmax because ties go to the
 // lowest index, so the result is the same and the epilogue stays mask-free.
 //
-// Two kernels share these pieces:
-//   fwd_stream_kernel  few query tokens (<= 128 in total): the corpus read is the cost.
-//                      Every wavefront works alone on its own run of documents; document
-//                      tiles go HBM -> registers directly in MFMA operand layout (32 rows x
-//                      32 contiguous bytes per load instruction), one tile ahead.
+// The kernels that share these pieces:
+//   fwd_stream_lin_kernel, fwd_stream_split_kernel, fwd_stream_kernel
+//                      few query tokens: the corpus read is the cost.  A wavefront holds whole queries and
+//                      walks its own run of documents (or half of one document's tiles), tiles read one ahead.
 //   fwd_tile_kernel    many query tokens: the contraction is the cost.  A workgroup keeps up
 //                      to 1024 query tokens stationary in registers (128 per wavefront) and
 //                      streams document tiles through LDS, shared by all its wavefronts.
+//   fwd_pack_kernel    the same for queries of one column block, over 32-row windows of the packed corpus.
 #pragma once
 #include "common.h"
 
@@ -35,7 +39,7 @@ hipError_t forward_tile_argmax_bf16(const FwdParams &p, int w, int num_cu, hipSt
 namespace {
 
 // ---------------------------------------------------------------------------------------
-// pieces shared by both kernels
+// pieces shared by the kernels
 // ---------------------------------------------------------------------------------------
 
 // Query fragments of column block `gb` (global block id): column rho of the block is query
@@ -155,7 +159,7 @@ template <int DT> __device__ __forceinline__ void load_q_block16(const FwdParams
     }
 }
 
-// Byte offset of a lane's u-th document fragment in an LDS tile, beside lds_off16
+// Byte offset of a lane's u-th document fragment in an LDS tile, from the lane's own (row lane % 16, chunk lane / 16)
 template <int DT, int STRIDE> __device__ __forceinline__ constexpr int frag_off16(int u)
 {
     constexpr int S = Traits<DT>::NU / 2;
@@ -702,20 +706,21 @@ __device__ __forceinline__ int key_row16(int key, int g)
 }
 constexpr int KEY_START = 7; // row 0 of the document's first tile
 
-// The main loop is software-pipelined by hand and pinned with scheduling barriers, one MFMA
-// (16-bit inputs) per step:
-//   * the MFMA chain of column block cb runs while the previous block's result tile is folded
-//     into the running max, one slice of the fold per step, so the VALU work sits under MFMAs
-//     whose results it does not need;
+// The main loop is software-pipelined by hand and pinned with scheduling barriers, one operand chunk per step (with
+// 16-bit inputs one 32x32 MFMA or two 16x16 ones):
+//   * the VALU work of the folds sits under MFMAs whose results it does not need, a slice per step: under the chains of
+//     column block cb the previous block's 32x32 result is folded; of 16x16 results the half that was finished last
+//     (half_pair: the previous block's second under the block's first, the block's own first under its second);
 //   * during the first chain of a tile the wavefront also reads the NEXT tile's A operands from
 //     LDS into a second register set, writes the tile after that from registers to LDS and
-//     issues the global loads of the tile after that, so no memory latency is exposed between
-//     tiles: three LDS buffers rotate (being computed / prefetched into registers / being
-//     written), one barrier per tile.  (The fp32 and the argmax variants have no registers
-//     left for the second operand set; there each operand chunk is replaced by the next tile's
-//     right after its last MFMA, during the last chain of the tile.)
-//   * with one or two column blocks per wavefront a tile takes too little time for a load issued
-//     one tile ahead to have arrived: PFD tiles are then in flight in a ring of registers.
+//     issues the global loads of the tile after that: three LDS buffers rotate (being computed / prefetched
+//     into registers / being written), one barrier per tile.  (The argmax variants, 512-byte rows and two
+//     wavefronts with four blocks have no registers left for the second operand set; there each operand chunk is
+//     replaced by the next tile's right after its last MFMA, during the last chain of the tile.)
+//   * with two or three column blocks per wavefront a tile takes too little time for a load issued
+//     one tile ahead to have arrived: PFD tiles are then on their way in a ring of registers.  (Less than that
+//     in the code: the ring's registers move from slot to slot, and before a move the compiler waits for the load;
+//     four wavefronts with two blocks without argmax wait for all of them every second tile.)
 template <int DT, int W, int NCB, bool ARGMAX, int PFD = 1>
 __global__ void __launch_bounds__(W * 64, Traits<DT>::NU <= 8 ? 2 : 1) fwd_tile_kernel(FwdParams p, OffsetsPtr off)
 {
@@ -1050,10 +1055,10 @@ __global__ void __launch_bounds__(W * 64, Traits<DT>::NU <= 8 ? 2 : 1) fwd_tile_
 // half of such a tile is padding.  Here a 32-row window may hold the last rows of document A and, from
 // the next multiple of 4 rows on, the first rows of the next (non-empty) document B; it is cut short
 // only where a third document would begin.  The MFMAs are the same.  The boundary sits on a multiple of
-// 4 rows because a lane of the 32x32 result keeps rows 8q + 4h .. 8q + 4h + 3 (h = its lane half) in
-// accumulator registers 4q .. 4q+3: a group of four registers then belongs to one document, and a window
-// with a boundary folds the maximum of each group into A's or B's maximum by one compare per group (no
-// per-row masks).  Such a window finishes A and carries B's maximum on.  Everything else (rotating LDS
+// 4 rows because a lane of the 16x16 results keeps rows 16i + 4g .. 16i + 4g + 3 (g = its quarter) in the four
+// registers of result i: they then belong to one document, and a window with a boundary folds their maximum into
+// A's or B's by two selects, decided once per lane and half of the window (no per-row masks).
+// Such a window finishes A and carries B's maximum on.  Everything else (rotating LDS
 // buffers, pinned pipeline) is fwd_tile_kernel's.  Queries have one column block here (L_q <= 32), so a
 // wavefront's lane writes a score directly and no partial sums are combined.
 
@@ -1458,9 +1463,9 @@ template <auto KERNEL> static int resident_workgroups(int threads)
     return n;
 }
 
-// HALF: half of the resident workgroups may do (four wavefronts with two blocks each and four tiles in flight: five
-// blocks x 1000 documents of 180 tokens of d = 64 9.7 us, 11.9 with all of them, whose beginnings cost more than they
-// bring)
+// HALF: half of the resident workgroups may do (four wavefronts with two blocks each and a ring of tiles: the beginnings
+// of all of them cost more than they bring; seven blocks x 1000 documents of 180 tokens of d = 64 9.9 us, 10.4 with all
+// of them, ragged 2000 x 8-60 9.8 and 10.8; d = 128, 600 x 64 8.6 and 9.2, but ragged 2000 x 8-60 15.6 and 13.7)
 template <auto KERNEL, bool HALF> static hipError_t launch_chunks(FwdParams p, int threads, int num_cu, hipStream_t stream)
 {
     const int resident = resident_workgroups<KERNEL>(threads);
