@@ -2,6 +2,8 @@
 // operator's library): what the machine sustains, measured beside the real kernels.
 //   probe_mfma   register-only MFMA loop on caller-supplied operand bits (random data makes the
 //                part run at the clocks it holds under load; zeros show the unthrottled rate)
+//   probe_tile   the products and folds of the tile kernel: document operands from LDS, query operands in registers,
+//                on 16x16 or 32x32 results (the two differ under the power limit, not on zeros)
 //   probe_read   pure streaming read of a buffer, with plain loads or with the non-temporal hint
 //   probe_copy   plain copy of known size (calibrates the HBM byte counters of the profiler)
 //   probe_gather random gathers of whole 256-byte rows from a table (what the caches deliver to the access
@@ -48,6 +50,66 @@ __global__ void __launch_bounds__(256) probe_mfma_kernel(const uint4 *in, int it
             s += c0[i] + c1[i] + c2[i] + c3[i];
     }
     if (s == 123.456f) // never true for real data; keeps the loop alive
+        sink[0] = s;
+}
+
+// Four tiles of 32 rows x 256 bytes in LDS against four column blocks per wavefront, over and over; eight wavefronts per CU
+constexpr int PROBE_TILE_BLOCKS = 256;
+template <int DTYPE, bool M16>
+__global__ void __launch_bounds__(512) probe_tile_kernel(const uint4 *in, int iters, float *sink)
+{
+    constexpr int F = fmt(DTYPE, 8), NU = Traits<F>::NU;
+    __shared__ uint4 tile[4][NU * 64];
+    for (int i = threadIdx.x; i < 4 * NU * 64; i += 512)
+        tile[i / (NU * 64)][i % (NU * 64)] = in[i];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint4 q[4][NU];
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            q[n][u] = in[4 * NU * 64 + ((w * 4 + n) * NU + u) * 64 + lane];
+    __syncthreads();
+    float m[4][2];
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+        m[n][0] = m[n][1] = neg_inf();
+    for (int it = 0; it < iters; ++it) {
+        uint4 a[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            a[u] = tile[it & 3][u * 64 + lane];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            if constexpr (M16) {
+                Acc16 acc;
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    mma_step16<F>(a[u], q[n], u, acc);
+                    __builtin_amdgcn_sched_barrier(0x86); // VALU and LDS may move, MFMAs keep their order
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    for (int r = 0; r < 4; r += 2)
+                        m[n][k & 1] = fmaxf(fmaxf(m[n][k & 1], acc.t[k >> 1][k & 1][r]), acc.t[k >> 1][k & 1][r + 1]);
+            } else {
+                f32x16 acc = {0};
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    Traits<F>::mma(a[u], q[n][u], acc);
+                    __builtin_amdgcn_sched_barrier(0x86);
+                }
+#pragma unroll
+                for (int r = 0; r < 16; r += 2)
+                    m[n][0] = fmaxf(fmaxf(m[n][0], acc[r]), acc[r + 1]);
+            }
+        }
+    }
+    float s = 0.0f;
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+        s += m[n][0] + (M16 ? m[n][1] : 0.0f);
+    if (s == 123.456f) // (as above)
         sink[0] = s;
 }
 
@@ -155,7 +217,11 @@ static hipError_t probe_mfma_launch(int kind, const void *operands, int iters, f
     switch (kind) {
     case 0: hipLaunchKernelGGL((probe_mfma_kernel<0>), dim3(PROBE_BLOCKS), dim3(256), 0, stream, in, iters, sink); break;
     case 1: hipLaunchKernelGGL((probe_mfma_kernel<1>), dim3(PROBE_BLOCKS), dim3(256), 0, stream, in, iters, sink); break;
-    default: hipLaunchKernelGGL((probe_mfma_kernel<2>), dim3(PROBE_BLOCKS), dim3(256), 0, stream, in, iters, sink); break;
+    case 2: hipLaunchKernelGGL((probe_mfma_kernel<2>), dim3(PROBE_BLOCKS), dim3(256), 0, stream, in, iters, sink); break;
+    case 3: hipLaunchKernelGGL((probe_tile_kernel<MAXSIM_F16, true>), dim3(PROBE_TILE_BLOCKS), dim3(512), 0, stream, in, iters, sink); break;
+    case 4: hipLaunchKernelGGL((probe_tile_kernel<MAXSIM_BF16, true>), dim3(PROBE_TILE_BLOCKS), dim3(512), 0, stream, in, iters, sink); break;
+    case 5: hipLaunchKernelGGL((probe_tile_kernel<MAXSIM_F16, false>), dim3(PROBE_TILE_BLOCKS), dim3(512), 0, stream, in, iters, sink); break;
+    default: hipLaunchKernelGGL((probe_tile_kernel<MAXSIM_BF16, false>), dim3(PROBE_TILE_BLOCKS), dim3(512), 0, stream, in, iters, sink); break;
     }
     return hipGetLastError();
 }
@@ -197,7 +263,7 @@ extern "C" {
 
 int maxsim_probe_mfma(int kind, const void *operands, int iters, float *sink, void *stream)
 {
-    if (!operands || !sink || iters < 1 || kind < 0 || kind > 2 || !probe_aligned16(operands))
+    if (!operands || !sink || iters < 1 || kind < 0 || kind > 6 || !probe_aligned16(operands))
         return MAXSIM_ERR_INVALID;
     return maxsim::probe_mfma_launch(kind, operands, iters, sink, static_cast<hipStream_t>(stream)) == hipSuccess ? MAXSIM_OK
                                                                                                          : MAXSIM_ERR_LAUNCH;

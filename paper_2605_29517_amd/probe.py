@@ -10,6 +10,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmaxsim_probe.so")
 SYMBOLS = ("maxsim_probe_mfma", "maxsim_probe_read", "maxsim_probe_read_streaming", "maxsim_probe_copy", "maxsim_probe_gather")
 PROBE_MFMA_OPS_PER_ITER = {0: 512 * 4 * 4 * 2 * 32 * 32 * 16, 1: 512 * 4 * 4 * 2 * 32 * 32 * 16, 2: 512 * 4 * 4 * 2 * 32 * 32 * 32}
+PROBE_MFMA_OPS_PER_ITER.update({kind: 256 * 8 * 4 * 2 * 32 * 32 * 128 for kind in (3, 4, 5, 6)})
 
 _lib = None
 
@@ -37,7 +38,7 @@ def load():
 
 
 def maxsim_probe_mfma(kind, operands, iters, sink):
-    """Register-only MFMA loop.  Returns the number of operations one launch performs."""
+    """Register-only MFMA loop, or from kind 3 on that of the tile kernel.  Returns the number of operations one launch performs."""
     L = load()
     if operands.numel() * operands.element_size() < (1 << 20):
         raise MaxSimError("operands must hold at least 1 MiB")
