@@ -176,6 +176,16 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
             wave_blocks = 2;
             w = 4;
             shape = 42;
+        } else if (total_blocks > 12 && !am && dtype != MAXSIM_F32 && nu == 8 && !ragged && p.b > num_cu && 2 * p.b <= 3 * (int64_t)num_cu &&
+                   p.l_d >= 16 * TILE_ROWS) {
+            // 13 to 16 blocks on more documents than CUs, at most three on two of them, of sixteen tiles and more: four
+            // wavefronts with four blocks each let a CU that has two documents walk both at once (bf16, one query of 512
+            // tokens x 300 documents of 512 / 1000 tokens 29.3 -> 28.2, 51.1 -> 46.3 us, of 400 tokens x 300 x 1000 49.3 ->
+            // 46.1).  Shorter documents take 2-17 % longer that way (300 x 300 21.0 against 21.7), as do 13 and 14 blocks
+            // from two documents per CU on (512 x 640 5 %), one per CU (150 x 1000 28.6 against 30.5) and ragged corpora
+            // (6-40 %).
+            w = 4;
+            shape = 4;
         } else { // eight wavefronts with one or two column blocks each (shape code 81 / 82)
             wave_blocks = total_blocks <= 8 ? 1 : 2;
             w = 8;

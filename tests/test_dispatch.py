@@ -104,6 +104,18 @@ def test_three_blocks_per_wavefront_on_few_documents(routes, docs, tokens, ragge
         assert routes([call])[0].shape == want, call
 
 
+# (dtype, d, n_q, l_q, documents, tokens of each, ragged, argmax) -> shape, of queries with 13 to 16 blocks
+SIXTEEN = [(F16, 128, 1, 512, 256, 1000, 0, 0, 82), (F16, 128, 1, 512, 257, 1000, 0, 0, 4), (BF16, 128, 1, 400, 384, 512, 0, 0, 4), (BF16, 128, 16, 32, 300, 512, 0, 0, 4),
+           (BF16, 128, 1, 400, 385, 512, 0, 0, 82), (BF16, 128, 1, 512, 300, 511, 0, 0, 82), (F16, 128, 1, 512, 300, 1000, 1, 0, 82), (F16, 128, 1, 512, 300, 1000, 0, 1, 82),
+           (F16, 64, 1, 512, 300, 1000, 0, 0, 82), (F32, 64, 1, 512, 300, 1000, 0, 0, 82), (F16, 128, 1, 384, 300, 1000, 0, 0, 43)]
+
+
+@pytest.mark.parametrize("dtype,d,n_q,l_q,docs,tokens,ragged,argmax,want", SIXTEEN)
+def test_four_blocks_per_wavefront_on_few_long_documents(routes, dtype, d, n_q, l_q, docs, tokens, ragged, argmax, want):
+    call = Call(dtype, d, n_q, l_q, docs, docs * tokens, ragged, argmax)
+    assert routes([call])[0].shape == want, call
+
+
 def test_fp32_and_narrow_rows_keep_three_blocks(routes):
     for dtype, d, l_q, docs, tokens, want in ((F32, 64, 300, 700, 64, 43), (F32, 32, 180, 3000, 300, 42), (F16, 64, 300, 700, 64, 82), (F16, 64, 300, 700, 65, 43),
                                              (F16, 64, 180, 768, 40, 23), (F16, 64, 180, 1500, 500, 23)):

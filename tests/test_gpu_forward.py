@@ -76,6 +76,16 @@ def _ragged_case(n_q, l_q, lens, dtype, seed, d=128):
     return Q, Dp, off
 
 
+# 13 to 16 blocks on a little more documents than CUs, of sixteen tiles and more: four wavefronts with four blocks each (16-bit)
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n_q,l_q,l_d", [(1, 400, 512), (4, 128, 513), (16, 32, 545), (13, 20, 530)])
+def test_sixteen_blocks_on_few_long_documents(n_q, l_q, l_d, dtype):
+    b = torch.cuda.get_device_properties(0).multi_processor_count + 3
+    Q = W.unit_rows((n_q, l_q, 128), dtype, 23 + l_q, DEV)
+    D = W.unit_rows((b, l_d, 128), dtype, 24 + l_d, DEV)
+    forward_parity_uniform(Q, D, M.maxsim_forward, False, 1e-5)  # (the bound: see THREES)
+
+
 # The same on ragged corpora with empty documents at both ends and in between; five and six blocks with more than four
 # documents per CU, which take two wavefronts with three blocks each (16-bit)
 @pytest.mark.parametrize("dtype,d", [("f16", 128), ("bf16", 64), ("f32", 64), ("f32", 32)])
