@@ -65,9 +65,9 @@ template <int F> struct Traits {
 };
 
 // 32 document tokens x 32 query tokens as four 16x16 results, for the kernels that are bound by the power limit: on
-// operands of unit-norm rows a loop of 16x16x32 MFMAs (operands from LDS, folds in between) sustains 1740 TFLOP/s fp16
-// and 1860 bf16 where one of 32x32x16 MFMAs holds 1515 and 1650, in whatever order they are issued -- half as many
-// accumulator words travel per product -- and on zero operands, where the clock does not drop, both 2250.
+// operands of unit-norm rows a loop of 16x16x32 MFMAs (operands from LDS, folds in between) sustains 1715-1745 TFLOP/s
+// fp16 and 1835-1870 bf16 where one of 32x32x16 MFMAs holds 1500-1525 and 1625-1660 (probe_tile_kernel) -- half as many
+// accumulator words travel per product -- and on zero operands, where the clock does not drop, both 2220-2240.
 // Lane (c = lane % 16, g = lane / 16) keeps, of result (i, j), query token 16 j + c and document tokens 16 i + 4 g + r,
 // r = 0 .. 3.  Operand fragment f = i * NU / 2 + u is chunk 4 u + g of document row 16 i + c, for queries alike.
 struct Acc16 {
