@@ -23,25 +23,15 @@
 // keeps the order among negative values and any non-negative value still beats them, so
 // the running max stays correct and a negative final max is doubled once per query token
 // at the end of the document.  |n| <= 128 * 127^2 < 2^21.
-#include "common.h"
+#include "int8_impl.h"
 
 namespace maxsim {
 
-constexpr int I8_ROW_BYTES = 128;
 constexpr int I8_NU = 4;          // 16-byte chunks per lane per row (chunks 2u + h)
 constexpr int I8_TILE_ROWS = 64;  // document tokens staged per barrier (two MFMA row tiles)
 constexpr int I8_ROW_STRIDE = I8_ROW_BYTES + 16;
 constexpr int I8_NCB = 4;
 constexpr int I8_PIPE = 1; // result blocks between a block's MFMAs and its epilogue (2 needs more registers than there are)
-
-struct I8Params {
-    const char *Q;      // [n_q, l_q, 128] int8
-    const float *qs;    // [n_q, l_q]
-    const char *D;      // [b, l_d, 128] int8
-    const float *ds;    // [b, l_d]
-    float *scores;      // [n_q, b]
-    FwdParams f;        // sizes, optional offsets and the work split
-};
 
 // (four wavefronts: asked to fit two per SIMD, which they do without spilling; one or two run faster unconstrained)
 template <int W>
@@ -275,7 +265,7 @@ constexpr int I8D_WAVES = 8;
 constexpr int I8D_LIN_BLOCKS = 2;                        // up to this many column blocks the tiles are read as whole lines (no gain from 4 on)
 constexpr int I8D_DEPTH = 2;                             // tiles in flight per wavefront (up to 16 blocks; beyond, a tile takes long enough): 128 tokens x 8000 x 300 66 -> 60 us
 constexpr int i8d_depth(int nb) { return nb <= 16 ? I8D_DEPTH : 1; }
-constexpr int I8D_SPLIT_BLOCKS = 16;                     // column blocks per group of the kernel whose wavefronts share documents
+constexpr int I8D_SPLIT_BLOCKS = 8;                      // column blocks of the kernel whose wavefronts share documents
 constexpr int I8D_MAX_BLOCKS = 32;                       // column blocks per group (1024 query tokens)
 constexpr int I8D_QSTRIDE = I8_ROW_BYTES + 16;           // padded LDS row of a query token
 
@@ -310,7 +300,7 @@ __device__ __forceinline__ void i8d_tile_scales(float *w_scale, float *w_bias, f
 // scales and biases); the whole-line variant adds a document tile per wavefront
 constexpr size_t i8_doc_lds(int nb) { return (size_t)nb * BLOCK_COLS * (I8D_QSTRIDE + 4) + I8D_WAVES * 64 * sizeof(float); }
 constexpr size_t i8_doc_lin_lds(int nb) { return i8_doc_lds(nb) + (size_t)I8D_WAVES * TILE_ROWS * I8D_QSTRIDE; }
-constexpr size_t i8_split_lds(int nb, int w)
+constexpr size_t i8_split_lds(int nb, int w) // (8 blocks, 4 wavefronts: 46 KB)
 {
     return (size_t)nb * BLOCK_COLS * (I8D_QSTRIDE + 4) + w * 64 * sizeof(float) + (size_t)2 * w * nb * BLOCK_COLS * sizeof(float);
 }
@@ -356,35 +346,6 @@ __device__ __forceinline__ void i8d_tile_blocks(const i32x4 (&a)[I8_NU], const f
         }
         __builtin_amdgcn_sched_barrier(0);
     }
-}
-
-// Cross-lane steps on the VALU: a shuffle goes through the LDS, and ten in a row per query at the end of every document
-// (five steps of an fp64 butterfly) took longer than the document's MFMAs (4 / 8 queries x 100 000 / 50 000
-// texts: 570 -> 533, 440 -> 409 us).
-__device__ __forceinline__ float max_halves(float x) // both lane halves get the maximum of the two
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-template <int N> __device__ __forceinline__ double add_rotated(double v) // + the value N lanes on within the row of sixteen
-{
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x120 + N, 0xf, 0xf, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), 0x120 + N, 0xf, 0xf, true);
-    return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-// Sum over lanes 0 .. 31 (lanes 32 .. 63 hold the same): a butterfly over distances 16, 8, 4, 2, 1.  Once the lanes repeat with
-// period 2N, the lane N away by XOR and the one N away by rotation hold the same value.
-__device__ __forceinline__ double sum32(double v)
-{
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
-    v = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) + __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
-    v = add_rotated<8>(v);
-    v = add_rotated<4>(v);
-    v = add_rotated<2>(v);
-    return add_rotated<1>(v);
 }
 
 // End of a document: mm[blk] is the maximum per query token (column rho of block blk; in lanes 0..31 and again
@@ -598,8 +559,7 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, 
 // tiles; the query tokens sit in LDS as above and every wavefront still streams its tiles HBM ->
 // registers, one tile ahead, across document borders.  At the end of a document the W partial maxima per query token
 // meet in LDS (double-buffered, one barrier per document) and one wavefront, a different one each time, finishes the
-// score.  Built for up to 16 column blocks (512 query tokens): beyond that the maxima of eight wavefronts no longer fit
-// beside the queries in LDS.
+// score.  (Documents of equal length of 256 tokens and more, and all with more query tokens: int8_rows64.hip.)
 template <int NB, int W>
 __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, OffsetsPtr off)
 {
@@ -634,13 +594,8 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
     const int doc0 = (int)doc0_, doc1 = (int)doc1_;
 
     // first row and length of a document (offsets forced into the corpus, see clamp_offset)
-    constexpr bool UNI = W == I8D_WAVES; // eight wavefronts share documents of equal length only
-    // Which tiles are a wavefront's: every W-th, or of documents of equal length and from three blocks on the w-th eighth,
-    // with a loader that counts tiles instead of rows (4 x 32 query tokens: 1000 x 300 18.6 -> 17.7 us, 3000 x 300 42.8
-    // -> 39.0, 900 x 1024 36.8 -> 33.9; one block: 2000 x 1024 43.5 -> 47)
-    constexpr bool RUNS = UNI && NB >= 3;
     auto extent = [&](int doc, int &first, int &len) {
-        if (!UNI && p.offsets) {
+        if (p.offsets) {
             const int t_all = (int)p.total_tokens;
             first = min(max(off[doc], 0), t_all);
             len = min(max(off[doc + 1], first), t_all) - first;
@@ -649,41 +604,23 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
             len = p.l_d;
         }
     };
-    // the loader walks this wavefront's tiles in order; past the end it stays on the last one
-    const int n_tiles = (p.l_d + TILE_ROWS - 1) / TILE_ROWS;
-    const int t_lo = w * (n_tiles / W) + min(w, n_tiles % W);
-    const int cnt = n_tiles / W + (w < n_tiles % W ? 1 : 0); // RUNS: tiles [t_lo, t_lo + cnt)
+    // the loader walks this wavefront's tiles, every W-th, in order; past the end it stays on the last one
     i32x4 a_n[I8_NU];
     float s_n = 0.0f;
-    int l_doc = doc0, l_first = 0, l_len = 0, l_t0 = w * TILE_ROWS, l_t = 0;
-    if (!RUNS)
-        extent(l_doc, l_first, l_len);
+    int l_doc = doc0, l_first = 0, l_len = 0, l_t0 = w * TILE_ROWS;
+    extent(l_doc, l_first, l_len);
     int l_row = 0, l_last = 0;
     auto gload = [&]() {
-        if constexpr (RUNS) {
-            if (cnt == 0)
-                return;
-            const int t0 = (t_lo + l_t) * TILE_ROWS;
-            l_row = l_doc * p.l_d + t0;
-            l_last = p.l_d - t0 - 1;
-            if (l_t + 1 < cnt) {
-                l_t += 1;
-            } else if (l_doc + 1 < doc1) {
-                l_doc += 1;
-                l_t = 0;
-            }
-        } else {
-            while (l_doc < doc1 && l_t0 >= l_len) {
-                l_doc += 1;
-                l_t0 = w * TILE_ROWS;
-                if (l_doc < doc1)
-                    extent(l_doc, l_first, l_len);
-            }
-            if (l_doc < doc1) {
-                l_row = l_first + l_t0;
-                l_last = l_len - l_t0 - 1; // rows past the document re-read its last token
-                l_t0 += W * TILE_ROWS;
-            }
+        while (l_doc < doc1 && l_t0 >= l_len) {
+            l_doc += 1;
+            l_t0 = w * TILE_ROWS;
+            if (l_doc < doc1)
+                extent(l_doc, l_first, l_len);
+        }
+        if (l_doc < doc1) {
+            l_row = l_first + l_t0;
+            l_last = l_len - l_t0 - 1; // rows past the document re-read its last token
+            l_t0 += W * TILE_ROWS;
         }
         const int64_t grow = (int64_t)l_row + (rho < l_last ? rho : l_last);
         const char *src = P.D + grow * I8_ROW_BYTES + h * 16;
@@ -717,7 +654,7 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
 #pragma unroll
         for (int blk = 0; blk < NB; ++blk)
             m[blk] = neg_inf();
-        const int mine_cnt = RUNS ? cnt : (len - w * TILE_ROWS + W * TILE_ROWS - 1) / (W * TILE_ROWS); // (not positive: none)
+        const int mine_cnt = (len - w * TILE_ROWS + W * TILE_ROWS - 1) / (W * TILE_ROWS); // (not positive: none)
         for (int t = 0; t < mine_cnt; ++t) {
             i32x4 a[I8_NU];
 #pragma unroll
@@ -803,6 +740,8 @@ template <int MAX, typename F> static hipError_t with_blocks(int nb, F &&f)
 // the current device (called once per device by the library's set-up).
 hipError_t forward_i8_init_device()
 {
+    if (hipError_t e = forward_i8_rows64_init_device(); e != hipSuccess)
+        return e;
     for (int nb = 1; nb <= I8D_MAX_BLOCKS; ++nb) {
         hipError_t e = with_blocks<I8D_MAX_BLOCKS>(nb, [](auto n) {
             constexpr int NB = decltype(n)::value;
@@ -811,15 +750,6 @@ hipError_t forward_i8_init_device()
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)i8_doc_lds(NB));
             return hipSuccess;
         });
-        if (e == hipSuccess && nb <= I8D_SPLIT_BLOCKS)
-            e = with_blocks<I8D_SPLIT_BLOCKS>(nb, [](auto n) {
-                constexpr int NB = decltype(n)::value;
-                if constexpr (i8_split_lds(NB, 8) > 64 * 1024)
-                    return hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_i8_split_kernel<NB, 8>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)i8_split_lds(NB, 8));
-                static_assert(i8_split_lds(8, 4) <= 64 * 1024, "the smaller workgroups need no more than that");
-                return hipSuccess;
-            });
         if (e != hipSuccess)
             return e;
     }
@@ -854,6 +784,9 @@ hipError_t forward_i8_launch(const int8_t *Q, const float *qs, int n_q, int l_q,
     if (p.bpq > I8D_MAX_BLOCKS)
         return hipErrorNotSupported; // l_q > 1024: would need a second pass with an fp64 carry
 
+    if (forward_i8_rows64_takes(n_q, l_q, offsets, b, l_d, num_cu))
+        return forward_i8_rows64_launch(P, num_cu, stream);
+
     // Large corpora: document-stationary kernel, one run of documents per wavefront.
     if (b >= (int64_t)num_cu * I8D_WAVES * 2) {
         const int most = I8D_MAX_BLOCKS / p.bpq; // whole queries, spread evenly over as few groups as hold them
@@ -874,32 +807,25 @@ hipError_t forward_i8_launch(const int8_t *Q, const float *qs, int n_q, int l_q,
         return with_blocks<I8D_MAX_BLOCKS>(nb, [&](auto n) { return launch_i8_doc<decltype(n)::value>(P, grid, stream); });
     }
 
-    // Fewer documents, up to 16 column blocks per query and one or two groups of 16: the wavefronts of a workgroup share
-    // each document (document-stationary like the kernel above, at any number of documents): eight of them where a
-    // document has a tile for each, else two, or four (fewer copies of the queries) from five blocks on.  One query x 1000 /
-    // 3000 texts of 64-300 tokens 26 -> 10, 53 -> 18 us against the kernel below, four x 1000 32 -> 21, eight x 2000 45 -> 44
-    // (with two wavefronts 59); with 16 blocks and documents of 60-512 tokens the kernel below is faster (46 against 80).
+    // Fewer documents, up to 8 column blocks: the wavefronts of a workgroup share each document (document-stationary like the
+    // kernel above, at any number of documents), two of them, or four (fewer copies of the queries) from five blocks on.  One
+    // query x 1000 / 3000 texts of 64-300 tokens 26 -> 10, 53 -> 18 us against the kernel below, four x 1000 32 -> 21, eight x
+    // 2000 45 -> 44 (with two wavefronts 59).
     const int64_t mean_len = (total_tokens + b - 1) / b; // (uniform: l_d)
-    const bool eight = !offsets && l_d >= I8D_WAVES * TILE_ROWS;
-    if (p.bpq <= I8D_SPLIT_BLOCKS && total_blocks <= 2 * I8D_SPLIT_BLOCKS && (eight || (mean_len >= 2 * TILE_ROWS && total_blocks <= 8))) {
-        const int most = I8D_SPLIT_BLOCKS / p.bpq;
-        p.n_groups = (n_q + most - 1) / most;
-        p.qpg = (n_q + p.n_groups - 1) / p.n_groups;
-        p.n_groups = (n_q + p.qpg - 1) / p.qpg;
-        const int nb = p.qpg * p.bpq;
-        // about four workgroups of eight wavefronts per CU while the queries are small, one when their LDS copy is large; eight
-        // wavefronts per CU in the smaller workgroups
-        const int64_t per_cu = eight ? (nb <= 4 ? 4 : 1) : nb <= 4 ? 4 : 2;
-        int64_t n_chunks = ((int64_t)num_cu * per_cu + p.n_groups - 1) / p.n_groups;
+    if (total_blocks <= I8D_SPLIT_BLOCKS && mean_len >= 2 * TILE_ROWS) {
+        p.n_groups = 1;
+        p.qpg = n_q;
+        // eight wavefronts per CU
+        int64_t n_chunks = (int64_t)num_cu * (total_blocks <= 4 ? 4 : 2);
         if (n_chunks > b)
             n_chunks = b;
         p.unit_per_chunk = (units + n_chunks - 1) / n_chunks;
         n_chunks = (units + p.unit_per_chunk - 1) / p.unit_per_chunk;
         p.n_chunks = (int)n_chunks;
-        const int grid = p.n_chunks * p.n_groups;
-        return with_blocks<I8D_SPLIT_BLOCKS>(nb, [&](auto n) {
+        const int grid = p.n_chunks;
+        return with_blocks<I8D_SPLIT_BLOCKS>((int)total_blocks, [&](auto n) {
             constexpr int NB = decltype(n)::value;
-            return eight ? launch_i8_split<NB, 8>(P, grid, stream) : launch_i8_split<(NB <= 8 ? NB : 8), (NB <= 4 ? 2 : 4)>(P, grid, stream);
+            return launch_i8_split<NB, (NB <= 4 ? 2 : 4)>(P, grid, stream);
         });
     }
 

@@ -224,6 +224,19 @@ def test_forward_i8_shared_documents_negative_maxima():
     assert float(s[0, 0]) < 0 < float(s[0, 1])
 
 
+# 64 document tokens per step (int8_rows64.hip): documents that end with a whole tile, half of one or a token more, fewer tiles than
+# wavefronts and shares that begin inside a document, several queries within 64 columns, every number of column blocks that is built
+@pytest.mark.parametrize("n_q,l_q,b,l_d", [(5, 16, 1, 64), (7, 5, 3, 65), (3, 17, 2, 96), (1, 70, 9, 97), (2, 40, 5, 127), (9, 16, 3, 128), (10, 3, 4, 129),
+                                           (1, 170, 13, 191), (1, 224, 6, 192), (2, 112, 7, 193), (20, 16, 300, 100), (5, 70, 5, 159), (7, 50, 300, 65), (1, 512, 2, 130),
+                                           (4, 140, 3, 64), (1, 600, 11, 96), (5, 129, 2, 65), (2, 384, 3, 225), (1, 820, 9, 97), (3, 290, 2, 640), (4, 240, 300, 70),
+                                           (1, 1009, 300, 64), (40, 100, 2, 400), (2, 30, 600, 256), (1, 1, 3, 300), (300, 33, 5, 70)])
+def test_forward_i8_64_tokens_per_step_bit_exact(n_q, l_q, b, l_d):
+    g, o = quantised_case(n_q, l_q, b, l_d, 61)
+    s = M.maxsim_forward_i8(*g)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(s.cpu().numpy()), bits(O.forward_i8(*o)))
+
+
 # Every number of column blocks the document kernels are built for, and one that is rounded up: small corpora, whose
 # documents are shared by two or four wavefronts (ragged, or uniform of under 256 tokens), and large ones
 @pytest.mark.parametrize("n_q,l_q", [(1, 30), (2, 32), (1, 90), (4, 20), (1, 160), (3, 60), (1, 224), (8, 32), (1, 290), (3, 128), (7, 50), (1, 500)])
