@@ -39,24 +39,28 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
     const int row_bytes = d * (dtype == MAXSIM_F32 ? 4 : 2);
     // any other width: both operands stream through LDS in slabs of the width; so do rows of 512 bytes from 8 column
     // blocks on (two blocks per wavefront in the register-stationary kernel: measured 3-11 % slower there).  Two
-    // kernels: macro tiles of 256 document tokens x 256 query tokens and whole cache lines (forward_wide.hip), or of
+    // kernels: macro tiles of 256 document tokens x 256 query tokens and whole cache lines (forward_wide_impl.h), or of
     // 128 x 512 and half lines (forward_splitd.hip).  Up to 8 blocks the first, except for half lines and documents of
-    // up to 128 tokens (8 blocks, d = 32: 121 against 113 us); beyond, 512 query tokens at once are ahead where
-    // documents are little work (narrow rows and 65-128 tokens: 20 000 x 100 tokens, 16 blocks, d = 256 / 160: 800 /
-    // 573 us in the first, 790 / 515 in the second) and where the first would multiply many padded blocks (three
-    // queries of 140 tokens x 4000 x 128, d = 512: 72 % of its time) or documents of a few tiles of 256 leave much of
-    // one empty: the estimates of both decide.  The other way round, the second's chunks fill the chip badly on some
-    // numbers of documents (16 queries x 1500 x 100 tokens, d = 512: 1.35 times the first's time).
+    // up to 128 tokens (8 blocks, d = 32: 121 against 113 us).  Beyond, 512 query tokens at once are ahead where the
+    // first would multiply many padded blocks (three queries of 140 tokens x 4000 x 128, d = 512: 72 % of its time) or
+    // documents of a few tiles of 256 leave much of one empty: the estimates of both decide.  The other way round, the
+    // second's chunks fill the chip badly on some numbers of documents (16 queries x 1500 x 100 tokens, d = 512: 1.35
+    // times the first's time).  The estimates are of 32x32 results; on 16x16 ones the first is 5-11 % faster, and where
+    // they say 0.86 to 1 it takes 0.77 to 1.0 of the second's time (three queries of 100 tokens x 500 x 1000, d = 256 /
+    // 1024: 114 -> 90, 488 -> 376 us; twelve of 32 x 3000 x 97 97 -> 91, 380 -> 346); of 1024 bytes and more than 128
+    // tokens from 0.92 on (three of 140 x 1000 x 300, d = 512: 0.90, 215 in the second, 224 in the first).  With argmax the second has narrow rows and 65-128 tokens (20 000 x 100, 16 blocks, d =
+    // 256 / 160, before 16x16 results without: 800 / 573 us in the first, 790 / 515 in the second).
     const int64_t all_blocks = (int64_t)p.n_q * ((p.l_q + BLOCK_COLS - 1) / BLOCK_COLS);
     if (!register_stationary_width(row_bytes) || (row_bytes == 512 && all_blocks >= 8)) {
         const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b; // (uniform corpora: total_tokens = b * l_d)
         bool slabs;
         if (all_blocks <= 8)
             slabs = dtype != MAXSIM_F32 && all_blocks == 8 && row_bytes == 64 && mean_len <= 128;
-        else if (dtype != MAXSIM_F32 && mean_len <= 128 && (row_bytes == 64 || (row_bytes <= 512 && mean_len > 64)))
+        else if (dtype != MAXSIM_F32 && mean_len <= 128 && (row_bytes == 64 || (p.argmax && row_bytes <= 512 && mean_len > 64)))
             slabs = true;
         else
-            slabs = forward_splitd_time(p, dtype, row_bytes, num_cu) <= forward_wide_time(p, num_cu);
+            slabs = forward_splitd_time(p, dtype, row_bytes, num_cu) <=
+                    forward_wide_time(p, num_cu) * (dtype == MAXSIM_F32 || p.argmax || row_bytes == 64 ? 1.0 : mean_len > 128 && row_bytes >= 1024 ? 0.92 : 0.86);
         return slabs ? forward_splitd_launch(p, dtype, row_bytes, num_cu, stream) : forward_wide_launch(p, dtype, row_bytes, num_cu, stream);
     }
     const int nu = row_bytes / 32; // 16-byte chunk pairs per row

@@ -1,5 +1,5 @@
 // Fused MaxSim forward for any embedding width, the variant for int8 codes and for short documents of narrow rows
-// (forward_wide.hip has the others; forward.hip and int8_wide.hip choose) (the "split-d" forward of the paper's appendix on fat
+// (forward_wide_impl.h has the others; forward.hip and int8_wide.hip choose) (the "split-d" forward of the paper's appendix on fat
 // embeddings: an inner loop over slabs of the embedding dimension, accumulated in fp32, with the
 // reduction of Alg. 1 unchanged), for gfx950.
 //

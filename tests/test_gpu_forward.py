@@ -290,6 +290,19 @@ def test_wide_many_documents(n_q, l_q):
     forward_parity_uniform(Q, W.unit_rows((n, 70, 96), "f16", 65, DEV), M.maxsim_forward, False, 1e-5)
 
 
+# Without argmax the wide kernel's results are 16x16: every shape, several ragged documents per workgroup with empty ones among them,
+# widths of one and a half, two and four and a half slabs
+@pytest.mark.parametrize("dtype,d", [("f16", 96), ("bf16", 128 + 128), ("bf16", 288)])
+@pytest.mark.parametrize("longest", [40, 120, 600])
+@pytest.mark.parametrize("n_q,l_q", [(1, 16), (2, 33), (3, 60), (8, 31), (1, 257), (1, 600)])
+def test_wide_16x16_results(n_q, l_q, longest, dtype, d):
+    n = torch.cuda.get_device_properties(0).multi_processor_count + 9
+    lens = np.random.default_rng(longest + l_q).integers(0, longest, n)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV)
+    Q = W.unit_rows((n_q, l_q, d), dtype, 64, DEV)
+    forward_parity_ragged(Q, W.unit_rows((int(lens.sum()), d), dtype, 63, DEV), off, M.maxsim_forward_ragged, False, 1e-5)
+
+
 # Rows of a single slab (d = 32 in 16 bits): one barrier per macro tile, so that with short documents the loads run up to three
 # documents ahead and the merge and the sum of one document fall into the next two.  Several documents per workgroup, a few of
 # them empty, in the shapes for 1 to 8 column blocks and for every height of the macro tiles
