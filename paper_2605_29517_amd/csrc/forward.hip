@@ -31,6 +31,60 @@ bool forward_width_supported(int dtype, int d)
     return d >= 32 && row_bytes % 64 == 0 && row_bytes <= MAX_ROW_BYTES;
 }
 
+// Forward with argmax on 16-bit inputs, fewer documents than CUs.  The tile kernel's workgroups of up to 32 column blocks then leave
+// most of the chip idle (16 documents x 16 queries: 16 workgroups).  Smaller column groups make more of them; and the kernel whose
+// wavefronts share a document's tiles (fwd_stream_split_kernel) makes most, with one or two blocks per workgroup, of one, two or
+// four wavefronts.  The estimate: a start, then what a CU's (a SIMD's) workgroups (wavefronts) have to multiply, or the chain of
+// one of them if that is longer.  us, n queries of 32 tokens x n documents, before -> after: n = 16 x 128 tokens 10.0 -> 4.1,
+// x 1024 32.7 -> 8.4; 33 x 83-333 24.9 -> 9.7; 50 x 100 16.6 -> 9.4, x 1024 52 -> 33; 64 x 75-300 29 -> 17; 103 queries of 24 x
+// 163-653 64 -> 54; from some hundred on the large groups are the best again (128 x 500 70, the others 70-85).
+struct FewDocs {
+    int shape, blocks; // of the tile kernel and blocks per group, or
+    int waves;         // wavefronts per workgroup of the other (0: tile kernel), with `blocks` each
+};
+static FewDocs few_documents(const FwdParams &p, int num_cu, int shape, int groups)
+{
+    const double mean_len = (double)p.total_tokens / (double)p.b;
+    const double tiles = p.offsets ? mean_len / TILE_ROWS + 0.5 : (double)((p.l_d + TILE_ROWS - 1) / TILE_ROWS);
+    const double longest = p.offsets ? 1.5 * tiles : tiles; // (lengths are not known here)
+    struct Shape {
+        int code, blocks;
+        double start, next, one, block; // us: of a workgroup, of one more on a CU; per tile of one by itself, per block where a CU is full
+    };
+    static const Shape shapes[] = {{81, 8, 4.5, 0.4, 0.62, 0.069}, {42, 8, 4.8, 0.44, 0.67, 0.069}, {43, 12, 5.9, 0.64, 0.81, 0.061}, {82, 16, 6.4, 0.4, 0.9, 0.067},
+                                   {4, 16, 6.9, 1.2, 0.96, 0.054}, {83, 24, 7.6, 1.8, 1.3, 0.061}, {8, 32, 9.0, 2.8, 1.8, 0.05}};
+    auto tile_time = [&](const Shape &s, int64_t n_groups) {
+        const double on_cu = (double)((p.b * n_groups + num_cu - 1) / num_cu);
+        const double work = on_cu * s.blocks * s.block;
+        return s.start + (on_cu - 1) * s.next + (work > s.one ? work : s.one) * (tiles + (longest - tiles) / on_cu);
+    };
+    FewDocs best = {shape, 0, 0};
+    double least = 1e30;
+    for (const Shape &s : shapes)
+        if (s.code == shape && groups > 0)
+            least = 0.9 * tile_time(s, groups);
+    for (const Shape &s : shapes)
+        if (p.bpq <= s.blocks) {
+            const double t = tile_time(s, (p.n_q + s.blocks / p.bpq - 1) / (s.blocks / p.bpq));
+            if (t < least) {
+                least = t;
+                best = {s.code, s.blocks, 0};
+            }
+        }
+    for (int blocks = p.bpq; blocks <= 2; blocks += p.bpq)
+        for (int waves = 1; waves <= 4; waves *= 2) {
+            const int64_t n = p.b * ((p.n_q + blocks / p.bpq - 1) / (blocks / p.bpq)) * waves;
+            const double chain = std::ceil(longest / waves) * (blocks == 1 ? 0.57 : 0.72);
+            const double work = (double)((n + 4 * num_cu - 1) / (4 * num_cu)) * tiles / waves * (blocks == 1 ? 0.43 : 0.66);
+            const double t = 2.5 + (double)n / (4.0 * num_cu) * (blocks == 1 ? 0.8 : 1.8) + (work > chain ? work : chain);
+            if (t < least) {
+                least = t;
+                best = {0, blocks, waves};
+            }
+        }
+    return best;
+}
+
 // Chooses kernel and launch shape from the problem size; `num_cu` is the device's CU count.
 hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t stream)
 {
@@ -113,6 +167,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         p.n_groups = 1;
         p.qpg = p.n_q;
         p.n_pass = 1;
+        p.unit_per_chunk = 2; // wavefronts
         const int64_t resident = (int64_t)num_cu * 4;
         return run(false, s_ncb, (int)(p.b < resident ? p.b : resident));
     }
@@ -277,6 +332,21 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         } else if (shape == 8 && p.n_pass == 2 && p.bpq <= 48) {
             shape = 83;
             share(24);
+        }
+    }
+    // Winners wanted of fewer documents than CUs (a training step on a small batch)
+    if (am && dtype != MAXSIM_F32 && nu <= 8 && p.b <= num_cu) {
+        const FewDocs few = few_documents(p, num_cu, shape, p.n_pass == 1 ? p.n_groups : 0);
+        if (few.waves) { // a document and a column group per workgroup
+            p.n_chunks = 0;
+            p.qpg = few.blocks / p.bpq;
+            p.n_groups = p.n_pass = 1;
+            p.unit_per_chunk = few.waves;
+            return run(false, few.blocks, (int)p.b);
+        }
+        if (few.shape != shape) {
+            shape = few.shape;
+            share(few.blocks);
         }
     }
     return run(true, shape, num_cu); // (the chunks: launch_chunks)

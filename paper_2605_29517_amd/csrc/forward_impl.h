@@ -492,25 +492,26 @@ __global__ void __launch_bounds__(lin_waves<DT>() * 64) fwd_stream_lin_kernel(Fw
     }
 }
 
-// The streaming kernel for corpora of up to some thousand documents: a workgroup of two wavefronts per document, each
-// taking every other tile.  With a thousand documents a run of one document per wavefront is a chain of memory round
+// The streaming kernel for corpora of up to some thousand documents: a workgroup of W wavefronts per document, each
+// taking every W-th tile.  With a thousand documents a run of one document per wavefront is a chain of memory round
 // trips on a chip that is mostly idle (and the runs of a ragged corpus, equal in tokens, hold up to three documents);
-// here twice as many wavefronts have half as long a chain, and nothing is searched for, since a workgroup's document
-// is its number.  At the end of a document the two sets of maxima (and winners) meet in LDS, lane by lane, and the first
+// here more wavefronts have a shorter chain, and nothing is searched for, since a workgroup's document
+// is its number.  At the end of a document the sets of maxima (and winners) meet in LDS, lane by lane, and the first
 // wavefront finishes it.  A maximum does not depend on how the tiles were shared out, and of equal ones the lower row
-// wins, so scores and winners are those of the other kernels.  Four wavefronts per document were no faster (they
+// wins, so scores and winners are those of the other kernels.  Two wavefronts; four were no faster (they
 // read the queries twice as often): ragged fp16 texts of 64-300 tokens, four queries, 1000 / 4000 documents: 20.8 /
 // 52.9 us one wavefront per run, 17.6 / 42.5 here, 18.7 / 46.1 with four; fp32, one query, 1000 x 128 tokens with
 // winners: 24.0 -> 18.5 us.
-constexpr int SPLIT_WAVES = 2;
-
-template <int DT, int NCB, bool ARGMAX>
-__global__ void __launch_bounds__(SPLIT_WAVES * 64) fwd_stream_split_kernel(FwdParams p, OffsetsPtr off)
+//
+// With many queries on few documents (few_documents in forward.hip; there one to four wavefronts) a document has a workgroup
+// per column group of NCB blocks: latency and start-up bound it, 16 queries x 16 documents of 128 / 1024 tokens take 4.2 / 8.6 us
+// where a workgroup of fwd_tile_kernel per document takes 10.0 / 32.7.
+template <int DT, int NCB, bool ARGMAX, int W>
+__global__ void __launch_bounds__(W * 64) fwd_stream_split_kernel(FwdParams p, OffsetsPtr off)
 {
     using TR = Traits<DT>;
     using LT = LdsTile<DT>;
     constexpr int NU = TR::NU;
-    constexpr int W = SPLIT_WAVES;
     constexpr int CPR = TR::ROW_BYTES / 16; // 16-byte chunks (= lanes) per row
     constexpr int RPI = 64 / CPR;           // rows per load instruction
     static_assert((ARGMAX ? 2 : 1) * NCB * 64 * 4 <= LT::BYTES, "a wavefront's maxima fit in its tile");
@@ -520,15 +521,20 @@ __global__ void __launch_bounds__(SPLIT_WAVES * 64) fwd_stream_split_kernel(FwdP
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     char *lds = lds_all[w];
 
+    // a document's column groups are neighbours on one XCD
+    const int v = p.n_groups == 1 ? (int)blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x);
+    const int group = p.n_groups == 1 ? 0 : v % p.n_groups;
+    const int first = p.n_groups == 1 ? v : v / p.n_groups, step = p.n_groups == 1 ? (int)gridDim.x : (int)gridDim.x / p.n_groups;
+    const int gb0 = group * NCB; // (whole queries)
     StreamState<DT, NCB, ARGMAX> st;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
-        load_q_block<DT>(p, cb, rho, h, st.qf[cb], st.col_valid[cb]);
+        load_q_block<DT>(p, gb0 + cb, rho, h, st.qf[cb], st.col_valid[cb]);
 
     const int lrow = lane / CPR, lcol = (lane % CPR) * 16;
     const int st_off = lrow * LT::ROW_STRIDE + lcol;
     const int rd_off = rho * LT::ROW_STRIDE + h * 16;
-    for (int doc = blockIdx.x; doc < p.b; doc += gridDim.x) {
+    for (int doc = first; doc < p.b; doc += step) {
         int64_t start;
         int len;
         if (p.offsets) {
@@ -539,7 +545,8 @@ __global__ void __launch_bounds__(SPLIT_WAVES * 64) fwd_stream_split_kernel(FwdP
             len = p.l_d;
         }
         if (len <= 0) {
-            write_empty_docs(p, doc, doc + 1, threadIdx.x, W * 64);
+            if (group == 0)
+                write_empty_docs(p, doc, doc + 1, threadIdx.x, W * 64);
             continue;
         }
         const char *base = p.D + start * TR::ROW_BYTES + lcol;
@@ -595,7 +602,7 @@ __global__ void __launch_bounds__(SPLIT_WAVES * 64) fwd_stream_split_kernel(FwdP
                     st.m[cb] = fmaxf(st.m[cb], mo);
                 }
             }
-            stream_finish(p, st, 0, doc, len, lane, rho, h);
+            stream_finish(p, st, gb0, doc, len, lane, rho, h);
         }
         __syncthreads(); // the tiles are overwritten by the next document
     }
@@ -1420,12 +1427,23 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
 // ---------------------------------------------------------------------------------------
 
 template <int DT, int NCB, bool ARGMAX>
-static hipError_t launch_stream(const FwdParams &p, int grid, hipStream_t stream)
+static hipError_t launch_stream(FwdParams p, int grid, hipStream_t stream)
 {
-    if (p.n_chunks == 0) { // small corpus: a workgroup per document (not with two blocks of 512-byte rows)
+    if (p.n_chunks == 0) { // a workgroup of unit_per_chunk wavefronts per document (not with two blocks of 512-byte rows) and qpg queries
         if constexpr (Traits<DT>::NU <= 8 || NCB == 1) {
-            hipLaunchKernelGGL((fwd_stream_split_kernel<DT, NCB, ARGMAX>), dim3(grid), dim3(SPLIT_WAVES * 64), 0, stream, p, p.offsets);
-            return hipGetLastError();
+            p.n_groups = (p.n_q + p.qpg - 1) / p.qpg;
+            auto go = [&](auto w) {
+                constexpr int W = decltype(w)::value;
+                hipLaunchKernelGGL((fwd_stream_split_kernel<DT, NCB, ARGMAX, W>), dim3(grid * p.n_groups), dim3(W * 64), 0, stream, p, p.offsets);
+                return hipGetLastError();
+            };
+            if constexpr (Traits<DT>::NU <= 8 && Traits<DT>::DT != MAXSIM_F32 && ARGMAX && NCB <= 2) { // (few_documents)
+                if (p.unit_per_chunk == 1)
+                    return go(std::integral_constant<int, 1>{});
+                if (p.unit_per_chunk == 4)
+                    return go(std::integral_constant<int, 4>{});
+            }
+            return go(std::integral_constant<int, 2>{});
         }
         return hipErrorInvalidValue;
     }

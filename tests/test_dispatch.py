@@ -123,6 +123,17 @@ def test_fp32_and_narrow_rows_keep_three_blocks(routes):
         assert routes([call])[0].shape == want, call
 
 
+# n queries of l_q tokens on as many documents, winners wanted -> kernel and blocks (split) or shape (tile): small batches take a workgroup
+# per document and one or two column blocks, then small column groups, large ones the groups that any other corpus takes
+@pytest.mark.parametrize("n,l_q,tokens,ragged,want", [(16, 32, 128, 0, ("split", 1)), (16, 64, 500, 0, ("split", 2)), (33, 32, 208, 1, ("split", 1)), (50, 32, 1024, 0, ("tile", 43)),
+                                                      (64, 32, 188, 1, ("tile", 81)), (128, 32, 500, 0, ("tile", 8)), (256, 32, 1024, 0, ("tile", 8)), (8, 300, 300, 0, ("tile", 43)),
+                                                      (12, 256, 1030, 0, ("tile", 81)), (8, 1030, 300, 0, ("tile", 83))])
+def test_few_documents_with_argmax(routes, n, l_q, tokens, ragged, want):
+    call = Call(BF16, 128, n, l_q, n, n * tokens, ragged, 1)
+    assert (routes([call])[0].kind, routes([call])[0].shape) == want, call
+    assert routes([call._replace(dtype=F32, d=64)])[0].kind == routes([call._replace(argmax=0)])[0].kind == "tile"
+
+
 def test_every_shape_is_reached_and_no_other(routes):
     """dispatch_tile and launch_stream instantiate exactly what forward_launch asks for."""
     calls = [Call(dt, row // (4 if dt == F32 else 2), n_q, l_q, b, b * t, ragged, am)

@@ -303,6 +303,19 @@ def test_wide_16x16_results(n_q, l_q, longest, dtype, d):
     forward_parity_ragged(Q, W.unit_rows((int(lens.sum()), d), dtype, 63, DEV), off, M.maxsim_forward_ragged, False, 1e-5)
 
 
+# Many queries on few documents with winners: a workgroup of one, two or four wavefronts per document and one or two column blocks, or
+# small column groups of the tile kernel; a last group that is not full, documents of fewer tiles than wavefronts, empty ones
+@pytest.mark.parametrize("dtype,d", [("f16", 128), ("bf16", 64)])
+@pytest.mark.parametrize("n_q,l_q,b,longest", [(16, 32, 16, 129), (17, 20, 3, 1000), (5, 64, 9, 400), (16, 50, 5, 33), (33, 32, 33, 333), (50, 17, 41, 100), (61, 32, 70, 60),
+                                               (23, 40, 90, 200), (9, 300, 8, 200), (7, 250, 13, 500), (90, 24, 80, 277)])
+def test_many_queries_on_few_documents(n_q, l_q, b, longest, dtype, d):
+    lens = np.random.default_rng(longest + l_q).integers(0, longest + 1, b)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV)
+    Q = W.unit_rows((n_q, l_q, d), dtype, 64, DEV)
+    forward_parity_ragged(Q, W.unit_rows((int(lens.sum()), d), dtype, 63, DEV), off, M.maxsim_forward_ragged, True, RTOL_16)
+    forward_parity_uniform(Q, W.unit_rows((b, longest, d), dtype, 65, DEV), M.maxsim_forward, True, RTOL_16)
+
+
 # Rows of a single slab (d = 32 in 16 bits): one barrier per macro tile, so that with short documents the loads run up to three
 # documents ahead and the merge and the sum of one document fall into the next two.  Several documents per workgroup, a few of
 # them empty, in the shapes for 1 to 8 column blocks and for every height of the macro tiles
