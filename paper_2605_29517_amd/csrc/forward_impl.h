@@ -506,7 +506,7 @@ __global__ void __launch_bounds__(lin_waves<DT>() * 64) fwd_stream_lin_kernel(Fw
 // With many queries on few documents (few_documents in forward.hip; there one to four wavefronts) a document has a workgroup
 // per column group of NCB blocks: latency and start-up bound it, 16 queries x 16 documents of 128 / 1024 tokens take 4.2 / 8.6 us
 // where a workgroup of fwd_tile_kernel per document takes 10.0 / 32.7.
-template <int DT, int NCB, bool ARGMAX, int W>
+template <int DT, int NCB, bool ARGMAX, int W, bool GROUPS>
 __global__ void __launch_bounds__(W * 64) fwd_stream_split_kernel(FwdParams p, OffsetsPtr off)
 {
     using TR = Traits<DT>;
@@ -521,10 +521,13 @@ __global__ void __launch_bounds__(W * 64) fwd_stream_split_kernel(FwdParams p, O
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     char *lds = lds_all[w];
 
-    // a document's column groups are neighbours on one XCD
-    const int v = p.n_groups == 1 ? (int)blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x);
-    const int group = p.n_groups == 1 ? 0 : v % p.n_groups;
-    const int first = p.n_groups == 1 ? v : v / p.n_groups, step = p.n_groups == 1 ? (int)gridDim.x : (int)gridDim.x / p.n_groups;
+    int group = 0, first = (int)blockIdx.x, step = (int)gridDim.x;
+    if (GROUPS) { // a document's column groups are neighbours on one XCD
+        const int v = xcd_grouped(blockIdx.x, gridDim.x);
+        group = v % p.n_groups;
+        first = v / p.n_groups;
+        step = (int)gridDim.x / p.n_groups;
+    }
     const int gb0 = group * NCB; // (whole queries)
     StreamState<DT, NCB, ARGMAX> st;
 #pragma unroll
@@ -605,6 +608,128 @@ __global__ void __launch_bounds__(W * 64) fwd_stream_split_kernel(FwdParams p, O
             stream_finish(p, st, gb0, doc, len, lane, rho, h);
         }
         __syncthreads(); // the tiles are overwritten by the next document
+    }
+}
+
+// The same for fp32 rows of 512 bytes and queries of one or two column blocks.  A tile takes a wavefront's matrix core 1.7 us,
+// so the even use of the SIMDs counts: W * C wavefronts share a document, wavefront (x, c) takes every W-th tile against column
+// block c.  Operands come from LDS chunk by chunk, which leaves the registers of a tile in flight.  What bounds it: the chain of
+// a document's tiles (6.8 us of MFMAs for 128 tokens) behind a launch and two loads; two tiles in flight were 5-15 % slower.
+template <bool ARGMAX, int W, int C>
+__global__ void __launch_bounds__(W * C * 64, 2) fwd_f32_split_kernel(FwdParams p, OffsetsPtr off)
+{
+    constexpr int F = fmt(MAXSIM_F32, 16);
+    using TR = Traits<F>;
+    using LT = LdsTile<F>;
+    constexpr int NU = TR::NU;
+    constexpr int CPR = TR::ROW_BYTES / 16; // 16-byte chunks (= lanes) per row
+    constexpr int RPI = 64 / CPR;           // rows per load instruction
+    __shared__ __attribute__((aligned(16))) char lds_all[W * C][LT::BYTES];
+    __shared__ float part[2][C];
+    const int lane = threadIdx.x & 63;
+    const int rho = lane & 31, h = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int x = w / C, c = w % C;
+    char *lds = lds_all[w];
+
+    uint4 qf[NU];
+    bool col_valid;
+    load_q_block<F>(p, c, rho, h, qf, col_valid);
+    const int lrow = lane / CPR, lcol = (lane % CPR) * 16;
+    const int st_off = lrow * LT::ROW_STRIDE + lcol;
+    const int rd_off = rho * LT::ROW_STRIDE + h * 16;
+    int par = 0;
+    for (int doc = blockIdx.x; doc < p.b; doc += gridDim.x) {
+        int64_t start;
+        int len;
+        if (p.offsets) {
+            start = clamp_offset(off[doc], 0, p.total_tokens);
+            len = (int)(clamp_offset(off[doc + 1], start, p.total_tokens) - start);
+        } else {
+            start = (int64_t)doc * p.l_d;
+            len = p.l_d;
+        }
+        if (len <= 0) {
+            write_empty_docs(p, doc, doc + 1, threadIdx.x, W * C * 64);
+            continue;
+        }
+        const char *base = p.D + start * TR::ROW_BYTES + lcol;
+        uint4 g[NU];
+        auto load_lin = [&](int t0) { // rows past the document's end repeat its last token
+#pragma unroll
+            for (int i = 0; i < NU; ++i) {
+                const int row = min(t0 + i * RPI + lrow, len - 1);
+                g[i] = load_stream16(base + (int64_t)row * TR::ROW_BYTES);
+            }
+        };
+        float m = neg_inf();
+        int idx = 0;
+        int t0 = x * TILE_ROWS;
+        if (t0 < len) {
+            load_lin(t0);
+            for (;;) {
+#pragma unroll
+                for (int i = 0; i < NU; ++i)
+                    *reinterpret_cast<uint4 *>(&lds[st_off + i * RPI * LT::ROW_STRIDE]) = g[i];
+                const int next = t0 + W * TILE_ROWS;
+                if (next < len)
+                    load_lin(next);
+                uint4 a[4]; // (a ring: three chunks ahead)
+                auto read = [&](int u) { a[u & 3] = *reinterpret_cast<const uint4 *>(&lds[rd_off + u * 32]); };
+                f32x16 acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    acc[r] = 0.0f;
+                read(0);
+                read(1);
+                read(2);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    if (u + 3 < NU)
+                        read(u + 3);
+                    TR::mma(a[u & 3], qf[u], acc);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                fold_tile<ARGMAX>(acc, m, idx, t0, h);
+                if (next >= len)
+                    break;
+                t0 = next;
+            }
+        }
+        if constexpr (W > 1) { // the maxima take the place of the wavefront's own tile
+            float *mine = reinterpret_cast<float *>(lds);
+            mine[lane] = m;
+            mine[64 + lane] = __int_as_float(idx);
+            __syncthreads();
+            if (x == 0) {
+#pragma unroll
+                for (int y = 1; y < W; ++y) {
+                    const float *other = reinterpret_cast<const float *>(lds_all[y * C + c]);
+                    const float mo = other[lane];
+                    if (ARGMAX) {
+                        const int io = __float_as_int(other[64 + lane]);
+                        const bool take = mo > m || (mo == m && io < idx); // of equal maxima the lower row
+                        idx = take ? io : idx;
+                    }
+                    m = fmaxf(m, mo);
+                }
+            }
+        }
+        if (x == 0) {
+            const float sum = finish_block<ARGMAX>(p, m, idx, col_valid, c, doc, len, rho, h);
+            if (C == 1 || p.bpq == 1) {
+                if (lane == 0 && c / p.bpq < p.n_q)
+                    p.scores[(int64_t)c * p.ld + doc] = sum;
+            } else if (lane == 0) {
+                part[par][c] = sum;
+            }
+        }
+        if constexpr (W > 1 || C > 1)
+            __syncthreads(); // (also: the tiles are overwritten by the next document)
+        if (C == 2 && p.bpq == 2 && threadIdx.x == 0)
+            p.scores[doc] = part[par][0] + part[par][C - 1];
+        par ^= 1;
     }
 }
 
@@ -1429,21 +1554,44 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
 template <int DT, int NCB, bool ARGMAX>
 static hipError_t launch_stream(FwdParams p, int grid, hipStream_t stream)
 {
-    if (p.n_chunks == 0) { // a workgroup of unit_per_chunk wavefronts per document (not with two blocks of 512-byte rows) and qpg queries
-        if constexpr (Traits<DT>::NU <= 8 || NCB == 1) {
-            p.n_groups = (p.n_q + p.qpg - 1) / p.qpg;
+    if constexpr (Traits<DT>::NU == 16 && Traits<DT>::DT == MAXSIM_F32) {
+        // fp32 rows of 512 bytes, up to 64 documents per CU: fwd_f32_split_kernel, with two blocks where documents are short or
+        // few (a wavefront that holds both reads a tile once: 64 tokens x 1000 x 128 28.0 us there, 31.6 here).  More wavefronts per
+        // document where there are fewer documents than SIMDs.  us, before -> now: 32 tokens x 1000 x 128 19.2 -> 17.3, x 300 x 300
+        // 26.8 -> 22.1, 20 x 1000 x 40 24.4 -> 9.6, x 200 x 30 15.8 -> 5.0, 62 x 209 x 64 21.2 -> 7.3, 60 x 1000 x 30 26.4 -> 12.0.
+        const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b;
+        if (p.n_groups == 1 && p.b <= 64 * 256 && (NCB == 1 || mean_len < 4 * TILE_ROWS || p.b <= 512)) {
+            const int64_t waves = p.b * NCB, tiles = (mean_len + TILE_ROWS - 1) / TILE_ROWS;
             auto go = [&](auto w) {
                 constexpr int W = decltype(w)::value;
-                hipLaunchKernelGGL((fwd_stream_split_kernel<DT, NCB, ARGMAX, W>), dim3(grid * p.n_groups), dim3(W * 64), 0, stream, p, p.offsets);
+                hipLaunchKernelGGL((fwd_f32_split_kernel<ARGMAX, W, NCB>), dim3((unsigned)p.b), dim3(W * NCB * 64), 0, stream, p, p.offsets);
+                return hipGetLastError();
+            };
+            if (tiles >= 4 && waves <= 640)
+                return go(std::integral_constant<int, 4>{});
+            if (tiles >= 2 && waves <= 512)
+                return go(std::integral_constant<int, 2>{});
+            return go(std::integral_constant<int, 1>{});
+        }
+    }
+    if (p.n_chunks == 0) { // a workgroup of unit_per_chunk wavefronts per document and qpg queries
+        if constexpr (Traits<DT>::NU <= 8 || (NCB == 1 && Traits<DT>::DT != MAXSIM_F32)) {
+            p.n_groups = (p.n_q + p.qpg - 1) / p.qpg;
+            auto go = [&](auto w, auto groups) {
+                constexpr int W = decltype(w)::value;
+                constexpr bool G = decltype(groups)::value;
+                hipLaunchKernelGGL((fwd_stream_split_kernel<DT, NCB, ARGMAX, W, G>), dim3(grid * p.n_groups), dim3(W * 64), 0, stream, p, p.offsets);
                 return hipGetLastError();
             };
             if constexpr (Traits<DT>::NU <= 8 && Traits<DT>::DT != MAXSIM_F32 && ARGMAX && NCB <= 2) { // (few_documents)
                 if (p.unit_per_chunk == 1)
-                    return go(std::integral_constant<int, 1>{});
+                    return go(std::integral_constant<int, 1>{}, std::true_type{});
                 if (p.unit_per_chunk == 4)
-                    return go(std::integral_constant<int, 4>{});
+                    return go(std::integral_constant<int, 4>{}, std::true_type{});
+                if (p.n_groups > 1)
+                    return go(std::integral_constant<int, 2>{}, std::true_type{});
             }
-            return go(std::integral_constant<int, 2>{});
+            return go(std::integral_constant<int, 2>{}, std::false_type{});
         }
         return hipErrorInvalidValue;
     }

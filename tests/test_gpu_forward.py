@@ -303,6 +303,19 @@ def test_wide_16x16_results(n_q, l_q, longest, dtype, d):
     forward_parity_ragged(Q, W.unit_rows((int(lens.sum()), d), dtype, 63, DEV), off, M.maxsim_forward_ragged, False, 1e-5)
 
 
+# fp32 rows of 512 bytes, one or two column blocks: one, two and four wavefronts per document and block, documents of fewer tiles than
+# wavefronts, of a single row, empty ones; two queries of one block and one of two
+@pytest.mark.parametrize("want_argmax", [False, True])
+@pytest.mark.parametrize("n_q,l_q", [(1, 32), (1, 7), (2, 20), (1, 33), (1, 64)])
+@pytest.mark.parametrize("b,longest", [(3, 300), (40, 130), (200, 33), (300, 70), (700, 30), (600, 150)])
+def test_fp32_short_queries(b, longest, n_q, l_q, want_argmax):
+    lens = np.random.default_rng(b + l_q).integers(0, longest + 1, b)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).to(DEV)
+    Q = W.unit_rows((n_q, l_q, 128), "f32", 64, DEV)
+    forward_parity_ragged(Q, W.unit_rows((int(lens.sum()), 128), "f32", 63, DEV), off, M.maxsim_forward_ragged, want_argmax, RTOL_F32)
+    forward_parity_uniform(Q, W.unit_rows((b, longest, 128), "f32", 65, DEV), M.maxsim_forward, want_argmax, RTOL_F32)
+
+
 # Many queries on few documents with winners: a workgroup of one, two or four wavefronts per document and one or two column blocks, or
 # small column groups of the tile kernel; a last group that is not full, documents of fewer tiles than wavefronts, empty ones
 @pytest.mark.parametrize("dtype,d", [("f16", 128), ("bf16", 64)])
