@@ -166,8 +166,11 @@ constexpr int DQ_AHEAD = 4; // documents between the rows being gathered and the
 // argmax entries are one 16-byte load and they share the weight).  With 4 the whole grid is resident at once at
 // 8192 query tokens, so the wavefronts of an XCD sweep the partition's documents side by side and a document row
 // that one group brought into the L2 is found there by the others.
+//
+// Adds documents [j0, j1), at least one, to the sums of the group's tokens n0 .. n0 + TPG - 1; `wave`: which of the
+// partition's wavefronts.
 template <int DT, int TPG>
-__global__ void __launch_bounds__(256) bwd_dq_kernel(BwdParams p, float *out, int n_part, int64_t docs_per_part)
+__device__ __forceinline__ void dq_gather(const BwdParams &p, int64_t n0, int64_t j0, int64_t j1, int64_t wave, float (&acc)[TPG][8])
 {
     constexpr int EB = Elem<DT>::BYTES;
     constexpr int U = DT == MAXSIM_F32 ? 4 : 8; // document rows per batch of loads (two batches in flight)
@@ -175,143 +178,149 @@ __global__ void __launch_bounds__(256) bwd_dq_kernel(BwdParams p, float *out, in
     static_assert(TPG == 1 || TPG == 4, "tokens per group");
     static_assert(DPB * TPG == U, "a batch holds whole documents");
     const int lane = threadIdx.x & 63;
-    const int grp = lane >> 4; // which of the wavefront's four groups
     const int c = lane & 15;   // which 8 columns of the slab
+    const int64_t nql = (int64_t)p.n_q * p.l_q;
+    const int col = (int)blockIdx.y * SLAB + c * 8;
+    const int64_t row_bytes = (int64_t)p.d * EB;
+    const char *Dcol = p.D + (int64_t)(col < p.d ? col : 0) * EB; // lanes past the row's end re-read its first columns
+    const int64_t nn = n0 < nql ? n0 : nql - TPG; // a group past the last token repeats the last one (nothing is stored)
+    const int q = (int)(nn / p.l_q);
+    const int i = (int)(nn - (int64_t)q * p.l_q);
+    const int32_t *Aq = p.A + (int64_t)q * p.b * p.l_q + i; // A[q, 0, i]
+    const float *gq = p.g + (int64_t)q * p.b;               // g[q, 0]
+    // Lane c of a group fetches, for document jb + c, the winning tokens and the weight and turns them into the
+    // rows' offsets in D (in units of 16 bytes: D is below 64 GiB, checked by the caller; the offset of a row that
+    // is not to be added is that of row 0) and a weight that is 0 where nothing is added; the group then takes
+    // them from each other's registers (a swizzle inside each half of the wavefront), so that one memory round trip
+    // brings the indices of 16 documents and a row costs a lane exchange or two, one address add, its load and
+    // its eight multiply-adds.
+    const uint32_t row16 = (uint32_t)(row_bytes >> 4);
+    uint32_t o[TPG];
+    float g;
+    auto fetch = [&](int64_t jb) {
+        const bool in = jb + c < j1;
+        const int64_t j = in ? jb + c : j1 - 1;
+        int64_t first;
+        int len;
+        if (p.offsets) {
+            first = p.offsets[j];
+            len = p.offsets[j + 1] - (int)first;
+        } else {
+            first = j * p.l_d;
+            len = p.l_d;
+        }
+        int tt[TPG];
+        if constexpr (TPG == 4) {
+            const int4 v = *reinterpret_cast<const int4 *>(Aq + j * p.l_q);
+            tt[0] = v.x;
+            tt[1] = v.y;
+            tt[2] = v.z;
+            tt[3] = v.w;
+        } else {
+            tt[0] = Aq[j * p.l_q];
+        }
+        const float gv = gq[j];
+        g = in ? gv : 0.0f;
+#pragma unroll
+        for (int t = 0; t < TPG; ++t) {
+            // also guards bad offsets; the row's weight is the document's unless the row is row 0 by default
+            const bool ok = tt[t] >= 0 && tt[t] < len && first >= 0 && first + tt[t] < p.total_tokens;
+            o[t] = ok ? (uint32_t)(first + tt[t]) * row16 : 0xffffffffu;
+        }
+    };
+    // With four tokens per group the whole grid is resident and the wavefronts of a partition walk its documents
+    // side by side, so (uniform corpora) they also read the documents a few steps ahead in order, one kilobyte
+    // per wavefront and step (wavefront k of the partition the k-th kilobyte of the step's DPB documents): most
+    // rows then reach the XCD's L2 as part of a stream before they are gathered.  It changes no time that could be
+    // measured (the gathers are bound by the L2's delivery rate, not by HBM) but takes a quarter off the traffic
+    // between the L2s and the fabric (137 -> 106 MB at 256 x 256 x 1024).
+    const bool ahead = TPG == 4 && !p.offsets;
+    const int64_t step_bytes = (int64_t)DPB * p.l_d * row_bytes;
+    const char *t_safe = p.D + j0 * p.l_d * row_bytes;    // a valid address of the partition
+    const char *t_lim = p.D + j1 * p.l_d * row_bytes - 16; // last 16 bytes of the partition
+    int64_t t_at = wave * 1024 + lane * 16;
+    const char *tp = t_safe + (int64_t)DQ_AHEAD * p.l_d * row_bytes + (t_at < step_bytes - 16 ? t_at : step_bytes - 16);
+    auto touch = [&]() {
+        const char *at = (ahead && tp <= t_lim) ? tp : t_safe;
+        tp += step_bytes;
+        return *reinterpret_cast<const uint4 *>(at);
+    };
+    fetch(j0);
+    for (int64_t jb = j0; jb < j1; jb += DQ_SB) {
+        uint32_t co[TPG];
+#pragma unroll
+        for (int t = 0; t < TPG; ++t)
+            co[t] = o[t];
+        const float cg = g;
+        fetch(jb + DQ_SB); // the next 16 documents' indices travel while these documents' rows do
+        Raw8 raw[2][U];
+        float gc[2][U];
+        auto issue = [&](auto batch_tag, Raw8(&dst)[U], float(&w)[U]) {
+            constexpr int m0 = decltype(batch_tag)::value * DPB;
+            static_for<0, U>([&](auto u_tag) {
+                constexpr int u = decltype(u_tag)::value;
+                constexpr int t = u % TPG;
+                constexpr int m = m0 + u / TPG;
+                // ds_swizzle, bit mode (and_mask | or_mask << 5 | xor_mask << 10 on the lane id inside each half of
+                // the wavefront): keep which group of sixteen, take lane m of it
+                constexpr int pat = 0x10 | ((m & 15) << 5);
+                const uint32_t off16 = (uint32_t)__builtin_amdgcn_ds_swizzle((int)co[t], pat);
+                const float gg = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(cg), pat));
+                w[u] = off16 == 0xffffffffu ? 0.0f : gg;
+                load_raw8<DT>(Dcol + ((uint64_t)(off16 == 0xffffffffu ? 0u : off16) << 4), dst[u]);
+            });
+        };
+        auto consume = [&](const Raw8(&src)[U], const float(&w)[U]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float v[8];
+                decode8<DT>(src[u], v);
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    acc[u % TPG][k] = fmaf(w[u], v[k], acc[u % TPG][k]);
+            }
+        };
+        // batches of DPB documents, two in flight; documents past the partition carry weight 0 (their rows are
+        // the last document's)
+        constexpr int NBATCH = DQ_SB / DPB;
+        issue(std::integral_constant<int, 0>(), raw[0], gc[0]);
+        static_for<0, NBATCH>([&](auto b_tag) {
+            constexpr int bi = decltype(b_tag)::value;
+            uint4 touched = make_uint4(0, 0, 0, 0);
+            if constexpr (TPG == 4)
+                touched = touch();
+            if constexpr (bi + 1 < NBATCH)
+                issue(std::integral_constant<int, bi + 1>(), raw[(bi + 1) & 1], gc[(bi + 1) & 1]);
+            consume(raw[bi & 1], gc[bi & 1]);
+            if constexpr (TPG == 4)
+                asm volatile("" ::"v"(touched.x), "v"(touched.y), "v"(touched.z), "v"(touched.w)); // the load is the point
+        });
+    }
+}
+
+template <int DT, int TPG>
+__global__ void __launch_bounds__(256) bwd_dq_kernel(BwdParams p, float *out, int n_part, int64_t docs_per_part)
+{
+    const int lane = threadIdx.x & 63;
+    const int grp = lane >> 4; // which of the wavefront's four groups
     const int part = (int)(blockIdx.x % (unsigned)n_part);
     const int64_t wave = (int64_t)(blockIdx.x / (unsigned)n_part) * 4 + (threadIdx.x >> 6);
     const int64_t nql = (int64_t)p.n_q * p.l_q;
     if (wave * 4 * TPG >= nql)
         return;
     const int64_t n0 = (wave * 4 + grp) * TPG; // the group's first query token
-    const int col = (int)blockIdx.y * SLAB + c * 8;
-    const bool col_ok = col < p.d;
-    const int64_t row_bytes = (int64_t)p.d * EB;
-    const char *Dcol = p.D + (int64_t)(col_ok ? col : 0) * EB; // lanes past the row's end re-read its first columns
+    const int col = (int)blockIdx.y * SLAB + (lane & 15) * 8;
     const int64_t j0 = (int64_t)part * docs_per_part;
     const int64_t j1 = j0 + docs_per_part < p.b ? j0 + docs_per_part : p.b;
-    const int64_t nn = n0 < nql ? n0 : nql - TPG; // a group past the last token repeats the last one (nothing is stored)
-    const int q = (int)(nn / p.l_q);
-    const int i = (int)(nn - (int64_t)q * p.l_q);
-    const int32_t *Aq = p.A + (int64_t)q * p.b * p.l_q + i; // A[q, 0, i]
-    const float *gq = p.g + (int64_t)q * p.b;               // g[q, 0]
-
     float acc[TPG][8];
 #pragma unroll
     for (int t = 0; t < TPG; ++t)
 #pragma unroll
         for (int k = 0; k < 8; ++k)
             acc[t][k] = 0.0f;
-    if (j0 < j1) {
-        // Lane c of a group fetches, for document jb + c, the winning tokens and the weight and turns them into the
-        // rows' offsets in D (in units of 16 bytes: D is below 64 GiB, checked by the caller; the offset of a row that
-        // is not to be added is that of row 0) and a weight that is 0 where nothing is added; the group then takes
-        // them from each other's registers (a swizzle inside each half of the wavefront), so that one memory round trip
-        // brings the indices of 16 documents and a row costs a lane exchange or two, one address add, its load and
-        // its eight multiply-adds.
-        const uint32_t row16 = (uint32_t)(row_bytes >> 4);
-        uint32_t o[TPG];
-        float g;
-        auto fetch = [&](int64_t jb) {
-            const bool in = jb + c < j1;
-            const int64_t j = in ? jb + c : j1 - 1;
-            int64_t first;
-            int len;
-            if (p.offsets) {
-                first = p.offsets[j];
-                len = p.offsets[j + 1] - (int)first;
-            } else {
-                first = j * p.l_d;
-                len = p.l_d;
-            }
-            int tt[TPG];
-            if constexpr (TPG == 4) {
-                const int4 v = *reinterpret_cast<const int4 *>(Aq + j * p.l_q);
-                tt[0] = v.x;
-                tt[1] = v.y;
-                tt[2] = v.z;
-                tt[3] = v.w;
-            } else {
-                tt[0] = Aq[j * p.l_q];
-            }
-            const float gv = gq[j];
-            g = in ? gv : 0.0f;
-#pragma unroll
-            for (int t = 0; t < TPG; ++t) {
-                // also guards bad offsets; the row's weight is the document's unless the row is row 0 by default
-                const bool ok = tt[t] >= 0 && tt[t] < len && first >= 0 && first + tt[t] < p.total_tokens;
-                o[t] = ok ? (uint32_t)(first + tt[t]) * row16 : 0xffffffffu;
-            }
-        };
-        // With four tokens per group the whole grid is resident and the wavefronts of a partition walk its documents
-        // side by side, so (uniform corpora) they also read the documents a few steps ahead in order, one kilobyte
-        // per wavefront and step (wavefront k of the partition the k-th kilobyte of the step's DPB documents): most
-        // rows then reach the XCD's L2 as part of a stream before they are gathered.  It changes no time that could be
-        // measured (the gathers are bound by the L2's delivery rate, not by HBM) but takes a quarter off the traffic
-        // between the L2s and the fabric (137 -> 106 MB at 256 x 256 x 1024).
-        const bool ahead = TPG == 4 && !p.offsets;
-        const int64_t step_bytes = (int64_t)DPB * p.l_d * row_bytes;
-        const char *t_safe = p.D + j0 * p.l_d * row_bytes;    // a valid address of the partition
-        const char *t_lim = p.D + j1 * p.l_d * row_bytes - 16; // last 16 bytes of the partition
-        int64_t t_at = (wave % ((int64_t)(gridDim.x / (unsigned)n_part) * 4)) * 1024 + lane * 16;
-        const char *tp = t_safe + (int64_t)DQ_AHEAD * p.l_d * row_bytes + (t_at < step_bytes - 16 ? t_at : step_bytes - 16);
-        auto touch = [&]() {
-            const char *at = (ahead && tp <= t_lim) ? tp : t_safe;
-            tp += step_bytes;
-            return *reinterpret_cast<const uint4 *>(at);
-        };
-        fetch(j0);
-        for (int64_t jb = j0; jb < j1; jb += DQ_SB) {
-            uint32_t co[TPG];
-#pragma unroll
-            for (int t = 0; t < TPG; ++t)
-                co[t] = o[t];
-            const float cg = g;
-            fetch(jb + DQ_SB); // the next 16 documents' indices travel while these documents' rows do
-            Raw8 raw[2][U];
-            float gc[2][U];
-            auto issue = [&](auto batch_tag, Raw8(&dst)[U], float(&w)[U]) {
-                constexpr int m0 = decltype(batch_tag)::value * DPB;
-                static_for<0, U>([&](auto u_tag) {
-                    constexpr int u = decltype(u_tag)::value;
-                    constexpr int t = u % TPG;
-                    constexpr int m = m0 + u / TPG;
-                    // ds_swizzle, bit mode (and_mask | or_mask << 5 | xor_mask << 10 on the lane id inside each half of
-                    // the wavefront): keep which group of sixteen, take lane m of it
-                    constexpr int pat = 0x10 | ((m & 15) << 5);
-                    const uint32_t off16 = (uint32_t)__builtin_amdgcn_ds_swizzle((int)co[t], pat);
-                    const float gg = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(cg), pat));
-                    w[u] = off16 == 0xffffffffu ? 0.0f : gg;
-                    load_raw8<DT>(Dcol + ((uint64_t)(off16 == 0xffffffffu ? 0u : off16) << 4), dst[u]);
-                });
-            };
-            auto consume = [&](const Raw8(&src)[U], const float(&w)[U]) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    float v[8];
-                    decode8<DT>(src[u], v);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        acc[u % TPG][k] = fmaf(w[u], v[k], acc[u % TPG][k]);
-                }
-            };
-            // batches of DPB documents, two in flight; documents past the partition carry weight 0 (their rows are
-            // the last document's)
-            constexpr int NBATCH = DQ_SB / DPB;
-            issue(std::integral_constant<int, 0>(), raw[0], gc[0]);
-            static_for<0, NBATCH>([&](auto b_tag) {
-                constexpr int bi = decltype(b_tag)::value;
-                uint4 touched = make_uint4(0, 0, 0, 0);
-                if constexpr (TPG == 4)
-                    touched = touch();
-                if constexpr (bi + 1 < NBATCH)
-                    issue(std::integral_constant<int, bi + 1>(), raw[(bi + 1) & 1], gc[(bi + 1) & 1]);
-                consume(raw[bi & 1], gc[bi & 1]);
-                if constexpr (TPG == 4)
-                    asm volatile("" ::"v"(touched.x), "v"(touched.y), "v"(touched.z), "v"(touched.w)); // the load is the point
-            });
-        }
-    }
-    if (col_ok) {
+    if (j0 < j1)
+        dq_gather<DT, TPG>(p, n0, j0, j1, wave, acc);
+    if (col < p.d) {
 #pragma unroll
         for (int t = 0; t < TPG; ++t) {
             if (n0 + t < nql) {
@@ -536,9 +545,22 @@ __device__ __forceinline__ void walk_rows(__amdgpu_buffer_rsrc_t rsrc, uint32_t 
     ry[s_now] = ay;
 }
 
+// seg and hist live from the filter to the placement, list and start from the placement to the end of the walk;
+// the weights staged during the walk reuse the first words of the wavefront's own seg row (dead by then).
+template <int RPW, int W> struct DdLds {
+    static constexpr int R = W * RPW;      // rows of the block
+    static constexpr int SEG = DW_COL / W; // entries each wavefront filters per round
+    static_assert(SEG >= 128, "a wavefront's staged weights fit in its seg row");
+    uint32_t seg[W][SEG];  // per filtering wavefront: kept entries, (number in round) | row << 16
+    uint16_t list[DW_COL]; // entry numbers by key (= owner wavefront * RPW + slot), in entry order
+    int hist[W][R];        // per filtering wavefront: entries per block row, then write cursors
+    int start[R + 1];      // list of key k: list[start[k] .. start[k + 1])
+};
+
+// Workgroup `id` of the grid that `order` describes
 template <int DT, int RPW, int W>
-__global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr off, Magic lq_magic, Magic ld_magic, int dq64,
-                                                        int di64, BlockOrder order)
+__device__ __forceinline__ void dd_block(const BwdParams &p, OffsetsPtr off, Magic lq_magic, Magic ld_magic, int dq64, int di64, BlockOrder order, unsigned id,
+                                         uint32_t (&seg)[W][DW_COL / W], uint16_t (&list)[DW_COL], int (&hist)[W][W * RPW], int (&start)[W * RPW + 1])
 {
     constexpr int R = W * RPW;          // rows of the block
     constexpr int WBITS = W == 16 ? 4 : 3;
@@ -548,17 +570,10 @@ __global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr 
     static_assert(RPW == 16 || RPW == 8 || RPW == 4, "rows per wavefront");
     static_assert(W == 8 || W == 16, "wavefronts per workgroup");
     constexpr int EB = Elem<DT>::BYTES;
-    // seg and hist live from the filter to the placement, list and start from the placement to the end of the walk;
-    // the weights staged during the walk reuse the first words of the wavefront's own seg row (dead by then).
-    static_assert(SEG >= 128, "a wavefront's staged weights fit in its seg row");
-    __shared__ __attribute__((aligned(16))) uint32_t seg[W][SEG]; // per filtering wavefront: kept entries, (number in round) | row << 16
-    __shared__ uint16_t list[DW_COL];          // entry numbers by key (= owner wavefront * RPW + slot), in entry order
-    __shared__ int hist[W][R];          // per filtering wavefront: entries per block row, then write cursors
-    __shared__ int start[R + 1];               // list of key k: list[start[k] .. start[k + 1])
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int blk = ordered_block(order, blockIdx.x);
+    const int blk = ordered_block(order, id);
     if (blk < 0)
         return;
     const int64_t row0 = (int64_t)blk * R;
@@ -773,6 +788,56 @@ __global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr 
     }
 }
 
+template <int DT, int RPW, int W>
+__global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr off, Magic lq_magic, Magic ld_magic, int dq64, int di64, BlockOrder order)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t seg[W][DW_COL / W];
+    __shared__ uint16_t list[DW_COL];
+    __shared__ int hist[W][W * RPW];
+    __shared__ int start[W * RPW + 1];
+    dd_block<DT, RPW, W>(p, off, lq_magic, ld_magic, dq64, di64, order, blockIdx.x, seg, list, hist, start);
+}
+
+// Both gradients in one launch, for small batches, where a launch and its start cost as much as the work: the first n_dq
+// workgroups (a multiple of eight, so that the others keep their XCDs) take four query tokens of dQ each, wavefront k adding the documents of
+// partition k, and add the partial sums up in LDS in partition order: the bits of bwd_dq_kernel and bwd_dq_combine_kernel,
+// without the detour through dD that keeps those from running beside the dD kernel.  n queries of 32 tokens x n documents, us in
+// a graph: n = 16 x 128 tokens 12.5 -> 7.3, 33 x 83-333 18.9 -> 13.0, 64 x 75-300 24.8 -> 20.0, 80 x 1024 38.1 -> 34.6.
+template <int DT, int RPW>
+__global__ void __launch_bounds__(DD_WAVES * 64) bwd_both_kernel(BwdParams p, OffsetsPtr off, Magic lq_magic, Magic ld_magic, int dq64, int di64, BlockOrder order, unsigned n_dq,
+                                                                 int n_part, int64_t docs_per_part)
+{
+    __shared__ __attribute__((aligned(16))) DdLds<RPW, DD_WAVES> lds;
+    if (blockIdx.x >= n_dq) {
+        dd_block<DT, RPW, DD_WAVES>(p, off, lq_magic, ld_magic, dq64, di64, order, blockIdx.x - n_dq, lds.seg, lds.list, lds.hist, lds.start);
+        return;
+    }
+    constexpr int TOKENS = 4; // one per group of sixteen lanes
+    static_assert(sizeof(lds.seg) >= DD_WAVES * TOKENS * SLAB * sizeof(float) && DD_WAVES * 64 == TOKENS * SLAB, "partial sums in LDS, one sum per thread");
+    float *part = reinterpret_cast<float *>(&lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t nql = (int64_t)p.n_q * p.l_q, first = (int64_t)blockIdx.x * TOKENS;
+    if (first >= nql)
+        return;
+    const int64_t j0 = (int64_t)w * docs_per_part;
+    const int64_t j1 = j0 + docs_per_part < p.b ? j0 + docs_per_part : p.b;
+    float acc[1][8] = {};
+    if (w < n_part && j0 < j1)
+        dq_gather<DT, 1>(p, first + (lane >> 4), j0, j1, 0, acc);
+    float4 *mine = reinterpret_cast<float4 *>(part + (w * TOKENS + (lane >> 4)) * SLAB + (lane & 15) * 8);
+    mine[0] = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
+    mine[1] = make_float4(acc[0][4], acc[0][5], acc[0][6], acc[0][7]);
+    __syncthreads();
+    float sum = part[tid];
+    for (int k = 1; k < n_part; ++k)
+        sum += part[k * (TOKENS * SLAB) + tid];
+    const int64_t n = first + tid / SLAB;
+    const int col = (int)blockIdx.y * SLAB + tid % SLAB;
+    if (n < nql && col < p.d)
+        p.dQ[n * p.d + col] = sum;
+}
+
 // The partial sums of dQ live in the dD buffer until the dD kernel overwrites it (dD is an output that the call
 // fully overwrites, and its n_part * n_q * l_q rows of d floats are free until then), so the library needs no
 // scratch memory.  n_part = the largest power of two <= 8 that fits there and leaves every partition a document.
@@ -816,9 +881,6 @@ template <int DT> static hipError_t launch_dq(const BwdParams &p, hipStream_t st
 
 template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, hipStream_t stream)
 {
-    hipError_t e = launch_dq<DT>(p, stream);
-    if (e != hipSuccess)
-        return e;
     // Rows per block.  Every block filters the argmax columns of its documents, so halving the blocks doubles that work;
     // but fewer than four blocks per CU leave some CUs with more of them than others, and a block that spans two
     // documents takes twice as long.  So, with documents of several blocks, blocks of 128 rows also where they fill a
@@ -840,6 +902,23 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
     const bool by64 = n64 >= 4 * cus || (several && n64 * 5 >= 8 * cus && n64 * 10 >= (n64 + cus - 1) / cus * cus * 7);
     const Magic lq_magic = magic_u31((uint32_t)p.l_q);
     const unsigned slabs = (unsigned)((p.d + SLAB - 1) / SLAB);
+    // Small batches: both gradients in one launch (us in a graph, two launches and a third for the sums -> one: 103 x 24 x 103 documents of 163-653
+    // tokens 39.4 -> 34.0, 180 x 12 46.7 -> 40.2, 64 x 64 x 64 37.4 -> 37.1; not 128 x 32 x 128 x 64 31.0 -> 32.2, 16 x 1000 x 16 x 500 31.5 -> 43.8)
+    if (!by128 && (int64_t)p.n_q * p.l_q <= 4096 && (int64_t)p.n_q * p.l_q * p.b <= 400000) {
+        auto both = [&](auto rpw_tag) {
+            constexpr int RPW = decltype(rpw_tag)::value;
+            const BlockOrder order = block_order((p.total_tokens + DD_WAVES * RPW - 1) / (DD_WAVES * RPW), num_cu);
+            const unsigned n_dq = (unsigned)(((int64_t)p.n_q * p.l_q + 31) / 32) * 8;
+            const int n_part = dq_partitions(p);
+            hipLaunchKernelGGL((bwd_both_kernel<DT, RPW>), dim3(n_dq + order.grid, slabs), dim3(DD_WAVES * 64), 0, stream, p, p.offsets, lq_magic,
+                               magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order, n_dq, n_part, (p.b + n_part - 1) / n_part);
+            return hipGetLastError();
+        };
+        return by64 ? both(std::integral_constant<int, 8>()) : both(std::integral_constant<int, 4>());
+    }
+    hipError_t e = launch_dq<DT>(p, stream);
+    if (e != hipSuccess)
+        return e;
     auto go = [&](auto rpw_tag, auto w_tag) {
         constexpr int RPW = decltype(rpw_tag)::value;
         constexpr int W = decltype(w_tag)::value;
@@ -1406,6 +1485,80 @@ __global__ void __launch_bounds__(1024) ce_loss_kernel(int n, int b, float inv_t
     }
 }
 
+// Butterflies over all 64 lanes on the VALU, the pairs of wave_max and wave_sum in their order: once lanes repeat with period 2N,
+// the lane N away by XOR and the one N away by rotation hold the same value.
+template <typename Op> __device__ __forceinline__ float wave_butterfly(float v, Op op)
+{
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true))); // rotated by 8 in a row of 16
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, true)));
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, true)));
+    return op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, true)));
+}
+
+// Gradient and loss of a small batch in one launch: one workgroup, a wavefront per row at a time, ROWS rows side by side.  The same
+// numbers in the same order as the two kernels above (the row's own number goes through LDS instead of g).  Latency bounds
+// it: in a graph 16 x 16 4.3 -> 2.5 us, 64 x 64 4.8 -> 3.9, and on the host a launch less, 12.0 -> 9.2 a call.
+constexpr int CE_SMALL_ROWS = 64;
+template <int KEEP, int ROWS>
+__global__ void __launch_bounds__(1024) ce_small_kernel(const float *s, int n, int b, float inv_tau, float *g, float *loss)
+{
+    __shared__ float own[16 * ROWS];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const float scale = inv_tau / (float)n;
+    if (w < n) {
+        float v[ROWS][KEEP];
+#pragma unroll
+        for (int x = 0; x < ROWS; ++x) {
+            const float *row = s + (int64_t)(w + 16 * x < n ? w + 16 * x : w) * b;
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k) {
+                const int j = lane + 64 * k;
+                v[x][k] = scaled(row[j < b ? j : b - 1], inv_tau);
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < ROWS; ++x) {
+            const int i = w + 16 * x;
+            float mx = neg_inf(), z = 0.0f, e[KEEP];
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k)
+                mx = lane + 64 * k < b ? fmaxf(mx, v[x][k]) : mx;
+            mx = wave_butterfly(mx, [](float p, float q) { return fmaxf(p, q); });
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k) {
+                e[k] = expf(v[x][k] - mx);
+                z += lane + 64 * k < b ? e[k] : 0.0f;
+            }
+            z = wave_butterfly(z, [](float p, float q) { return p + q; });
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k) {
+                const int j = lane + 64 * k;
+                if (i < n && j < b && j != i)
+                    g[(int64_t)i * b + j] = e[k] / z * scale;
+                if (i < n && j == i)
+                    own[i] = ce_own_pack(v[x][k], mx, z);
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) { // (at most 64 rows: the other wavefronts' sums are zero)
+        float local = 0.0f;
+        if (lane < n) {
+            const CeOwn x = ce_own_unpack(own[lane]);
+            local += x.term;
+            g[(int64_t)lane * b + lane] = (x.p - 1.0f) * scale;
+        }
+        local = wave_butterfly(local, [](float p, float q) { return p + q; });
+        if (lane == 0)
+            *loss = local / (float)n;
+    }
+}
+
 template <bool STASH> static void launch_ce_grad(const float *s, int n, int b, float inv_tau, float *g, hipStream_t stream)
 {
     const dim3 grid((n + 3) / 4), block(256);
@@ -1420,6 +1573,15 @@ template <bool STASH> static void launch_ce_grad(const float *s, int n, int b, f
 hipError_t ce_grad_launch(const float *scores, int n, int b, float tau, float *g, float *loss, hipStream_t stream)
 {
     const float inv_tau = 1.0f / tau;
+    if (loss && n <= CE_SMALL_ROWS && b <= 256) {
+        auto go = [&](auto keep, auto rows) {
+            hipLaunchKernelGGL((ce_small_kernel<decltype(keep)::value, decltype(rows)::value>), dim3(1), dim3(1024), 0, stream, scores, n, b, inv_tau, g, loss);
+            return hipGetLastError();
+        };
+        const std::integral_constant<int, 1> one{};
+        const std::integral_constant<int, 4> four{};
+        return b <= 64 ? (n <= 16 ? go(one, one) : go(one, four)) : n <= 16 ? go(four, one) : go(four, four);
+    }
     if (loss)
         launch_ce_grad<true>(scores, n, b, inv_tau, g, stream);
     else

@@ -349,3 +349,46 @@ def test_ce_grad_of_one_document(value):
     torch.cuda.synchronize()
     for x in (float(g), float(loss)):
         assert x == 0.0 if np.isfinite(value) else np.isnan(x)
+
+
+# Small batches take both gradients in one launch (up to 4096 query tokens and 400 000 edges): the bits of the two kernels that larger
+# ones take, one row either side of the rule, fewer documents than partitions, widths of less than a slab and of two, tokens that fill
+# no workgroup of four; dD as it is, dQ with the documents cut up the same way
+@pytest.mark.parametrize("n_q,l_q,b,l_d,d", [(1, 1, 1, 1, 128), (3, 7, 5, 40, 128), (16, 32, 16, 128, 128), (5, 33, 9, 300, 64), (33, 30, 33, 100, 256), (2, 2048, 7, 70, 128), (2, 2049, 7, 70, 128),
+                                             (100, 32, 125, 20, 128), (100, 32, 126, 20, 128)])
+def test_both_gradients_in_one_launch(n_q, l_q, b, l_d, d):
+    Q = W.unit_rows((n_q, l_q, d), "f16", 3, DEV)
+    D = W.unit_rows((b, l_d, d), "f16", 4, DEV)
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    A = torch.randint(-1, l_d, (n_q, b, l_q), dtype=torch.int32, device=DEV, generator=gen)
+    g = torch.randn(n_q, b, device=DEV, generator=gen)
+    dQ, dD = M.maxsim_backward(Q, D, A, g)
+    torch.cuda.synchronize()
+    rQ, rD = O.backward(W.to_raw_numpy(Q), W.to_raw_numpy(D), "f16", A.cpu().numpy(), g.cpu().numpy().astype(np.float64))
+    for x, r in ((dQ, rQ), (dD, rD)):
+        assert np.abs(x.cpu().numpy() - r).max() <= 1e-4 * max(np.abs(r).max(), 1e-30)
+    cQ, cD, _, _ = M.maxsim_backward_csr(Q, D, A, g)
+    assert torch.equal(dQ, cQ) and torch.equal(dD, cD)
+    off = torch.arange(0, (b + 1) * l_d, l_d, dtype=torch.int32, device=DEV)
+    pQ, pD = M.maxsim_backward_ragged(Q, D.view(-1, d), off, A, g)
+    assert torch.equal(dQ, pQ) and torch.equal(dD.view(-1, d), pD)
+
+
+# One launch up to 64 rows of 256 columns, gradient and loss the bits that the larger kernels give for the same rows
+@pytest.mark.parametrize("n,b", [(1, 1), (2, 64), (15, 65), (16, 256), (17, 17), (33, 64), (64, 64), (64, 256), (64, 257), (65, 65)])
+def test_ce_small_batches(n, b):
+    s = torch.randn(n, b, device=DEV, generator=torch.Generator(device=DEV).manual_seed(n + b)) + 20
+    g, loss = M.maxsim_ce_grad(s, 0.02)
+    rloss, rg = O.ce_grad(s.cpu().numpy().astype(np.float64), 0.02)
+    # score / tau is up to 1250 and rounded (2^-24) after a product with a rounded 1 / tau (2^-24): two of them in a difference are
+    # off by up to 2 * 2 * 1250 * 2^-24 = 3e-4, and so is a softmax, relative to itself, and a row's term of the loss
+    bound = 3e-4
+    assert np.abs(g.cpu().numpy() - rg).max() <= bound / (0.02 * n) and abs(float(loss) - rloss) <= bound + 1e-5 * abs(rloss)
+    g2 = torch.empty_like(g)  # (without a loss: the gradient's own kernel)
+    assert M.load().maxsim_ce_grad(s.data_ptr(), n, b, 0.02, g2.data_ptr(), None, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    off_diagonal = ~torch.eye(n, b, dtype=torch.bool, device=DEV)
+    assert torch.equal(g[off_diagonal], g2[off_diagonal])
+    a = s.clone()
+    _, l2 = M.maxsim_ce_grad(a, 0.02, g=a)  # in place
+    assert torch.equal(a, g) and torch.equal(l2, loss)
