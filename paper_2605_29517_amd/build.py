@@ -1,12 +1,15 @@
-"""Build libmaxsim.so, and libmaxsim_probe.so (the benchmark's diagnostics), HIP for gfx950 only, in-tree with hipcc."""
+"""Build libmaxsim.so, and libmaxsim_probe.so (the benchmark's diagnostics), HIP for gfx950 only, in-tree with hipcc, and
+_marshal.so, the native part of binding.py."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmaxsim.so")
 PROBE_LIB = os.path.join(HERE, "libmaxsim_probe.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["api.hip", "forward.hip", "forward_f16.hip", "forward_bf16.hip", "forward_f32.hip", "forward_argmax.hip", "forward_wide.hip", "forward_wide_f16.hip", "forward_wide_bf16.hip", "forward_wide_f32.hip", "forward_splitd.hip", "backward.hip", "int8.hip", "int8_rows64.hip", "int8_wide.hip"]
 PROBE_SOURCES = ["probe.hip"]
 # packed fp32 VALU forms are switched off on purpose (they have produced wrong results on
@@ -17,6 +20,15 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-fno-honor-nans",
          "-Wall", "-Wno-unused-function"]
 FILE_FLAGS = {"forward_argmax.hip": ["-falign-loops=64"]}  # (the reason is at its top)
+
+
+def marshal_command(out):
+    """The compiler's call for the native part of binding.py, against the installed torch's headers and libraries."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1"]
+            + ["-isystem" + d for d in (os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include", sysconfig.get_paths()["include"])]
+            + [os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"])
 
 
 def build(verbose: bool = False) -> str:
@@ -32,17 +44,20 @@ def build(verbose: bool = False) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    marshal_tmp = MARSHAL + ".tmp%d" % os.getpid()
+    procs.append(("marshal.cpp", subprocess.Popen(marshal_command(marshal_tmp), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, pr in procs:
         out, _ = pr.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if pr.returncode != 0:
             failed = True
-            sys.stderr.write("hipcc failed for %s:\n%s\n" % (src, out))
+            sys.stderr.write("the compiler failed for %s:\n%s\n" % (src, out))
         elif verbose and out.strip():
             print(out)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("compilation failed")
+    os.replace(marshal_tmp, MARSHAL)
     n = len(SOURCES)
     for lib, lib_objs in ((LIB, objs[:n]), (PROBE_LIB, objs[n:])):
         tmp = lib + ".tmp%d" % os.getpid()
