@@ -51,6 +51,8 @@ struct BwdParams {
     int64_t total_tokens;   // b * l_d for a uniform corpus
     int n_q, l_q, l_d;
     int d;                  // embedding width: a multiple of 8, columns are handled in slabs of 128
+    int doc_blocks;         // dD: blocks per document, of doc_rows rows each but for the last; 0: blocks take no notice of documents
+    int doc_rows;
 };
 
 constexpr int SLAB = 128; // columns a wavefront handles (blockIdx.y selects the slab of wider rows)
@@ -352,7 +354,7 @@ __global__ void __launch_bounds__(256) bwd_dq_combine_kernel(const float4 *part,
 // ---------------------------------------------------------------------------------------
 // dD[j,t,:] = sum over edges (q,i) with A[q,j,i] = t of g[q,j] * Q[q,i,:]              (Eq. 3)
 //
-// A workgroup owns R = 8 * RPW consecutive rows of the (packed) corpus, whichever documents they belong to;
+// A workgroup owns up to R = 8 * RPW consecutive rows, of one document of a uniform corpus or, of a packed one, whichever documents they belong to;
 // wavefront w owns the rows row0 + 8 * s + w (s = 0 .. RPW-1; neighbouring rows, often hot together, go to
 // different wavefronts).  For every document with rows in the block and every round of DW_COL entries of that
 // document's argmax column:
@@ -576,8 +578,12 @@ __device__ __forceinline__ void dd_block(const BwdParams &p, OffsetsPtr off, Mag
     const int blk = ordered_block(order, id);
     if (blk < 0)
         return;
-    const int64_t row0 = (int64_t)blk * R;
-    const int64_t row_end = min(row0 + R, p.total_tokens);
+    int64_t row0 = (int64_t)blk * R, row_end = min(row0 + R, p.total_tokens);
+    if (p.doc_blocks) {
+        const int doc = blk / p.doc_blocks;
+        row0 = (int64_t)doc * p.l_d + (int64_t)(blk - doc * p.doc_blocks) * p.doc_rows;
+        row_end = min(row0 + p.doc_rows, (int64_t)(doc + 1) * p.l_d);
+    }
     const int col = (int)blockIdx.y * SLAB + 2 * lane;
     const bool col_ok = col < p.d;
     // lanes past the row's end re-read its first columns and store nothing
@@ -883,7 +889,7 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
 {
     // Rows per block.  Every block filters the argmax columns of its documents, so halving the blocks doubles that work;
     // but fewer than four blocks per CU leave some CUs with more of them than others, and a block that spans two
-    // documents takes twice as long.  So, with documents of several blocks, blocks of 128 rows also where they fill a
+    // documents (ragged corpora) takes twice as long.  (The times below are of blocks of consecutive rows.)  So, with documents of several blocks, blocks of 128 rows also where they fill a
     // round of two per CU (what is resident) to five sixths or two rounds to three quarters, and blocks of 64 also where
     // there are 1.6 per CU and the CUs with most of them are no more than 0.3 ahead of the mean.  A slab of 128 columns
     // is a workgroup of its own.  Ragged corpora with several rounds per document: by four per CU alone, there a block of
@@ -902,12 +908,26 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
     const bool by64 = n64 >= 4 * cus || (several && n64 * 5 >= 8 * cus && n64 * 10 >= (n64 + cus - 1) / cus * cus * 7);
     const Magic lq_magic = magic_u31((uint32_t)p.l_q);
     const unsigned slabs = (unsigned)((p.d + SLAB - 1) / SLAB);
+    // Documents of equal length are cut into blocks by themselves, as even as they come: a block that spans two documents filters
+    // and sorts twice, and where there are a few blocks per CU the last of those sets the time.  Both gradients, us, blocks of
+    // consecutive rows -> by document: 26 x 1007 x 26 x 902 64.9 -> 53.3, 16 x 1000 x 16 x 300 35.4 -> 27.4, 250 x 64 x 250 x 1000 202
+    // -> 189, 256 x 32 x 256 x 33 113 -> 71, 16 x 32 x 5000 x 20 160 -> 142, and nothing slower of thirty shapes.
+    auto by_document = [&](int rows) {
+        BwdParams r = p;
+        const int n = (int)(((int64_t)p.l_d + rows - 1) / rows);
+        if (!p.offsets && p.b * n <= (int64_t)1 << 22) { // (more of them would be a grid that HIP refuses)
+            r.doc_blocks = n;
+            r.doc_rows = (p.l_d + n - 1) / n;
+        }
+        return r;
+    };
     // Small batches: both gradients in one launch (us in a graph, two launches and a third for the sums -> one: 103 x 24 x 103 documents of 163-653
     // tokens 39.4 -> 34.0, 180 x 12 46.7 -> 40.2, 64 x 64 x 64 37.4 -> 37.1; not 128 x 32 x 128 x 64 31.0 -> 32.2, 16 x 1000 x 16 x 500 31.5 -> 43.8)
     if (!by128 && (int64_t)p.n_q * p.l_q <= 4096 && (int64_t)p.n_q * p.l_q * p.b <= 400000) {
         auto both = [&](auto rpw_tag) {
             constexpr int RPW = decltype(rpw_tag)::value;
-            const BlockOrder order = block_order((p.total_tokens + DD_WAVES * RPW - 1) / (DD_WAVES * RPW), num_cu);
+            BwdParams p = by_document(DD_WAVES * RPW);
+            const BlockOrder order = block_order(p.doc_blocks ? p.b * p.doc_blocks : (p.total_tokens + DD_WAVES * RPW - 1) / (DD_WAVES * RPW), num_cu);
             const unsigned n_dq = (unsigned)(((int64_t)p.n_q * p.l_q + 31) / 32) * 8;
             const int n_part = dq_partitions(p);
             hipLaunchKernelGGL((bwd_both_kernel<DT, RPW>), dim3(n_dq + order.grid, slabs), dim3(DD_WAVES * 64), 0, stream, p, p.offsets, lq_magic,
@@ -922,7 +942,8 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
     auto go = [&](auto rpw_tag, auto w_tag) {
         constexpr int RPW = decltype(rpw_tag)::value;
         constexpr int W = decltype(w_tag)::value;
-        const BlockOrder order = block_order((p.total_tokens + W * RPW - 1) / (W * RPW), num_cu);
+        BwdParams p = by_document(W * RPW);
+        const BlockOrder order = block_order(p.doc_blocks ? p.b * p.doc_blocks : (p.total_tokens + W * RPW - 1) / (W * RPW), num_cu);
         hipLaunchKernelGGL((bwd_dd_kernel<DT, RPW, W>), dim3(order.grid, slabs), dim3(W * 64), 0, stream, p, p.offsets,
                            lq_magic, magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order);
     };
@@ -939,7 +960,7 @@ hipError_t backward_launch(const void *Q, int n_q, int l_q, const void *D, const
                            int64_t total_tokens, int d, int dtype, const int32_t *argmax, const float *dscore, float *dQ,
                            float *dD, int num_cu, hipStream_t stream)
 {
-    BwdParams p;
+    BwdParams p = {};
     p.Q = static_cast<const char *>(Q);
     p.D = static_cast<const char *>(D);
     p.offsets = offsets;
@@ -1275,7 +1296,7 @@ hipError_t backward_csr_launch(const void *Q, int n_q, int l_q, const void *D, i
     hipError_t e = csr_build_launch(argmax, n_q, b, l_q, l_d, row_ptr, col_idx, num_cu, stream);
     if (e != hipSuccess)
         return e;
-    BwdParams p;
+    BwdParams p = {};
     p.Q = static_cast<const char *>(Q);
     p.D = static_cast<const char *>(D);
     p.offsets = nullptr;

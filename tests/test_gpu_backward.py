@@ -392,3 +392,20 @@ def test_ce_small_batches(n, b):
     a = s.clone()
     _, l2 = M.maxsim_ce_grad(a, 0.02, g=a)  # in place
     assert torch.equal(a, g) and torch.equal(l2, loss)
+
+
+# Blocks of dD rows end with their document: lengths around 32, 64 and 128 rows and a little more than a multiple, one to several
+# rounds of argmax entries, through both launches
+@pytest.mark.parametrize("n_q,l_q,b,l_d", [(3, 20, 40, 1), (4, 10, 9, 31), (5, 9, 9, 33), (2, 100, 7, 63), (3, 30, 600, 65), (40, 33, 300, 129), (9, 1000, 2, 277), (6, 3000, 3, 257), (64, 40, 200, 130)])
+def test_blocks_of_a_document(n_q, l_q, b, l_d):
+    Q = W.unit_rows((n_q, l_q, 128), "bf16", 13, DEV)
+    D = W.unit_rows((b, l_d, 128), "bf16", 14, DEV)
+    gen = torch.Generator(device=DEV).manual_seed(15)
+    A = torch.randint(-1, l_d, (n_q, b, l_q), dtype=torch.int32, device=DEV, generator=gen)
+    g = torch.randn(n_q, b, device=DEV, generator=gen)
+    dQ, dD = M.maxsim_backward(Q, D, A, g)
+    cQ, cD, _, _ = M.maxsim_backward_csr(Q, D, A, g)  # walks rows, whatever the blocks
+    assert torch.equal(dQ, cQ) and torch.equal(dD, cD)
+    off = torch.arange(0, (b + 1) * l_d, l_d, dtype=torch.int32, device=DEV)
+    _, pD = M.maxsim_backward_ragged(Q, D.view(-1, 128), off, A, g)
+    assert torch.equal(dD.view(-1, 128), pD)
