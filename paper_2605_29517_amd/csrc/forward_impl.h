@@ -1417,8 +1417,9 @@ __global__ void __launch_bounds__(W * 64, 2) fwd_pack_kernel(FwdParams p, Offset
             // thread instead of two clamps and a multiplication per chunk, which the wavefronts spend between their
             // matrix instructions.  Corpora of 100 000 documents of 64 to 300 tokens, 8 queries of 32 tokens 1148 ->
             // 1121 us; 20 000 documents of 8 to 600 tokens, 5 / 8 / 16 queries 324 / 382 / 637 -> 310 / 371 / 621.
-            // Where several groups read a window the copy is a smaller part of the work and nothing is gained beyond
-            // the noise of a percent: 64 queries x 20 000 documents of 45 tokens 353 and 357, of 8 to 600 2155 and 2157.
+            // Where several groups read a window it is a trade: 48 / 64 queries x 100 000 documents of 64 to 300 tokens 5329 /
+            // 6645 -> 5176 / 6602, but 33 / 64 x 40 000 of 1 to 30 tokens 293 / 351 -> 301 / 358, also where a rule on the mean
+            // length leaves the branch untaken; not there.
             if (READ_ONCE && lw.pa == lw.n_a && lw.n_a + lw.n_b == TILE_ROWS) {
                 const char *src = base + tid * 16;
                 static_for<CPT>([&](auto i) { g(i) = load_stream16(src + decltype(i)::value * (NT * 16)); });
