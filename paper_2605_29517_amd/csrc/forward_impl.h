@@ -1571,6 +1571,10 @@ static hipError_t launch_stream(FwdParams p, int grid, hipStream_t stream)
         // few (a wavefront that holds both reads a tile once: 64 tokens x 1000 x 128 28.0 us there, 31.6 here).  More wavefronts per
         // document where there are fewer documents than SIMDs.  us, before -> now: 32 tokens x 1000 x 128 19.2 -> 17.3, x 300 x 300
         // 26.8 -> 22.1, 20 x 1000 x 40 24.4 -> 9.6, x 200 x 30 15.8 -> 5.0, 62 x 209 x 64 21.2 -> 7.3, 60 x 1000 x 30 26.4 -> 12.0.
+        // Two wavefronts per document up to 2000 documents would be slower on operands in the caches or read from HBM (1000 x 128
+        // 19.4 -> 21.0, 20.8 -> 21.9; 1500 x 128 29.2 -> 33.0), and faster where the launch follows a write of 512 MB that the
+        // memory-side cache still has to put away, which one tile in flight per wavefront meets four times in turn: 1000 x 128
+        // 27.0 -> 22.3 (the former kernel 22.9; 1500 x 128 31.6, 29.5 here).
         const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b;
         if (p.n_groups == 1 && p.b <= 64 * 256 && (NCB == 1 || mean_len < 4 * TILE_ROWS || p.b <= 512)) {
             const int64_t waves = p.b * NCB, tiles = (mean_len + TILE_ROWS - 1) / TILE_ROWS;
