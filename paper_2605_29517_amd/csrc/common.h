@@ -155,6 +155,7 @@ struct FwdParams {
     int n_groups;          // column groups (tile kernel only)
     int qpg;               // queries per column group (tile kernel, bpq <= group size)
     int n_pass;            // passes over the corpus per group (tile kernel, bpq > group size)
+    int doc_waves;         // wavefronts that share a document (the split kernels; 0: runs of documents)
 };
 
 // Offsets come from device memory the host cannot check.  Every offset is forced into

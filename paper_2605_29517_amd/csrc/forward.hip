@@ -85,6 +85,25 @@ static FewDocs few_documents(const FwdParams &p, int num_cu, int shape, int grou
     return best;
 }
 
+// fp32 rows of 512 bytes, queries of one or two column blocks: the wavefronts of fwd_f32_split_kernel that share a document, or 0 for
+// runs of documents.
+// Up to 64 documents per CU, with two blocks where documents are short or
+// few (a wavefront that holds both reads a tile once: 64 tokens x 1000 x 128 28.0 us there, 31.6 here).  More wavefronts per
+// document where there are fewer documents than SIMDs.  us, before -> now: 32 tokens x 1000 x 128 19.2 -> 17.3, x 300 x 300
+// 26.8 -> 22.1, 20 x 1000 x 40 24.4 -> 9.6, x 200 x 30 15.8 -> 5.0, 62 x 209 x 64 21.2 -> 7.3, 60 x 1000 x 30 26.4 -> 12.0.
+// Two wavefronts per document up to 2000 documents would be slower on operands in the caches or read from HBM (1000 x 128
+// 19.4 -> 21.0, 20.8 -> 21.9; 1500 x 128 29.2 -> 33.0), and faster where the launch follows a write of 512 MB that the
+// memory-side cache still has to put away, which one tile in flight per wavefront meets four times in turn: 1000 x 128
+// 27.0 -> 22.3 (the former kernel 22.9; 1500 x 128 31.6, 29.5 here).
+static int fp32_doc_waves(const FwdParams &p, int num_cu, int blocks)
+{
+    const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b, cus = num_cu;
+    if (p.b > 64 * cus || (blocks > 1 && mean_len >= 4 * TILE_ROWS && p.b > 2 * cus))
+        return 0;
+    const int64_t waves = p.b * blocks, tiles = (mean_len + TILE_ROWS - 1) / TILE_ROWS;
+    return tiles >= 4 && 2 * waves <= 5 * cus ? 4 : tiles >= 2 && waves <= 2 * cus ? 2 : 1;
+}
+
 // Chooses kernel and launch shape from the problem size; `num_cu` is the device's CU count.
 hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t stream)
 {
@@ -157,6 +176,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         s_groups = 0;
 
     const int64_t tokens = ragged ? p.total_tokens : p.b * (int64_t)p.l_d;
+    const bool fp32_512 = dtype == MAXSIM_F32 && nu == 16; // (fp32_doc_waves; up to 64 documents per CU with one block, always)
     // Up to 64 documents per CU and two tiles per document on average: a workgroup of two wavefronts per document, four
     // workgroups per CU resident (512 to 2048 workgroups in all were slower).  At one query (fp16, 64-300 tokens) 1000 / 4000 / 16 000 documents take 12.6 / 32.1 /
     // 114.7 us instead of 14.3 / 35.2 / 117.3, four queries 142 instead of 147 us at 16 000; at 32 000 documents and four
@@ -167,7 +187,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         p.n_groups = 1;
         p.qpg = p.n_q;
         p.n_pass = 1;
-        p.unit_per_chunk = 2; // wavefronts
+        p.doc_waves = fp32_512 ? fp32_doc_waves(p, num_cu, s_ncb) : 2;
         const int64_t resident = (int64_t)num_cu * 4;
         return run(false, s_ncb, (int)(p.b < resident ? p.b : resident));
     }
@@ -204,6 +224,8 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         p.n_pass = 1;
         const int chunks_per_block = 4 / s_groups;
         int grid = (int)((n_chunks + chunks_per_block - 1) / chunks_per_block);
+        if (fp32_512 && s_groups == 1)
+            p.doc_waves = fp32_doc_waves(p, num_cu, s_ncb);
         return run(false, s_ncb, grid);
     }
 
@@ -341,7 +363,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
             p.n_chunks = 0;
             p.qpg = few.blocks / p.bpq;
             p.n_groups = p.n_pass = 1;
-            p.unit_per_chunk = few.waves;
+            p.doc_waves = few.waves;
             return run(false, few.blocks, (int)p.b);
         }
         if (few.shape != shape) {

@@ -1567,30 +1567,16 @@ template <int DT, int NCB, bool ARGMAX>
 static hipError_t launch_stream(FwdParams p, int grid, hipStream_t stream)
 {
     if constexpr (Traits<DT>::NU == 16 && Traits<DT>::DT == MAXSIM_F32) {
-        // fp32 rows of 512 bytes, up to 64 documents per CU: fwd_f32_split_kernel, with two blocks where documents are short or
-        // few (a wavefront that holds both reads a tile once: 64 tokens x 1000 x 128 28.0 us there, 31.6 here).  More wavefronts per
-        // document where there are fewer documents than SIMDs.  us, before -> now: 32 tokens x 1000 x 128 19.2 -> 17.3, x 300 x 300
-        // 26.8 -> 22.1, 20 x 1000 x 40 24.4 -> 9.6, x 200 x 30 15.8 -> 5.0, 62 x 209 x 64 21.2 -> 7.3, 60 x 1000 x 30 26.4 -> 12.0.
-        // Two wavefronts per document up to 2000 documents would be slower on operands in the caches or read from HBM (1000 x 128
-        // 19.4 -> 21.0, 20.8 -> 21.9; 1500 x 128 29.2 -> 33.0), and faster where the launch follows a write of 512 MB that the
-        // memory-side cache still has to put away, which one tile in flight per wavefront meets four times in turn: 1000 x 128
-        // 27.0 -> 22.3 (the former kernel 22.9; 1500 x 128 31.6, 29.5 here).
-        const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b;
-        if (p.n_groups == 1 && p.b <= 64 * 256 && (NCB == 1 || mean_len < 4 * TILE_ROWS || p.b <= 512)) {
-            const int64_t waves = p.b * NCB, tiles = (mean_len + TILE_ROWS - 1) / TILE_ROWS;
+        if (p.doc_waves) { // (fp32_doc_waves)
             auto go = [&](auto w) {
                 constexpr int W = decltype(w)::value;
                 hipLaunchKernelGGL((fwd_f32_split_kernel<ARGMAX, W, NCB>), dim3((unsigned)p.b), dim3(W * NCB * 64), 0, stream, p, p.offsets);
                 return hipGetLastError();
             };
-            if (tiles >= 4 && waves <= 640)
-                return go(std::integral_constant<int, 4>{});
-            if (tiles >= 2 && waves <= 512)
-                return go(std::integral_constant<int, 2>{});
-            return go(std::integral_constant<int, 1>{});
+            return p.doc_waves == 4 ? go(std::integral_constant<int, 4>{}) : p.doc_waves == 2 ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
         }
     }
-    if (p.n_chunks == 0) { // a workgroup of unit_per_chunk wavefronts per document and qpg queries
+    if (p.doc_waves) { // a workgroup of doc_waves wavefronts per document and qpg queries
         if constexpr (Traits<DT>::NU <= 8 || (NCB == 1 && Traits<DT>::DT != MAXSIM_F32)) {
             p.n_groups = (p.n_q + p.qpg - 1) / p.qpg;
             auto go = [&](auto w, auto groups) {
@@ -1600,9 +1586,9 @@ static hipError_t launch_stream(FwdParams p, int grid, hipStream_t stream)
                 return hipGetLastError();
             };
             if constexpr (Traits<DT>::NU <= 8 && Traits<DT>::DT != MAXSIM_F32 && ARGMAX && NCB <= 2) { // (few_documents)
-                if (p.unit_per_chunk == 1)
+                if (p.doc_waves == 1)
                     return go(std::integral_constant<int, 1>{}, std::true_type{});
-                if (p.unit_per_chunk == 4)
+                if (p.doc_waves == 4)
                     return go(std::integral_constant<int, 4>{}, std::true_type{});
                 if (p.n_groups > 1)
                     return go(std::integral_constant<int, 2>{}, std::true_type{});

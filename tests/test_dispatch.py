@@ -14,10 +14,11 @@ pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
 HARNESS = r"""
 #include "%(csrc)s/forward.hip"
 #include <cstdio>
+#include <cstdlib>
 namespace maxsim {
 static void print(const char *kind, const FwdParams &p, int nu, int x)
 {
-    printf("%%s %%d %%d %%d %%d %%d\n", kind, nu, x, p.n_groups, p.qpg, p.n_pass);
+    printf("%%s %%d %%d %%d %%d %%d %%d\n", kind, nu, x, p.n_groups, p.qpg, p.n_pass, p.doc_waves);
 }
 static hipError_t one(const FwdParams &p, int nu, bool tile, int x) { print(tile ? "tile" : p.n_chunks ? "stream" : "split", p, nu, x); return hipSuccess; }
 hipError_t forward_run_f16(const FwdParams &p, int nu, bool, bool tile, int x, int, hipStream_t) { return one(p, nu, tile, x); }
@@ -28,8 +29,9 @@ hipError_t forward_wide_launch(FwdParams p, int, int, int, hipStream_t) { print(
 double forward_splitd_time(FwdParams, int, int, int) { return 1; }
 double forward_wide_time(FwdParams, int) { return 1; }
 }
-int main()
+int main(int argc, char **argv)
 {
+    const int cus = argc > 1 ? atoi(argv[1]) : 256;
     int dtype, d, n_q, l_q, ragged, argmax;
     long b, tokens;
     static int32_t some[1];
@@ -42,7 +44,7 @@ int main()
         p.total_tokens = tokens;
         p.offsets = ragged ? some : nullptr;
         p.argmax = argmax ? some : nullptr;
-        if (maxsim::forward_launch(p, dtype, d, 256, nullptr) != hipSuccess)
+        if (maxsim::forward_launch(p, dtype, d, cus, nullptr) != hipSuccess)
             return 1;
     }
     return 0;
@@ -50,7 +52,7 @@ int main()
 """
 
 Call = collections.namedtuple("Call", "dtype d n_q l_q b tokens ragged argmax")
-Route = collections.namedtuple("Route", "kind nu shape n_groups qpg n_pass")
+Route = collections.namedtuple("Route", "kind nu shape n_groups qpg n_pass doc_waves")
 F32, F16, BF16 = 0, 1, 2
 
 
@@ -62,9 +64,9 @@ def routes(tmp_path_factory):
     exe = d / "harness"
     subprocess.run([HIPCC, "-std=c++17", "-O1", "--cuda-host-only", str(src), "-o", str(exe)], check=True, stderr=subprocess.DEVNULL)
 
-    def run(calls):
+    def run(calls, cus=256):
         text = "".join(" ".join(str(int(v)) for v in c) + "\n" for c in calls)
-        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+        out = subprocess.run([str(exe), str(cus)], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
         assert len(out) == len(calls)
         return [Route(f[0], *(int(v) for v in f[1:])) for f in (line.split() for line in out)]
     return run
@@ -132,6 +134,20 @@ def test_few_documents_with_argmax(routes, n, l_q, tokens, ragged, want):
     call = Call(BF16, 128, n, l_q, n, n * tokens, ragged, 1)
     assert (routes([call])[0].kind, routes([call])[0].shape) == want, call
     assert routes([call._replace(dtype=F32, d=64)])[0].kind == routes([call._replace(argmax=0)])[0].kind == "tile"
+
+
+@pytest.mark.parametrize("cus", [64, 256, 304])
+def test_fp32_short_queries(routes, cus):
+    """What launch_stream builds for fp32 rows of 512 bytes: wavefronts per document, by documents per CU, wherever there are no runs."""
+    def waves(l_q, b, tokens):
+        r, = routes([Call(F32, 128, 1, l_q, b, b * tokens, 0, 1)], cus)
+        assert r.kind == "stream" or r.doc_waves in (1, 2, 4)
+        return r.doc_waves
+    assert [waves(32, 2 * cus, t) for t in (32, 33, 96, 97)] == [1, 2, 2, 4]
+    assert [waves(32, b, 64) for b in (2 * cus + 1, 64 * cus, 64 * cus + 1)] == [1, 1, 0]
+    assert [waves(32, 5 * cus // 2 + x, 128) for x in (0, 1)] == [4, 1]
+    assert [waves(64, b, t) for b, t in ((cus, 64), (cus + 1, 64), (5 * cus // 4, 128), (2 * cus, 128), (2 * cus + 1, 128), (2 * cus + 1, 127))] == [2, 1, 4, 1, 0, 1]
+    assert [routes([Call(F16, 256, 1, 32, b, b * 64, 0, 1)], cus)[0].doc_waves for b in (2 * cus, 64 * cus + 1)] == [2, 0]
 
 
 def test_every_shape_is_reached_and_no_other(routes):
