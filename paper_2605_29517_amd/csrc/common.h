@@ -156,6 +156,7 @@ struct FwdParams {
     int qpg;               // queries per column group (tile kernel, bpq <= group size)
     int n_pass;            // passes over the corpus per group (tile kernel, bpq > group size)
     int doc_waves;         // wavefronts that share a document (the split kernels; 0: runs of documents)
+    int docs_per_wg;       // documents per workgroup (fwd_f32_split_kernel)
 };
 
 // Offsets come from device memory the host cannot check.  Every offset is forced into

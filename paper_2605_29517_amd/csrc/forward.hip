@@ -85,23 +85,40 @@ static FewDocs few_documents(const FwdParams &p, int num_cu, int shape, int grou
     return best;
 }
 
-// fp32 rows of 512 bytes, queries of one or two column blocks: the wavefronts of fwd_f32_split_kernel that share a document, or 0 for
-// runs of documents.
-// Up to 64 documents per CU, with two blocks where documents are short or
-// few (a wavefront that holds both reads a tile once: 64 tokens x 1000 x 128 28.0 us there, 31.6 here).  More wavefronts per
-// document where there are fewer documents than SIMDs.  us, before -> now: 32 tokens x 1000 x 128 19.2 -> 17.3, x 300 x 300
-// 26.8 -> 22.1, 20 x 1000 x 40 24.4 -> 9.6, x 200 x 30 15.8 -> 5.0, 62 x 209 x 64 21.2 -> 7.3, 60 x 1000 x 30 26.4 -> 12.0.
-// Two wavefronts per document up to 2000 documents would be slower on operands in the caches or read from HBM (1000 x 128
-// 19.4 -> 21.0, 20.8 -> 21.9; 1500 x 128 29.2 -> 33.0), and faster where the launch follows a write of 512 MB that the
-// memory-side cache still has to put away, which one tile in flight per wavefront meets four times in turn: 1000 x 128
-// 27.0 -> 22.3 (the former kernel 22.9; 1500 x 128 31.6, 29.5 here).
-static int fp32_doc_waves(const FwdParams &p, int num_cu, int blocks)
+// fp32 rows of 512 bytes, queries of one or two column blocks: fwd_f32_split_kernel's wavefronts per document and documents per
+// workgroup (0 wavefronts: not that kernel but runs of documents).  `run`: documents of such a run, `runs`: how many there are.
+//
+// What counts is how many tiles the fullest SIMD has to multiply.  us in a graph (right behind a write of 512 MB), the kernels of
+// runs or of two wavefronts per document that were there before -> now, 32 query tokens:
+//  - fewer documents than SIMDs: four or two wavefronts on each (100 x 300 tokens 14.7 -> 11.4, 300 x 300 26.6 -> 21.0), from two
+//    documents per CU on one (700 x 128 16.9 -> 14.7); with more than three per CU four documents to a workgroup (1000 x 128
+//    19.4 -> 17.1 (22.4 -> 20.8; workgroups of one document 26.2), 1000 x 260 35.3 -> 33.5 (37.9 -> 36.0; 49.4)).
+//  - beyond: one wavefront, but two on each of two documents where that makes the fullest SIMD's share smaller by a tenth, just beyond
+//    4, 8, 12 or 16 per CU (1025 x 128 21.0 -> 21.1, one wavefront 23.0; 1400 x 260 55.7 -> 48.5, 51.0; 2300 x 260 72.7 -> 72.8,
+//    77; not of three tiles, 1025 x 96 19.5 against 18.3; ragged from six on, 1500 x 200 50.4 against 51.5, x 128 35.2 against 33.4).
+// Two blocks (64 tokens): a wavefront on each, where a SIMD's share is smaller by an eighth than that of a wavefront that holds both and
+// reads a tile once (4000 x 40 equal shares: 48.5 in runs, 56 here; 1536 x 64 three quarters: 27.1 -> 24.5; 2200 x 64 five eighths: 46.8
+// -> 34.8).  Two documents to a workgroup with two or six per CU (500 x 300 47.9 -> 34.4, by themselves 49.5; 1536 x 90 35.9 -> 32.3,
+// 40.3; but 600 x 100 26.8 against 24.3, 2500 x 20 25.5 against 23.6).
+static void fp32_shape(FwdParams &p, int num_cu, int blocks, int64_t run, int64_t runs)
 {
-    const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b, cus = num_cu;
-    if (p.b > 64 * cus || (blocks > 1 && mean_len >= 4 * TILE_ROWS && p.b > 2 * cus))
-        return 0;
-    const int64_t waves = p.b * blocks, tiles = (mean_len + TILE_ROWS - 1) / TILE_ROWS;
-    return tiles >= 4 && 2 * waves <= 5 * cus ? 4 : tiles >= 2 && waves <= 2 * cus ? 2 : 1;
+    const int64_t mean_len = (p.total_tokens + p.b - 1) / p.b, cus = num_cu, simds = 4 * cus;
+    const int64_t tiles = (mean_len + TILE_ROWS - 1) / TILE_ROWS;
+    auto rounds = [&](int64_t n) { return (n + simds - 1) / simds; };
+    auto set = [&](int waves, int docs) {
+        p.doc_waves = waves;
+        p.docs_per_wg = docs;
+    };
+    set(0, 1);
+    if (p.b > 64 * cus || (blocks > 1 && ((mean_len >= 4 * TILE_ROWS && p.b > 2 * cus) || rounds(2 * p.b) * 8 >= rounds(runs) * run * 2 * 7)))
+        return;
+    if (p.b * blocks <= 2 * cus && tiles > 1)
+        return set(tiles >= 4 ? 4 : 2, 1);
+    if (blocks > 1) // (with four to a CU the workgroups of two happen to spread well)
+        return set(1, (p.b > cus && p.b <= 2 * cus) || (p.b > 5 * cus && p.b <= 6 * cus) ? 2 : 1);
+    if (p.b > 4 * cus && tiles >= (p.offsets ? 6 : 4) && rounds(2 * p.b) * 10 <= rounds(p.b) * 2 * 9)
+        return set(2, 2);
+    set(1, p.b > 3 * cus && p.b <= 4 * cus ? 4 : 1);
 }
 
 // Chooses kernel and launch shape from the problem size; `num_cu` is the device's CU count.
@@ -176,7 +193,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         s_groups = 0;
 
     const int64_t tokens = ragged ? p.total_tokens : p.b * (int64_t)p.l_d;
-    const bool fp32_512 = dtype == MAXSIM_F32 && nu == 16; // (fp32_doc_waves; up to 64 documents per CU with one block, always)
+    const bool fp32_512 = dtype == MAXSIM_F32 && nu == 16; // (fp32_shape; up to 64 documents per CU with one block, always)
     // Up to 64 documents per CU and two tiles per document on average: a workgroup of two wavefronts per document, four
     // workgroups per CU resident (512 to 2048 workgroups in all were slower).  At one query (fp16, 64-300 tokens) 1000 / 4000 / 16 000 documents take 12.6 / 32.1 /
     // 114.7 us instead of 14.3 / 35.2 / 117.3, four queries 142 instead of 147 us at 16 000; at 32 000 documents and four
@@ -187,7 +204,9 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         p.n_groups = 1;
         p.qpg = p.n_q;
         p.n_pass = 1;
-        p.doc_waves = fp32_512 ? fp32_doc_waves(p, num_cu, s_ncb) : 2;
+        p.doc_waves = 2;
+        if (fp32_512)
+            fp32_shape(p, num_cu, s_ncb, 1, p.b);
         const int64_t resident = (int64_t)num_cu * 4;
         return run(false, s_ncb, (int)(p.b < resident ? p.b : resident));
     }
@@ -225,7 +244,7 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
         const int chunks_per_block = 4 / s_groups;
         int grid = (int)((n_chunks + chunks_per_block - 1) / chunks_per_block);
         if (fp32_512 && s_groups == 1)
-            p.doc_waves = fp32_doc_waves(p, num_cu, s_ncb);
+            fp32_shape(p, num_cu, s_ncb, ragged ? (p.unit_per_chunk * p.b + p.total_tokens - 1) / p.total_tokens : p.unit_per_chunk, n_chunks);
         return run(false, s_ncb, grid);
     }
 

@@ -613,10 +613,13 @@ __global__ void __launch_bounds__(W * 64) fwd_stream_split_kernel(FwdParams p, O
 
 // The same for fp32 rows of 512 bytes and queries of one or two column blocks.  A tile takes a wavefront's matrix core 1.7 us,
 // so the even use of the SIMDs counts: W * C wavefronts share a document, wavefront (x, c) takes every W-th tile against column
-// block c.  Operands come from LDS chunk by chunk, which leaves the registers of a tile in flight.  What bounds it: the chain of
+// block c, and G documents share a workgroup: the four wavefronts of a workgroup go to the four SIMDs of a CU, where
+// workgroups of one or two may meet on one SIMD while others idle (the dispatcher's turn at the launch decides: one query
+// x 1000 x 128 right behind a kernel that writes, three documents on one SIMD, 26.2 us, in workgroups of four 20.8).  Operands come
+// from LDS chunk by chunk, which leaves the registers of a tile in flight.  What bounds it: the chain of
 // a document's tiles (6.8 us of MFMAs for 128 tokens) behind a launch and two loads; two tiles in flight were 5-15 % slower.
-template <bool ARGMAX, int W, int C>
-__global__ void __launch_bounds__(W * C * 64, 2) fwd_f32_split_kernel(FwdParams p, OffsetsPtr off)
+template <bool ARGMAX, int W, int C, int G>
+__global__ void __launch_bounds__(G * W * C * 64, 2) fwd_f32_split_kernel(FwdParams p, OffsetsPtr off)
 {
     constexpr int F = fmt(MAXSIM_F32, 16);
     using TR = Traits<F>;
@@ -624,12 +627,12 @@ __global__ void __launch_bounds__(W * C * 64, 2) fwd_f32_split_kernel(FwdParams 
     constexpr int NU = TR::NU;
     constexpr int CPR = TR::ROW_BYTES / 16; // 16-byte chunks (= lanes) per row
     constexpr int RPI = 64 / CPR;           // rows per load instruction
-    __shared__ __attribute__((aligned(16))) char lds_all[W * C][LT::BYTES];
-    __shared__ float part[2][C];
+    __shared__ __attribute__((aligned(16))) char lds_all[G * W * C][LT::BYTES];
+    __shared__ float part[G][C];
     const int lane = threadIdx.x & 63;
     const int rho = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int x = w / C, c = w % C;
+    const int sub = w / (W * C), x = w / C % W, c = w % C;
     char *lds = lds_all[w];
 
     uint4 qf[NU];
@@ -638,21 +641,24 @@ __global__ void __launch_bounds__(W * C * 64, 2) fwd_f32_split_kernel(FwdParams 
     const int lrow = lane / CPR, lcol = (lane % CPR) * 16;
     const int st_off = lrow * LT::ROW_STRIDE + lcol;
     const int rd_off = rho * LT::ROW_STRIDE + h * 16;
-    int par = 0;
-    for (int doc = blockIdx.x; doc < p.b; doc += gridDim.x) {
-        int64_t start;
-        int len;
-        if (p.offsets) {
-            start = clamp_offset(off[doc], 0, p.total_tokens);
-            len = (int)(clamp_offset(off[doc + 1], start, p.total_tokens) - start);
-        } else {
-            start = (int64_t)doc * p.l_d;
-            len = p.l_d;
+    auto document = [&](int doc) {
+        int64_t start = 0;
+        int len = 0;
+        if (G == 1 || doc < p.b) {
+            if (p.offsets) {
+                start = clamp_offset(off[doc], 0, p.total_tokens);
+                len = (int)(clamp_offset(off[doc + 1], start, p.total_tokens) - start);
+            } else {
+                start = (int64_t)doc * p.l_d;
+                len = p.l_d;
+            }
+            if (len <= 0)
+                write_empty_docs(p, doc, doc + 1, (int)threadIdx.x - sub * (W * C * 64), W * C * 64);
         }
-        if (len <= 0) {
-            write_empty_docs(p, doc, doc + 1, threadIdx.x, W * C * 64);
-            continue;
-        }
+        // (where documents meet in barriers, those of the workgroup's other documents are kept)
+        constexpr bool LEAVE = G == 1 || W * C == 1;
+        if (LEAVE && len <= 0)
+            return;
         const char *base = p.D + start * TR::ROW_BYTES + lcol;
         uint4 g[NU];
         auto load_lin = [&](int t0) { // rows past the document's end repeat its last token
@@ -705,7 +711,7 @@ __global__ void __launch_bounds__(W * C * 64, 2) fwd_f32_split_kernel(FwdParams 
             if (x == 0) {
 #pragma unroll
                 for (int y = 1; y < W; ++y) {
-                    const float *other = reinterpret_cast<const float *>(lds_all[y * C + c]);
+                    const float *other = reinterpret_cast<const float *>(lds_all[(sub * W + y) * C + c]);
                     const float mo = other[lane];
                     if (ARGMAX) {
                         const int io = __float_as_int(other[64 + lane]);
@@ -716,21 +722,27 @@ __global__ void __launch_bounds__(W * C * 64, 2) fwd_f32_split_kernel(FwdParams 
                 }
             }
         }
-        if (x == 0) {
+        if (x == 0 && (LEAVE || len > 0)) {
             const float sum = finish_block<ARGMAX>(p, m, idx, col_valid, c, doc, len, rho, h);
             if (C == 1 || p.bpq == 1) {
                 if (lane == 0 && c / p.bpq < p.n_q)
                     p.scores[(int64_t)c * p.ld + doc] = sum;
             } else if (lane == 0) {
-                part[par][c] = sum;
+                part[sub][c] = sum;
             }
         }
-        if constexpr (W > 1 || C > 1)
-            __syncthreads(); // (also: the tiles are overwritten by the next document)
-        if (C == 2 && p.bpq == 2 && threadIdx.x == 0)
-            p.scores[doc] = part[par][0] + part[par][C - 1];
-        par ^= 1;
-    }
+        if constexpr (C == 2) {
+            __syncthreads();
+            if (p.bpq == 2 && x == 0 && c == 0 && lane == 0 && (LEAVE || len > 0))
+                p.scores[doc] = part[sub][0] + part[sub][1];
+        }
+    };
+    const int doc = (int)blockIdx.x * G + sub;
+    if constexpr (G > 1 && W * C == 1) // (once; but as a loop the first tiles are asked for a little later, and 1000 x 128 from the caches take 17.2 and not 17.8 us)
+        for (int j = doc; j < p.b; j += (int)gridDim.x * G)
+            document(j);
+    else
+        document(doc);
 }
 
 // Folds of 16x16 results.  The two cells a v_max3 takes at a time are pair k = 0 .. 7 of an Acc16: result (i, j) =
@@ -1567,13 +1579,22 @@ template <int DT, int NCB, bool ARGMAX>
 static hipError_t launch_stream(FwdParams p, int grid, hipStream_t stream)
 {
     if constexpr (Traits<DT>::NU == 16 && Traits<DT>::DT == MAXSIM_F32) {
-        if (p.doc_waves) { // (fp32_doc_waves)
-            auto go = [&](auto w) {
-                constexpr int W = decltype(w)::value;
-                hipLaunchKernelGGL((fwd_f32_split_kernel<ARGMAX, W, NCB>), dim3((unsigned)p.b), dim3(W * NCB * 64), 0, stream, p, p.offsets);
+        if (p.doc_waves) { // (fp32_shape)
+            auto go = [&](auto w, auto g) {
+                constexpr int W = decltype(w)::value, G = decltype(g)::value;
+                hipLaunchKernelGGL((fwd_f32_split_kernel<ARGMAX, W, NCB, G>), dim3((unsigned)((p.b + G - 1) / G)), dim3(G * W * NCB * 64), 0, stream, p, p.offsets);
                 return hipGetLastError();
             };
-            return p.doc_waves == 4 ? go(std::integral_constant<int, 4>{}) : p.doc_waves == 2 ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
+            constexpr std::integral_constant<int, 1> one{};
+            constexpr std::integral_constant<int, 2> two{};
+            constexpr std::integral_constant<int, 4> four{};
+            if (p.docs_per_wg > 1) { // workgroups of four wavefronts
+                if constexpr (NCB == 1)
+                    return p.doc_waves == 2 ? go(two, two) : go(one, four);
+                else
+                    return go(one, two);
+            }
+            return p.doc_waves == 4 ? go(four, one) : p.doc_waves == 2 ? go(two, one) : go(one, one);
         }
     }
     if (p.doc_waves) { // a workgroup of doc_waves wavefronts per document and qpg queries

@@ -18,7 +18,7 @@ HARNESS = r"""
 namespace maxsim {
 static void print(const char *kind, const FwdParams &p, int nu, int x)
 {
-    printf("%%s %%d %%d %%d %%d %%d %%d\n", kind, nu, x, p.n_groups, p.qpg, p.n_pass, p.doc_waves);
+    printf("%%s %%d %%d %%d %%d %%d %%d %%d\n", kind, nu, x, p.n_groups, p.qpg, p.n_pass, p.doc_waves, p.docs_per_wg);
 }
 static hipError_t one(const FwdParams &p, int nu, bool tile, int x) { print(tile ? "tile" : p.n_chunks ? "stream" : "split", p, nu, x); return hipSuccess; }
 hipError_t forward_run_f16(const FwdParams &p, int nu, bool, bool tile, int x, int, hipStream_t) { return one(p, nu, tile, x); }
@@ -52,7 +52,7 @@ int main(int argc, char **argv)
 """
 
 Call = collections.namedtuple("Call", "dtype d n_q l_q b tokens ragged argmax")
-Route = collections.namedtuple("Route", "kind nu shape n_groups qpg n_pass doc_waves")
+Route = collections.namedtuple("Route", "kind nu shape n_groups qpg n_pass doc_waves docs_per_wg")
 F32, F16, BF16 = 0, 1, 2
 
 
@@ -138,16 +138,30 @@ def test_few_documents_with_argmax(routes, n, l_q, tokens, ragged, want):
 
 @pytest.mark.parametrize("cus", [64, 256, 304])
 def test_fp32_short_queries(routes, cus):
-    """What launch_stream builds for fp32 rows of 512 bytes: wavefronts per document, by documents per CU, wherever there are no runs."""
-    def waves(l_q, b, tokens):
-        r, = routes([Call(F32, 128, 1, l_q, b, b * tokens, 0, 1)], cus)
-        assert r.kind == "stream" or r.doc_waves in (1, 2, 4)
-        return r.doc_waves
-    assert [waves(32, 2 * cus, t) for t in (32, 33, 96, 97)] == [1, 2, 2, 4]
-    assert [waves(32, b, 64) for b in (2 * cus + 1, 64 * cus, 64 * cus + 1)] == [1, 1, 0]
-    assert [waves(32, 5 * cus // 2 + x, 128) for x in (0, 1)] == [4, 1]
-    assert [waves(64, b, t) for b, t in ((cus, 64), (cus + 1, 64), (5 * cus // 4, 128), (2 * cus, 128), (2 * cus + 1, 128), (2 * cus + 1, 127))] == [2, 1, 4, 1, 0, 1]
+    """Wavefronts per document and documents per workgroup for fp32 rows of 512 bytes, by documents per CU: what launch_stream builds
+    wherever there are no runs of documents."""
+    def shape(l_q, b, tokens, ragged=0):
+        r, = routes([Call(F32, 128, 1, l_q, b, b * tokens, ragged, 1)], cus)
+        assert r.kind == "stream" or r.doc_waves
+        assert (r.doc_waves, r.docs_per_wg) in ({(4, 1), (2, 1), (1, 1), (2, 2), (1, 4), (0, 1)} if l_q <= 32 else {(4, 1), (2, 1), (1, 1), (1, 2), (0, 1)})
+        return r.doc_waves, r.docs_per_wg
+    assert [shape(32, 2 * cus, t) for t in (32, 33, 96, 97)] == [(1, 1), (2, 1), (2, 1), (4, 1)]
+    assert [shape(32, b, 128) for b in (2 * cus + 1, 3 * cus, 3 * cus + 1, 4 * cus, 4 * cus + 1, 6 * cus, 6 * cus + 1, 8 * cus, 8 * cus + 1, 10 * cus + 1, 64 * cus, 64 * cus + 1)] == [
+        (1, 1), (1, 1), (1, 4), (1, 4), (2, 2), (2, 2), (1, 1), (1, 1), (2, 2), (1, 1), (1, 1), (0, 1)]
+    assert [shape(32, 4 * cus + 1, t) for t in (96, 97)] == [(1, 1), (2, 2)]
+    assert [shape(32, 4 * cus + 1, t, 1) for t in (160, 161)] == [(1, 1), (2, 2)]
+    # two blocks: by themselves, two to a workgroup, in runs
+    assert [shape(64, cus, t) for t in (20, 64, 300)] == [(1, 1), (2, 1), (4, 1)]
+    assert [shape(64, b, 64) for b in (cus + 1, 2 * cus, 2 * cus + 1, 5 * cus, 5 * cus + 1, 6 * cus, 8 * cus)] == [(1, 2), (1, 2), (1, 1), (1, 1), (1, 2), (1, 2), (0, 1)]
+    assert [shape(64, 2 * cus + x, t) for x, t in ((0, 300), (1, 300), (1, 128))] == [(1, 2), (0, 1), (0, 1)]
     assert [routes([Call(F16, 256, 1, 32, b, b * 64, 0, 1)], cus)[0].doc_waves for b in (2 * cus, 64 * cus + 1)] == [2, 0]
+
+
+# two blocks of fp32: runs of documents where a SIMD's share of tiles is no smaller without them (by an eighth at least)
+@pytest.mark.parametrize("b,tokens,ragged,waves", [(1536, 64, 0, 1), (2048, 64, 0, 0), (2200, 64, 0, 1), (1700, 100, 0, 0), (2000, 100, 0, 0), (4000, 40, 0, 0), (2200, 127, 0, 1), (8000, 32, 0, 0),
+                                                   (8000, 20, 0, 1), (5000, 33, 0, 1), (5000, 90, 0, 1), (2000, 100, 1, 1), (3000, 60, 1, 1), (3000, 40, 1, 1)])
+def test_fp32_two_blocks_in_runs(routes, b, tokens, ragged, waves):
+    assert routes([Call(F32, 128, 1, 64, b, b * tokens, ragged, 1)])[0].doc_waves == waves
 
 
 def test_every_shape_is_reached_and_no_other(routes):

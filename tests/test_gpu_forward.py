@@ -316,6 +316,14 @@ def test_fp32_short_queries(b, longest, n_q, l_q, want_argmax):
     forward_parity_uniform(Q, W.unit_rows((b, longest, 128), "f32", 65, DEV), M.maxsim_forward, want_argmax, RTOL_F32)
 
 
+# The same with two or four documents to a workgroup, the last of which is not full (three to six documents per CU of 256)
+@pytest.mark.parametrize("want_argmax", [False, True])
+@pytest.mark.parametrize("n_q,l_q", [(1, 32), (1, 7), (2, 20), (1, 64)])
+@pytest.mark.parametrize("b,longest", [(301, 70), (769, 130), (1023, 33), (1027, 130), (1027, 400), (1301, 40)])
+def test_fp32_short_queries_documents_to_a_workgroup(b, longest, n_q, l_q, want_argmax):
+    test_fp32_short_queries(b, longest, n_q, l_q, want_argmax)
+
+
 # Many queries on few documents with winners: a workgroup of one, two or four wavefronts per document and one or two column blocks, or
 # small column groups of the tile kernel; a last group that is not full, documents of fewer tiles than wavefronts, empty ones
 @pytest.mark.parametrize("dtype,d", [("f16", 128), ("bf16", 64)])
