@@ -805,43 +805,51 @@ __global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr 
 }
 
 // Both gradients in one launch, for small batches, where a launch and its start cost as much as the work: the first n_dq
-// workgroups (a multiple of eight, so that the others keep their XCDs) take four query tokens of dQ each, wavefront k adding the documents of
-// partition k, and add the partial sums up in LDS in partition order: the bits of bwd_dq_kernel and bwd_dq_combine_kernel,
-// without the detour through dD that keeps those from running beside the dD kernel.  n queries of 32 tokens x n documents, us in
+// workgroups (a multiple of eight, so that the others keep their XCDs) take dQ, n_part wavefronts per four query tokens, each adding the
+// documents of one partition, and add the partial sums up in LDS in partition order: the bits of bwd_dq_kernel and bwd_dq_combine_kernel,
+// without the detour through dD that keeps those from running beside the dD kernel.  `sets` of n_part wavefronts share a workgroup:
+// as many as it holds, or with fewer tokens than a workgroup per CU takes, one.  (One set each whatever the partitions left up to seven
+// of eight wavefronts idle where the corpus holds few partial sums: 2 x 2000 x 90 x 64 39.2 us, 20.8 now, 25.8 in three launches, 64 x 64 x
+// 64 x 64 30.4, 18.2, 23.6; but 25 x 32 x 25 x 230 8.2, 8.9 with all sets.)  n queries of 32 tokens x n documents, us in
 // a graph: n = 16 x 128 tokens 12.5 -> 7.3, 33 x 83-333 18.9 -> 13.0, 64 x 75-300 24.8 -> 20.0, 80 x 1024 38.1 -> 34.6.
 template <int DT, int RPW>
 __global__ void __launch_bounds__(DD_WAVES * 64) bwd_both_kernel(BwdParams p, OffsetsPtr off, Magic lq_magic, Magic ld_magic, int dq64, int di64, BlockOrder order, unsigned n_dq,
-                                                                 int n_part, int64_t docs_per_part)
+                                                                 int n_part, int sets, int64_t docs_per_part)
 {
     __shared__ __attribute__((aligned(16))) DdLds<RPW, DD_WAVES> lds;
     if (blockIdx.x >= n_dq) {
         dd_block<DT, RPW, DD_WAVES>(p, off, lq_magic, ld_magic, dq64, di64, order, blockIdx.x - n_dq, lds.seg, lds.list, lds.hist, lds.start);
         return;
     }
-    constexpr int TOKENS = 4; // one per group of sixteen lanes
-    static_assert(sizeof(lds.seg) >= DD_WAVES * TOKENS * SLAB * sizeof(float) && DD_WAVES * 64 == TOKENS * SLAB, "partial sums in LDS, one sum per thread");
+    constexpr int TOKENS = 4; // of a wavefront: one per group of sixteen lanes
+    static_assert(sizeof(lds.seg) >= DD_WAVES * TOKENS * SLAB * sizeof(float) && DD_WAVES * 64 == TOKENS * SLAB, "partial sums in LDS, a sum per thread and set of partitions");
     float *part = reinterpret_cast<float *>(&lds);
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t nql = (int64_t)p.n_q * p.l_q, first = (int64_t)blockIdx.x * TOKENS;
+    const int log_parts = __builtin_ctz(n_part);
+    const int64_t nql = (int64_t)p.n_q * p.l_q, first = (int64_t)blockIdx.x * (sets * TOKENS);
     if (first >= nql)
         return;
-    const int64_t j0 = (int64_t)w * docs_per_part;
+    const int64_t j0 = (int64_t)(w & (n_part - 1)) * docs_per_part;
     const int64_t j1 = j0 + docs_per_part < p.b ? j0 + docs_per_part : p.b;
+    const int64_t mine_first = first + (w >> log_parts) * TOKENS;
     float acc[1][8] = {};
-    if (w < n_part && j0 < j1)
-        dq_gather<DT, 1>(p, first + (lane >> 4), j0, j1, 0, acc);
+    if (w < sets << log_parts && mine_first < nql && j0 < j1)
+        dq_gather<DT, 1>(p, mine_first + (lane >> 4), j0, j1, 0, acc);
     float4 *mine = reinterpret_cast<float4 *>(part + (w * TOKENS + (lane >> 4)) * SLAB + (lane & 15) * 8);
     mine[0] = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
     mine[1] = make_float4(acc[0][4], acc[0][5], acc[0][6], acc[0][7]);
     __syncthreads();
-    float sum = part[tid];
-    for (int k = 1; k < n_part; ++k)
-        sum += part[k * (TOKENS * SLAB) + tid];
-    const int64_t n = first + tid / SLAB;
     const int col = (int)blockIdx.y * SLAB + tid % SLAB;
-    if (n < nql && col < p.d)
-        p.dQ[n * p.d + col] = sum;
+    for (int s = 0; s < sets; ++s) {
+        const float *of_set = part + (s << log_parts) * (TOKENS * SLAB) + tid;
+        float sum = of_set[0];
+        for (int k = 1; k < n_part; ++k)
+            sum += of_set[k * (TOKENS * SLAB)];
+        const int64_t n = first + s * TOKENS + tid / SLAB;
+        if (n < nql && col < p.d)
+            p.dQ[n * p.d + col] = sum;
+    }
 }
 
 // The partial sums of dQ live in the dD buffer until the dD kernel overwrites it (dD is an output that the call
@@ -928,10 +936,12 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
             constexpr int RPW = decltype(rpw_tag)::value;
             BwdParams p = by_document(DD_WAVES * RPW);
             const BlockOrder order = block_order(p.doc_blocks ? p.b * p.doc_blocks : (p.total_tokens + DD_WAVES * RPW - 1) / (DD_WAVES * RPW), num_cu);
-            const unsigned n_dq = (unsigned)(((int64_t)p.n_q * p.l_q + 31) / 32) * 8;
             const int n_part = dq_partitions(p);
+            const int64_t nql = (int64_t)p.n_q * p.l_q;
+            const int sets = nql > 4 * cus ? DD_WAVES / n_part : 1;
+            const unsigned n_dq = (unsigned)((nql + 32 * sets - 1) / (32 * sets)) * 8;
             hipLaunchKernelGGL((bwd_both_kernel<DT, RPW>), dim3(n_dq + order.grid, slabs), dim3(DD_WAVES * 64), 0, stream, p, p.offsets, lq_magic,
-                               magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order, n_dq, n_part, (p.b + n_part - 1) / n_part);
+                               magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order, n_dq, n_part, sets, (p.b + n_part - 1) / n_part);
             return hipGetLastError();
         };
         return by64 ? both(std::integral_constant<int, 8>()) : both(std::integral_constant<int, 4>());

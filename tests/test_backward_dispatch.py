@@ -1,0 +1,71 @@
+"""What the backward's host code (csrc/backward.hip) launches: the code by itself, its launches replaced by a line of text (no GPU
+needed)."""
+import collections
+import os
+import subprocess
+
+import pytest
+
+from paper_2605_29517_amd import build as B
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+
+HARNESS = r"""
+#include "%(csrc)s/common.h"
+#include <cstdio>
+#include <tuple>
+#undef hipLaunchKernelGGL
+#define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) report(#kernel, grid, __VA_ARGS__)
+template <typename P, typename... A> void report(const char *kernel, dim3 grid, const P &, A... a)
+{
+    if constexpr (sizeof...(A) >= 9) { // bwd_both_kernel
+        const auto t = std::make_tuple(a...);
+        printf("both %%u %%u %%d\n", grid.x, (unsigned)std::get<6>(t), (int)std::get<7>(t));
+    } else if constexpr (sizeof...(A) == 6) {
+        printf("dD %%u 0 0\n", grid.x);
+    }
+}
+#include "%(csrc)s/backward.hip"
+int main()
+{
+    int n_q, l_q, ragged;
+    long b, tokens;
+    static int32_t some[4];
+    static float grad[4];
+    while (scanf("%%d %%d %%ld %%ld %%d", &n_q, &l_q, &b, &tokens, &ragged) == 5) // (the results tell of the device that is not there)
+        (void)maxsim::backward_launch(some, n_q, l_q, some, ragged ? some : nullptr, b, ragged ? 0 : (int)(tokens / b), tokens, 128, MAXSIM_F16, some, grad, grad, grad, 256, nullptr);
+    return 0;
+}
+"""
+
+Call = collections.namedtuple("Call", "n_q l_q b tokens ragged")
+Launch = collections.namedtuple("Launch", "kind workgroups n_dq n_part")
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    d = tmp_path_factory.mktemp("backward")
+    src = d / "harness.hip"
+    src.write_text(HARNESS % {"csrc": B.CSRC})
+    exe = d / "harness"
+    subprocess.run([HIPCC, "-std=c++17", "-O1", "--cuda-host-only", "-Wl,--unresolved-symbols=ignore-all", str(src), "-o", str(exe)], check=True, stderr=subprocess.DEVNULL)
+
+    def run(calls):
+        text = "".join(" ".join(str(int(v)) for v in c) + "\n" for c in calls)
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+        assert len(out) == len(calls)
+        return [Launch(f[0], *(int(v) for v in f[1:])) for f in (line.split() for line in out)]
+    return run
+
+
+# (queries, tokens, documents, tokens of each, partitions, sets of as many wavefronts in a workgroup)
+@pytest.mark.parametrize("n_q,l_q,b,l_d,parts,sets", [(64, 64, 64, 64, 1, 8), (2, 2000, 90, 64, 1, 8), (16, 250, 90, 64, 1, 8), (50, 40, 100, 50, 2, 4), (41, 25, 100, 50, 4, 2), (64, 20, 100, 128, 8, 1),
+                                                      (16, 64, 64, 16, 1, 1), (16, 32, 16, 128, 4, 1), (1, 1, 1, 1, 1, 1)])
+@pytest.mark.parametrize("ragged", [0, 1])
+def test_one_launch_has_no_idle_wavefronts(launches, n_q, l_q, b, l_d, parts, sets, ragged):
+    """A wavefront per four query tokens and partition, in workgroups of eight, from a workgroup per CU on; their number is rounded up to a
+    multiple of eight."""
+    r, = launches([Call(n_q, l_q, b, b * l_d, ragged)])
+    assert r.kind == "both" and r.n_part == parts
+    assert r.n_dq == -(-n_q * l_q // (32 * sets)) * 8
