@@ -814,7 +814,7 @@ __global__ void __launch_bounds__(W * 64) bwd_dd_kernel(BwdParams p, OffsetsPtr 
 // a graph: n = 16 x 128 tokens 12.5 -> 7.3, 33 x 83-333 18.9 -> 13.0, 64 x 75-300 24.8 -> 20.0, 80 x 1024 38.1 -> 34.6.
 template <int DT, int RPW>
 __global__ void __launch_bounds__(DD_WAVES * 64) bwd_both_kernel(BwdParams p, OffsetsPtr off, Magic lq_magic, Magic ld_magic, int dq64, int di64, BlockOrder order, unsigned n_dq,
-                                                                 int n_part, int sets, int64_t docs_per_part)
+                                                                 int n_part, int sets, int docs_per_part)
 {
     __shared__ __attribute__((aligned(16))) DdLds<RPW, DD_WAVES> lds;
     if (blockIdx.x >= n_dq) {
@@ -830,7 +830,7 @@ __global__ void __launch_bounds__(DD_WAVES * 64) bwd_both_kernel(BwdParams p, Of
     const int64_t nql = (int64_t)p.n_q * p.l_q, first = (int64_t)blockIdx.x * (sets * TOKENS);
     if (first >= nql)
         return;
-    const int64_t j0 = (int64_t)(w & (n_part - 1)) * docs_per_part;
+    const int64_t j0 = (int64_t)(w & (n_part - 1)) * docs_per_part; // (documents: 400 000 at most)
     const int64_t j1 = j0 + docs_per_part < p.b ? j0 + docs_per_part : p.b;
     const int64_t mine_first = first + (w >> log_parts) * TOKENS;
     float acc[1][8] = {};
@@ -841,12 +841,12 @@ __global__ void __launch_bounds__(DD_WAVES * 64) bwd_both_kernel(BwdParams p, Of
     mine[1] = make_float4(acc[0][4], acc[0][5], acc[0][6], acc[0][7]);
     __syncthreads();
     const int col = (int)blockIdx.y * SLAB + tid % SLAB;
-    for (int s = 0; s < sets; ++s) {
-        const float *of_set = part + (s << log_parts) * (TOKENS * SLAB) + tid;
-        float sum = of_set[0];
-        for (int k = 1; k < n_part; ++k)
-            sum += of_set[k * (TOKENS * SLAB)];
-        const int64_t n = first + s * TOKENS + tid / SLAB;
+    const float *from = part + tid;
+    int64_t n = first + tid / SLAB;
+    for (int s = 0; s < sets; ++s, n += TOKENS) {
+        float sum = 0.0f;
+        for (int k = 0; k < n_part; ++k, from += TOKENS * SLAB)
+            sum = k ? sum + *from : *from;
         if (n < nql && col < p.d)
             p.dQ[n * p.d + col] = sum;
     }
@@ -930,18 +930,25 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
         return r;
     };
     // Small batches: both gradients in one launch (us in a graph, two launches and a third for the sums -> one: 103 x 24 x 103 documents of 163-653
-    // tokens 39.4 -> 34.0, 180 x 12 46.7 -> 40.2, 64 x 64 x 64 37.4 -> 37.1; not 128 x 32 x 128 x 64 31.0 -> 32.2, 16 x 1000 x 16 x 500 31.5 -> 43.8)
-    if (!by128 && (int64_t)p.n_q * p.l_q <= 4096 && (int64_t)p.n_q * p.l_q * p.b <= 400000) {
+    // tokens 39.4 -> 34.0, 180 x 12 46.7 -> 40.2, 64 x 64 x 64 37.4 -> 31.5; not 128 x 32 x 128 x 64 31.0 -> 32.2, 16 x 1000 x 16 x 500 31.5 -> 43.8).
+    // By themselves the partitions of dQ go to the XCDs, an eighth of D to each L2, and dD's kernel needs fewer registers.  So with more
+    // than 512 tokens and 94 MB of rows to gather, only beside up to 4.5 blocks of dD per CU: in three launches 40 x 32 x 300 x 200, d = 128 / 256:
+    // 42.6 / 72.9 us, in one 45.9 / 86.8 (2100 / 4200 blocks), fp32 116 x 27 x 116 x 336, d = 256 / 512: 85 / 157, 97 / 185 (2552 / 5104); but
+    // 116 x 27 x 116 x 60, d = 256: 44.7, 39.7 (464), 8 x 60 x 800 x 128, d = 128, fp32 58.1, 50.7 (480 tokens), 60 x 32 x 60 x 200 24.3, 17.9.
+    const int64_t nql = (int64_t)p.n_q * p.l_q, edges = nql * p.b;
+    auto n_blocks = [&](const BwdParams &r, int rows) { return r.doc_blocks ? r.b * r.doc_blocks : (r.total_tokens + rows - 1) / rows; };
+    const int small_rows = DD_WAVES * (by64 ? 8 : 4);
+    if (!by128 && nql <= 4096 && edges <= 400000 &&
+        (nql <= 512 || edges * p.d * Elem<DT>::BYTES <= 94000000 || n_blocks(by_document(small_rows), small_rows) * slabs * 2 <= 9 * cus)) {
         auto both = [&](auto rpw_tag) {
             constexpr int RPW = decltype(rpw_tag)::value;
             BwdParams p = by_document(DD_WAVES * RPW);
-            const BlockOrder order = block_order(p.doc_blocks ? p.b * p.doc_blocks : (p.total_tokens + DD_WAVES * RPW - 1) / (DD_WAVES * RPW), num_cu);
+            const BlockOrder order = block_order(n_blocks(p, DD_WAVES * RPW), num_cu);
             const int n_part = dq_partitions(p);
-            const int64_t nql = (int64_t)p.n_q * p.l_q;
             const int sets = nql > 4 * cus ? DD_WAVES / n_part : 1;
             const unsigned n_dq = (unsigned)((nql + 32 * sets - 1) / (32 * sets)) * 8;
             hipLaunchKernelGGL((bwd_both_kernel<DT, RPW>), dim3(n_dq + order.grid, slabs), dim3(DD_WAVES * 64), 0, stream, p, p.offsets, lq_magic,
-                               magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order, n_dq, n_part, sets, (p.b + n_part - 1) / n_part);
+                               magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order, n_dq, n_part, sets, (int)((p.b + n_part - 1) / n_part));
             return hipGetLastError();
         };
         return by64 ? both(std::integral_constant<int, 8>()) : both(std::integral_constant<int, 4>());
@@ -953,7 +960,7 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
         constexpr int RPW = decltype(rpw_tag)::value;
         constexpr int W = decltype(w_tag)::value;
         BwdParams p = by_document(W * RPW);
-        const BlockOrder order = block_order(p.doc_blocks ? p.b * p.doc_blocks : (p.total_tokens + W * RPW - 1) / (W * RPW), num_cu);
+        const BlockOrder order = block_order(n_blocks(p, W * RPW), num_cu);
         hipLaunchKernelGGL((bwd_dd_kernel<DT, RPW, W>), dim3(order.grid, slabs), dim3(W * 64), 0, stream, p, p.offsets,
                            lq_magic, magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order);
     };

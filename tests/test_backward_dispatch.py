@@ -16,6 +16,7 @@ HARNESS = r"""
 #include <cstdio>
 #include <tuple>
 #undef hipLaunchKernelGGL
+#define hipGetLastError() hipSuccess // (there is no device)
 #define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) report(#kernel, grid, __VA_ARGS__)
 template <typename P, typename... A> void report(const char *kernel, dim3 grid, const P &, A... a)
 {
@@ -29,17 +30,19 @@ template <typename P, typename... A> void report(const char *kernel, dim3 grid, 
 #include "%(csrc)s/backward.hip"
 int main()
 {
-    int n_q, l_q, ragged;
+    int n_q, l_q, ragged, d, dtype;
     long b, tokens;
     static int32_t some[4];
     static float grad[4];
-    while (scanf("%%d %%d %%ld %%ld %%d", &n_q, &l_q, &b, &tokens, &ragged) == 5) // (the results tell of the device that is not there)
-        (void)maxsim::backward_launch(some, n_q, l_q, some, ragged ? some : nullptr, b, ragged ? 0 : (int)(tokens / b), tokens, 128, MAXSIM_F16, some, grad, grad, grad, 256, nullptr);
+    while (scanf("%%d %%d %%ld %%ld %%d %%d %%d", &n_q, &l_q, &b, &tokens, &ragged, &d, &dtype) == 7)
+        if (maxsim::backward_launch(some, n_q, l_q, some, ragged ? some : nullptr, b, ragged ? 0 : (int)(tokens / b), tokens, d, dtype, some, grad, grad, grad, 256, nullptr) != hipSuccess)
+            return 1;
     return 0;
 }
 """
 
-Call = collections.namedtuple("Call", "n_q l_q b tokens ragged")
+F32, F16 = 0, 1
+Call = collections.namedtuple("Call", "n_q l_q b tokens ragged d dtype", defaults=(128, F16))
 Launch = collections.namedtuple("Launch", "kind workgroups n_dq n_part")
 
 
@@ -69,3 +72,11 @@ def test_one_launch_has_no_idle_wavefronts(launches, n_q, l_q, b, l_d, parts, se
     r, = launches([Call(n_q, l_q, b, b * l_d, ragged)])
     assert r.kind == "both" and r.n_part == parts
     assert r.n_dq == -(-n_q * l_q // (32 * sets)) * 8
+
+
+# Many rows to gather beside many blocks of dD: three launches
+@pytest.mark.parametrize("n_q,l_q,b,l_d,d,dtype,kind", [(40, 32, 300, 100, 128, F16, "dD"), (40, 32, 300, 96, 128, F16, "both"), (40, 32, 280, 128, 128, F16, "both"), (40, 32, 300, 200, 256, F16, "dD"),
+                                                        (116, 27, 116, 60, 256, F16, "both"), (116, 27, 116, 336, 256, F32, "dD"), (103, 24, 103, 400, 128, F16, "both"), (80, 24, 80, 1024, 128, F16, "both"),
+                                                        (64, 64, 64, 64, 512, F32, "both"), (8, 64, 700, 128, 128, F32, "both"), (9, 60, 700, 128, 128, F32, "dD")])
+def test_one_launch_by_what_is_gathered(launches, n_q, l_q, b, l_d, d, dtype, kind):
+    assert launches([Call(n_q, l_q, b, b * l_d, 0, d, dtype)])[0].kind == kind
