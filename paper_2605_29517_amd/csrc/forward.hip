@@ -375,8 +375,12 @@ hipError_t forward_launch(FwdParams p, int dtype, int d, int num_cu, hipStream_t
             share(24);
         }
     }
-    // Winners wanted of fewer documents than CUs (a training step on a small batch)
-    if (am && dtype != MAXSIM_F32 && nu <= 8 && p.b <= num_cu) {
+    // Winners wanted of fewer documents than CUs (a training step on a small batch), which large column groups leave idle: up to three of
+    // their workgroups per CU, six of queries of up to six blocks.  Beyond, the small differences of the estimate's long sums are not to
+    // be trusted: 54 of 785 shapes (up to 300 queries x 256 documents, d = 64 and 128) were more than 3 % slower by it than in the large
+    // groups, up to 1.48 times, with this line 11, up to 1.1 (278 queries of 496 x 256 x 28, d = 64, 351 us, 520 by the estimate; 160 of
+    // 399 x 160 x 62 202, 263; but 57 of 58 x 195 x 27, 780 workgroups, 18.9, 13.4).
+    if (am && dtype != MAXSIM_F32 && nu <= 8 && p.b <= num_cu && p.b * p.n_groups <= (p.bpq <= 6 ? 6 : 3) * (int64_t)num_cu) {
         const FewDocs few = few_documents(p, num_cu, shape, p.n_pass == 1 ? p.n_groups : 0);
         if (few.waves) { // a document and a column group per workgroup
             p.n_chunks = 0;

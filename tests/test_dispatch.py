@@ -125,6 +125,15 @@ def test_fp32_and_narrow_rows_keep_three_blocks(routes):
         assert routes([call])[0].shape == want, call
 
 
+# The same with many column groups, which fill the chip: large ones, whatever the estimate says (queries, tokens, documents, tokens)
+@pytest.mark.parametrize("n_q,l_q,b,tokens,ragged,want", [(278, 496, 256, 28, 0, 8), (160, 399, 160, 62, 0, 8), (65, 412, 65, 36, 1, 8), (104, 238, 104, 19, 1, 8), (286, 55, 173, 67, 1, 8), (65, 458, 57, 88, 0, 8), (217, 210, 93, 17, 0, 8),
+                                                          (57, 58, 195, 27, 0, 81), (32 * 32, 32, 48, 60, 0, 82), (32 * 32 + 1, 32, 48, 60, 0, 8)])
+def test_many_column_groups_with_argmax(routes, n_q, l_q, b, tokens, ragged, want):
+    for d in (64, 128):
+        r, = routes([Call(BF16, d, n_q, l_q, b, b * tokens, ragged, 1)])
+        assert r.kind == "tile" and r.shape == want
+
+
 # n queries of l_q tokens on as many documents, winners wanted -> kernel and blocks (split) or shape (tile): small batches take a workgroup
 # per document and one or two column blocks, then small column groups, large ones the groups that any other corpus takes
 @pytest.mark.parametrize("n,l_q,tokens,ragged,want", [(16, 32, 128, 0, ("split", 1)), (16, 64, 500, 0, ("split", 2)), (33, 32, 208, 1, ("split", 1)), (50, 32, 1024, 0, ("tile", 43)),
