@@ -265,7 +265,7 @@ constexpr int I8D_WAVES = 8;
 constexpr int I8D_LIN_BLOCKS = 2;                        // up to this many column blocks the tiles are read as whole lines (no gain from 4 on)
 constexpr int I8D_DEPTH = 2;                             // tiles in flight per wavefront (up to 16 blocks; beyond, a tile takes long enough): 128 tokens x 8000 x 300 66 -> 60 us
 constexpr int i8d_depth(int nb) { return nb <= 16 ? I8D_DEPTH : 1; }
-constexpr int I8D_SPLIT_BLOCKS = 8;                      // column blocks of the kernel whose wavefronts share documents
+constexpr int I8D_SPLIT_BLOCKS = 16;                     // column blocks of the kernel whose wavefronts share documents
 constexpr int I8D_MAX_BLOCKS = 32;                       // column blocks per group (1024 query tokens)
 constexpr int I8D_QSTRIDE = I8_ROW_BYTES + 16;           // padded LDS row of a query token
 
@@ -300,7 +300,7 @@ __device__ __forceinline__ void i8d_tile_scales(float *w_scale, float *w_bias, f
 // scales and biases); the whole-line variant adds a document tile per wavefront
 constexpr size_t i8_doc_lds(int nb) { return (size_t)nb * BLOCK_COLS * (I8D_QSTRIDE + 4) + I8D_WAVES * 64 * sizeof(float); }
 constexpr size_t i8_doc_lin_lds(int nb) { return i8_doc_lds(nb) + (size_t)I8D_WAVES * TILE_ROWS * I8D_QSTRIDE; }
-constexpr size_t i8_split_lds(int nb, int w) // (8 blocks, 4 wavefronts: 46 KB)
+constexpr size_t i8_split_lds(int nb, int w)
 {
     return (size_t)nb * BLOCK_COLS * (I8D_QSTRIDE + 4) + w * 64 * sizeof(float) + (size_t)2 * w * nb * BLOCK_COLS * sizeof(float);
 }
@@ -559,7 +559,8 @@ __global__ void __launch_bounds__(I8D_WAVES * 64) fwd_i8_doc_kernel(I8Params P, 
 // tiles; the query tokens sit in LDS as above and every wavefront still streams its tiles HBM ->
 // registers, one tile ahead, across document borders.  At the end of a document the W partial maxima per query token
 // meet in LDS (double-buffered, one barrier per document) and one wavefront, a different one each time, finishes the
-// score.  (Documents of equal length of 256 tokens and more, and all with more query tokens: int8_rows64.hip.)
+// score.  Built for up to 16 column blocks (512 query tokens): beyond that the maxima of eight wavefronts no longer fit
+// beside the queries in LDS.  (Eight wavefronts, documents of equal length: where int8_rows64.hip is not ahead, by an estimate.)
 template <int NB, int W>
 __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, OffsetsPtr off)
 {
@@ -594,8 +595,13 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
     const int doc0 = (int)doc0_, doc1 = (int)doc1_;
 
     // first row and length of a document (offsets forced into the corpus, see clamp_offset)
+    constexpr bool UNI = W == I8D_WAVES; // eight wavefronts share documents of equal length only
+    // Which tiles are a wavefront's: every W-th, or of documents of equal length and from three blocks on the w-th eighth,
+    // with a loader that counts tiles instead of rows (4 x 32 query tokens: 1000 x 300 18.6 -> 17.7 us, 3000 x 300 42.8
+    // -> 39.0, 900 x 1024 36.8 -> 33.9; one block: 2000 x 1024 43.5 -> 47)
+    constexpr bool RUNS = UNI && NB >= 3;
     auto extent = [&](int doc, int &first, int &len) {
-        if (p.offsets) {
+        if (!UNI && p.offsets) {
             const int t_all = (int)p.total_tokens;
             first = min(max(off[doc], 0), t_all);
             len = min(max(off[doc + 1], first), t_all) - first;
@@ -604,23 +610,41 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
             len = p.l_d;
         }
     };
-    // the loader walks this wavefront's tiles, every W-th, in order; past the end it stays on the last one
+    // the loader walks this wavefront's tiles in order; past the end it stays on the last one
+    const int n_tiles = (p.l_d + TILE_ROWS - 1) / TILE_ROWS;
+    const int t_lo = w * (n_tiles / W) + min(w, n_tiles % W);
+    const int cnt = n_tiles / W + (w < n_tiles % W ? 1 : 0); // RUNS: tiles [t_lo, t_lo + cnt)
     i32x4 a_n[I8_NU];
     float s_n = 0.0f;
-    int l_doc = doc0, l_first = 0, l_len = 0, l_t0 = w * TILE_ROWS;
-    extent(l_doc, l_first, l_len);
+    int l_doc = doc0, l_first = 0, l_len = 0, l_t0 = w * TILE_ROWS, l_t = 0;
+    if (!RUNS)
+        extent(l_doc, l_first, l_len);
     int l_row = 0, l_last = 0;
     auto gload = [&]() {
-        while (l_doc < doc1 && l_t0 >= l_len) {
-            l_doc += 1;
-            l_t0 = w * TILE_ROWS;
-            if (l_doc < doc1)
-                extent(l_doc, l_first, l_len);
-        }
-        if (l_doc < doc1) {
-            l_row = l_first + l_t0;
-            l_last = l_len - l_t0 - 1; // rows past the document re-read its last token
-            l_t0 += W * TILE_ROWS;
+        if constexpr (RUNS) {
+            if (cnt == 0)
+                return;
+            const int t0 = (t_lo + l_t) * TILE_ROWS;
+            l_row = l_doc * p.l_d + t0;
+            l_last = p.l_d - t0 - 1;
+            if (l_t + 1 < cnt) {
+                l_t += 1;
+            } else if (l_doc + 1 < doc1) {
+                l_doc += 1;
+                l_t = 0;
+            }
+        } else {
+            while (l_doc < doc1 && l_t0 >= l_len) {
+                l_doc += 1;
+                l_t0 = w * TILE_ROWS;
+                if (l_doc < doc1)
+                    extent(l_doc, l_first, l_len);
+            }
+            if (l_doc < doc1) {
+                l_row = l_first + l_t0;
+                l_last = l_len - l_t0 - 1; // rows past the document re-read its last token
+                l_t0 += W * TILE_ROWS;
+            }
         }
         const int64_t grow = (int64_t)l_row + (rho < l_last ? rho : l_last);
         const char *src = P.D + grow * I8_ROW_BYTES + h * 16;
@@ -654,7 +678,7 @@ __global__ void __launch_bounds__(W * 64) fwd_i8_split_kernel(I8Params P, Offset
 #pragma unroll
         for (int blk = 0; blk < NB; ++blk)
             m[blk] = neg_inf();
-        const int mine_cnt = (len - w * TILE_ROWS + W * TILE_ROWS - 1) / (W * TILE_ROWS); // (not positive: none)
+        const int mine_cnt = RUNS ? cnt : (len - w * TILE_ROWS + W * TILE_ROWS - 1) / (W * TILE_ROWS); // (not positive: none)
         for (int t = 0; t < mine_cnt; ++t) {
             i32x4 a[I8_NU];
 #pragma unroll
@@ -750,10 +774,47 @@ hipError_t forward_i8_init_device()
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)i8_doc_lds(NB));
             return hipSuccess;
         });
+        if (e == hipSuccess && nb <= I8D_SPLIT_BLOCKS)
+            e = with_blocks<I8D_SPLIT_BLOCKS>(nb, [](auto n) {
+                constexpr int NB = decltype(n)::value;
+                if constexpr (i8_split_lds(NB, I8D_WAVES) > 64 * 1024)
+                    return hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_i8_split_kernel<NB, I8D_WAVES>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)i8_split_lds(NB, I8D_WAVES));
+                static_assert(i8_split_lds(8, 4) <= 64 * 1024, "the smaller workgroups need no more than that");
+                return hipSuccess;
+            });
         if (e != hipSuccess)
             return e;
     }
     return hipSuccess;
+}
+
+// Workgroups of fwd_i8_split_kernel: about four of eight wavefronts per CU while the queries are small, one when their LDS copy is
+// large; eight wavefronts per CU in the smaller workgroups
+static int64_t i8_share_chunks(const FwdParams &p, int blocks, bool eight, int num_cu)
+{
+    const int64_t chunks = (int64_t)num_cu * (blocks <= 4 ? 4 : eight ? 1 : 2);
+    return chunks < p.b ? chunks : p.b;
+}
+
+// Documents of equal length shared by eight wavefronts (fwd_i8_split_kernel), against 64 rows per step (int8_rows64.hip), up to 16 column
+// blocks and some thousand documents.  Where a CU has a document or two, the chain of one document's tiles is all there is, and
+// half as many tiles of twice the work make a longer one: 32 tokens x 149 x 634 7.7 us by 64 rows, 5.4 here, 73 x 9 x 351 6.4, 4.8, six
+// of 32 x 400 x 1030 27.1, 17.8.  With more documents 64 rows even the wavefronts out and read half as much from LDS, and of many
+// queries on few documents they make more workgroups (64 tokens x 1000 x 300 10.5, 14.2 here, 16 x 32 x 4 x 1030 9.1, 18.7).  Fitted to 1900
+// shapes of 4 to 2500 documents, 8 to 10 % off, and beyond three documents per CU asked for 7 % of difference; what it takes is more than a
+// tenth slower than the other for 23 of 2400 shapes (at most 1.2 times), for some 500 each if always one or the other.
+static bool i8_eight_share(const I8Params &P, int blocks, int num_cu)
+{
+    const FwdParams &p = P.f;
+    if (p.offsets || p.l_d < I8D_WAVES * TILE_ROWS || blocks > I8D_SPLIT_BLOCKS || p.b >= (int64_t)num_cu * I8D_WAVES * 2)
+        return false;
+    const int64_t chunks = i8_share_chunks(p, blocks, true, num_cu), docs = (p.b + chunks - 1) / chunks;
+    const double on_cu = (double)(docs * (((p.b + docs - 1) / docs + num_cu - 1) / num_cu)); // documents of a CU
+    const double tiles = (double)((p.l_d + TILE_ROWS - 1) / TILE_ROWS) / I8D_WAVES;          // of a wavefront
+    const double us = blocks <= 4 ? 1.84 + on_cu * (0.71 + 1.03 * tiles + (0.053 * std::ceil(tiles) + 0.244) * blocks + 0.07 * p.n_q)
+                                  : 3.1 + on_cu * (-0.88 + 0.95 * tiles + (0.1 * std::ceil(tiles) + 0.25) * blocks + 0.07 * p.n_q);
+    return us < forward_i8_rows64_time(P, num_cu) * (p.b <= 3 * (int64_t)num_cu ? 1.0 : 0.93);
 }
 
 // offsets == nullptr: uniform corpus [b, l_d, 128]; otherwise packed [total_tokens, 128] with int32 offsets [b + 1]
@@ -784,7 +845,8 @@ hipError_t forward_i8_launch(const int8_t *Q, const float *qs, int n_q, int l_q,
     if (p.bpq > I8D_MAX_BLOCKS)
         return hipErrorNotSupported; // l_q > 1024: would need a second pass with an fp64 carry
 
-    if (forward_i8_rows64_takes(n_q, l_q, offsets, b, l_d, num_cu))
+    const bool eight = i8_eight_share(P, (int)total_blocks, num_cu);
+    if (!eight && forward_i8_rows64_takes(n_q, l_q, offsets, b, l_d, num_cu))
         return forward_i8_rows64_launch(P, num_cu, stream);
 
     // Large corpora: document-stationary kernel, one run of documents per wavefront.
@@ -807,25 +869,21 @@ hipError_t forward_i8_launch(const int8_t *Q, const float *qs, int n_q, int l_q,
         return with_blocks<I8D_MAX_BLOCKS>(nb, [&](auto n) { return launch_i8_doc<decltype(n)::value>(P, grid, stream); });
     }
 
-    // Fewer documents, up to 8 column blocks: the wavefronts of a workgroup share each document (document-stationary like the
-    // kernel above, at any number of documents), two of them, or four (fewer copies of the queries) from five blocks on.  One
-    // query x 1000 / 3000 texts of 64-300 tokens 26 -> 10, 53 -> 18 us against the kernel below, four x 1000 32 -> 21, eight x
-    // 2000 45 -> 44 (with two wavefronts 59).
+    // Fewer documents, up to 8 column blocks, or 16 and documents of equal length: the wavefronts of a workgroup share each document
+    // (document-stationary like the kernel above, at any number of documents), eight of them (i8_eight_share) or two, or four (fewer
+    // copies of the queries) from five blocks on.  One query x 1000 / 3000 texts of 64-300 tokens 26 -> 10, 53 -> 18 us against the
+    // kernel below, four x 1000 32 -> 21, eight x 2000 45 -> 44 (with two wavefronts 59).
     const int64_t mean_len = (total_tokens + b - 1) / b; // (uniform: l_d)
-    if (total_blocks <= I8D_SPLIT_BLOCKS && mean_len >= 2 * TILE_ROWS) {
+    if (eight || (total_blocks <= 8 && mean_len >= 2 * TILE_ROWS)) {
         p.n_groups = 1;
         p.qpg = n_q;
-        // eight wavefronts per CU
-        int64_t n_chunks = (int64_t)num_cu * (total_blocks <= 4 ? 4 : 2);
-        if (n_chunks > b)
-            n_chunks = b;
-        p.unit_per_chunk = (units + n_chunks - 1) / n_chunks;
-        n_chunks = (units + p.unit_per_chunk - 1) / p.unit_per_chunk;
-        p.n_chunks = (int)n_chunks;
+        const int64_t chunks = i8_share_chunks(p, (int)total_blocks, eight, num_cu);
+        p.unit_per_chunk = (units + chunks - 1) / chunks;
+        p.n_chunks = (int)((units + p.unit_per_chunk - 1) / p.unit_per_chunk);
         const int grid = p.n_chunks;
         return with_blocks<I8D_SPLIT_BLOCKS>((int)total_blocks, [&](auto n) {
             constexpr int NB = decltype(n)::value;
-            return launch_i8_split<NB, (NB <= 4 ? 2 : 4)>(P, grid, stream);
+            return eight ? launch_i8_split<NB, I8D_WAVES>(P, grid, stream) : launch_i8_split<(NB <= 8 ? NB : 8), (NB <= 4 ? 2 : 4)>(P, grid, stream);
         });
     }
 

@@ -47,6 +47,7 @@ __device__ __forceinline__ double sum32(double v)
 // int8_rows64.hip: the calls that forward_i8_rows64_takes
 bool forward_i8_rows64_takes(int n_q, int l_q, const int32_t *offsets, int64_t b, int l_d, int num_cu);
 hipError_t forward_i8_rows64_launch(I8Params P, int num_cu, hipStream_t stream);
+double forward_i8_rows64_time(I8Params P, int num_cu); // an estimate, us, for up to 1024 tokens per query
 hipError_t forward_i8_rows64_init_device();
 
 } // namespace maxsim

@@ -319,13 +319,19 @@ bool forward_i8_rows64_takes(int n_q, int l_q, const int32_t *offsets, int64_t b
     return !many || (l_d >= 128 && r64_rows(blocks > R64_HALF_BLOCKS, l_d) * 7 <= r64_rows(false, l_d) * 8);
 }
 
-hipError_t forward_i8_rows64_launch(I8Params P, int num_cu, hipStream_t stream)
+namespace {
+
+// Queries per group: what the fullest CU has to do is least.  A workgroup (there is one per CU, whose registers it fills) copies its
+// queries first.  Returns the rounds of workgroups, a wavefront's tiles in one and the blocks that are multiplied.
+struct R64Plan {
+    int64_t rounds, tiles, nc;
+};
+R64Plan r64_plan(FwdParams &p, int num_cu)
 {
-    FwdParams &p = P.f;
     p.bpq = (p.l_q + R64_COLS - 1) / R64_COLS;
-    // Queries per group: what the fullest CU has to do is least.  A workgroup (there is one per CU, whose registers it fills) copies its queries first.
     const int most = R64_MAX_BLOCKS / p.bpq;
     int64_t best = INT64_MAX;
+    R64Plan plan = {};
     for (int qpg = 1; qpg <= most && qpg <= p.n_q; ++qpg) {
         const int64_t groups = (p.n_q + qpg - 1) / qpg;
         int64_t chunks = num_cu / groups;
@@ -338,12 +344,28 @@ hipError_t forward_i8_rows64_launch(I8Params P, int num_cu, hipStream_t stream)
         const int64_t time = rounds * (tiles * (nc + 4) + nc);
         if (time < best) {
             best = time;
+            plan = {rounds, tiles, nc};
             p.qpg = qpg;
             p.n_groups = (int)groups;
             p.n_chunks = (int)chunks;
             p.unit_per_chunk = docs;
         }
     }
+    return plan;
+}
+
+} // namespace
+
+double forward_i8_rows64_time(I8Params P, int num_cu)
+{
+    const R64Plan r = r64_plan(P.f, num_cu);
+    return 4.0 + 0.035 * (double)r.nc + (double)(r.rounds * r.tiles) * (1.24 + 0.169 * (double)r.nc);
+}
+
+hipError_t forward_i8_rows64_launch(I8Params P, int num_cu, hipStream_t stream)
+{
+    FwdParams &p = P.f;
+    (void)r64_plan(p, num_cu);
     const int grid = p.n_chunks * p.n_groups;
     return r64_with_blocks(p.qpg * p.bpq, [&](auto k) {
         constexpr int NC = decltype(k)::value;

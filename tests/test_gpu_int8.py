@@ -237,6 +237,17 @@ def test_forward_i8_64_tokens_per_step_bit_exact(n_q, l_q, b, l_d):
     assert np.array_equal(bits(s.cpu().numpy()), bits(O.forward_i8(*o)))
 
 
+# Eight wavefronts share each document: tiles that are as many as wavefronts, one more, one row more, several documents per workgroup, one to
+# sixteen column blocks in whole and ragged queries
+@pytest.mark.parametrize("n_q,l_q,b,l_d", [(1, 32, 3, 256), (1, 33, 2, 257), (2, 40, 5, 287), (3, 32, 4, 288), (5, 20, 3, 289), (1, 190, 2, 300), (7, 32, 130, 511), (2, 200, 128, 512),
+                                           (1, 400, 5, 513), (1, 288, 7, 256), (1, 330, 130, 270), (10, 32, 200, 1030), (1, 512, 2, 1030), (1, 64, 300, 260), (1, 1, 257, 320), (6, 32, 400, 300)])
+def test_forward_i8_documents_shared_by_eight_bit_exact(n_q, l_q, b, l_d):
+    g, o = quantised_case(n_q, l_q, b, l_d, 67)
+    s = M.maxsim_forward_i8(*g)
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(s.cpu().numpy()), bits(O.forward_i8(*o)))
+
+
 # Every number of column blocks the document kernels are built for, and one that is rounded up: small corpora, whose
 # documents are shared by two or four wavefronts (ragged, or uniform of under 256 tokens), and large ones
 @pytest.mark.parametrize("n_q,l_q", [(1, 30), (2, 32), (1, 90), (4, 20), (1, 160), (3, 60), (1, 224), (8, 32), (1, 290), (3, 128), (7, 50), (1, 500)])
