@@ -1611,14 +1611,15 @@ template <bool STASH> static void launch_ce_grad(const float *s, int n, int b, f
 hipError_t ce_grad_launch(const float *scores, int n, int b, float tau, float *g, float *loss, hipStream_t stream)
 {
     const float inv_tau = 1.0f / tau;
-    if (loss && n <= CE_SMALL_ROWS && b <= 256) {
+    // (one workgroup walks all rows: four to a wavefront, of up to 64 columns, 4.6 -> 3.9 us in a graph, of 256 6.4-7.1)
+    if (loss && (n <= 16 ? b <= 256 : n <= CE_SMALL_ROWS && b <= 64)) {
         auto go = [&](auto keep, auto rows) {
             hipLaunchKernelGGL((ce_small_kernel<decltype(keep)::value, decltype(rows)::value>), dim3(1), dim3(1024), 0, stream, scores, n, b, inv_tau, g, loss);
             return hipGetLastError();
         };
         const std::integral_constant<int, 1> one{};
         const std::integral_constant<int, 4> four{};
-        return b <= 64 ? (n <= 16 ? go(one, one) : go(one, four)) : n <= 16 ? go(four, one) : go(four, four);
+        return n > 16 ? go(one, four) : b <= 64 ? go(one, one) : go(four, one);
     }
     if (loss)
         launch_ce_grad<true>(scores, n, b, inv_tau, g, stream);

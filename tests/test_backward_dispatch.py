@@ -14,12 +14,15 @@ pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
 HARNESS = r"""
 #include "%(csrc)s/common.h"
 #include <cstdio>
+#include <cstring>
 #include <tuple>
 #undef hipLaunchKernelGGL
 #define hipGetLastError() hipSuccess // (there is no device)
 #define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) report(#kernel, grid, __VA_ARGS__)
 template <typename P, typename... A> void report(const char *kernel, dim3 grid, const P &, A... a)
 {
+    if (strstr(kernel, "ce_"))
+        printf("%%s ", strstr(kernel, "small") ? "small" : strstr(kernel, "loss") ? "loss" : "grad");
     if constexpr (sizeof...(A) >= 9) { // bwd_both_kernel
         const auto t = std::make_tuple(a...);
         printf("both %%u %%u %%d\n", grid.x, (unsigned)std::get<6>(t), (int)std::get<7>(t));
@@ -28,8 +31,15 @@ template <typename P, typename... A> void report(const char *kernel, dim3 grid, 
     }
 }
 #include "%(csrc)s/backward.hip"
-int main()
+int main(int argc, char **)
 {
+    if (argc > 1) {
+        int n, b;
+        float x;
+        while (scanf("%%d %%d", &n, &b) == 2)
+            printf("%%s\n", maxsim::ce_grad_launch(&x, n, b, 1.0f, &x, &x, nullptr) == hipSuccess ? "" : "error");
+        return 0;
+    }
     int n_q, l_q, ragged, d, dtype;
     long b, tokens;
     static int32_t some[4];
@@ -54,10 +64,12 @@ def launches(tmp_path_factory):
     exe = d / "harness"
     subprocess.run([HIPCC, "-std=c++17", "-O1", "--cuda-host-only", "-Wl,--unresolved-symbols=ignore-all", str(src), "-o", str(exe)], check=True, stderr=subprocess.DEVNULL)
 
-    def run(calls):
+    def run(calls, *mode):
         text = "".join(" ".join(str(int(v)) for v in c) + "\n" for c in calls)
-        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+        out = subprocess.run([str(exe), *mode], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
         assert len(out) == len(calls)
+        if mode:
+            return [line.split() for line in out]
         return [Launch(f[0], *(int(v) for v in f[1:])) for f in (line.split() for line in out)]
     return run
 
@@ -80,3 +92,9 @@ def test_one_launch_has_no_idle_wavefronts(launches, n_q, l_q, b, l_d, parts, se
                                                         (64, 64, 64, 64, 512, F32, "both"), (8, 64, 700, 128, 128, F32, "both"), (9, 60, 700, 128, 128, F32, "dD")])
 def test_one_launch_by_what_is_gathered(launches, n_q, l_q, b, l_d, d, dtype, kind):
     assert launches([Call(n_q, l_q, b, b * l_d, 0, d, dtype)])[0].kind == kind
+
+
+# gradient and loss in one launch, of one workgroup: sixteen rows of up to 256 columns, 64 rows of up to 64
+@pytest.mark.parametrize("n,b,one", [(1, 1, True), (16, 256, True), (16, 257, False), (17, 64, True), (17, 65, False), (64, 64, True), (33, 256, False), (64, 256, False), (65, 65, False)])
+def test_cross_entropy_in_one_launch(launches, n, b, one):
+    assert launches([(n, b)], "ce") == [["small"] if one else ["grad", "loss"]]

@@ -374,7 +374,7 @@ def test_both_gradients_in_one_launch(n_q, l_q, b, l_d, d):
     assert torch.equal(dQ, pQ) and torch.equal(dD.view(-1, d), pD)
 
 
-# One launch up to 64 rows of 256 columns, gradient and loss the bits that the larger kernels give for the same rows
+# One launch up to 16 rows of 256 columns and 64 of 64, gradient and loss the bits that the larger kernels give for the same rows
 @pytest.mark.parametrize("n,b", [(1, 1), (2, 64), (15, 65), (16, 256), (17, 17), (33, 64), (64, 64), (64, 256), (64, 257), (65, 65)])
 def test_ce_small_batches(n, b):
     s = torch.randn(n, b, device=DEV, generator=torch.Generator(device=DEV).manual_seed(n + b)) + 20
