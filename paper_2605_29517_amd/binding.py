@@ -7,8 +7,11 @@ is not on the device, the call raises.
 """
 import ctypes
 import os
+import warnings
 
 import torch
+
+from .build import marshal_abi
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmaxsim.so")
@@ -72,14 +75,27 @@ def load():
     L.maxsim_ce_grad.argtypes = [p, i, i, f, p, p, p]
     L.maxsim_init.restype = i
     L.maxsim_init.argtypes = []
+    native = _load_native()
+    if native is not None:
+        native.bind(*(ctypes.cast(f, p).value for f in (L.maxsim_forward, L.maxsim_forward_ragged, L.maxsim_backward, L.maxsim_backward_ragged, L.maxsim_ce_grad,
+                                                        L.maxsim_quantize_rows_i8, L.maxsim_forward_i8, L.maxsim_forward_i8_ragged)))
+    _lib, _native = L, native
+    return L
+
+
+def _load_native():
+    """The native part, or None with a warning: it speaks the C++ interface of the torch (and Python) that it was built for, which
+    another version may have changed without a symbol's name telling.  The Python code does all of its work."""
     try:
         from . import _marshal
     except ImportError as e:
-        raise MaxSimError("_marshal.so is missing or does not load (%s): build it with `python -m paper_2605_29517_amd.build`" % e)
-    _marshal.bind(*(ctypes.cast(f, p).value for f in (L.maxsim_forward, L.maxsim_forward_ragged, L.maxsim_backward, L.maxsim_backward_ragged, L.maxsim_ce_grad,
-                                                      L.maxsim_quantize_rows_i8, L.maxsim_forward_i8, L.maxsim_forward_i8_ragged)))
-    _lib, _native = L, _marshal
-    return L
+        why = "is missing or does not load (%s)" % e
+    else:
+        if _marshal.BUILT_FOR == marshal_abi():
+            return _marshal
+        why = "is built for %s, this is %s" % (_marshal.BUILT_FOR, marshal_abi())
+    warnings.warn("the native part of the binding, _marshal.so, %s: calls take twice the host time; build it with `python -m paper_2605_29517_amd.build`" % why, RuntimeWarning, stacklevel=3)
+    return None
 
 
 def _check(rc: int, what: str):

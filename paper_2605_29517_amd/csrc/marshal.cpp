@@ -367,4 +367,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "BUILT_FOR", MARSHAL_ABI) < 0) { // (binding.py looks at it before anything else)
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
