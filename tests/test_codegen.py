@@ -50,6 +50,34 @@ def registers(operand):
     return range(0) if not m else range(int(m[3]), int(m[3]) + 1) if m[3] else range(int(m[1]), int(m[2]) + 1)
 
 
+def test_wide_kernel_waits_for_its_mfmas(tmp_path):
+    """The 16x16 MFMAs of the wide kernel are assembly, which the compiler does not see through: an accumulator is read or written by
+    other instructions only some cycles after the MFMA that writes it (11 for four passes), an MFMA does not read what a vector
+    instruction wrote less than two cycles ago, and nothing spills."""
+    shapes = ["fwd_wide_kernel<MAXSIM_%s, WideShape<%s>, false, WD_16%s>" % (dt, shape, half)
+              for dt, shape in (("BF16", "2, 4, 4, 2"), ("F16", "4, 2, 2, 3"), ("BF16", "8, 1, 1, 1")) for half in ("", "_HALF")]
+    for name, body in zip(shapes, kernel_bodies(tmp_path, shapes, (), "forward_wide_impl.h", ", int, int")):
+        assert "scratch_" not in body, name
+        now, by_mfma, by_move = 0, {}, {}
+        count = 0
+        for line in body.split("\n"):
+            line = line.split(";")[0].strip()
+            if not line or line.startswith("."):
+                continue
+            op, _, rest = line.partition(" ")
+            operands = [x.strip() for x in rest.split(",")]
+            now += int(operands[0]) + 1 if op == "s_nop" else 1
+            if op.startswith("v_mfma"):
+                count += 1
+                assert all(now - by_move.get(r, -9) > 2 for o in operands[1:] for r in registers(o)), (name, line)
+                by_mfma.update((r, now) for r in registers(operands[0]))
+            else:
+                assert all(now - by_mfma.get(r, -99) >= 12 for o in operands for r in registers(o)), (name, line)
+                if op.startswith("v_"):
+                    by_move.update((r, now) for r in registers(operands[0]))
+        assert count > 0, name
+
+
 def blocks(body):
     """The basic blocks of a kernel's assembly, [(instructions, numbers of the blocks that may follow)]."""
     parts, labels = [[]], {}
@@ -140,7 +168,7 @@ def wide_kernels(tmp_path_factory):
 
 @pytest.mark.parametrize("results", ["WD_16", "WD_16_HALF"])
 @pytest.mark.parametrize("dtype", ["F16", "BF16"])
-def test_wide_kernel_waits_for_its_mfmas(wide_kernels, dtype, results):
+def test_wide_kernel_waits_along_every_path(wide_kernels, dtype, results):
     """The 16x16 MFMAs of the wide kernel are assembly, which the compiler does not see through: an accumulator is read or written by
     other instructions only some cycles after the MFMA that writes it (11 for four passes), an MFMA does not read what a vector
     instruction wrote less than two cycles ago, along any path, and nothing spills.  In every shape that with_shape knows."""
