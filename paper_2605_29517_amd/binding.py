@@ -91,9 +91,10 @@ def _load_native():
     except ImportError as e:
         why = "is missing or does not load (%s)" % e
     else:
-        if _marshal.BUILT_FOR == marshal_abi():
+        built_for = getattr(_marshal, "BUILT_FOR", "a torch that it does not name")
+        if built_for == marshal_abi():
             return _marshal
-        why = "is built for %s, this is %s" % (_marshal.BUILT_FOR, marshal_abi())
+        why = "is built for %s, this is %s" % (built_for, marshal_abi())
     warnings.warn("the native part of the binding, _marshal.so, %s: calls take twice the host time; build it with `python -m paper_2605_29517_amd.build`" % why, RuntimeWarning, stacklevel=3)
     return None
 

@@ -43,6 +43,13 @@ def test_built_for_another_torch(unloaded):
     assert M._native is None
 
 
+def test_built_before_it_said_for_what(unloaded):
+    unloaded(types.ModuleType("_marshal"))
+    with pytest.warns(RuntimeWarning, match="does not name"):
+        M.load()
+    assert M._native is None
+
+
 def test_loaded_without_a_word(unloaded, recwarn):
     M.load()
     assert M._native is not None and not recwarn.list
