@@ -893,20 +893,72 @@ template <int DT> static hipError_t launch_dq(const BwdParams &p, hipStream_t st
     return hipGetLastError();
 }
 
+// Rows per block of the dD kernel, and whether blocks end with their document (uniform corpora) or take no notice of documents.
+struct DdBlocks {
+    int rows;
+    bool by_document;
+};
+
+// The same for a uniform corpus beside dQ's launches, by an estimate.  `start` (launch_bwd's rule, by document) stands unless something
+// else promises seven percent of dD's time.  The terms, us: a document that a block enters beside its first one, the filter of its
+// argmax entries, the walk over the edges of its rows, the rows; then what a CU's second block adds beside the first (both are resident;
+// those of several slabs hide in each other), and every further one.  Consecutive rows only where all their blocks are resident and none
+// holds more than a document: of more rounds the estimate is too kind to them (fp32, d = 256, 95 x 935 x 440 x 27 4766 / 6681).
+// It sees two things.  Blocks by document are more, and just beyond one or two per CU the launch takes a round longer (both gradients,
+// us, consecutive / by document: fp32 146 x 104 x 146 x 48 156 / 184 of 32 rows (219 and 292 blocks), 105 x 86 x 151 x 52 104 / 121
+// (246, 302), bf16, d = 256, 24 x 86 x 67 x 473 37 / 41 of 128).  And the rows, with the blocks that are launched (32 / 128
+// by document: fp16, d = 256, 74 x 15 x 229 x 220 55 / 44, bf16, d = 512, 159 x 536 x 159 x 297 2297 / 1767; 64 / 128: fp16 38 x 486 x 38 x
+// 1288 73 / 60).  Fitted to six variants of 1964 shapes with d of 64 to 1024, by the rule alone -> by this: more than 2 % slower than the rule with
+// consecutive rows 81 -> 38, more than 3 % behind the best of the six 447 -> 234, on the mean 1.1 % faster.
+template <int DT> static DdBlocks dd_blocks(const BwdParams &p, int num_cu, DdBlocks start)
+{
+    const double entries = (double)p.n_q * p.l_q, rounds = std::ceil(entries / DW_COL);
+    const int slabs = (p.d + SLAB - 1) / SLAB;
+    const double width = (p.d < SLAB ? p.d : SLAB) * Elem<DT>::BYTES / 256.0;
+    const double second = slabs == 1 ? 1.0 : slabs == 2 ? 0.0 : 0.45, further = slabs == 1 ? 1.0 : 0.77;
+    auto blocks = [&](DdBlocks x) {
+        return (x.by_document ? p.b * (((int64_t)p.l_d + x.rows - 1) / x.rows) : (p.total_tokens + x.rows - 1) / x.rows) * slabs;
+    };
+    auto time = [&](DdBlocks x) {
+        const int64_t n = ((int64_t)p.l_d + x.rows - 1) / x.rows;
+        const double rows = x.by_document ? (double)((p.l_d + n - 1) / n) : x.rows;
+        const double docs = x.by_document ? 1.0 : 1.0 + (x.rows - 1) / (double)p.l_d;
+        const double per_cu = (double)blocks(x) / num_cu, on_cu = std::fmax(0.86 * std::ceil(per_cu) + 0.14 * per_cu, 1.0);
+        const double walk = entries * rows / p.l_d / 1000;
+        return 3.3 * (docs - 1) * rounds + 0.9 * docs * entries / 1000 + walk * (4.1 + 1.8 * width) + 0.015 * rows +
+               second * std::fmin(on_cu - 1, 1.0) * (1.3 * docs * rounds + 3.4 * walk * width) +
+               further * std::fmax(on_cu - 2, 0.0) * (1.4 * docs * rounds + 3.2 * walk * width + 0.023 * rows);
+    };
+    DdBlocks best = start;
+    double least = 0.93 * time(start);
+    for (int rows = 32; rows <= 128; rows *= 2)
+        for (const bool by_document : {true, false}) {
+            const DdBlocks x = {rows, by_document};
+            if (!by_document && (rows > p.l_d || blocks(x) > 2 * (int64_t)num_cu))
+                continue;
+            const double t = time(x);
+            if (t < least) {
+                least = t;
+                best = x;
+            }
+        }
+    return best;
+}
+
 template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, hipStream_t stream)
 {
     // Rows per block.  Every block filters the argmax columns of its documents, so halving the blocks doubles that work;
     // but fewer than four blocks per CU leave some CUs with more of them than others, and a block that spans two
-    // documents (ragged corpora) takes twice as long.  (The times below are of blocks of consecutive rows.)  So, with documents of several blocks, blocks of 128 rows also where they fill a
+    // documents (ragged corpora) takes twice as long.  So, with documents of several blocks, blocks of 128 rows also where they fill a
     // round of two per CU (what is resident) to five sixths or two rounds to three quarters, and blocks of 64 also where
     // there are 1.6 per CU and the CUs with most of them are no more than 0.3 ahead of the mean.  A slab of 128 columns
     // is a workgroup of its own.  Ragged corpora with several rounds per document: by four per CU alone, there a block of
-    // three documents takes three times as long. Both gradients, f16, in us, with blocks of 32 / 64 / 128 rows (queries x
+    // three documents takes three times as long. Both gradients, f16, in us, with blocks of 32 / 64 / 128 consecutive rows (queries x
     // tokens x documents x tokens): 256 x 32 x 256 x 180 85 / 84 / 100 (360 blocks of 128), 256 x 300 89 / 88 / 103
     // (600), 256 x 1030 128 / 117 / 110 (2060), 128 x 32 x 128 x 500 47 / 45 / 40 (500), 128 x 128 x 128 x 700 113 / 107
     // / 111 (700), 19 x 456 x 102 x 1024 88 / 79 / 72 (816), 64 x 1000 x 64 x 500 205 / 191 / 211 (500 blocks of 64), x
     // 700 225 / 204 / 226 (700), x 2000 367 / 330 / 282 (1000 of 128), 32 x 1024 x 32 x 1030 81 / 86 / 92 (515 of 64,
-    // three on three CUs), 256 x 32 x 256 x 130 89 / 98 / 122 (520, documents of two blocks).
+    // three on three CUs), 256 x 32 x 256 x 130 89 / 98 / 122 (520, documents of two blocks).  Uniform corpora start from it (dd_blocks).
     const int64_t cus = num_cu;
     const int64_t mean_len = p.total_tokens / p.b;
     const bool several = mean_len >= 384 && !(p.offsets && (int64_t)p.n_q * p.l_q > DW_COL);
@@ -916,10 +968,10 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
     const bool by64 = n64 >= 4 * cus || (several && n64 * 5 >= 8 * cus && n64 * 10 >= (n64 + cus - 1) / cus * cus * 7);
     const Magic lq_magic = magic_u31((uint32_t)p.l_q);
     const unsigned slabs = (unsigned)((p.d + SLAB - 1) / SLAB);
-    // Documents of equal length are cut into blocks by themselves, as even as they come: a block that spans two documents filters
+    // Documents of equal length can be cut into blocks by themselves, as even as they come: a block that spans two documents filters
     // and sorts twice, and where there are a few blocks per CU the last of those sets the time.  Both gradients, us, blocks of
     // consecutive rows -> by document: 26 x 1007 x 26 x 902 64.9 -> 53.3, 16 x 1000 x 16 x 300 35.4 -> 27.4, 250 x 64 x 250 x 1000 202
-    // -> 189, 256 x 32 x 256 x 33 113 -> 71, 16 x 32 x 5000 x 20 160 -> 142, and nothing slower of thirty shapes.
+    // -> 189, 256 x 32 x 256 x 33 113 -> 71, 16 x 32 x 5000 x 20 160 -> 142.  They are more blocks, though (dd_blocks).
     auto by_document = [&](int rows) {
         BwdParams r = p;
         const int n = (int)(((int64_t)p.l_d + rows - 1) / rows);
@@ -956,17 +1008,20 @@ template <int DT> static hipError_t launch_bwd(const BwdParams &p, int num_cu, h
     hipError_t e = launch_dq<DT>(p, stream);
     if (e != hipSuccess)
         return e;
-    auto go = [&](auto rpw_tag, auto w_tag) {
+    DdBlocks blocks_of = {by128 ? 128 : by64 ? 64 : 32, true};
+    if (!p.offsets)
+        blocks_of = dd_blocks<DT>(p, num_cu, blocks_of);
+    auto go = [&, &all = p](auto rpw_tag, auto w_tag) {
         constexpr int RPW = decltype(rpw_tag)::value;
         constexpr int W = decltype(w_tag)::value;
-        BwdParams p = by_document(W * RPW);
+        const BwdParams p = blocks_of.by_document ? by_document(W * RPW) : all;
         const BlockOrder order = block_order(n_blocks(p, W * RPW), num_cu);
         hipLaunchKernelGGL((bwd_dd_kernel<DT, RPW, W>), dim3(order.grid, slabs), dim3(W * 64), 0, stream, p, p.offsets,
                            lq_magic, magic_u31((uint32_t)(p.l_d > 0 ? p.l_d : 1)), 64 / p.l_q, 64 % p.l_q, order);
     };
-    if (by128)
+    if (blocks_of.rows == 128)
         go(std::integral_constant<int, 16>(), std::integral_constant<int, 8>());
-    else if (by64)
+    else if (blocks_of.rows == 64)
         go(std::integral_constant<int, 8>(), std::integral_constant<int, 8>());
     else
         go(std::integral_constant<int, 4>(), std::integral_constant<int, 8>());

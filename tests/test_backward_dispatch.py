@@ -19,15 +19,16 @@ HARNESS = r"""
 #undef hipLaunchKernelGGL
 #define hipGetLastError() hipSuccess // (there is no device)
 #define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) report(#kernel, grid, __VA_ARGS__)
-template <typename P, typename... A> void report(const char *kernel, dim3 grid, const P &, A... a)
+template <typename P, typename... A> void report(const char *kernel, dim3 grid, const P &p, A... a)
 {
     if (strstr(kernel, "ce_"))
         printf("%%s ", strstr(kernel, "small") ? "small" : strstr(kernel, "loss") ? "loss" : "grad");
     if constexpr (sizeof...(A) >= 9) { // bwd_both_kernel
         const auto t = std::make_tuple(a...);
         printf("both %%u %%u %%d\n", grid.x, (unsigned)std::get<6>(t), (int)std::get<7>(t));
-    } else if constexpr (sizeof...(A) == 6) {
-        printf("dD %%u 0 0\n", grid.x);
+    } else if constexpr (sizeof...(A) == 6) { // bwd_dd_kernel
+        const auto t = std::make_tuple(a...);
+        printf("dD %%u %%d %%d\n", grid.x, std::get<5>(t).n_blocks, p.doc_blocks);
     }
 }
 #include "%(csrc)s/backward.hip"
@@ -53,7 +54,7 @@ int main(int argc, char **)
 
 F32, F16 = 0, 1
 Call = collections.namedtuple("Call", "n_q l_q b tokens ragged d dtype", defaults=(128, F16))
-Launch = collections.namedtuple("Launch", "kind workgroups n_dq n_part")
+Launch = collections.namedtuple("Launch", "kind workgroups n_dq n_part")  # of dD by itself: blocks, blocks per document (0: consecutive rows)
 
 
 @pytest.fixture(scope="module")
@@ -92,6 +93,19 @@ def test_one_launch_has_no_idle_wavefronts(launches, n_q, l_q, b, l_d, parts, se
                                                         (64, 64, 64, 64, 512, F32, "both"), (8, 64, 700, 128, 128, F32, "both"), (9, 60, 700, 128, 128, F32, "dD")])
 def test_one_launch_by_what_is_gathered(launches, n_q, l_q, b, l_d, d, dtype, kind):
     assert launches([Call(n_q, l_q, b, b * l_d, 0, d, dtype)])[0].kind == kind
+
+
+# dD by itself: blocks of 32, 64 or 128 rows that end with their document, or of consecutive rows where those by document would need
+# one round more; ragged corpora have consecutive rows, as many as the rule by itself says
+@pytest.mark.parametrize("n_q,l_q,b,l_d,d,dtype,rows,by_document", [(146, 104, 146, 48, 128, F32, 32, False), (24, 86, 67, 473, 256, F16, 128, False), (105, 86, 151, 52, 128, F32, 32, False),
+                                                                    (114, 870, 114, 504, 128, F16, 128, True), (256, 32, 256, 1024, 128, F16, 128, True), (38, 486, 38, 1288, 128, F16, 128, True), (26, 1007, 26, 902, 128, F16, 32, True),
+                                                                    (250, 64, 250, 1000, 128, F16, 128, True), (256, 32, 256, 33, 128, F16, 32, True), (64, 1000, 64, 100, 128, F16, 32, True),
+                                                                                    (95, 935, 440, 27, 256, F32, 32, True)])
+def test_blocks_of_dd(launches, n_q, l_q, b, l_d, d, dtype, rows, by_document):
+    n = -(-l_d // rows)
+    r, ragged = launches([Call(n_q, l_q, b, b * l_d, 0, d, dtype), Call(n_q, l_q, b, b * l_d, 1, d, dtype)])
+    assert (r.kind, *r[2:]) == ("dD", *((b * n, n) if by_document else (-(-b * l_d // rows), 0)))
+    assert ragged.n_part == 0 and ragged.n_dq in [-(-b * l_d // x) for x in (32, 64, 128)]
 
 
 # gradient and loss in one launch, of one workgroup: sixteen rows of up to 256 columns, 64 rows of up to 64
