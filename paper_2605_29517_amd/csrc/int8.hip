@@ -798,23 +798,28 @@ static int64_t i8_share_chunks(const FwdParams &p, int blocks, bool eight, int n
 }
 
 // Documents of equal length shared by eight wavefronts (fwd_i8_split_kernel), against 64 rows per step (int8_rows64.hip), up to 16 column
-// blocks and some thousand documents.  Where a CU has a document or two, the chain of one document's tiles is all there is, and
+// blocks and five documents per CU.  Where a CU has a document or two, the chain of one document's tiles is all there is, and
 // half as many tiles of twice the work make a longer one: 32 tokens x 149 x 634 7.7 us by 64 rows, 5.4 here, 73 x 9 x 351 6.4, 4.8, six
 // of 32 x 400 x 1030 27.1, 17.8.  With more documents 64 rows even the wavefronts out and read half as much from LDS, and of many
-// queries on few documents they make more workgroups (64 tokens x 1000 x 300 10.5, 14.2 here, 16 x 32 x 4 x 1030 9.1, 18.7).  Fitted to 1900
-// shapes of 4 to 2500 documents, 8 to 10 % off, and beyond three documents per CU asked for 7 % of difference; what it takes is more than a
-// tenth slower than the other for 23 of 2400 shapes (at most 1.2 times), for some 500 each if always one or the other.
+// queries on few documents they make more workgroups (64 tokens x 1000 x 300 10.5, 14.2 here, 16 x 32 x 4 x 1030 9.1, 18.7).  Beyond five per
+// CU they are never behind (of 5171 shapes six by 3 to 6 %).  Both times by estimates, fitted to 14 000 shapes of 4 to 4095 documents of 256
+// to 1100 tokens, 6 % off: what is taken is more than a twentieth slower than eight wavefronts for 152 of them, than 64 rows for 240 (at
+// most 1.27 times); always the one or the other would be for 4502 and 7298.
 static bool i8_eight_share(const I8Params &P, int blocks, int num_cu)
 {
     const FwdParams &p = P.f;
-    if (p.offsets || p.l_d < I8D_WAVES * TILE_ROWS || blocks > I8D_SPLIT_BLOCKS || p.b >= (int64_t)num_cu * I8D_WAVES * 2)
+    if (p.offsets || p.l_d < I8D_WAVES * TILE_ROWS || blocks > I8D_SPLIT_BLOCKS || p.b > 5 * (int64_t)num_cu)
         return false;
     const int64_t chunks = i8_share_chunks(p, blocks, true, num_cu), docs = (p.b + chunks - 1) / chunks;
     const double on_cu = (double)(docs * (((p.b + docs - 1) / docs + num_cu - 1) / num_cu)); // documents of a CU
     const double tiles = (double)((p.l_d + TILE_ROWS - 1) / TILE_ROWS) / I8D_WAVES;          // of a wavefront
-    const double us = blocks <= 4 ? 1.84 + on_cu * (0.71 + 1.03 * tiles + (0.053 * std::ceil(tiles) + 0.244) * blocks + 0.07 * p.n_q)
-                                  : 3.1 + on_cu * (-0.88 + 0.95 * tiles + (0.1 * std::ceil(tiles) + 0.25) * blocks + 0.07 * p.n_q);
-    return us < forward_i8_rows64_time(P, num_cu) * (p.b <= 3 * (int64_t)num_cu ? 1.0 : 0.93);
+    struct Fit {
+        double start, blocks, doc, tile, block_tile, doc_block, query; // us: of the launch, and of each document of a CU
+    };
+    static const Fit fits[] = {{2.2, -0.06, 0.82, 0.95, 0.028, 0.292, 0.082}, {3.0, 0.087, -1.1, 1.09, 0.041, 0.325, 0.066}, {2.7, 0.139, -2.3, 1.66, 0.056, 0.302, 0.063}};
+    const Fit &f = fits[blocks <= 4 ? 0 : blocks <= 8 ? 1 : 2];
+    const double us = f.start + f.blocks * blocks + on_cu * (f.doc + f.tile * tiles + (f.block_tile * std::ceil(tiles) + f.doc_block) * blocks + f.query * p.n_q);
+    return us < 0.98 * forward_i8_rows64_time(P, num_cu);
 }
 
 // offsets == nullptr: uniform corpus [b, l_d, 128]; otherwise packed [total_tokens, 128] with int32 offsets [b + 1]

@@ -359,7 +359,7 @@ R64Plan r64_plan(FwdParams &p, int num_cu)
 double forward_i8_rows64_time(I8Params P, int num_cu)
 {
     const R64Plan r = r64_plan(P.f, num_cu);
-    return 4.0 + 0.035 * (double)r.nc + (double)(r.rounds * r.tiles) * (1.24 + 0.169 * (double)r.nc);
+    return -5.9 + 0.056 * (double)r.nc + 0.037 * P.f.n_q + (double)r.rounds * (10.1 + (double)r.tiles * (1.36 + 0.15 * (double)r.nc));
 }
 
 hipError_t forward_i8_rows64_launch(I8Params P, int num_cu, hipStream_t stream)

@@ -55,6 +55,7 @@ def kernels(tmp_path_factory):
 @pytest.mark.parametrize("n_q,l_q,b,l_d,want", [
     (1, 32, 149, 634, "i8_split"), (1, 20, 7, 334, "i8_split"), (1, 73, 9, 351, "i8_split"), (1, 32, 253, 939, "i8_split"), (4, 31, 237, 776, "i8_split"), (3, 32, 20, 665, "i8_split"),
     (6, 32, 400, 1030, "i8_split"), (1, 509, 128, 1030, "i8_split"), (1, 32, 149, 255, "i8_split"),
+    (9, 18, 1160, 807, "i8_split"), (9, 18, 1290, 807, "i8_rows64"), (3, 145, 3705, 378, "i8_rows64"), (4, 114, 282, 959, "i8_rows64"), (13, 16, 249, 1072, "i8_rows64"),
     (1, 29, 1024, 1030, "i8_rows64"), (1, 224, 1050, 332, "i8_rows64"), (16, 32, 4, 1030, "i8_rows64"), (17, 32, 20, 300, "i8_rows64"), (1, 602, 3, 300, "i8_rows64"), (4, 310, 500, 1000, "i8_rows64"),
     (1, 64, 3000, 1024, "i8_rows64"), (5, 70, 5, 159, "i8_rows64"), (1, 1009, 300, 64, "i8_rows64"), (1, 1024, 40000, 1024, "i8_rows64"), (1, 32, 40000, 300, "i8_doc")])
 def test_equal_documents(kernels, n_q, l_q, b, l_d, want):
