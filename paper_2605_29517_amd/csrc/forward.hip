@@ -96,8 +96,9 @@ static FewDocs few_documents(const FwdParams &p, int num_cu, int shape, int grou
 //  - beyond: one wavefront, but two on each of two documents where that makes the fullest SIMD's share smaller by a tenth, just beyond
 //    4, 8, 12 or 16 per CU (1025 x 128 21.0 -> 21.1, one wavefront 23.0; 1400 x 260 55.7 -> 48.5, 51.0; 2300 x 260 72.7 -> 72.8,
 //    77; not of three tiles, 1025 x 96 19.5 against 18.3; ragged from six on, 1500 x 200 50.4 against 51.5, x 128 35.2 against 33.4).
-// Two blocks (64 tokens): a wavefront on each, where a SIMD's share is smaller by an eighth than that of a wavefront that holds both and
-// reads a tile once (4000 x 40 equal shares: 48.5 in runs, 56 here; 1536 x 64 three quarters: 27.1 -> 24.5; 2200 x 64 five eighths: 46.8
+// Two blocks (64 tokens): a wavefront on each, with argmax where a SIMD's share is smaller by an eighth than that of a wavefront that holds
+// both and reads a tile once, without (of whose runs a SIMD holds one at a time) always (no argmax, 52 tokens x 3098 x 34 68 in runs, 41
+// here, 55 x 1575 x 120 69, 47; with: 4000 x 40 equal shares: 48.5 in runs, 56 here; 1536 x 64 three quarters: 27.1 -> 24.5; 2200 x 64 five eighths: 46.8
 // -> 34.8).  Two documents to a workgroup with two or six per CU (500 x 300 47.9 -> 34.4, by themselves 49.5; 1536 x 90 35.9 -> 32.3,
 // 40.3; but 600 x 100 26.8 against 24.3, 2500 x 20 25.5 against 23.6).
 static void fp32_shape(FwdParams &p, int num_cu, int blocks, int64_t run, int64_t runs)
@@ -110,7 +111,7 @@ static void fp32_shape(FwdParams &p, int num_cu, int blocks, int64_t run, int64_
         p.docs_per_wg = docs;
     };
     set(0, 1);
-    if (p.b > 64 * cus || (blocks > 1 && ((mean_len >= 4 * TILE_ROWS && p.b > 2 * cus) || rounds(2 * p.b) * 8 >= rounds(runs) * run * 2 * 7)))
+    if (p.b > 64 * cus || (blocks > 1 && ((mean_len >= 4 * TILE_ROWS && p.b > 2 * cus) || (p.argmax && rounds(2 * p.b) * 8 >= rounds(runs) * run * 2 * 7))))
         return;
     if (p.b * blocks <= 2 * cus && tiles > 1)
         return set(tiles >= 4 ? 4 : 2, 1);

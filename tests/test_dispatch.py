@@ -173,6 +173,12 @@ def test_fp32_two_blocks_in_runs(routes, b, tokens, ragged, waves):
     assert routes([Call(F32, 128, 1, 64, b, b * tokens, ragged, 1)])[0].doc_waves == waves
 
 
+# without argmax always by themselves, up to 127 tokens
+@pytest.mark.parametrize("b,tokens,ragged,waves", [(2048, 64, 0, 1), (2000, 100, 0, 1), (4000, 40, 0, 1), (3098, 34, 0, 1), (5000, 90, 0, 1), (1575, 120, 1, 1), (1575, 128, 0, 0), (64 * 256 + 1, 40, 0, 0)])
+def test_fp32_two_blocks_without_argmax(routes, b, tokens, ragged, waves):
+    assert routes([Call(F32, 128, 1, 64, b, b * tokens, ragged, 0)])[0].doc_waves == waves
+
+
 def test_every_shape_is_reached_and_no_other(routes):
     """dispatch_tile and launch_stream instantiate exactly what forward_launch asks for."""
     calls = [Call(dt, row // (4 if dt == F32 else 2), n_q, l_q, b, b * t, ragged, am)
