@@ -92,7 +92,8 @@ static FewDocs few_documents(const FwdParams &p, int num_cu, int shape, int grou
 // runs or of two wavefronts per document that were there before -> now, 32 query tokens:
 //  - fewer documents than SIMDs: four or two wavefronts on each (100 x 300 tokens 14.7 -> 11.4, 300 x 300 26.6 -> 21.0), from two
 //    documents per CU on one (700 x 128 16.9 -> 14.7); with more than three per CU four documents to a workgroup (1000 x 128
-//    19.4 -> 17.1 (22.4 -> 20.8; workgroups of one document 26.2), 1000 x 260 35.3 -> 33.5 (37.9 -> 36.0; 49.4)).
+//    19.4 -> 17.1 (22.4 -> 20.8; workgroups of one document 26.2), 1000 x 260 35.3 -> 33.5 (37.9 -> 36.0; 49.4); launched one after another by
+//    the host workgroups of one are 2 % ahead, 15.1 against 15.5, and 17.0 before).
 //  - beyond: one wavefront, but two on each of two documents where that makes the fullest SIMD's share smaller by a tenth, just beyond
 //    4, 8, 12 or 16 per CU (1025 x 128 21.0 -> 21.1, one wavefront 23.0; 1400 x 260 55.7 -> 48.5, 51.0; 2300 x 260 72.7 -> 72.8,
 //    77; not of three tiles, 1025 x 96 19.5 against 18.3; ragged from six on, 1500 x 200 50.4 against 51.5, x 128 35.2 against 33.4).
