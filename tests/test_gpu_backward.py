@@ -409,3 +409,18 @@ def test_blocks_of_a_document(n_q, l_q, b, l_d):
     off = torch.arange(0, (b + 1) * l_d, l_d, dtype=torch.int32, device=DEV)
     _, pD = M.maxsim_backward_ragged(Q, D.view(-1, 128), off, A, g)
     assert torch.equal(dD.view(-1, 128), pD)
+
+
+# Blocks of 32, 64 and 128 consecutive rows on uniform corpora, where blocks by document would take a round longer (a block may hold rows of
+# two documents, the last one of all is not full), and the rows per block that documents of several blocks get
+@pytest.mark.parametrize("n_q,l_q,b,l_d,d,dtype", [(105, 86, 151, 52, 128, "f32"), (146, 104, 146, 48, 128, "f32"), (36, 727, 36, 450, 256, "f32"), (24, 86, 67, 473, 256, "bf16"), (38, 486, 38, 1288, 128, "f16"),
+                                                   (159, 53, 159, 297, 512, "bf16")])
+def test_blocks_of_consecutive_rows(n_q, l_q, b, l_d, d, dtype):
+    Q = W.unit_rows((n_q, l_q, d), dtype, 23, DEV)
+    D = W.unit_rows((b, l_d, d), dtype, 24, DEV)
+    gen = torch.Generator(device=DEV).manual_seed(25)
+    A = torch.randint(-1, l_d, (n_q, b, l_q), dtype=torch.int32, device=DEV, generator=gen)
+    g = torch.randn(n_q, b, device=DEV, generator=gen)
+    dQ, dD = M.maxsim_backward(Q, D, A, g)
+    cQ, cD, _, _ = M.maxsim_backward_csr(Q, D, A, g)  # walks rows, whatever the blocks
+    assert torch.equal(dQ, cQ) and torch.equal(dD, cD)
